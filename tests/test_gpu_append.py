@@ -123,3 +123,35 @@ def test_appended_chunks_match_oracle_and_decode_keeps_parity(loc, d, c):
                                     g, state, cache, ocache)
         assert np.all((sel == s // c - 1).any(axis=1)), "the appended chunk should be among the selected ones"
         _check_decode(wl, S.Params.from_workload(wl, ctx_len=s, ctx_capacity=cap), _op(wl, s, cap), q, t, g, state)
+
+
+@pytest.mark.parametrize("hkv,d,c,r,kd", [(1, 64, 1, 8, 0), (2, 96, 3, 24, 0), (3, 64, 17, 200, 1), (8, 128, 8, 160, 0),
+                                          (32, 96, 64, 256, 0), (8, 128, 16, 136, 1)])
+def test_projection_tiles_and_remainders(hkv, d, c, r, kd):
+    """The projection's 16-token and 16-rank tiles and its cut of the key width over eight waves (widths 64 ... 3072,
+    one to six rounds of steps, ranks and chunk sizes that leave tiles partly empty), rows of A against the oracle."""
+    print(f"\n[case] hkv {hkv} d {d} c {c} r {r} kv_dtype {kd}", flush=True)
+    b, s, o = 2, 4 * c, 1
+    cap = s + 2 * c
+    st = torch.float8_e5m2 if kd else torch.bfloat16
+    gen = torch.Generator(device="cuda").manual_seed(c * r + d)
+
+    def rnd(*shape):
+        return torch.randn(*shape, generator=gen, device="cuda").to(st)
+    k_pre, k_rope, v, B = rnd(b, c, hkv * d), rnd(b, hkv, c, d), rnd(b, hkv, c, d), rnd(b, hkv, r, d)
+    A, L, V = rnd(b, cap, r), rnd(b, hkv, cap // c - o, d), rnd(b, hkv, cap, d)
+    ids = torch.zeros(b, hkv, cap // c - o, dtype=torch.int32, device="cuda")
+    op = O.OracleParams(b, hkv, hkv, d, s, c, r, o, 1, 1, rope_theta=1e4, ctx_capacity=cap, kv_dtype=kd)
+    ref = [to_bits(x, kd).copy() for x in (A, L)] + [ids.cpu().numpy().copy(), to_bits(V, kd).copy()]
+    O.append_chunk(op, *(to_bits(x, kd) for x in (k_pre, k_rope, v, B)), ref[0], ref[1], ref[2], ref[3])
+    p = S.Params(b, hkv, hkv, d, s, chunk_size=c, rank=r, n_outlier_chunks=o, topk_chunks=1, local_len=1,
+                 rope_theta=1e4, ctx_capacity=cap, kv_dtype=kd)
+    S.append_chunk(p, k_pre, k_rope, v, B, A, L, ids, V)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(to_bits(L, kd), ref[1])
+    np.testing.assert_array_equal(ids.cpu().numpy(), ref[2])
+    np.testing.assert_array_equal(to_bits(V, kd), ref[3])
+    ga, wa = to_bits(A, kd).astype(np.int64), ref[0].astype(np.int64)
+    # both sides sum exact products in fp64, in different orders: a sum within ~1e-13 of a rounding boundary may land
+    # on the other side of it, by one unit in the last place
+    assert np.abs(ga - wa).max() <= 1 and (ga != wa).sum() <= max(1, ga.size // 1000)
