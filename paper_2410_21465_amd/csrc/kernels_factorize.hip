@@ -18,11 +18,10 @@
 #include <cstdlib>
 #include <type_traits>
 
+#include "factorize_small.hpp"
 #include "kernels.hpp"
 
 namespace skv {
-
-typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // four consecutive stored elements starting at element index `at` of `base` (zero when !ok), kept as stored and
 // widened to fp64 when they are used: what a prefetch holds
@@ -156,55 +155,6 @@ __global__ __launch_bounds__(256) void gram_finish_kernel(const double* __restri
 }
 
 // ---- 2. small fp64 linear algebra --------------------------------------------------------------------
-// C[i][j] = sum_k A(i, k) B(k, j), all fp64, element (i, k) of A at A[i * sai + k * sak] (likewise B), C row-major
-// with leading dimension ldc; batched by strides.  64 x 64 x 16 tiles through LDS, 4 x 4 results per thread.
-__global__ __launch_bounds__(256) void dgemm_kernel(const double* __restrict__ A, const double* __restrict__ B,
-                                                    double* __restrict__ C, int M, int N, int Kd, long sai, long sak,
-                                                    long sbk, long sbj, int ldc, long strideA, long strideB,
-                                                    long strideC) {
-  __shared__ double As[16][65], Bs[16][65];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
-  A += (size_t)blockIdx.z * strideA; B += (size_t)blockIdx.z * strideB; C += (size_t)blockIdx.z * strideC;
-  double acc[4][4];
-#pragma unroll
-  for (int x = 0; x < 4; ++x)
-#pragma unroll
-    for (int y = 0; y < 4; ++y) acc[x][y] = 0.0;
-  for (int k0 = 0; k0 < Kd; k0 += 16) {
-    for (int e = threadIdx.x; e < 16 * 64; e += 256) {
-      // the index that is contiguous in memory runs fastest over the threads
-      int kk, ii;
-      if (sak == 1) { kk = e & 15; ii = e >> 4; } else { ii = e & 63; kk = e >> 6; }
-      const int gi = i0 + ii, gk = k0 + kk;
-      As[kk][ii] = (gi < M && gk < Kd) ? A[(size_t)gi * sai + (size_t)gk * sak] : 0.0;
-      int kb, jj;
-      if (sbk == 1) { kb = e & 15; jj = e >> 4; } else { jj = e & 63; kb = e >> 6; }
-      const int gj = j0 + jj, gk2 = k0 + kb;
-      Bs[kb][jj] = (gj < N && gk2 < Kd) ? B[(size_t)gk2 * sbk + (size_t)gj * sbj] : 0.0;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      double a[4], bq[4];
-#pragma unroll
-      for (int x = 0; x < 4; ++x) { a[x] = As[kk][ty + 16 * x]; bq[x] = Bs[kk][tx + 16 * x]; }
-#pragma unroll
-      for (int x = 0; x < 4; ++x)
-#pragma unroll
-        for (int y = 0; y < 4; ++y) acc[x][y] = fma(a[x], bq[y], acc[x][y]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int x = 0; x < 4; ++x)
-#pragma unroll
-    for (int y = 0; y < 4; ++y) {
-      const int gi = i0 + ty + 16 * x, gj = j0 + tx + 16 * y;
-      if (gi < M && gj < N) C[(size_t)gi * ldc + gj] = acc[x][y];
-    }
-}
-
 __device__ __forceinline__ double block_sum_256(double v, double* sm) {
   v = wave_sum_f64(v);
   const int wave = threadIdx.x >> 6;
@@ -380,27 +330,27 @@ __global__ __launch_bounds__(64) void jacobi_step_kernel(double* __restrict__ W,
   }
 }
 
-// the r columns of W with the largest norms (ties: lower index), strongest first: their eigenvectors (columns
-// of V, restricted to the first m entries) become the rows of Wsel [r][m]
-__global__ __launch_bounds__(256) void ritz_select_kernel(const double* __restrict__ W, const double* __restrict__ V,
-                                                          double* __restrict__ Wsel, double* __restrict__ sigma_out,
-                                                          int mp, int m, int r) {
-  extern __shared__ double nrm[];  // [mp]
-  const int b = blockIdx.x;
-  for (int p = threadIdx.x; p < mp; p += 256) {
+// order [r]: the columns of W with the largest norms (ties: lower index), strongest first.  A wave per column for the
+// norms, then every column counts the ones before it.
+__global__ __launch_bounds__(1024) void ritz_select_kernel(const double* __restrict__ W, int32_t* __restrict__ order,
+                                                           double* __restrict__ sigma_out, int mp, int m, int r) {
+  extern __shared__ double nrm[];  // [m]
+  const int b = blockIdx.x, lane = threadIdx.x & (kWave - 1);
+  for (int p = threadIdx.x / kWave; p < m; p += 1024 / kWave) {
     const double* w = W + ((size_t)b * mp + p) * mp;
     double n = 0.0;
-    for (int x = 0; x < mp; ++x) n = fma(w[x], w[x], n);
-    nrm[p] = p < m ? n : -1.0;   // padding columns never win
+    for (int x = lane; x < mp; x += kWave) n = fma(w[x], w[x], n);
+    n = wave_sum_f64(n);
+    if (lane == 0) nrm[p] = n;
   }
+  // (norms that are not numbers have no place in the order: every entry is a valid column whatever the input)
+  for (int p = threadIdx.x; p < r; p += 1024) order[(size_t)b * r + p] = p;
   __syncthreads();
-  for (int p = threadIdx.x; p < m; p += 256) {
+  for (int p = threadIdx.x; p < m; p += 1024) {
     int rank = 0;
     for (int o = 0; o < m; ++o) rank += (nrm[o] > nrm[p]) || (nrm[o] == nrm[p] && o < p);
     if (rank < r) {
-      const double* v = V + ((size_t)b * mp + p) * mp;
-      double* dst = Wsel + ((size_t)b * r + rank) * m;
-      for (int x = 0; x < m; ++x) dst[x] = v[x];
+      order[(size_t)b * r + rank] = p;
       if (sigma_out) sigma_out[(size_t)b * r + rank] = sqrt(sqrt(nrm[p]));  // |column| = eigenvalue of G = sigma^2
     }
   }
@@ -531,18 +481,28 @@ __global__ __launch_bounds__(64) void project_kernel(const void* __restrict__ K,
 }
 
 // ---- launch sequence ----------------------------------------------------------------------------------------
-static hipError_t dgemm(const double* A, const double* B, double* C, int M, int N, int Kd, long sai, long sak, long sbk,
-                        long sbj, int ldc, long strideA, long strideB, long strideC, int batch, hipStream_t st) {
-  dim3 grid((N + 63) / 64, (M + 63) / 64, batch);
-  hipLaunchKernelGGL(dgemm_kernel, grid, dim3(256), 0, st, A, B, C, M, N, Kd, sai, sak, sbk, sbj, ldc, strideA, strideB,
-                     strideC);
+// C (Mw x Nw, zero outside M x N) = A B, see gemm64_kernel; ?.ld = elements from row to row, ?.stride = from sequence to
+// sequence.  32 x 32 tiles with the contraction cut eight ways while that leaves the chip room (fewer than 1024 tiles:
+// 192 x 1024 x 1024 takes 20 us for one sequence, 211 us with a tile per workgroup on the vector unit), else 64 x 64
+// blocks cut in two (16 sequences: 182 us, 298 us on the vector unit).
+struct Mat { const double* p; int ld; size_t stride; };
+template <bool BT>
+static hipError_t gemm64(Mat A, Mat B, double* C, int ldc, size_t strideC, int M, int N, int K, int Kb, int Mw, int Nw,
+                         int batch, hipStream_t st, const int32_t* a_rows = nullptr, int a_rows_stride = 0) {
+  const long tiles = (long)((Mw + 31) / 32) * ((Nw + 31) / 32) * batch;
+  if (tiles < 1024)
+    hipLaunchKernelGGL((gemm64_kernel<1, 1, 8, BT>), dim3((Nw + 31) / 32, (Mw + 31) / 32, batch), dim3(512), 0, st, A.p, B.p, C,
+                       M, N, K, Kb, A.ld, B.ld, ldc, Mw, Nw, A.stride, B.stride, strideC, a_rows, a_rows_stride);
+  else
+    hipLaunchKernelGGL((gemm64_kernel<2, 2, 2, BT>), dim3((Nw + 63) / 64, (Mw + 63) / 64, batch), dim3(512), 0, st, A.p, B.p, C,
+                       M, N, K, Kb, A.ld, B.ld, ldc, Mw, Nw, A.stride, B.stride, strideC, a_rows, a_rows_stride);
   return hipGetLastError();
 }
 
 FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample) {
   FactorizePlan p{};
   p.m = std::min(D, r + oversample);
-  p.mp = (p.m + 1) & ~1;
+  p.mp = (p.m + 31) / 32 * 32;
   p.nb = (D + 63) / 64;
   const long pairs = (long)p.nb * (p.nb + 1) / 2;
   // enough waves to fill the chip: split the tokens when there are few column-block pairs
@@ -563,7 +523,7 @@ FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample) {
   p.Yt = off; off += up((size_t)batch * p.m * D * 8);
   p.W = off; off += up((size_t)batch * p.mp * p.mp * 8);
   p.V = off; off += up((size_t)batch * p.mp * p.mp * 8);
-  p.Wsel = off; off += up((size_t)batch * r * p.m * 8);
+  p.order = off; off += up((size_t)batch * r * 4);
   p.Psi_t = off; off += up((size_t)batch * r * D * 8);
   p.total = off;
   return p;
@@ -579,7 +539,7 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
   double* Yt = reinterpret_cast<double*>(ws + pl.Yt);
   double* W = reinterpret_cast<double*>(ws + pl.W);
   double* V = reinterpret_cast<double*>(ws + pl.V);
-  double* Wsel = reinterpret_cast<double*>(ws + pl.Wsel);
+  int32_t* order = reinterpret_cast<int32_t*>(ws + pl.order);
   double* Psi_t = psi_out ? psi_out : reinterpret_cast<double*>(ws + pl.Psi_t);
   hipError_t e;
 #define SKV_CHECK() do { e = hipGetLastError(); if (e != hipSuccess) return e; } while (0)
@@ -623,10 +583,13 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
     hipLaunchKernelGGL(normalize_rows_kernel, dim3(batch * m), dim3(256), 0, st, X, D);
     return hipGetLastError();
   };
+  auto times_gram = [&](const double* X, double* Y) {   // Y = X G; G is symmetric, so its rows are its columns
+    return gemm64<true>({X, D, (size_t)m * D}, {G, D, (size_t)D * D}, Y, D, (size_t)m * D, m, D, D, D, m, D, batch, st);
+  };
   if ((e = orthonormalise(Xt)) != hipSuccess) return e;
   for (int it = 0; it < n_iter; ++it) {
     // Yt [m x D] = Xt [m x D] G [D x D]   (G is symmetric)
-    if ((e = dgemm(Xt, G, Yt, m, D, D, D, 1, D, 1, D, (long)m * D, (long)D * D, (long)m * D, batch, st)) != hipSuccess) return e;
+    if ((e = times_gram(Xt, Yt)) != hipSuccess) return e;
     // every second product only: two products square the condition number of the basis (~1e8 at most for the
     // spectra this is meant for), which modified Gram-Schmidt still handles; the last basis is done twice
     if (((it & 1) || it + 1 == n_iter) && (e = orthonormalise(Yt)) != hipSuccess) return e;
@@ -634,14 +597,11 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
     double* tmp = Xt; Xt = Yt; Yt = tmp;
   }
   // Rayleigh-Ritz: T = X^T G X = Xt (Xt G)^T
-  if ((e = dgemm(Xt, G, Yt, m, D, D, D, 1, D, 1, D, (long)m * D, (long)D * D, (long)m * D, batch, st)) != hipSuccess) return e;
+  if ((e = times_gram(Xt, Yt)) != hipSuccess) return e;
   {
-    // W [mp x mp] = 0 outside the leading m x m block
-    const size_t nw = (size_t)batch * mp * mp;
-    e = launch_fill_i32(reinterpret_cast<int32_t*>(W), nw * 2, 0, st);
-    if (e != hipSuccess) return e;
-    // T(i, j) = sum_x Xt[i][x] Yt[j][x]
-    if ((e = dgemm(Xt, Yt, W, m, m, D, D, 1, 1, D, mp, (long)m * D, (long)m * D, (long)mp * mp, batch, st)) != hipSuccess) return e;
+    // W [mp x mp]: T(i, j) = sum_x Xt[i][x] Yt[j][x], zero outside the leading m x m block
+    if ((e = gemm64<true>({Xt, D, (size_t)m * D}, {Yt, D, (size_t)m * D}, W, mp, (size_t)mp * mp, m, m, D, D, mp, mp, batch, st)) != hipSuccess)
+      return e;
     hipLaunchKernelGGL(identity_kernel, dim3((unsigned)(((size_t)mp * mp + 255) / 256), batch), dim3(256), 0, st, V, mp);
     SKV_CHECK();
     for (int sw = 0; sw < n_sweeps; ++sw)
@@ -649,12 +609,13 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
         hipLaunchKernelGGL(jacobi_step_kernel, dim3(mp / 2, batch), dim3(64), 0, st, W, V, mp, stp);
         SKV_CHECK();
       }
-    hipLaunchKernelGGL(ritz_select_kernel, dim3(batch), dim3(256), (size_t)mp * sizeof(double), st, W, V, Wsel, sigma_out, mp,
-                       m, r);
+    hipLaunchKernelGGL(ritz_select_kernel, dim3(batch), dim3(1024), (size_t)m * sizeof(double), st, W, order, sigma_out, mp, m, r);
     SKV_CHECK();
   }
-  // Psi_t [r x D] = Wsel [r x m] Xt [m x D]
-  if ((e = dgemm(Wsel, Xt, Psi_t, r, D, m, m, 1, D, 1, D, (long)r * m, (long)m * D, (long)r * D, batch, st)) != hipSuccess) return e;
+  // Psi_t [r x D] = (the chosen columns of V)^T [r x mp] Xt [m x D]; V is zero in those rows beyond m
+  if ((e = gemm64<false>({V, mp, (size_t)mp * mp}, {Xt, D, (size_t)m * D}, Psi_t, D, (size_t)r * D, r, D, mp, m, r, D, batch, st,
+                         order, r)) != hipSuccess)
+    return e;
   // 3. sign convention, B, A = K Psi
   if (kv_bytes == 1) hipLaunchKernelGGL(emit_b_kernel<1>, dim3(r, batch), dim3(256), 0, st, Psi_t, B, D, r, hkv, d);
   else hipLaunchKernelGGL(emit_b_kernel<2>, dim3(r, batch), dim3(256), 0, st, Psi_t, B, D, r, hkv, d);
