@@ -7,7 +7,7 @@
 //      elements are exact, the sum is fp64) -- the dense contraction, 2 s D^2 flops, K streamed once per
 //      column-block pair; only blocks on and above the diagonal are formed, gram_finish sums the token
 //      splits and mirrors;
-//   2. subspace iteration on m = r + oversample vectors (X <- orth(G X), modified Gram-Schmidt in groups), then one
+//   2. subspace iteration on m = r + oversample vectors (X <- orth(G X), by Cholesky factorisation of the vectors' products), then one
 //      Rayleigh-Ritz step: T = X^T G X, eigenvectors of the small T by one-sided Jacobi rotations, the r
 //      largest kept -- all fp64, small, one launch per dependent step;
 //   3. sign convention (largest-magnitude component positive), B written, and project_kernel: A = K Psi on
@@ -155,15 +155,6 @@ __global__ __launch_bounds__(256) void gram_finish_kernel(const double* __restri
 }
 
 // ---- 2. small fp64 linear algebra --------------------------------------------------------------------
-__device__ __forceinline__ double block_sum_256(double v, double* sm) {
-  v = wave_sum_f64(v);
-  const int wave = threadIdx.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sm[wave] = v;
-  __syncthreads();
-  return sm[0] + sm[1] + sm[2] + sm[3];
-}
-
 // start vectors: Xt[b][i][x] uniform in (-1, 1) from a counter-based hash (same numbers on every run)
 __global__ __launch_bounds__(256) void subspace_init_kernel(double* __restrict__ Xt, size_t n) {
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
@@ -173,126 +164,6 @@ __global__ __launch_bounds__(256) void subspace_init_kernel(double* __restrict__
   z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
   z ^= z >> 31;
   Xt[i] = (double)(int64_t)(z >> 11) * (1.0 / 4503599627370496.0) - 1.0;  // 53 bits -> [-1, 1)
-}
-
-// sums of NV values per thread over the 256 threads of the workgroup (result in every thread)
-template <int NV>
-__device__ __forceinline__ void block_sum_multi(double (&v)[NV], double (*sm)[NV]) {
-  const int wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int i = 0; i < NV; ++i) v[i] = wave_sum_f64(v[i]);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0)
-#pragma unroll
-    for (int i = 0; i < NV; ++i) sm[wave][i] = v[i];
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < NV; ++i) v[i] = sm[0][i] + sm[1][i] + sm[2][i] + sm[3][i];
-}
-
-// Modified Gram-Schmidt in groups of Q vectors (vectors are not normalised until the end), two launches per group
-// instead of one per vector.  First the Q pivots j .. j+q-1 are made orthogonal among themselves by one workgroup
-// per sequence that keeps them in registers (EPT elements per thread and vector) ...
-template <int Q, int EPT>
-__global__ __launch_bounds__(256) void mgs_pivots_kernel(double* __restrict__ Xt, int D, int m, int j, int q) {
-  __shared__ double sm[4][Q];
-  double* X0 = Xt + ((size_t)blockIdx.x * m + j) * D;
-  double p[Q][EPT];
-#pragma unroll
-  for (int a = 0; a < Q; ++a)
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      const int x = threadIdx.x + 256 * e;
-      p[a][e] = (a < q && x < D) ? X0[(size_t)a * D + x] : 0.0;
-    }
-#pragma unroll
-  for (int a = 0; a + 1 < Q; ++a) {
-    double v[Q];  // v[a] = |p_a|^2, v[b] = p_a . p_b for b > a
-#pragma unroll
-    for (int bb = 0; bb < Q; ++bb) {
-      v[bb] = 0.0;
-      if (bb >= a)
-#pragma unroll
-        for (int e = 0; e < EPT; ++e) v[bb] = fma(p[a][e], p[bb][e], v[bb]);
-    }
-    block_sum_multi<Q>(v, sm);
-    if (v[a] > 0.0) {
-#pragma unroll
-      for (int bb = a + 1; bb < Q; ++bb) {
-        const double f = v[bb] / v[a];
-#pragma unroll
-        for (int e = 0; e < EPT; ++e) p[bb][e] = fma(-f, p[a][e], p[bb][e]);
-      }
-    }
-  }
-#pragma unroll
-  for (int a = 1; a < Q; ++a)
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      const int x = threadIdx.x + 256 * e;
-      if (a < q && x < D) X0[(size_t)a * D + x] = p[a][e];
-    }
-}
-// ... then every later vector k loses its components along the q pivots, one after the other
-template <int Q, int EPT>
-__global__ __launch_bounds__(256) void mgs_project_kernel(double* __restrict__ Xt, int D, int m, int j, int q) {
-  __shared__ double sm[4][2];
-  const int k = j + q + blockIdx.x, b = blockIdx.y;
-  const double* P0 = Xt + ((size_t)b * m + j) * D;
-  double* xk = Xt + ((size_t)b * m + k) * D;
-  double x[EPT];
-#pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    const int c = threadIdx.x + 256 * e;
-    x[e] = c < D ? xk[c] : 0.0;
-  }
-#pragma unroll
-  for (int a = 0; a < Q; ++a) {
-    if (a >= q) break;
-    double pa[EPT], v[2] = {0.0, 0.0};
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      const int c = threadIdx.x + 256 * e;
-      pa[e] = c < D ? P0[(size_t)a * D + c] : 0.0;
-      v[0] = fma(pa[e], pa[e], v[0]);
-      v[1] = fma(pa[e], x[e], v[1]);
-    }
-    block_sum_multi<2>(v, sm);
-    if (v[0] > 0.0) {
-      const double f = v[1] / v[0];
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) x[e] = fma(-f, pa[e], x[e]);
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    const int c = threadIdx.x + 256 * e;
-    if (c < D) xk[c] = x[e];
-  }
-}
-// key widths beyond what the grouped kernels hold in registers: one launch per vector
-__global__ __launch_bounds__(256) void mgs_step_kernel(double* __restrict__ Xt, int D, int m, int j) {
-  __shared__ double sm[4];
-  const int k = j + 1 + blockIdx.x, b = blockIdx.y;
-  double* xj = Xt + ((size_t)b * m + j) * D;
-  double* xk = Xt + ((size_t)b * m + k) * D;
-  double njj = 0.0, d = 0.0;
-  for (int x = threadIdx.x; x < D; x += 256) { const double a = xj[x]; njj = fma(a, a, njj); d = fma(a, xk[x], d); }
-  njj = block_sum_256(njj, sm);
-  d = block_sum_256(d, sm);
-  if (!(njj > 0.0)) return;
-  const double f = d / njj;
-  for (int x = threadIdx.x; x < D; x += 256) xk[x] = fma(-f, xj[x], xk[x]);
-}
-__global__ __launch_bounds__(256) void normalize_rows_kernel(double* __restrict__ Xt, int D) {
-  __shared__ double sm[4];
-  double* x = Xt + (size_t)blockIdx.x * D;
-  double n = 0.0;
-  for (int i = threadIdx.x; i < D; i += 256) n = fma(x[i], x[i], n);
-  n = block_sum_256(n, sm);
-  if (!(n > 0.0)) return;
-  const double inv = 1.0 / sqrt(n);
-  for (int i = threadIdx.x; i < D; i += 256) x[i] *= inv;
 }
 
 // V <- identity (mp x mp per sequence); W is filled by the product X^T G X before
@@ -521,6 +392,8 @@ FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample) {
   p.G = off; off += up((size_t)batch * DD * 8);
   p.Xt = off; off += up((size_t)batch * p.m * D * 8);
   p.Yt = off; off += up((size_t)batch * p.m * D * 8);
+  p.S = off; off += up((size_t)batch * p.m * p.m * 8);
+  p.Lp = off; off += up((size_t)batch * ((p.m + 15) / 16) * ((p.m + 15) / 16 + 1) / 2 * 256 * 8);
   p.W = off; off += up((size_t)batch * p.mp * p.mp * 8);
   p.V = off; off += up((size_t)batch * p.mp * p.mp * 8);
   p.order = off; off += up((size_t)batch * r * 4);
@@ -537,6 +410,8 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
   double* G = reinterpret_cast<double*>(ws + pl.G);
   double* Xt = reinterpret_cast<double*>(ws + pl.Xt);
   double* Yt = reinterpret_cast<double*>(ws + pl.Yt);
+  double* S = reinterpret_cast<double*>(ws + pl.S);
+  double* Lp = reinterpret_cast<double*>(ws + pl.Lp);
   double* W = reinterpret_cast<double*>(ws + pl.W);
   double* V = reinterpret_cast<double*>(ws + pl.V);
   int32_t* order = reinterpret_cast<int32_t*>(ws + pl.order);
@@ -557,45 +432,35 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
   const size_t nx = (size_t)batch * m * D;
   hipLaunchKernelGGL(subspace_init_kernel, dim3((unsigned)((nx + 255) / 256)), dim3(256), 0, st, Xt, nx);
   SKV_CHECK();
-  auto orthonormalise = [&](double* X) -> hipError_t {
-    hipError_t err = hipSuccess;
-    if (D <= 1024) {          // groups of 8 vectors, 4 elements per thread
-      for (int j = 0; j < m && err == hipSuccess; j += 8) {
-        const int q = std::min(8, m - j);
-        hipLaunchKernelGGL((mgs_pivots_kernel<8, 4>), dim3(batch), dim3(256), 0, st, X, D, m, j, q);
-        if (j + q < m) hipLaunchKernelGGL((mgs_project_kernel<8, 4>), dim3(m - j - q, batch), dim3(256), 0, st, X, D, m, j, q);
-        err = hipGetLastError();
-      }
-    } else if (D <= 3072) {   // groups of 4 vectors, 12 elements per thread
-      for (int j = 0; j < m && err == hipSuccess; j += 4) {
-        const int q = std::min(4, m - j);
-        hipLaunchKernelGGL((mgs_pivots_kernel<4, 12>), dim3(batch), dim3(256), 0, st, X, D, m, j, q);
-        if (j + q < m) hipLaunchKernelGGL((mgs_project_kernel<4, 12>), dim3(m - j - q, batch), dim3(256), 0, st, X, D, m, j, q);
-        err = hipGetLastError();
-      }
-    } else {
-      for (int j = 0; j + 1 < m && err == hipSuccess; ++j) {
-        hipLaunchKernelGGL(mgs_step_kernel, dim3(m - 1 - j, batch), dim3(256), 0, st, X, D, m, j);
-        err = hipGetLastError();
-      }
-    }
+  // X <- orthonormal basis of the rows of Y, each row from the ones before it (see chol_kernel)
+  const int nbc = (m + 15) / 16;
+  auto orthonormalise = [&](const double* Y, double* X) -> hipError_t {
+    hipError_t err = gemm64<true>({Y, D, (size_t)m * D}, {Y, D, (size_t)m * D}, S, m, (size_t)m * m, m, m, D, D, m, m, batch, st);
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(normalize_rows_kernel, dim3(batch * m), dim3(256), 0, st, X, D);
+#define SKV_ORTH(NBW_, NB_)                                                                                       \
+  do {                                                                                                            \
+    hipLaunchKernelGGL(chol_kernel<NBW_>, dim3(batch), dim3(512), 0, st, S, Lp, m, m, nbc);                         \
+    hipLaunchKernelGGL(trsm_kernel<NB_>, dim3(D / 16, batch), dim3(64), 0, st, Lp, Y, X, m, nbc, D);                \
+  } while (0)
+    // (blocks per wave of the eight, block rows held): up to 80, 192, 224, 288 vectors
+    if (nbc <= 5) SKV_ORTH(2, 5);
+    else if (nbc <= 12) SKV_ORTH(10, 12);
+    else if (nbc <= 14) SKV_ORTH(14, 14);
+    else SKV_ORTH(22, kMaxFactorBlocks);
+#undef SKV_ORTH
     return hipGetLastError();
   };
   auto times_gram = [&](const double* X, double* Y) {   // Y = X G; G is symmetric, so its rows are its columns
     return gemm64<true>({X, D, (size_t)m * D}, {G, D, (size_t)D * D}, Y, D, (size_t)m * D, m, D, D, D, m, D, batch, st);
   };
-  if ((e = orthonormalise(Xt)) != hipSuccess) return e;
   for (int it = 0; it < n_iter; ++it) {
-    // Yt [m x D] = Xt [m x D] G [D x D]   (G is symmetric)
     if ((e = times_gram(Xt, Yt)) != hipSuccess) return e;
-    // every second product only: two products square the condition number of the basis (~1e8 at most for the
-    // spectra this is meant for), which modified Gram-Schmidt still handles; the last basis is done twice
-    if (((it & 1) || it + 1 == n_iter) && (e = orthonormalise(Yt)) != hipSuccess) return e;
-    if (it + 1 == n_iter && (e = orthonormalise(Yt)) != hipSuccess) return e;  // once more before the Ritz step
-    double* tmp = Xt; Xt = Yt; Yt = tmp;
+    if ((e = orthonormalise(Yt, Xt)) != hipSuccess) return e;
   }
+  // twice more before the Ritz step: the first brings the basis to the rounding unit, the second does the same for
+  // vectors whose pivots were rounding in the one before
+  if ((e = orthonormalise(Xt, Yt)) != hipSuccess) return e;
+  if ((e = orthonormalise(Yt, Xt)) != hipSuccess) return e;
   // Rayleigh-Ritz: T = X^T G X = Xt (Xt G)^T
   if ((e = times_gram(Xt, Yt)) != hipSuccess) return e;
   {
