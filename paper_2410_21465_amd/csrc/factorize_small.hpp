@@ -110,11 +110,20 @@ __device__ __forceinline__ double lane_f64(double x, int l) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l), __builtin_amdgcn_readlane(__double2loint(x), l));
 }
 
+// 1 / sqrt(x) for a positive normal x: the hardware's estimate and two Newton steps (the library's 1.0 / sqrt(x) is
+// three times the chain)
+__device__ __forceinline__ double rsqrt_f64(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) y = fma(y * 0.5, fma(-x * y, y, 1.0), y);
+  return y;
+}
+
 // Cholesky factor of S [m][ld] (lower triangle read), one workgroup of eight waves per sequence.  Lp: packed blocks in
 // operand order, off the diagonal -L, on it the inverse of L's block (what trsm_kernel multiplies by).
 // The trailing blocks stay in the accumulators of the waves (blocks dealt out in turn, NBW per wave) for the whole
 // factorisation; only the current block column goes through LDS.  What bounds it is the chain of pivots: 16 rsqrt + updates
-// per diagonal block in one wave, which carries the unit matrix along in a second group of lanes and so ends with the
+// per diagonal block in one wave (60 us for 192 vectors, 79 us with the library's square root and division), which carries the unit matrix along in a second group of lanes and so ends with the
 // inverse as well.
 // A pivot below kPivotFloor of the vector's own square is rounding: it is set to that floor, which leaves the vector's
 // remainder at a size that the next pass can work on, and nothing is projected on it; a zero vector stays zero.
@@ -163,16 +172,13 @@ __global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S,
 #pragma unroll
       for (int p = 0; p < 16; ++p) {
         const double d = lane_f64(a[p], p), e = lane_f64(e0, p);
-        const bool none = !(e > 0.0), low = !none && d < kPivotFloor * e;
+        const bool none = !(e > 1e-280), low = !none && d < kPivotFloor * e, skip = none || low;
         const double piv = none ? 1.0 : (low ? kPivotFloor * e : d);
-        const double mult = a[p] * (1.0 / sqrt(piv));
-        a[p] = mult;
-        if (none || low) {
-          floored |= 1u << p;
-        } else {
+        a[p] *= rsqrt_f64(piv);
+        floored |= skip ? 1u << p : 0u;
+        const double mult = skip ? 0.0 : a[p];
 #pragma unroll
-          for (int j = p + 1; j < 16; ++j) a[j] = fma(-mult, lane_f64(mult, j), a[j]);
-        }
+        for (int j = p + 1; j < 16; ++j) a[j] = fma(-mult, lane_f64(mult, j), a[j]);
       }
       if (kq == 1) {
 #pragma unroll
@@ -261,6 +267,184 @@ __global__ __launch_bounds__(64) void trsm_kernel(const double* __restrict__ Lp,
       if (i > k && i < nb)
 #pragma unroll
         for (int t = 0; t < 4; ++t) acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(cur[i][t], x[t], acc[i], 0, 0, 0);
+    }
+  }
+}
+
+// ---- eigenvectors of a small symmetric matrix: one-sided Jacobi in blocks ----------------------------------
+// Columns of W (initially T; column p is the row W[p*mp ...] in memory) are rotated until they are orthogonal, the same
+// rotations accumulated in V: then the norms of W's columns are the eigenvalues of T and the columns of V its eigenvectors.
+// The columns are taken as nb = mp / 16 blocks; a step pairs the blocks up (circle method: (nb-1, st), ((st+i) mod (nb-1),
+// (st-i) mod (nb-1))), and a workgroup makes the 16 x 16 pairs of columns between its two blocks orthogonal (in the first
+// step of a sweep all pairs of its 32 columns): it forms the 32 x 32 products of the columns on the matrix instruction,
+// rotates those (two-sided, in LDS, 16 disjoint rotations at a time, accumulated in J) and applies J to its columns as one
+// product.  A rotation's angle thus costs two rounds of LDS and a barrier, not a pass over the columns and a launch: a
+// sweep of 192 columns is 11 launches of 17 us where a launch per set of 96 single rotations took 191 of 4.5 us, and six
+// sweeps do (1.2 ms in all, 8.1 ms before, one sequence; 16 sequences: 1.5 ms, 11.4 ms).
+// V is not needed before the end: its product with J is done by other workgroups of the next step's launch.
+// A sweep in which every cosine met was below kJacobiDone needs no successor (what is left is its square): the launches of
+// the later ones end at once.  sweep_max [batch][sweeps]: the largest cosine of each sweep (its bits; cosines are >= 0).
+constexpr float kJacobiDone = 1e-10f;
+__device__ __forceinline__ bool jacobi_active(const int32_t* sweep_max, int sweep) {
+  // (written so that a cosine that is not a number goes on)
+  return sweep == 0 || !(__int_as_float(sweep_max[sweep - 1]) < kJacobiDone);
+}
+// (c, s) of the rotation that makes two columns with squares al, be and product ga orthogonal: tan 2 theta = 2 ga / (be - al),
+// |theta| <= pi / 4, through cos 2 theta and two reciprocal square roots; the exponent is taken out first.
+__device__ __forceinline__ void rotation(double al, double be, double ga, double& c, double& s) {
+  double d = be - al, g = 2.0 * ga;
+  const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(d), fabs(g)));
+  d = ldexp(d, ex); g = ldexp(g, ex);
+  const double r = rsqrt_f64(fma(d, d, g * g));
+  const double c2 = fma(0.5 * fabs(d), r, 0.5), rc = rsqrt_f64(c2);
+  c = c2 * rc;
+  s = 0.5 * g * r * rc;
+  if (d < 0.0) s = -s;
+}
+// step = sweep * (nb - 1) + st.  Workgroups [0, nb/2): step `step` on W (none when step == n_steps); [nb/2, nb): the step
+// before, on V.  J and idle (whether its J is the identity) alternate between two halves from step to step.
+__global__ __launch_bounds__(512) void jacobi_block_kernel(double* __restrict__ W, double* __restrict__ V,
+                                                           double* __restrict__ Jbuf, int32_t* __restrict__ idle,
+                                                           int32_t* __restrict__ sweep_max, int mp, int step, int n_steps,
+                                                           int n_sweeps) {
+  constexpr int P = 33;                     // pitch of the 32 x 32 matrices in LDS
+  __shared__ double red[8 * 3 * 256];       // partial products of the waves; then the second copy of S, and J
+  __shared__ double S0[32 * P];
+  __shared__ float wmax[8];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int sub = lane & 15, kq = lane >> 4;
+  const int nb = mp / 16, np = nb / 2, b = blockIdx.y, batch = gridDim.y;
+  const bool on_v = (int)blockIdx.x >= np;
+  const int mine = on_v ? step - 1 : step, pair = on_v ? blockIdx.x - np : blockIdx.x;
+  if (mine < 0 || mine >= n_steps) return;
+  const int sweep = mine / (nb - 1), st = mine - sweep * (nb - 1);
+  sweep_max += (size_t)b * n_sweeps;
+  if (!jacobi_active(sweep_max, sweep)) return;
+  const int slot = ((mine & 1) * batch + b) * np + pair;
+  double* Jg = Jbuf + (size_t)slot * 1024;
+  int pb, qb;
+  if (pair == 0) { pb = nb - 1; qb = st; }
+  else { pb = (st + pair) % (nb - 1); qb = (st - pair + (nb - 1)) % (nb - 1); }
+  double* M = (on_v ? V : W) + (size_t)b * mp * mp;
+  auto row = [&](int i) { return M + (size_t)((i < 16 ? pb * 16 : qb * 16 - 16) + i) * mp; };
+  const double* Js;                         // J, row p, column q at Js[p * pitch + q]
+  int pitch;
+  if (on_v) {
+    if (idle[slot]) return;
+    Js = Jg; pitch = 32;
+  } else {
+    // products of the 32 columns: tiles (0,0), (0,1), (1,1), the contraction dealt to the waves 16 at a time
+    f64x4 g[3];
+#pragma unroll
+    for (int t = 0; t < 3; ++t) g[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+    const double* r0 = row(sub) + 4 * kq;
+    const double* r1 = row(16 + sub) + 4 * kq;
+    for (int k0 = 16 * wave; k0 < mp; k0 += 16 * 8) {
+      const double2 a0 = *reinterpret_cast<const double2*>(r0 + k0), a1 = *reinterpret_cast<const double2*>(r0 + k0 + 2);
+      const double2 c0 = *reinterpret_cast<const double2*>(r1 + k0), c1 = *reinterpret_cast<const double2*>(r1 + k0 + 2);
+      const double x[4] = {a0.x, a0.y, a1.x, a1.y}, y[4] = {c0.x, c0.y, c1.x, c1.y};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        g[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[e], x[e], g[0], 0, 0, 0);
+        g[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[e], y[e], g[1], 0, 0, 0);
+        g[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(y[e], y[e], g[2], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) red[(wave * 3 + t) * 256 + (4 * j + kq) * 16 + sub] = g[t][j];
+    __syncthreads();
+    for (int i = threadIdx.x; i < 3 * 256; i += 512) {
+      double v = 0.0;
+#pragma unroll
+      for (int w = 0; w < 8; ++w) v += red[w * 768 + i];
+      const int t = i >> 8, r = (i >> 4) & 15, c = i & 15;
+      if (t == 0) S0[r * P + c] = v;
+      if (t == 1) { S0[r * P + 16 + c] = v; S0[(16 + c) * P + r] = v; }
+      if (t == 2) S0[(16 + r) * P + 16 + c] = v;
+    }
+    __syncthreads();
+    // largest cosine among the pairs this step is about
+    float big = 0.0f;
+    for (int i = threadIdx.x; i < 1024; i += 512) {
+      const int r = i >> 5, c = i & 31;
+      if (r < c && (st == 0 || (r < 16 && c >= 16))) {
+        const double ga = fabs(S0[r * P + c]), n2 = sqrt(fmax(S0[r * P + r], 0.0)) * sqrt(fmax(S0[c * P + c], 0.0));
+        if (!(ga <= 1e-300)) { const float x = (float)(ga / n2); big = !(x <= big) ? x : big; }
+      }
+    }
+#pragma unroll
+    for (int x = 32; x >= 1; x >>= 1) { const float o = __shfl_xor(big, x, kWave); big = !(o <= big) ? o : big; }
+    if (lane == 0) wmax[wave] = big;
+    double* S1 = red;                      // (the partial products have been read)
+    double* J = red + 32 * P;
+    for (int i = threadIdx.x; i < 32 * P; i += 512) J[i] = i / P == i % P ? 1.0 : 0.0;
+    __syncthreads();
+    big = wmax[0];
+#pragma unroll
+    for (int w = 1; w < 8; ++w) big = !(wmax[w] <= big) ? wmax[w] : big;
+    const bool rest = big <= 1e-17f;       // nothing that a rotation would change
+    if (threadIdx.x == 0) {
+      atomicMax(&sweep_max[sweep], __float_as_int(big));
+      idle[slot] = rest ? 1 : 0;
+    }
+    if (rest) return;
+    const int rounds = st == 0 ? 31 : 16;
+    double *Sa = S0, *Sb = S1;
+    for (int t = 0; t < rounds; ++t) {
+      // the 16 disjoint pairs of this round: across the two blocks, or the circle method over all 32 columns
+      auto members = [&](int i, int& p, int& q) {
+        if (st != 0) { p = i; q = 16 + ((i + t) & 15); }
+        else if (i == 0) { p = 31; q = t; }
+        else { p = t + i; p -= p >= 31 ? 31 : 0; q = t - i; q += q < 0 ? 31 : 0; }
+      };
+      int p, q;
+      members(sub, p, q);
+      const double al = Sa[p * P + p], be = Sa[q * P + q], ga = Sa[p * P + q];
+      double c = 1.0, sn = 0.0;
+      if (fabs(ga) > 1e-300 && ga * ga > 1e-34 * (al * be)) rotation(al, be, ga, c, sn);
+      if (wave < 4) {                      // S: rows of pair u, columns of pair sub
+        const int u = wave * 4 + kq;
+        const double cu = __shfl(c, u, kWave), su = __shfl(sn, u, kWave);
+        int pu, qu;
+        members(u, pu, qu);
+        const double pp = Sa[pu * P + p], pq = Sa[pu * P + q], qp = Sa[qu * P + p], qq = Sa[qu * P + q];
+        const double tp = cu * pp - su * qp, tq = cu * pq - su * qq, bp = su * pp + cu * qp, bq = su * pq + cu * qq;
+        const bool own = u == sub;         // (the rotated pair itself: zero by construction)
+        Sb[pu * P + p] = c * tp - sn * tq; Sb[pu * P + q] = own && sn != 0.0 ? 0.0 : sn * tp + c * tq;
+        Sb[qu * P + p] = own && sn != 0.0 ? 0.0 : c * bp - sn * bq; Sb[qu * P + q] = sn * bp + c * bq;
+      } else {                             // J: columns of pair sub, eight rows per wave
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          double* jr = J + ((wave - 4) * 8 + kq * 2 + e) * P;
+          const double x = jr[p], y = jr[q];
+          jr[p] = c * x - sn * y; jr[q] = sn * x + c * y;
+        }
+      }
+      __syncthreads();
+      double* tmp = Sa; Sa = Sb; Sb = tmp;
+    }
+    for (int i = threadIdx.x; i < 1024; i += 512) Jg[i] = J[(i >> 5) * P + (i & 31)];
+    Js = J; pitch = P;
+  }
+  // new column q = sum_p J[p][q] column p, 16 entries of the 32 columns per wave at a time
+  double ja[2][8];
+#pragma unroll
+  for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+    for (int t = 0; t < 8; ++t) ja[mt][t] = Js[(4 * t + kq) * pitch + 16 * mt + sub];
+  for (int c0 = 16 * wave; c0 < mp; c0 += 16 * 8) {
+    double x[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) x[t] = row(4 * t + kq)[c0 + sub];
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) {
+      f64x4 y = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int t = 0; t < 8; ++t) y = __builtin_amdgcn_mfma_f64_16x16x4f64(ja[mt][t], x[t], y, 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) row(16 * mt + 4 * j + kq)[c0 + sub] = y[j];
     }
   }
 }

@@ -8,8 +8,8 @@
 //      column-block pair; only blocks on and above the diagonal are formed, gram_finish sums the token
 //      splits and mirrors;
 //   2. subspace iteration on m = r + oversample vectors (X <- orth(G X), by Cholesky factorisation of the vectors' products), then one
-//      Rayleigh-Ritz step: T = X^T G X, eigenvectors of the small T by one-sided Jacobi rotations, the r
-//      largest kept -- all fp64, small, one launch per dependent step;
+//      Rayleigh-Ritz step: T = X^T G X, eigenvectors of the small T by one-sided Jacobi rotations in
+//      blocks, the r largest kept -- all fp64, small, one launch per dependent step (factorize_small.hpp);
 //   3. sign convention (largest-magnitude component positive), B written, and project_kernel: A = K Psi on
 //      the same matrix instruction.
 // Operand layout of v_mfma_f64_16x16x4f64 as measured on gfx950: A lane l holds (m = l % 16, k = l / 16),
@@ -140,18 +140,32 @@ __global__ __launch_bounds__(64) void gram_kernel(const void* __restrict__ K, do
       }
 }
 
-// G[b][i][j] = sum over the splits of the block that holds (i, j) or, below the diagonal blocks, (j, i)
+// G[b][i][j] = sum over the splits of the block that holds (i, j), written to (j, i) as well.  One 32 x 32 tile on or above
+// the diagonal per workgroup; the mirrored copy goes through LDS so that both are written in rows.  (Reading the mirrored
+// element per thread instead took 165 us for 32 splits of 1024 columns.)
 __global__ __launch_bounds__(256) void gram_finish_kernel(const double* __restrict__ part, double* __restrict__ G, int D,
-                                                          int n_splits, int batch) {
-  const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-  const int b = blockIdx.y;
-  if (idx >= (size_t)D * D) return;
-  const int i = (int)(idx / D), j = (int)(idx % D);
-  const bool upper = i / 64 <= j / 64;
-  const size_t src = upper ? (size_t)i * D + j : (size_t)j * D + i;
-  double sum = 0.0;
-  for (int sp = 0; sp < n_splits; ++sp) sum += part[((size_t)sp * batch + b) * D * D + src];
-  G[(size_t)b * D * D + idx] = sum;
+                                                          int nt, int n_splits, int batch) {
+  __shared__ double tile[32][33];
+  int p = blockIdx.x, ti = 0;   // tile index -> (ti, tj), ti <= tj, row by row of the upper triangle
+  while (p >= nt - ti) { p -= nt - ti; ++ti; }
+  const int tj = ti + p, b = blockIdx.y;
+  const int x = threadIdx.x & 31, y0 = threadIdx.x >> 5;
+  const size_t DD = (size_t)D * D, off = (size_t)b * DD;
+  double sum[4] = {0.0, 0.0, 0.0, 0.0};
+  const double* src = part + off + (size_t)(ti * 32 + y0) * D + tj * 32 + x;
+#pragma unroll 4
+  for (int sp = 0; sp < n_splits; ++sp)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) sum[u] += src[(size_t)sp * batch * DD + (size_t)8 * u * D];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    G[off + (size_t)(ti * 32 + y0 + 8 * u) * D + tj * 32 + x] = sum[u];
+    tile[y0 + 8 * u][x] = sum[u];
+  }
+  if (ti == tj) return;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 4; ++u) G[off + (size_t)(tj * 32 + y0 + 8 * u) * D + ti * 32 + x] = tile[x][y0 + 8 * u];
 }
 
 // ---- 2. small fp64 linear algebra --------------------------------------------------------------------
@@ -166,39 +180,13 @@ __global__ __launch_bounds__(256) void subspace_init_kernel(double* __restrict__
   Xt[i] = (double)(int64_t)(z >> 11) * (1.0 / 4503599627370496.0) - 1.0;  // 53 bits -> [-1, 1)
 }
 
-// V <- identity (mp x mp per sequence); W is filled by the product X^T G X before
-__global__ __launch_bounds__(256) void identity_kernel(double* __restrict__ V, int mp) {
+// before the Jacobi sweeps: V <- identity (mp x mp per sequence), the largest cosine of every sweep <- 0
+__global__ __launch_bounds__(256) void jacobi_init_kernel(double* __restrict__ V, int32_t* __restrict__ sweep_max, int mp,
+                                                          int n_sweeps) {
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < (size_t)n_sweeps) sweep_max[(size_t)blockIdx.y * n_sweeps + i] = 0;
   if (i >= (size_t)mp * mp) return;
   V[(size_t)blockIdx.y * mp * mp + i] = (i / mp == i % mp) ? 1.0 : 0.0;
-}
-
-// One step of a one-sided Jacobi sweep on the columns of W (initially T = X^T G X, symmetric; column p is
-// W[p*mp ...]) with the rotations accumulated in V: after convergence the columns of W are orthogonal, their
-// norms are the eigenvalues of T and the columns of V its eigenvectors.  Pairs of step `st` by the circle
-// method over mp (even) players: (mp-1, st), ((st+i) mod (mp-1), (st-i) mod (mp-1)).  One wave per pair.
-__global__ __launch_bounds__(64) void jacobi_step_kernel(double* __restrict__ W, double* __restrict__ V, int mp, int st) {
-  const int i = blockIdx.x, b = blockIdx.y, lane = threadIdx.x;
-  int p, q;
-  if (i == 0) { p = mp - 1; q = st; }
-  else { p = (st + i) % (mp - 1); q = (st - i + (mp - 1)) % (mp - 1); }
-  double* wp = W + ((size_t)b * mp + p) * mp;
-  double* wq = W + ((size_t)b * mp + q) * mp;
-  double al = 0.0, be = 0.0, ga = 0.0;
-  for (int x = lane; x < mp; x += 64) { const double a = wp[x], c = wq[x]; al = fma(a, a, al); be = fma(c, c, be); ga = fma(a, c, ga); }
-  al = wave_sum_f64(al); be = wave_sum_f64(be); ga = wave_sum_f64(ga);
-  if (!(fabs(ga) > 1e-300) || fabs(ga) <= 1e-17 * sqrt(al) * sqrt(be)) return;
-  const double zeta = (be - al) / (2.0 * ga);
-  const double t = (zeta >= 0.0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-  const double c = 1.0 / sqrt(1.0 + t * t), sn = c * t;
-  double* vp = V + ((size_t)b * mp + p) * mp;
-  double* vq = V + ((size_t)b * mp + q) * mp;
-  for (int x = lane; x < mp; x += 64) {
-    const double a = wp[x], d = wq[x];
-    wp[x] = c * a - sn * d; wq[x] = sn * a + c * d;
-    const double e = vp[x], f = vq[x];
-    vp[x] = c * e - sn * f; vq[x] = sn * e + c * f;
-  }
 }
 
 // order [r]: the columns of W with the largest norms (ties: lower index), strongest first.  A wave per column for the
@@ -370,7 +358,7 @@ static hipError_t gemm64(Mat A, Mat B, double* C, int ldc, size_t strideC, int M
   return hipGetLastError();
 }
 
-FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample) {
+FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int n_sweeps) {
   FactorizePlan p{};
   p.m = std::min(D, r + oversample);
   p.mp = (p.m + 31) / 32 * 32;
@@ -396,6 +384,9 @@ FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample) {
   p.Lp = off; off += up((size_t)batch * ((p.m + 15) / 16) * ((p.m + 15) / 16 + 1) / 2 * 256 * 8);
   p.W = off; off += up((size_t)batch * p.mp * p.mp * 8);
   p.V = off; off += up((size_t)batch * p.mp * p.mp * 8);
+  p.Jbuf = off; off += up((size_t)2 * batch * (p.mp / 32) * 1024 * 8);
+  p.idle = off; off += up((size_t)2 * batch * (p.mp / 32) * 4);
+  p.sweep_max = off; off += up((size_t)batch * n_sweeps * 4);
   p.order = off; off += up((size_t)batch * r * 4);
   p.Psi_t = off; off += up((size_t)batch * r * D * 8);
   p.total = off;
@@ -414,6 +405,9 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
   double* Lp = reinterpret_cast<double*>(ws + pl.Lp);
   double* W = reinterpret_cast<double*>(ws + pl.W);
   double* V = reinterpret_cast<double*>(ws + pl.V);
+  double* Jbuf = reinterpret_cast<double*>(ws + pl.Jbuf);
+  int32_t* idle = reinterpret_cast<int32_t*>(ws + pl.idle);
+  int32_t* sweep_max = reinterpret_cast<int32_t*>(ws + pl.sweep_max);
   int32_t* order = reinterpret_cast<int32_t*>(ws + pl.order);
   double* Psi_t = psi_out ? psi_out : reinterpret_cast<double*>(ws + pl.Psi_t);
   hipError_t e;
@@ -424,8 +418,8 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
     if (kv_bytes == 1) hipLaunchKernelGGL(gram_kernel<1>, grid, dim3(64), 0, st, k_pre, part, s, D, pl.nb, pl.tokens_per_split, batch);
     else hipLaunchKernelGGL(gram_kernel<2>, grid, dim3(64), 0, st, k_pre, part, s, D, pl.nb, pl.tokens_per_split, batch);
     SKV_CHECK();
-    hipLaunchKernelGGL(gram_finish_kernel, dim3((unsigned)(((size_t)D * D + 255) / 256), batch), dim3(256), 0, st, part, G, D,
-                       pl.n_splits, batch);
+    const int nt = D / 32;   // (the key width is a multiple of 32)
+    hipLaunchKernelGGL(gram_finish_kernel, dim3(nt * (nt + 1) / 2, batch), dim3(256), 0, st, part, G, D, nt, pl.n_splits, batch);
     SKV_CHECK();
   }
   // 2. subspace iteration: X <- orth(G X); rows of Xt are the vectors
@@ -467,13 +461,14 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
     // W [mp x mp]: T(i, j) = sum_x Xt[i][x] Yt[j][x], zero outside the leading m x m block
     if ((e = gemm64<true>({Xt, D, (size_t)m * D}, {Yt, D, (size_t)m * D}, W, mp, (size_t)mp * mp, m, m, D, D, mp, mp, batch, st)) != hipSuccess)
       return e;
-    hipLaunchKernelGGL(identity_kernel, dim3((unsigned)(((size_t)mp * mp + 255) / 256), batch), dim3(256), 0, st, V, mp);
+    hipLaunchKernelGGL(jacobi_init_kernel, dim3((unsigned)(((size_t)mp * mp + 255) / 256), batch), dim3(256), 0, st, V, sweep_max,
+                       mp, n_sweeps);
     SKV_CHECK();
-    for (int sw = 0; sw < n_sweeps; ++sw)
-      for (int stp = 0; stp < mp - 1; ++stp) {
-        hipLaunchKernelGGL(jacobi_step_kernel, dim3(mp / 2, batch), dim3(64), 0, st, W, V, mp, stp);
-        SKV_CHECK();
-      }
+    const int nbj = mp / 16, n_steps = n_sweeps * (nbj - 1);
+    for (int step = 0; step <= n_steps; ++step)   // (the last launch only brings V up to date)
+      hipLaunchKernelGGL(jacobi_block_kernel, dim3(nbj, batch), dim3(512), 0, st, W, V, Jbuf, idle, sweep_max, mp, step, n_steps,
+                         n_sweeps);
+    SKV_CHECK();
     hipLaunchKernelGGL(ritz_select_kernel, dim3(batch), dim3(1024), (size_t)m * sizeof(double), st, W, order, sigma_out, mp, m, r);
     SKV_CHECK();
   }

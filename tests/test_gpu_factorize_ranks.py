@@ -1,0 +1,59 @@
+"""shadowkv_factorize_keys over the ranks at which its small linear algebra changes shape (-m gpu): block rows of the
+Cholesky factor held per kernel (5 / 12 / 14 / 18 blocks of 16 vectors), vector counts that are no multiple of 16 or 32,
+as many vectors as the keys are wide, several sequences, and a spectrum with a few directions far above the rest."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2410_21465_amd import shadowkv as S
+
+pytestmark = pytest.mark.gpu
+
+# (batch, KV heads, head_dim, tokens, rank, leading directions of 1000 times the others' scale)
+CASES = [
+    (1, 1, 64, 96, 8, 0),         # 40 vectors
+    (2, 1, 64, 500, 64, 0),       # as many vectors as columns
+    (1, 3, 64, 1500, 48, 2),      # 80 vectors: the last size of the smallest kernel
+    (3, 2, 96, 700, 56, 0),       # 88 vectors: the first of the next
+    (1, 4, 96, 1111, 160, 3),     # 192 vectors, the default rank
+    (1, 4, 128, 2048, 168, 0),    # 200 vectors
+    (1, 4, 128, 1024, 192, 3),    # 224 vectors
+    (1, 5, 96, 1500, 200, 0),     # 232 vectors
+    (2, 6, 64, 1024, 256, 0),     # 288 vectors
+]
+
+
+@pytest.mark.parametrize("b,h,d,s,r,lead", CASES)
+def test_factors_at_every_shape_of_the_small_algebra(b, h, d, s, r, lead):
+    D = h * d
+    print(f"\n[case] b {b} h {h} d {d} s {s} r {r} lead {lead}", flush=True)
+    gen = torch.Generator(device="cpu").manual_seed(1000 * r + D)
+    scale = torch.exp(-torch.arange(D, dtype=torch.float64) / 24.0)
+    scale[:lead] *= 1000.0
+    k = torch.stack([torch.randn(s, D, generator=gen, dtype=torch.float64) * scale @
+                     torch.linalg.qr(torch.randn(D, D, generator=gen, dtype=torch.float64))[0] for _ in range(b)])
+    k = k.to(torch.bfloat16)
+    p = S.Params(batch=b, n_q_heads=h, n_kv_heads=h, head_dim=d, ctx_len=s, chunk_size=1, rank=r, n_outlier_chunks=0,
+                 topk_chunks=1, local_len=0)
+    got = S.factorize_keys(p, k.cuda(), want_vectors=True)
+    torch.cuda.synchronize()
+    psi, sig = got["psi"].cpu().numpy(), got["sigma"].cpu().numpy()
+    for i in range(b):
+        K = k[i].double().numpy()
+        G = K.T @ K
+        lam = np.linalg.eigvalsh(G)[::-1]
+        assert np.abs(psi[i] @ psi[i].T - np.eye(r)).max() < 1e-12
+        # rounding: 1e-12 of the largest eigenvalue.  Convergence: 16 iterations leave of the directions outside the
+        # m = r + 32 vectors a share (lam_{m+1} / lam_r)^16 of the start's, whose angle to a wanted direction has a tangent of
+        # order sqrt(D), 100 with room; a Ritz residual goes with that angle, a Ritz value with its square (the rounding of
+        # the keys to bf16 makes the end of these spectra flat, where it shows)
+        m = min(D, r + 32)
+        tan = min(1.0, 100.0 * (max(lam[m], 0.0) / lam[r - 1]) ** 16) if m < D else 0.0
+        resid = np.abs(psi[i] @ G - (sig[i] ** 2)[:, None] * psi[i]).max()
+        assert np.abs(sig[i] ** 2 - lam[:r]).max() <= 1e-12 * lam[0] + lam[r - 1] * tan ** 2
+        assert resid <= 1e-12 * lam[0] + lam[r - 1] * tan, (resid / lam[0], tan)
+        assert np.all(np.diff(sig[i]) <= 0)
+        want = torch.from_numpy(psi[i]).to(torch.float32).to(torch.bfloat16).view(r, h, d).permute(1, 0, 2)
+        assert (got["B"][i].cpu().float() - want.float()).abs().max() <= 2.0 ** -8
+        A = K @ psi[i].T
+        assert np.abs(got["A"][i, :s].cpu().double().numpy() - A).max() <= 2.0 ** -8 * np.abs(A).max()
