@@ -21,15 +21,20 @@ __device__ __forceinline__ bf16_t f32_to_bf16(float f) {
   return (bf16_t)(u >> 16);
 }
 
-// fp64 -> bf16 with a single rounding: truncate to fp32, make the result odd if
-// anything was lost (round-to-odd keeps the sticky information), then round the
-// fp32 to bf16 nearest-even.  fp32 carries 16 more fraction bits than bf16, so
-// the second rounding sees exactly what a direct rounding would.
-__device__ __forceinline__ bf16_t f64_to_bf16(double x) {
-  float f = __double2float_rz(x);
-  if ((double)f != x) f = __uint_as_float(__float_as_uint(f) | 1u);
-  return f32_to_bf16(f);
+// fp64 -> fp32, truncated and made odd if anything was lost (round-to-odd keeps the sticky information); NaN stays NaN.
+// From the nearest-even conversion, one step back where that went up: the library's truncating conversion branches.
+__device__ __forceinline__ float f64_to_f32_odd(double x) {
+  const float f = (float)x;
+  const double d = (double)f;
+  uint32_t u = __float_as_uint(f);
+  u -= fabs(d) > fabs(x) ? 1u : 0u;
+  u |= d != x ? 1u : 0u;
+  return __uint_as_float(u);
 }
+
+// fp64 -> bf16 with a single rounding: to fp32 by round-to-odd, then to bf16 nearest-even.  fp32 carries 16 more
+// fraction bits than bf16, so the second rounding sees exactly what a direct rounding would.
+__device__ __forceinline__ bf16_t f64_to_bf16(double x) { return f32_to_bf16(f64_to_f32_odd(x)); }
 
 // ---- FP8 E5M2 storage of the KV cache (section "Precision Sensitivity") --------------------
 // One byte per element: sign, 5 exponent bits (bias 15), 2 fraction bits, subnormals, infinities and
@@ -52,22 +57,17 @@ __device__ __forceinline__ uint32_t e5m2x2_to_bf16x2(uint32_t w) {
 }
 
 // fp64 -> E5M2 with a single rounding (nearest, ties to even; beyond the largest finite value 57344
-// the result is infinity, as in IEEE 754): fp64 -> fp32 by truncation with a sticky last bit, then
+// the result is infinity, as in IEEE 754): fp64 -> fp32 by round-to-odd, then
 // the fp32 is rounded at its 21st fraction bit, in integer arithmetic so that a carry moves into the
 // exponent by itself; below 2^-14 the codes are equally spaced (2^-16).
 __device__ __forceinline__ uint8_t f64_to_e5m2(double x) {
-  float f = __double2float_rz(x);
-  if ((double)f != x) f = __uint_as_float(__float_as_uint(f) | 1u);
-  const uint32_t u = __float_as_uint(f);
+  const uint32_t u = __float_as_uint(f64_to_f32_odd(x));
   const uint32_t sign = (u >> 24) & 0x80u, a = u & 0x7fffffffu;
-  if (a > 0x7f800000u) return (uint8_t)(sign | 0x7fu);
-  if (a >= 0x38800000u) {  // |f| >= 2^-14: a normal E5M2 number, or overflow
-    const uint32_t r = (a + 0xfffffu + ((a >> 21) & 1u)) >> 21;  // 8 exponent bits | 2 fraction bits
-    const int e = (int)(r >> 2) - 127 + 15;
-    if (e >= 31) return (uint8_t)(sign | 0x7cu);
-    return (uint8_t)(sign | ((uint32_t)e << 2) | (r & 3u));
-  }
-  return (uint8_t)(sign | (uint32_t)rintf(__uint_as_float(a) * 65536.0f));  // 0..4; 4 is the smallest normal
+  // |f| >= 2^-14: 8 exponent bits | 2 fraction bits, rebiased, infinity beyond; else 0..4 (4 is the smallest normal)
+  const uint32_t big = min(((a + 0xfffffu + ((a >> 21) & 1u)) >> 21) - (uint32_t)((127 - 15) << 2), 0x7cu);
+  const uint32_t tiny = (uint32_t)rintf(__uint_as_float(min(a, 0x38800000u)) * 65536.0f);
+  const uint32_t code = a >= 0x38800000u ? big : tiny;
+  return (uint8_t)(sign | (a > 0x7f800000u ? 0x7fu : code));
 }
 
 // ---- order-preserving key of a double (larger value <=> larger key, never 0 for

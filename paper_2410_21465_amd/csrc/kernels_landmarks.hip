@@ -61,7 +61,7 @@ __device__ __forceinline__ double reduce_scatter16_f64(const double (&v)[16], in
   return d[0];
 }
 
-// REG: the chunk's rows are kept in registers (c <= 8); otherwise they are read twice.
+// REG: the chunk's rows are kept in registers (c <= 8); otherwise they are read twice, eight at a time.
 // EB: bytes per stored element (2 = bf16, 1 = FP8 E5M2); the means are written in the same type.
 template <int D, bool REG, int EB>
 __global__ __launch_bounds__(256) void chunk_stats_kernel(const uint8_t* __restrict__ k_rope,
@@ -77,29 +77,24 @@ __global__ __launch_bounds__(256) void chunk_stats_kernel(const uint8_t* __restr
   const bool ok = j < n_ch;
   const uint8_t* base = k_rope + (((size_t)unit * s + (size_t)(ok ? j : 0) * c) * D + sub * EPL) * EB;
 
-  uint32_t raw[REG ? 8 : 1][RW];
+  uint32_t raw[8][RW];
   double mean[EPL];
 #pragma unroll
   for (int e = 0; e < EPL; ++e) mean[e] = 0.0;
-  if constexpr (REG) {
+  auto load_rows = [&](int t0) {   // rows t0 .. t0 + 7 of the chunk; beyond its end zeros (0.0 in either type)
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
 #pragma unroll
-      for (int e = 0; e < RW; ++e) raw[t][e] = 0u;   // all-zero bits are 0.0 in either type
-      if (t < c) load_raw<EPL, EB>(base + (size_t)t * D * EB, raw[t]);
+      for (int e = 0; e < RW; ++e) raw[t][e] = 0u;
+      if (t0 + t < c) load_raw<EPL, EB>(base + (size_t)(t0 + t) * D * EB, raw[t]);
     }
+  };
+  for (int t0 = 0; t0 < (REG ? 8 : c); t0 += 8) {
+    load_rows(t0);
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
       float x[EPL];
       unpack_kv<EPL, EB>(raw[t], x);
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) mean[e] += (double)x[e];
-    }
-  } else {
-    for (int t = 0; t < c; ++t) {
-      float x[EPL];
-      load_raw<EPL, EB>(base + (size_t)t * D * EB, raw[0]);
-      unpack_kv<EPL, EB>(raw[0], x);
 #pragma unroll
       for (int e = 0; e < EPL; ++e) mean[e] += (double)x[e];
     }
@@ -116,7 +111,18 @@ __global__ __launch_bounds__(256) void chunk_stats_kernel(const uint8_t* __restr
   const double cn = fmax(sqrt(allsum16_f64(cn2)), 1e-8);
 
   double mn = INFINITY;
-  if constexpr (REG) {
+  for (int t0 = 0; t0 < (REG ? 8 : c); t0 += 8) {
+    if constexpr (!REG) {
+      load_rows(t0);
+    } else if constexpr (EB == 1) {
+      // FP8 rows are widened again here: kept as fp64 they take 128 registers, and with half the bytes per row it is waves
+      // in flight that the loads need (3 x 61K tokens, 8 KV heads of 128: 84 -> 76 us; bf16 rows, whose loads fill the
+      // memory system from two waves per SIMD, lose: 937 -> 960 us at 16 x 128K)
+#pragma unroll
+      for (int t = 0; t < 8; ++t)
+#pragma unroll
+        for (int e = 0; e < RW; ++e) asm volatile("" : "+v"(raw[t][e]));
+    }
     double v[16];  // v[t] = partial <mean, k_t>, v[8 + t] = partial |k_t|^2
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
@@ -131,28 +137,11 @@ __global__ __launch_bounds__(256) void chunk_stats_kernel(const uint8_t* __restr
       }
       v[t] = dot; v[8 + t] = kn2;
     }
-    const double mine = reduce_scatter16_f64(v, sub);   // lane t: dot_t, lane 8+t: |k_t|^2
+    const double mine = reduce_scatter16_f64(v, sub);   // lane t: dot of row t0 + t, lane 8 + t: its squared norm
     const double kn2 = dpp_f64<kDppXor8>(mine);
-    double cs = INFINITY;
-    if (sub < c) cs = mine / (cn * fmax(sqrt(kn2), 1e-8));
-    mn = allmin16_f64(cs);
-  } else {
-    for (int t = 0; t < c; ++t) {
-      float x[EPL];
-      load_raw<EPL, EB>(base + (size_t)t * D * EB, raw[0]);
-      unpack_kv<EPL, EB>(raw[0], x);
-      double dot = 0.0, kn2 = 0.0;
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) {
-        const double xd = (double)x[e];
-        dot = fma(mean[e], xd, dot);
-        kn2 = fma(xd, xd, kn2);
-      }
-      dot = allsum16_f64(dot);
-      kn2 = allsum16_f64(kn2);
-      mn = fmin(mn, dot / (cn * fmax(sqrt(kn2), 1e-8)));
-    }
+    if (sub < min(8, c - t0)) mn = fmin(mn, mine / (cn * fmax(sqrt(kn2), 1e-8)));
   }
+  mn = allmin16_f64(mn);
   if (ok) {
     uint32_t hm[RW];
     pack_kv<EPL, EB>(mean, hm);
