@@ -364,13 +364,26 @@ FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int
   p.mp = (p.m + 31) / 32 * 32;
   p.nb = (D + 63) / 64;
   const long pairs = (long)p.nb * (p.nb + 1) / 2;
-  // enough waves to fill the chip: split the tokens when there are few column-block pairs
-  // tuning override: waves aimed at (default 8192; 16384 gains 5 % at the price of twice the partial sums)
-  static const long target = [] { const char* e = getenv("SHADOWKV_GRAM_WAVES"); return e ? atol(e) : 8192l; }();
-  long splits = (target + pairs * batch - 1) / (pairs * batch);
-  const long max_splits = (s + 1023) / 1024;
-  if (splits > max_splits) splits = max_splits;
-  if (splits < 1) splits = 1;
+  const long max_splits = (s + 1023) / 1024, blocks = pairs * batch;
+  // tuning override: waves aimed at
+  static const long target = [] { const char* e = getenv("SHADOWKV_GRAM_WAVES"); return e ? atol(e) : 0l; }();
+  long splits = 1;
+  if (target > 0) {
+    splits = std::max(1l, std::min(max_splits, (target + blocks - 1) / blocks));
+  } else {
+    // The tokens are split so that the last round of waves is nearly full: 2048 waves are resident (two per SIMD) and a wave
+    // takes 245 us for 1024 tokens (64 x 8 matrix instructions per 16 tokens and pair of waves, with what a large matrix
+    // reaches of the peak), a round of at most one wave per SIMD 0.6 of that; every split costs its partial sums once
+    // written and once read (1.06 x 8 bytes D^2 per sequence at 4.6 TB/s).  16 x 128K x 1024: 16 splits, 17 rounds, where 4
+    // splits make 4.25 rounds; 1 x 32K: 15 splits, one round, where 32 make 2.1.
+    double best = 0.0;
+    for (long sp = 1; sp <= std::min(max_splits, 512l); ++sp) {
+      const long waves = blocks * sp, rest = waves % 2048;
+      const double rounds = (double)(waves / 2048) + (rest == 0 ? 0.0 : rest <= 1024 ? 0.6 : 1.0);
+      const double cost = rounds * (double)((s + sp - 1) / sp) * (245.0 / 1024.0) + (double)sp * batch * D * D * (1.06 * 8.0 / 4.6e6);
+      if (sp == 1 || cost < best * 0.995) { best = cost; splits = sp; }
+    }
+  }
   p.tokens_per_split = (int)(((s + splits - 1) / splits + 15) / 16 * 16);
   p.n_splits = (s + p.tokens_per_split - 1) / p.tokens_per_split;
   size_t off = 0;
