@@ -311,6 +311,7 @@ __global__ __launch_bounds__(512) void jacobi_block_kernel(double* __restrict__ 
   __shared__ double red[8 * 3 * 256];       // partial products of the waves; then the second copy of S, and J
   __shared__ double S0[32 * P];
   __shared__ float wmax[8];
+  __shared__ double2 cs[2][16];             // rotations of the last two rounds
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int sub = lane & 15, kq = lane >> 4;
   const int nb = mp / 16, np = nb / 2, b = blockIdx.y, batch = gridDim.y;
@@ -384,7 +385,7 @@ __global__ __launch_bounds__(512) void jacobi_block_kernel(double* __restrict__ 
     big = wmax[0];
 #pragma unroll
     for (int w = 1; w < 8; ++w) big = !(wmax[w] <= big) ? wmax[w] : big;
-    const bool rest = big <= 1e-17f;       // nothing that a rotation would change
+    const bool rest = big <= 2e-16f;       // what the rounding of the products leaves: nothing to rotate
     if (threadIdx.x == 0) {
       atomicMax(&sweep_max[sweep], __float_as_int(big));
       idle[slot] = rest ? 1 : 0;
@@ -392,34 +393,41 @@ __global__ __launch_bounds__(512) void jacobi_block_kernel(double* __restrict__ 
     if (rest) return;
     const int rounds = st == 0 ? 31 : 16;
     double *Sa = S0, *Sb = S1;
-    for (int t = 0; t < rounds; ++t) {
-      // the 16 disjoint pairs of this round: across the two blocks, or the circle method over all 32 columns
-      auto members = [&](int i, int& p, int& q) {
-        if (st != 0) { p = i; q = 16 + ((i + t) & 15); }
-        else if (i == 0) { p = 31; q = t; }
-        else { p = t + i; p -= p >= 31 ? 31 : 0; q = t - i; q += q < 0 ? 31 : 0; }
+    // waves 0-3 rotate S, each lane forming the rotation of its column's pair (one such wave per SIMD); waves 4-7 apply
+    // the rotations of the round before to J, taken from LDS
+    for (int t = 0; t <= rounds; ++t) {
+      // the 16 disjoint pairs of round u: across the two blocks, or the circle method over all 32 columns
+      auto members = [&](int u, int i, int& p, int& q) {
+        if (st != 0) { p = i; q = 16 + ((i + u) & 15); }
+        else if (i == 0) { p = 31; q = u; }
+        else { p = u + i; p -= p >= 31 ? 31 : 0; q = u - i; q += q < 0 ? 31 : 0; }
       };
       int p, q;
-      members(sub, p, q);
-      const double al = Sa[p * P + p], be = Sa[q * P + q], ga = Sa[p * P + q];
-      double c = 1.0, sn = 0.0;
-      if (fabs(ga) > 1e-300 && ga * ga > 1e-34 * (al * be)) rotation(al, be, ga, c, sn);
-      if (wave < 4) {                      // S: rows of pair u, columns of pair sub
-        const int u = wave * 4 + kq;
-        const double cu = __shfl(c, u, kWave), su = __shfl(sn, u, kWave);
-        int pu, qu;
-        members(u, pu, qu);
-        const double pp = Sa[pu * P + p], pq = Sa[pu * P + q], qp = Sa[qu * P + p], qq = Sa[qu * P + q];
-        const double tp = cu * pp - su * qp, tq = cu * pq - su * qq, bp = su * pp + cu * qp, bq = su * pq + cu * qq;
-        const bool own = u == sub;         // (the rotated pair itself: zero by construction)
-        Sb[pu * P + p] = c * tp - sn * tq; Sb[pu * P + q] = own && sn != 0.0 ? 0.0 : sn * tp + c * tq;
-        Sb[qu * P + p] = own && sn != 0.0 ? 0.0 : c * bp - sn * bq; Sb[qu * P + q] = sn * bp + c * bq;
-      } else {                             // J: columns of pair sub, eight rows per wave
+      if (wave < 4) {
+        if (t < rounds) {
+          members(t, sub, p, q);
+          const double al = Sa[p * P + p], be = Sa[q * P + q], ga = Sa[p * P + q];
+          const int u = wave * 4 + kq;      // this lane: rows of pair u, columns of pair sub
+          int pu, qu;
+          members(t, u, pu, qu);
+          const double pp = Sa[pu * P + p], pq = Sa[pu * P + q], qp = Sa[qu * P + p], qq = Sa[qu * P + q];
+          double c = 1.0, sn = 0.0;
+          if (fabs(ga) > 1e-300 && ga * ga > 1e-34 * (al * be)) rotation(al, be, ga, c, sn);
+          if (threadIdx.x < 16) cs[t & 1][sub] = make_double2(c, sn);
+          const double cu = __shfl(c, u, kWave), su = __shfl(sn, u, kWave);
+          const double tp = cu * pp - su * qp, tq = cu * pq - su * qq, bp = su * pp + cu * qp, bq = su * pq + cu * qq;
+          const bool own = u == sub && sn != 0.0;   // (the rotated pair itself: zero by construction)
+          Sb[pu * P + p] = c * tp - sn * tq; Sb[pu * P + q] = own ? 0.0 : sn * tp + c * tq;
+          Sb[qu * P + p] = own ? 0.0 : c * bp - sn * bq; Sb[qu * P + q] = sn * bp + c * bq;
+        }
+      } else if (t > 0) {                  // J: columns of pair sub, eight rows per wave
+        members(t - 1, sub, p, q);
+        const double2 r = cs[(t - 1) & 1][sub];
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
           double* jr = J + ((wave - 4) * 8 + kq * 2 + e) * P;
           const double x = jr[p], y = jr[q];
-          jr[p] = c * x - sn * y; jr[q] = sn * x + c * y;
+          jr[p] = r.x * x - r.y * y; jr[q] = r.y * x + r.x * y;
         }
       }
       __syncthreads();
