@@ -46,33 +46,6 @@ struct Raw4 {
   }
 };
 
-// sixteen consecutive stored elements (32 or 16 bytes), widened four at a time
-template <int EB>
-struct Raw16 {
-  uint32_t w[EB == 2 ? 8 : 4];
-  __device__ __forceinline__ void load(const void* base, size_t at, bool ok) {
-    uint4 lo = make_uint4(0u, 0u, 0u, 0u), hi = lo;
-    if (ok) {
-      if constexpr (EB == 2) {
-        const uint4* p = reinterpret_cast<const uint4*>(static_cast<const bf16_t*>(base) + at);
-        lo = p[0]; hi = p[1];
-      } else {
-        lo = *reinterpret_cast<const uint4*>(static_cast<const uint8_t*>(base) + at);
-      }
-    }
-    w[0] = lo.x; w[1] = lo.y; w[2] = lo.z; w[3] = lo.w;
-    if constexpr (EB == 2) { w[4] = hi.x; w[5] = hi.y; w[6] = hi.z; w[7] = hi.w; }
-  }
-  template <int U>
-  __device__ __forceinline__ void widen4(double (&x)[4]) const {
-    float f[4];
-    if constexpr (EB == 2) { f[0] = bf16_lo(w[2 * U]); f[1] = bf16_hi(w[2 * U]); f[2] = bf16_lo(w[2 * U + 1]); f[3] = bf16_hi(w[2 * U + 1]); }
-    else e5m2x4_to_f32(w[U], f);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) x[e] = (double)f[e];
-  }
-};
-
 // ---- 1. Gram matrix ---------------------------------------------------------------------------------
 // One wave per (pair of 64-column blocks bi <= bj, token split, sequence).  Tile (mt, nt) of the 64 x 64
 // block holds columns i0 + 4 m + mt against j0 + 4 n + nt, so that a lane's four consecutive columns feed
@@ -248,13 +221,16 @@ __global__ __launch_bounds__(256) void emit_b_kernel(double* __restrict__ Psi_t,
 }
 
 // ---- 3. A = K Psi -----------------------------------------------------------------------------------------
-// One wave per (48 tokens, up to 80 rank columns, sequence): M = tokens (three 16-row tiles), N = rank index,
-// contraction over the key columns (a lane's four consecutive stored elements are four contraction steps).  Every fragment of Psi read from L2 serves the three token tiles (120 accumulator registers: a fourth
-// tile makes the compiler move accumulators in and out of the matrix register file every step).
-template <int EB>
-__global__ __launch_bounds__(64) void project_kernel(const void* __restrict__ K, const double* __restrict__ Psi_t,
+// One wave per (32 tokens, 16 NT rank columns, sequence): M = tokens (two 16-row tiles), N = rank index, contraction over
+// the key columns (a lane's four consecutive stored elements are four contraction steps).  Every fragment of Psi read
+// from L2 serves both token tiles; two tiles and not three so that two waves share a SIMD and one widens while the
+// other's matrix instructions run.  16 x 128K x 1024, rank 160: 13.4 ms with three tiles and a lane's columns in one
+// 32-byte piece (a quarter of each line of Psi used per step, the rest evicted before its turn), 12.5 ms now
+// (55 TFLOP/s); one sequence of 32K 307 -> 225 us.
+template <int EB, int NT>
+__global__ __launch_bounds__(64, 2) void project_kernel(const void* __restrict__ K, const double* __restrict__ Psi_t,
                                                      void* __restrict__ Aout, int s, int s_cap, int D, int r) {
-  constexpr int NT = 5, MT = 3;
+  constexpr int MT = 2;
   const int lane = threadIdx.x, mrow = lane & 15, kq = lane >> 4;
   const int tok0 = blockIdx.x * (16 * MT), n0 = blockIdx.y * (16 * NT), b = blockIdx.z;
   size_t krow[MT];
@@ -273,16 +249,20 @@ __global__ __launch_bounds__(64) void project_kernel(const void* __restrict__ K,
     okn[nt] = rho < r;
     prow[nt] = Psi_t + ((size_t)b * r + min(rho, r - 1)) * D;
   }
-  // The contraction runs over 64 key columns per outer step: lane group kq owns columns c0 + 16 kq .. + 15 (one
-  // 32-byte piece of each of its token rows, requested a whole outer step ahead: it comes from HBM) and takes them
-  // four at a time; the Psi fragments of the next inner step (from L2) are requested before the matrix
+  // The contraction runs over 64 key columns per outer step, 16 per inner step: lane group kq takes columns 4 kq .. + 3 of the
+  // 16, so that what a wave reads of a row of Psi in one step is one whole cache line.  The token rows are requested a
+  // whole outer step ahead (they come from HBM), the Psi fragments of the next inner step (from L2) before the matrix
   // instructions of the current one.
-  Raw16<EB> kn[MT];
+  Raw4<EB> kn[MT][4];
   double pn[NT][4];
   auto request_k = [&](int c0) {
-    const int col = c0 + 16 * kq;
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) kn[mt].load(K, krow[mt] + col, col < D);
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int col = c0 + 16 * u + 4 * kq;
+        kn[mt][u].load(K, krow[mt] + min(col, D - 4), col < D);
+      }
   };
   auto request_psi = [&](int col) {   // col = first of this lane group's four columns
     const bool ok = col < D;
@@ -297,18 +277,20 @@ __global__ __launch_bounds__(64) void project_kernel(const void* __restrict__ K,
     }
   };
   request_k(0);
-  request_psi(16 * kq);
+  request_psi(4 * kq);
 #pragma unroll 1
   for (int c0 = 0; c0 < D; c0 += 64) {
-    Raw16<EB> kc[MT];
+    Raw4<EB> kc[MT][4];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) kc[mt] = kn[mt];
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) kc[mt][u] = kn[mt][u];
     request_k(c0 + 64);
     auto inner = [&](auto u_tag, int next_col) {
       constexpr int U = decltype(u_tag)::value;
       double a[MT][4], pb[NT][4];
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) kc[mt].template widen4<U>(a[mt]);
+      for (int mt = 0; mt < MT; ++mt) kc[mt][U].widen(a[mt]);
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -322,10 +304,10 @@ __global__ __launch_bounds__(64) void project_kernel(const void* __restrict__ K,
           for (int mt = 0; mt < MT; ++mt)
             acc[mt][nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[mt][e], pb[nt][e], acc[mt][nt], 0, 0, 0);
     };
-    const int cb = c0 + 16 * kq;
-    inner(std::integral_constant<int, 0>{}, cb + 4);
-    inner(std::integral_constant<int, 1>{}, cb + 8);
-    inner(std::integral_constant<int, 2>{}, cb + 12);
+    const int cb = c0 + 4 * kq;
+    inner(std::integral_constant<int, 0>{}, cb + 16);
+    inner(std::integral_constant<int, 1>{}, cb + 32);
+    inner(std::integral_constant<int, 2>{}, cb + 48);
     inner(std::integral_constant<int, 3>{}, cb + 64);
   }
 #pragma unroll
@@ -494,9 +476,16 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
   else hipLaunchKernelGGL(emit_b_kernel<2>, dim3(r, batch), dim3(256), 0, st, Psi_t, B, D, r, hkv, d);
   SKV_CHECK();
   {
-    dim3 grid((s + 47) / 48, (r + 79) / 80, batch);
-    if (kv_bytes == 1) hipLaunchKernelGGL(project_kernel<1>, grid, dim3(64), 0, st, k_pre, Psi_t, A, s, s_cap, D, r);
-    else hipLaunchKernelGGL(project_kernel<2>, grid, dim3(64), 0, st, k_pre, Psi_t, A, s, s_cap, D, r);
+    // up to five 16-rank tiles per wave, the tiles dealt evenly to as few waves as that takes (rank 96: 2 x 3, not 5 + 1)
+    const int tiles = (r + 15) / 16, blocks = (tiles + 4) / 5, nt = (tiles + blocks - 1) / blocks;
+    const dim3 grid((s + 31) / 32, blocks, batch);
+#define SKV_PROJECT(EB_, NT_) hipLaunchKernelGGL((project_kernel<EB_, NT_>), grid, dim3(64), 0, st, k_pre, Psi_t, A, s, s_cap, D, r)
+    if (kv_bytes == 1) {
+      if (nt == 5) SKV_PROJECT(1, 5); else if (nt == 4) SKV_PROJECT(1, 4); else SKV_PROJECT(1, 3);
+    } else {
+      if (nt == 5) SKV_PROJECT(2, 5); else if (nt == 4) SKV_PROJECT(2, 4); else SKV_PROJECT(2, 3);
+    }
+#undef SKV_PROJECT
     SKV_CHECK();
   }
 #undef SKV_CHECK
