@@ -23,18 +23,18 @@
 
 namespace skv {
 
-// four consecutive stored elements starting at element index `at` of `base` (zero when !ok), kept as stored and
-// widened to fp64 when they are used: what a prefetch holds
+// four consecutive stored elements, kept as stored and widened to fp64 when they are used: what a prefetch holds.
+// Loads are never predicated here and in the loops below (indices are clamped instead): a load under a lane mask made the
+// compiler wait for it before the matrix instructions it was meant to overlap.
 template <int EB>
 struct Raw4 {
   uint32_t w[EB == 2 ? 2 : 1];
-  __device__ __forceinline__ void load(const void* base, size_t at, bool ok) {
+  __device__ __forceinline__ void load(const uint8_t* p) {
     if constexpr (EB == 2) {
-      uint2 v = make_uint2(0u, 0u);
-      if (ok) v = *reinterpret_cast<const uint2*>(static_cast<const bf16_t*>(base) + at);
+      const uint2 v = *reinterpret_cast<const uint2*>(p);
       w[0] = v.x; w[1] = v.y;
     } else {
-      w[0] = ok ? *reinterpret_cast<const uint32_t*>(static_cast<const uint8_t*>(base) + at) : 0u;
+      w[0] = *reinterpret_cast<const uint32_t*>(p);
     }
   }
   __device__ __forceinline__ void widen(double (&x)[4]) const {
@@ -50,8 +50,10 @@ struct Raw4 {
 // One wave per (pair of 64-column blocks bi <= bj, token split, sequence).  Tile (mt, nt) of the 64 x 64
 // block holds columns i0 + 4 m + mt against j0 + 4 n + nt, so that a lane's four consecutive columns feed
 // four tiles and every load is 8 (or 4) contiguous bytes.  part [split][b][D][D] fp64, blocks bi <= bj only.
+// Bound by the matrix pipe: 67 TFLOP/s at 16 x 128K x 1024 (a large library product reaches 73; 61 with loads under lane
+// masks, whose results the matrix instructions then waited for).
 template <int EB>
-__global__ __launch_bounds__(64) void gram_kernel(const void* __restrict__ K, double* __restrict__ part, int s, int D,
+__global__ __launch_bounds__(64, 2) void gram_kernel(const void* __restrict__ K, double* __restrict__ part, int s, int D,
                                                   int nb, int tokens_per_split, int batch) {
   const int lane = threadIdx.x, mrow = lane & 15, kq = lane >> 4;
   // pair index -> (bi, bj), bi <= bj, row by row of the upper triangle
@@ -60,9 +62,9 @@ __global__ __launch_bounds__(64) void gram_kernel(const void* __restrict__ K, do
   const int bj = bi + p;
   const int split = blockIdx.y, b = blockIdx.z;
   const int t_begin = split * tokens_per_split, t_end = min(s, t_begin + tokens_per_split);
-  const int ci = bi * 64 + 4 * mrow, cj = bj * 64 + 4 * mrow;
-  const bool oki = ci < D, okj = cj < D;
-  const size_t base = (size_t)b * s * D;
+  // columns past the end repeat the last four; their results are not written
+  const int ci = min(bi * 64 + 4 * mrow, D - 4), cj = min(bj * 64 + 4 * mrow, D - 4);
+  const uint8_t* Kb = static_cast<const uint8_t*>(K) + (size_t)b * s * D * EB;
 
   f64x4 acc[4][4];
 #pragma unroll
@@ -71,16 +73,15 @@ __global__ __launch_bounds__(64) void gram_kernel(const void* __restrict__ K, do
     for (int nt = 0; nt < 4; ++nt) acc[mt][nt] = f64x4{0.0, 0.0, 0.0, 0.0};
 
   // 16 tokens (four matrix steps) per iteration; the next iteration's rows are requested before this one's 64
-  // matrix instructions, which is about the latency of a load
+  // matrix instructions, which is longer than a load takes
   constexpr int PF = 4;
   Raw4<EB> an[PF], bn[PF];
   auto request = [&](int t0) {
 #pragma unroll
     for (int u = 0; u < PF; ++u) {
-      const int t = t0 + 4 * u + kq;
-      const size_t row = base + (size_t)min(t, s - 1) * D;
-      an[u].load(K, row + ci, oki && t < t_end);
-      bn[u].load(K, row + cj, okj && t < t_end);
+      const uint8_t* row = Kb + (size_t)min(t0 + 4 * u + kq, s - 1) * D * EB;
+      an[u].load(row + ci * EB);
+      bn[u].load(row + cj * EB);
     }
   };
   request(t_begin);
@@ -89,6 +90,13 @@ __global__ __launch_bounds__(64) void gram_kernel(const void* __restrict__ K, do
 #pragma unroll
     for (int u = 0; u < PF; ++u) { ac[u] = an[u]; bc[u] = bn[u]; }
     request(t0 + 4 * PF);
+    if (t0 + 4 * PF > t_end) {   // fewer than 16 tokens left: the ones past the end count as zero
+#pragma unroll
+      for (int u = 0; u < PF; ++u)
+        if (t0 + 4 * u + kq >= t_end)
+#pragma unroll
+          for (int x = 0; x < (EB == 2 ? 2 : 1); ++x) { ac[u].w[x] = 0u; bc[u].w[x] = 0u; }
+    }
 #pragma unroll
     for (int u = 0; u < PF; ++u) {
       double a[4], bb[4];
@@ -225,30 +233,26 @@ __global__ __launch_bounds__(256) void emit_b_kernel(double* __restrict__ Psi_t,
 // the key columns (a lane's four consecutive stored elements are four contraction steps).  Every fragment of Psi read
 // from L2 serves both token tiles; two tiles and not three so that two waves share a SIMD and one widens while the
 // other's matrix instructions run.  16 x 128K x 1024, rank 160: 13.4 ms with three tiles and a lane's columns in one
-// 32-byte piece (a quarter of each line of Psi used per step, the rest evicted before its turn), 12.5 ms now
-// (55 TFLOP/s); one sequence of 32K 307 -> 225 us.
+// 32-byte piece (a quarter of each line of Psi used per step, the rest evicted before its turn), 12.2 ms with loads under lane
+// masks, 11.4 ms now (60 TFLOP/s); one sequence of 32K 307 -> 195 us.
 template <int EB, int NT>
 __global__ __launch_bounds__(64, 2) void project_kernel(const void* __restrict__ K, const double* __restrict__ Psi_t,
                                                      void* __restrict__ Aout, int s, int s_cap, int D, int r) {
   constexpr int MT = 2;
   const int lane = threadIdx.x, mrow = lane & 15, kq = lane >> 4;
   const int tok0 = blockIdx.x * (16 * MT), n0 = blockIdx.y * (16 * NT), b = blockIdx.z;
-  size_t krow[MT];
+  const uint8_t* krow[MT];   // tokens and ranks past the end repeat the last real one; their results are not written
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt) krow[mt] = ((size_t)b * s + min(tok0 + 16 * mt + mrow, s - 1)) * D;
+  for (int mt = 0; mt < MT; ++mt)
+    krow[mt] = static_cast<const uint8_t*>(K) + ((size_t)b * s + min(tok0 + 16 * mt + mrow, s - 1)) * D * EB;
   f64x4 acc[MT][NT];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f64x4{0.0, 0.0, 0.0, 0.0};
   const double* prow[NT];
-  bool okn[NT];
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    const int rho = n0 + 16 * nt + mrow;
-    okn[nt] = rho < r;
-    prow[nt] = Psi_t + ((size_t)b * r + min(rho, r - 1)) * D;
-  }
+  for (int nt = 0; nt < NT; ++nt) prow[nt] = Psi_t + ((size_t)b * r + min(n0 + 16 * nt + mrow, r - 1)) * D;
   // The contraction runs over 64 key columns per outer step, 16 per inner step: lane group kq takes columns 4 kq .. + 3 of the
   // 16, so that what a wave reads of a row of Psi in one step is one whole cache line.  The token rows are requested a
   // whole outer step ahead (they come from HBM), the Psi fragments of the next inner step (from L2) before the matrix
@@ -260,19 +264,14 @@ __global__ __launch_bounds__(64, 2) void project_kernel(const void* __restrict__
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int col = c0 + 16 * u + 4 * kq;
-        kn[mt][u].load(K, krow[mt] + min(col, D - 4), col < D);
+        kn[mt][u].load(krow[mt] + min(c0 + 16 * u + 4 * kq, D - 4) * EB);
       }
   };
   auto request_psi = [&](int col) {   // col = first of this lane group's four columns
-    const bool ok = col < D;
+    col = min(col, D - 4);
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-      double2 lo = make_double2(0.0, 0.0), hi = make_double2(0.0, 0.0);
-      if (okn[nt] && ok) {
-        lo = *reinterpret_cast<const double2*>(prow[nt] + col);
-        hi = *reinterpret_cast<const double2*>(prow[nt] + col + 2);
-      }
+      const double2 lo = *reinterpret_cast<const double2*>(prow[nt] + col), hi = *reinterpret_cast<const double2*>(prow[nt] + col + 2);
       pn[nt][0] = lo.x; pn[nt][1] = lo.y; pn[nt][2] = hi.x; pn[nt][3] = hi.y;
     }
   };
@@ -307,8 +306,10 @@ __global__ __launch_bounds__(64, 2) void project_kernel(const void* __restrict__
     const int cb = c0 + 4 * kq;
     inner(std::integral_constant<int, 0>{}, cb + 16);
     inner(std::integral_constant<int, 1>{}, cb + 32);
-    inner(std::integral_constant<int, 2>{}, cb + 48);
-    inner(std::integral_constant<int, 3>{}, cb + 64);
+    if (c0 + 32 < D) {   // (the key width is a multiple of 32)
+      inner(std::integral_constant<int, 2>{}, cb + 48);
+      inner(std::integral_constant<int, 3>{}, cb + 64);
+    }
   }
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
