@@ -13,36 +13,36 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 // C[i][j] = sum_k A[i][k] B(k, j), K a multiple of 16, rows of A 16-byte aligned.  BT: B is given by its columns
 // (B(k, j) = B[j][k], as A is); otherwise row-major with Kb rows (A is zero beyond).  Rows of A may be taken through a_rows.  C is written over
 // Mw x Nw, zero outside M x N.
-// A workgroup is WM x WN tiles of 32 x 32 with the contraction cut WK ways; every operand goes from L2 straight to the
+// A workgroup is WM x WN tiles of 16 T x 16 T with the contraction cut WK ways; every operand goes from L2 straight to the
 // matrix instruction (a lane's four consecutive elements are four contraction steps), the next 16 steps requested
 // before the current ones' 16 instructions.  The products here are small (192 x 1024 x 1024 per sequence), so what
-// bounds them is how many waves there are: for one sequence WK = 8 gives 1536 waves of 128 steps each; with several
-// sequences the 2 x 2 x 2 form halves the L2 traffic instead.
-template <int WM, int WN, int WK, bool BT>
+// bounds them is how many waves there are: for one sequence T = 2, WK = 8 gives 1536 waves of 128 steps each; with several
+// sequences the 2 x 2 x 2 form halves the L2 traffic instead; the m x m products have so few tiles that T = 1 is faster.
+template <int T, int WM, int WN, int WK, bool BT>
 __global__ __launch_bounds__(64 * WM * WN * WK) void gemm64_kernel(const double* __restrict__ A,
                                                                    const double* __restrict__ B, double* __restrict__ C,
                                                                    int M, int N, int K, int Kb, int lda, int ldb, int ldc,
                                                                    int Mw, int Nw, size_t strideA, size_t strideB, size_t strideC,
                                                                    const int32_t* __restrict__ a_rows, int a_rows_stride) {
-  __shared__ double red[WM * WN][WK][16][kWave];
+  __shared__ double red[WM * WN][WK][4 * T * T][kWave];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int sub = lane & 15, kq = lane >> 4;
   const int wk = wave % WK, wt = wave / WK, wn = wt % WN, wm = wt / WN;
-  const int i0 = (blockIdx.y * WM + wm) * 32, j0 = (blockIdx.x * WN + wn) * 32;
+  const int i0 = (blockIdx.y * WM + wm) * 16 * T, j0 = (blockIdx.x * WN + wn) * 16 * T;
   A += blockIdx.z * strideA; B += blockIdx.z * strideB; C += blockIdx.z * strideC;
   if (a_rows) a_rows += (size_t)blockIdx.z * a_rows_stride;
-  const double* ap[2];
-  const double* bp[2];
+  const double* ap[T];
+  const double* bp[T];
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {   // rows and columns past the end repeat the last real one; their results are not used
+  for (int t = 0; t < T; ++t) {   // rows and columns past the end repeat the last real one; their results are not used
     const int i = min(i0 + 16 * t + sub, M - 1), j = min(j0 + 16 * t + sub, N - 1);
     ap[t] = A + (size_t)(a_rows ? a_rows[i] : i) * lda + 4 * kq;
     bp[t] = BT ? B + (size_t)j * ldb + 4 * kq : B + j;
   }
-  double an[2][4], bn[2][4];
+  double an[T][4], bn[T][4];
   auto request = [&](int k0) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    for (int t = 0; t < T; ++t) {
       const double2 lo = *reinterpret_cast<const double2*>(ap[t] + k0), hi = *reinterpret_cast<const double2*>(ap[t] + k0 + 2);
       an[t][0] = lo.x; an[t][1] = lo.y; an[t][2] = hi.x; an[t][3] = hi.y;
       if constexpr (BT) {
@@ -54,42 +54,42 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm64_kernel(const double*
       }
     }
   };
-  f64x4 acc[2][2];
+  f64x4 acc[T][T];
 #pragma unroll
-  for (int x = 0; x < 2; ++x)
+  for (int x = 0; x < T; ++x)
 #pragma unroll
-    for (int y = 0; y < 2; ++y) acc[x][y] = f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int y = 0; y < T; ++y) acc[x][y] = f64x4{0.0, 0.0, 0.0, 0.0};
   const int step = 16 * WK;
   if (16 * wk < K) request(16 * wk);
   for (int k0 = 16 * wk; k0 < K; k0 += step) {
-    double a[2][4], b[2][4];
+    double a[T][4], b[T][4];
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < T; ++t)
 #pragma unroll
       for (int e = 0; e < 4; ++e) { a[t][e] = an[t][e]; b[t][e] = bn[t][e]; }
     if (k0 + step < K) request(k0 + step);
 #pragma unroll
     for (int e = 0; e < 4; ++e)
 #pragma unroll
-      for (int x = 0; x < 2; ++x)
+      for (int x = 0; x < T; ++x)
 #pragma unroll
-        for (int y = 0; y < 2; ++y) acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x][e], b[y][e], acc[x][y], 0, 0, 0);
+        for (int y = 0; y < T; ++y) acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x][e], b[y][e], acc[x][y], 0, 0, 0);
   }
 #pragma unroll
-  for (int x = 0; x < 2; ++x)
+  for (int x = 0; x < T; ++x)
 #pragma unroll
-    for (int y = 0; y < 2; ++y)
+    for (int y = 0; y < T; ++y)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) red[wt][wk][(x * 2 + y) * 4 + j][lane] = acc[x][y][j];
+      for (int j = 0; j < 4; ++j) red[wt][wk][(x * T + y) * 4 + j][lane] = acc[x][y][j];
   __syncthreads();
-  // each of the WK waves of a tile adds up 16 / WK of its registers
+  // each of the WK waves of a tile adds up 4 T T / WK of its registers
 #pragma unroll
-  for (int u = 0; u < 16 / WK; ++u) {
-    const int reg = wk * (16 / WK) + u;
+  for (int u = 0; u < 4 * T * T / WK; ++u) {
+    const int reg = wk * (4 * T * T / WK) + u, tile = reg >> 2;
     double sum = 0.0;
 #pragma unroll
     for (int w = 0; w < WK; ++w) sum += red[wt][w][reg][lane];
-    const int i = i0 + 16 * (reg >> 3) + 4 * (reg & 3) + kq, j = j0 + 16 * ((reg >> 2) & 1) + sub;
+    const int i = i0 + 16 * (tile / T) + 4 * (reg & 3) + kq, j = j0 + 16 * (tile % T) + sub;
     if (i < Mw && j < Nw) C[(size_t)i * ldc + j] = (i < M && j < N) ? sum : 0.0;
   }
 }
@@ -215,58 +215,69 @@ __global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S,
   }
 }
 
-// X = L^-1 Y, rows of length D: one wave per 16 columns holds all its rows in accumulators and goes down the block rows; a
-// finished block is in the operand layout already (result register t of a lane is the row of contraction step t).
-// The blocks of the next block column are requested while the current one's instructions run, as far as registers go.
+// X = L^-1 Y, rows of length D: four waves per 16 columns, wave w with the block rows w, w + 4, ... in accumulators.  Down the
+// block rows: the owner of row k multiplies it by the inverse of the diagonal block and leaves the result in LDS -- in the
+// operand layout it is in already (result register t of a lane is the row of contraction step t) --, then every wave takes
+// it out of its later rows.  The blocks of the next block column are requested while the current one's instructions run.
+// 192 vectors of 1024 columns: 12.5 us (one wave for all rows, 312 matrix instructions in a row: 18.5 us).
 template <int NB>
-__global__ __launch_bounds__(64) void trsm_kernel(const double* __restrict__ Lp, const double* __restrict__ Y,
-                                                  double* __restrict__ X, int m, int nb, int D) {
-  const int lane = threadIdx.x, sub = lane & 15, kq = lane >> 4;
+__global__ __launch_bounds__(256) void trsm_kernel(const double* __restrict__ Lp, const double* __restrict__ Y,
+                                                   double* __restrict__ X, int m, int nb, int D) {
+  constexpr int NR = (NB + 3) / 4;           // block rows per wave
+  __shared__ double xs[2][kWave][4];
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int sub = lane & 15, kq = lane >> 4;
   const size_t base = (size_t)blockIdx.y * m * D + blockIdx.x * 16 + sub;
   Lp += (size_t)blockIdx.y * (nb * (nb + 1) / 2) * 256 + lane * 4;
-  constexpr bool kAhead = NB <= 14;
-  double next[NB][4];
-  auto request = [&](int k) {
+  double next[NR][4];
+  auto request = [&](int k) {   // this wave's blocks of block column k (rows above it: nothing; clamped, not guarded)
 #pragma unroll
-    for (int i = 0; i < NB; ++i)
-      if (i >= k && i < nb) {
-        const double2* p = reinterpret_cast<const double2*>(Lp + (size_t)tri_block(nb, i, k) * 256);
-        const double2 lo = p[0], hi = p[1];
-        next[i][0] = lo.x; next[i][1] = lo.y; next[i][2] = hi.x; next[i][3] = hi.y;
-      }
+    for (int x = 0; x < NR; ++x) {
+      const int i = min(max(wave + 4 * x, k), nb - 1);
+      const double2* p = reinterpret_cast<const double2*>(Lp + (size_t)tri_block(nb, i, k) * 256);
+      const double2 lo = p[0], hi = p[1];
+      next[x][0] = lo.x; next[x][1] = lo.y; next[x][2] = hi.x; next[x][3] = hi.y;
+    }
   };
-  if (kAhead) request(0);
-  f64x4 acc[NB];
+  request(0);
+  f64x4 acc[NR];
 #pragma unroll
-  for (int i = 0; i < NB; ++i)
+  for (int x = 0; x < NR; ++x)
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int r = 16 * i + 4 * j + kq;
-      acc[i][j] = r < m ? Y[base + (size_t)r * D] : 0.0;
+      const int r = 16 * (wave + 4 * x) + 4 * j + kq;
+      const double y = Y[base + (size_t)min(r, m - 1) * D];
+      acc[x][j] = r < m ? y : 0.0;
     }
 #pragma unroll
   for (int k = 0; k < NB; ++k) {
     if (k < nb) {
-    double cur[NB][4];
-    if (!kAhead) request(k);
+      double cur[NR][4];
 #pragma unroll
-    for (int i = 0; i < NB; ++i)
+      for (int x = 0; x < NR; ++x)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) cur[i][t] = i >= k ? next[i][t] : 0.0;
-    if (kAhead && k + 1 < nb) request(k + 1);
-    f64x4 x = {0.0, 0.0, 0.0, 0.0};
+        for (int t = 0; t < 4; ++t) cur[x][t] = next[x][t];
+      request(min(k + 1, nb - 1));
+      if (wave == (k & 3)) {
+        f64x4 v = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int t = 0; t < 4; ++t) x = __builtin_amdgcn_mfma_f64_16x16x4f64(cur[k][t], acc[k][t], x, 0, 0, 0);
+        for (int t = 0; t < 4; ++t) v = __builtin_amdgcn_mfma_f64_16x16x4f64(cur[k >> 2][t], acc[k >> 2][t], v, 0, 0, 0);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int r = 16 * k + 4 * j + kq;
-      if (r < m) X[base + (size_t)r * D] = x[j];
-    }
+        for (int j = 0; j < 4; ++j) {
+          const int r = 16 * k + 4 * j + kq;
+          xs[k & 1][lane][j] = v[j];
+          if (r < m) X[base + (size_t)r * D] = v[j];
+        }
+      }
+      __syncthreads();   // (two buffers: the next owner writes the other one while late waves still read this one)
+      double xk[4];
 #pragma unroll
-    for (int i = 0; i < NB; ++i)
-      if (i > k && i < nb)
+      for (int t = 0; t < 4; ++t) xk[t] = xs[k & 1][lane][t];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(cur[i][t], x[t], acc[i], 0, 0, 0);
+      for (int x = 0; x < NR; ++x)
+        if (wave + 4 * x > k && wave + 4 * x < nb)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) acc[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(cur[x][t], xk[t], acc[x], 0, 0, 0);
     }
   }
 }

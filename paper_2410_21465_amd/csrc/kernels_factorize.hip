@@ -324,20 +324,23 @@ __global__ __launch_bounds__(64, 2) void project_kernel(const void* __restrict__
 
 // ---- launch sequence ----------------------------------------------------------------------------------------
 // C (Mw x Nw, zero outside M x N) = A B, see gemm64_kernel; ?.ld = elements from row to row, ?.stride = from sequence to
-// sequence.  32 x 32 tiles with the contraction cut eight ways while that leaves the chip room (fewer than 1024 tiles:
-// 192 x 1024 x 1024 takes 20 us for one sequence, 211 us with a tile per workgroup on the vector unit), else 64 x 64
-// blocks cut in two (16 sequences: 182 us, 298 us on the vector unit).
+// sequence.  Fewer than 64 tiles of 32 x 32 (the m x m products of one sequence): 16 x 16 tiles, the contraction cut in
+// four (192 x 192 x 1024: 11.5 us, 18.5 us on 36 tiles of 32 x 32).  Up to 1024: 32 x 32 tiles with the contraction cut eight ways (192 x 1024 x 1024 takes 18 us for one sequence, 211
+// us with a tile per workgroup on the vector unit).  More: 64 x 64 blocks cut in two (16 sequences: 177 us, 298 us on the
+// vector unit).
 struct Mat { const double* p; int ld; size_t stride; };
 template <bool BT>
 static hipError_t gemm64(Mat A, Mat B, double* C, int ldc, size_t strideC, int M, int N, int K, int Kb, int Mw, int Nw,
                          int batch, hipStream_t st, const int32_t* a_rows = nullptr, int a_rows_stride = 0) {
   const long tiles = (long)((Mw + 31) / 32) * ((Nw + 31) / 32) * batch;
-  if (tiles < 1024)
-    hipLaunchKernelGGL((gemm64_kernel<1, 1, 8, BT>), dim3((Nw + 31) / 32, (Mw + 31) / 32, batch), dim3(512), 0, st, A.p, B.p, C,
-                       M, N, K, Kb, A.ld, B.ld, ldc, Mw, Nw, A.stride, B.stride, strideC, a_rows, a_rows_stride);
-  else
-    hipLaunchKernelGGL((gemm64_kernel<2, 2, 2, BT>), dim3((Nw + 63) / 64, (Mw + 63) / 64, batch), dim3(512), 0, st, A.p, B.p, C,
-                       M, N, K, Kb, A.ld, B.ld, ldc, Mw, Nw, A.stride, B.stride, strideC, a_rows, a_rows_stride);
+#define SKV_GEMM(T_, WM_, WN_, WK_)                                                                                       \
+  hipLaunchKernelGGL((gemm64_kernel<T_, WM_, WN_, WK_, BT>), dim3((Nw + 16 * T_ * WN_ - 1) / (16 * T_ * WN_),             \
+                     (Mw + 16 * T_ * WM_ - 1) / (16 * T_ * WM_), batch), dim3(64 * WM_ * WN_ * WK_), 0, st, A.p, B.p, C, M, N, \
+                     K, Kb, A.ld, B.ld, ldc, Mw, Nw, A.stride, B.stride, strideC, a_rows, a_rows_stride)
+  if (tiles < 64) SKV_GEMM(1, 1, 1, 4);
+  else if (tiles < 1024) SKV_GEMM(2, 1, 1, 8);
+  else SKV_GEMM(2, 2, 2, 2);
+#undef SKV_GEMM
   return hipGetLastError();
 }
 
@@ -430,7 +433,7 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
 #define SKV_ORTH(NBW_, NB_)                                                                                       \
   do {                                                                                                            \
     hipLaunchKernelGGL(chol_kernel<NBW_>, dim3(batch), dim3(512), 0, st, S, Lp, m, m, nbc);                         \
-    hipLaunchKernelGGL(trsm_kernel<NB_>, dim3(D / 16, batch), dim3(64), 0, st, Lp, Y, X, m, nbc, D);                \
+    hipLaunchKernelGGL(trsm_kernel<NB_>, dim3(D / 16, batch), dim3(256), 0, st, Lp, Y, X, m, nbc, D);                \
   } while (0)
     // (blocks per wave of the eight, block rows held): up to 80, 192, 224, 288 vectors
     if (nbc <= 5) SKV_ORTH(2, 5);
