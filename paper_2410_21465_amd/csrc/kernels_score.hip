@@ -88,7 +88,10 @@ __global__ __launch_bounds__(256) void score_kernel(const bf16_t* __restrict__ q
 
   const uint8_t* Lu = L + (size_t)unit * nc_stride * D * EB;  // the landmark array may have room to grow
   const int row0 = tile * kScoreTile + wave * kWave;
-  uint32_t w[4][NI][PW];  // requested before q: the landmark rows are the long-latency loads
+  // requested before q: the landmark rows are the long-latency loads.  FP8 rows past the end repeat the last one and count
+  // as -inf below: a clamped index costs less than a lane mask around every load (step of 16 x 128K 129.5 -> 126.1 us; 1M tokens with 16 heads per group 104.8 -> 103 us);
+  // bf16 rows are bound by the memory system and lose by it (168.4 -> 169.5 us)
+  uint32_t w[4][NI][PW];
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
     const int r = row0 + t * 16 + blk * 4 + ij;
@@ -96,8 +99,8 @@ __global__ __launch_bounds__(256) void score_kernel(const bf16_t* __restrict__ q
     for (int i = 0; i < NI; ++i) {
 #pragma unroll
       for (int x = 0; x < PW; ++x) w[t][i][x] = 0u;
-      if (r < n_c) {
-        const uint8_t* src = Lu + (size_t)r * D * EB + (size_t)(4 * PE * i + PE * kq) * EB;
+      if (EB == 1 || r < n_c) {
+        const uint8_t* src = Lu + (size_t)(EB == 1 ? min(r, n_c - 1) : r) * D * EB + (size_t)(4 * PE * i + PE * kq) * EB;
         if constexpr (PW == 4) {
           const uint4 v = *reinterpret_cast<const uint4*>(src);
           w[t][i][0] = v.x; w[t][i][1] = v.y; w[t][i][2] = v.z; w[t][i][3] = v.w;
@@ -194,20 +197,16 @@ __global__ __launch_bounds__(256) void score_kernel_g16(const bf16_t* __restrict
   uint32_t w[4][NI][PW];
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    const int r = row0 + t * 16 + rl;
+    const uint8_t* row = Lu + (size_t)min(row0 + t * 16 + rl, n_c - 1) * D * EB + PE * kq * EB;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-#pragma unroll
-      for (int x = 0; x < PW; ++x) w[t][i][x] = 0u;
-      if (r < n_c) {
-        const uint8_t* src = Lu + (size_t)r * D * EB + (size_t)(4 * PE * i + PE * kq) * EB;
-        if constexpr (PW == 4) {
-          const uint4 v = *reinterpret_cast<const uint4*>(src);
-          w[t][i][0] = v.x; w[t][i][1] = v.y; w[t][i][2] = v.z; w[t][i][3] = v.w;
-        } else {
-          const uint2 v = *reinterpret_cast<const uint2*>(src);
-          w[t][i][0] = v.x; w[t][i][1] = v.y;
-        }
+      const uint8_t* src = row + 4 * PE * i * EB;
+      if constexpr (PW == 4) {
+        const uint4 v = *reinterpret_cast<const uint4*>(src);
+        w[t][i][0] = v.x; w[t][i][1] = v.y; w[t][i][2] = v.z; w[t][i][3] = v.w;
+      } else {
+        const uint2 v = *reinterpret_cast<const uint2*>(src);
+        w[t][i][0] = v.x; w[t][i][1] = v.y;
       }
     }
   }
