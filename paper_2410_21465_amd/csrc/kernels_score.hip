@@ -89,8 +89,9 @@ __global__ __launch_bounds__(256) void score_kernel(const bf16_t* __restrict__ q
   const uint8_t* Lu = L + (size_t)unit * nc_stride * D * EB;  // the landmark array may have room to grow
   const int row0 = tile * kScoreTile + wave * kWave;
   // requested before q: the landmark rows are the long-latency loads.  FP8 rows past the end repeat the last one and count
-  // as -inf below: a clamped index costs less than a lane mask around every load (step of 16 x 128K 129.5 -> 126.1 us; 1M tokens with 16 heads per group 104.8 -> 103 us);
-  // bf16 rows are bound by the memory system and lose by it (168.4 -> 169.5 us)
+  // as -inf below: a clamped index costs less than a lane mask around every load (step of 16 x 128K 129.5 -> 126.1 us; in
+  // the 16-head kernel, 1M tokens, 104.8 -> 103 us); bf16 rows are bound by the memory system and lose by it (168.4 ->
+  // 169.5 us).
   uint32_t w[4][NI][PW];
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
