@@ -49,14 +49,15 @@ struct Raw4 {
 // ---- 1. Gram matrix ---------------------------------------------------------------------------------
 // One wave per (pair of 64-column blocks bi <= bj, token split, sequence).  Tile (mt, nt) of the 64 x 64
 // block holds columns i0 + 4 m + mt against j0 + 4 n + nt, so that a lane's four consecutive columns feed
-// four tiles and every load is 8 (or 4) contiguous bytes.  part [split][b][D][D] fp64, blocks bi <= bj only.
+// four tiles and every load is 8 (or 4) contiguous bytes.  part [split][b][pair][64][64] fp64: the blocks bi <= bj packed,
+// a little over half of D x D.
 // Bound by the matrix pipe: 67 TFLOP/s at 16 x 128K x 1024 (a large library product reaches 73; 61 with loads under lane
 // masks, whose results the matrix instructions then waited for).
 template <int EB>
 __global__ __launch_bounds__(64, 2) void gram_kernel(const void* __restrict__ K, double* __restrict__ part, int s, int D,
                                                   int nb, int tokens_per_split, int batch) {
   const int lane = threadIdx.x, mrow = lane & 15, kq = lane >> 4;
-  // pair index -> (bi, bj), bi <= bj, row by row of the upper triangle
+  // pair index -> (bi, bj), bi <= bj, row by row of the upper triangle (upper_block the other way round)
   int p = blockIdx.x, bi = 0;
   while (p >= nb - bi) { p -= nb - bi; ++bi; }
   const int bj = bi + p;
@@ -109,35 +110,39 @@ __global__ __launch_bounds__(64, 2) void gram_kernel(const void* __restrict__ K,
           acc[mt][nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[mt], bb[nt], acc[mt][nt], 0, 0, 0);
     }
   }
-  double* out = part + ((size_t)split * batch + b) * D * D;
+  double* out = part + (((size_t)split * batch + b) * gridDim.x + blockIdx.x) * 4096;
 #pragma unroll
   for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int gi = bi * 64 + 4 * (4 * j + kq) + mt, gj = bj * 64 + 4 * mrow + nt;
-        if (gi < D && gj < D) out[(size_t)gi * D + gj] = acc[mt][nt][j];
+        const int i = 4 * (4 * j + kq) + mt, x = 4 * mrow + nt;
+        if (bi * 64 + i < D && bj * 64 + x < D) out[i * 64 + x] = acc[mt][nt][j];
       }
 }
+
+// index of the pair (bi, bj), bi <= bj < nb, in the order of gram_kernel's grid
+__device__ __forceinline__ int upper_block(int nb, int bi, int bj) { return bi * nb - bi * (bi - 1) / 2 + (bj - bi); }
 
 // G[b][i][j] = sum over the splits of the block that holds (i, j), written to (j, i) as well.  One 32 x 32 tile on or above
 // the diagonal per workgroup; the mirrored copy goes through LDS so that both are written in rows.  (Reading the mirrored
 // element per thread instead took 165 us for 32 splits of 1024 columns.)
 __global__ __launch_bounds__(256) void gram_finish_kernel(const double* __restrict__ part, double* __restrict__ G, int D,
-                                                          int nt, int n_splits, int batch) {
+                                                          int nt, int nb, int n_splits, int batch) {
   __shared__ double tile[32][33];
   int p = blockIdx.x, ti = 0;   // tile index -> (ti, tj), ti <= tj, row by row of the upper triangle
   while (p >= nt - ti) { p -= nt - ti; ++ti; }
   const int tj = ti + p, b = blockIdx.y;
   const int x = threadIdx.x & 31, y0 = threadIdx.x >> 5;
-  const size_t DD = (size_t)D * D, off = (size_t)b * DD;
+  const size_t off = (size_t)b * D * D, pairs = (size_t)nb * (nb + 1) / 2;
   double sum[4] = {0.0, 0.0, 0.0, 0.0};
-  const double* src = part + off + (size_t)(ti * 32 + y0) * D + tj * 32 + x;
+  // the tile's quarter of the 64 x 64 block that holds it
+  const double* src = part + (b * pairs + upper_block(nb, ti >> 1, tj >> 1)) * 4096 + ((ti & 1) * 32 + y0) * 64 + (tj & 1) * 32 + x;
 #pragma unroll 4
   for (int sp = 0; sp < n_splits; ++sp)
 #pragma unroll
-    for (int u = 0; u < 4; ++u) sum[u] += src[(size_t)sp * batch * DD + (size_t)8 * u * D];
+    for (int u = 0; u < 4; ++u) sum[u] += src[(size_t)sp * batch * pairs * 4096 + 8 * u * 64];
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     G[off + (size_t)(ti * 32 + y0 + 8 * u) * D + tj * 32 + x] = sum[u];
@@ -351,44 +356,59 @@ FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int
   p.nb = (D + 63) / 64;
   const long pairs = (long)p.nb * (p.nb + 1) / 2;
   const long max_splits = (s + 1023) / 1024, blocks = pairs * batch;
-  // tuning override: waves aimed at
+  auto up = [](size_t x) { return (x + 255) / 256 * 256; };
+  auto doubles = [&](size_t per_sequence) { return up(per_sequence * batch * 8); };
+  auto split_tokens = [&](long splits) {
+    p.tokens_per_split = (int)(((s + splits - 1) / splits + 15) / 16 * 16);
+    p.n_splits = (s + p.tokens_per_split - 1) / p.tokens_per_split;
+  };
+  const size_t m = p.m, mp = p.mp, DD = (size_t)D * D, nbc = (m + 15) / 16;
+
+  // Workspace: G, then one region that first holds the partial sums of the Gram matrix and, once G is formed, everything
+  // else.  V takes G's place (G is last read by the product that forms T; mp <= D), S is W's place (last read before T is
+  // written), J and Psi_t that of Lp and Yt (last read by T's products; r <= m).
+  p.G = p.V = 0;
+  size_t off = doubles(DD);
+  p.part = p.Xt = off;
+  size_t end = off + doubles(m * D);
+  p.W = p.S = end; end += doubles(mp * mp);
+  p.idle = end; end += up((size_t)2 * batch * (mp / 32) * 4);
+  p.sweep_max = end; end += up((size_t)batch * n_sweeps * 4);
+  p.order = end; end += up((size_t)batch * r * 4);
+  p.Lp = p.Jbuf = p.Psi_t = end;
+  p.Yt = end + doubles(nbc * (nbc + 1) / 2 * 256);
+  end = std::max(p.Yt + doubles(m * D), end + doubles(2 * (mp / 32) * 1024));
+  const size_t split_bytes = (size_t)blocks * 4096 * 8;
+
+  // What a workspace may take: programs that keep one were given room for D x D partial sums of every split, the tokens
+  // split for 8192 waves, and all other arrays side by side.  That room holds about twice as many packed ones.
+  // (SHADOWKV_GRAM_WAVES, a tuning override: waves aimed at)
   static const long target = [] { const char* e = getenv("SHADOWKV_GRAM_WAVES"); return e ? atol(e) : 0l; }();
+  const long aim = target > 0 ? target : 8192l;
+  const long aim_splits = std::max(1l, std::min(max_splits, (aim + blocks - 1) / blocks));
+  split_tokens(aim_splits);
+  const size_t even = (m + 1) / 2 * 2;
+  const size_t room = doubles(p.n_splits * DD) + doubles(DD) + 2 * doubles(m * D) + 2 * doubles(even * even) + doubles(r * m) +
+                      doubles((size_t)r * D);
+  const long fit = std::max(1l, (long)((room - off) / split_bytes));
   long splits = 1;
   if (target > 0) {
-    splits = std::max(1l, std::min(max_splits, (target + blocks - 1) / blocks));
+    splits = std::min(aim_splits, fit);
   } else {
-    // The tokens are split so that the last round of waves is nearly full: 2048 waves are resident (two per SIMD) and a wave
-    // takes 245 us for 1024 tokens (64 x 8 matrix instructions per 16 tokens and pair of waves, with what a large matrix
-    // reaches of the peak), a round of at most one wave per SIMD 0.6 of that; every split costs its partial sums once
-    // written and once read (1.06 x 8 bytes D^2 per sequence at 4.6 TB/s).  16 x 128K x 1024: 16 splits, 17 rounds, where 4
-    // splits make 4.25 rounds; 1 x 32K: 15 splits, one round, where 32 make 2.1.
+    // The token splits that cost least: 2048 waves are resident (two per SIMD) and a wave takes 245 us for 1024 tokens
+    // (64 x 8 matrix instructions per 16 tokens and pair of waves, with what a large matrix reaches of the peak), a round of
+    // at most one wave per SIMD 0.6 of that; every split costs its partial sums once written and once read (1.06 x 8 bytes
+    // D^2 per sequence at 4.6 TB/s).  More splits have to be worth half a per cent.
     double best = 0.0;
-    for (long sp = 1; sp <= std::min(max_splits, 512l); ++sp) {
+    for (long sp = 1; sp <= std::min({max_splits, 512l, fit}); ++sp) {
       const long waves = blocks * sp, rest = waves % 2048;
       const double rounds = (double)(waves / 2048) + (rest == 0 ? 0.0 : rest <= 1024 ? 0.6 : 1.0);
       const double cost = rounds * (double)((s + sp - 1) / sp) * (245.0 / 1024.0) + (double)sp * batch * D * D * (1.06 * 8.0 / 4.6e6);
       if (sp == 1 || cost < best * 0.995) { best = cost; splits = sp; }
     }
   }
-  p.tokens_per_split = (int)(((s + splits - 1) / splits + 15) / 16 * 16);
-  p.n_splits = (s + p.tokens_per_split - 1) / p.tokens_per_split;
-  size_t off = 0;
-  auto up = [](size_t x) { return (x + 255) / 256 * 256; };
-  const size_t DD = (size_t)D * D;
-  p.part = off; off += up((size_t)p.n_splits * batch * DD * 8);
-  p.G = off; off += up((size_t)batch * DD * 8);
-  p.Xt = off; off += up((size_t)batch * p.m * D * 8);
-  p.Yt = off; off += up((size_t)batch * p.m * D * 8);
-  p.S = off; off += up((size_t)batch * p.m * p.m * 8);
-  p.Lp = off; off += up((size_t)batch * ((p.m + 15) / 16) * ((p.m + 15) / 16 + 1) / 2 * 256 * 8);
-  p.W = off; off += up((size_t)batch * p.mp * p.mp * 8);
-  p.V = off; off += up((size_t)batch * p.mp * p.mp * 8);
-  p.Jbuf = off; off += up((size_t)2 * batch * (p.mp / 32) * 1024 * 8);
-  p.idle = off; off += up((size_t)2 * batch * (p.mp / 32) * 4);
-  p.sweep_max = off; off += up((size_t)batch * n_sweeps * 4);
-  p.order = off; off += up((size_t)batch * r * 4);
-  p.Psi_t = off; off += up((size_t)batch * r * D * 8);
-  p.total = off;
+  split_tokens(splits);
+  p.total = std::max(end, off + up(p.n_splits * split_bytes));
   return p;
 }
 
@@ -418,7 +438,7 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
     else hipLaunchKernelGGL(gram_kernel<2>, grid, dim3(64), 0, st, k_pre, part, s, D, pl.nb, pl.tokens_per_split, batch);
     SKV_CHECK();
     const int nt = D / 32;   // (the key width is a multiple of 32)
-    hipLaunchKernelGGL(gram_finish_kernel, dim3(nt * (nt + 1) / 2, batch), dim3(256), 0, st, part, G, D, nt, pl.n_splits, batch);
+    hipLaunchKernelGGL(gram_finish_kernel, dim3(nt * (nt + 1) / 2, batch), dim3(256), 0, st, part, G, D, nt, pl.nb, pl.n_splits, batch);
     SKV_CHECK();
   }
   // 2. subspace iteration: X <- orth(G X); rows of Xt are the vectors

@@ -140,6 +140,28 @@ def test_factorize_keys_rejects_bad_arguments_without_a_gpu():
     assert "key width" in S.last_error()
 
 
+@pytest.mark.parametrize("hkv,d", [(1, 64), (1, 96), (1, 128), (3, 64), (5, 96), (8, 128), (32, 96), (32, 128)])
+@pytest.mark.parametrize("b,s", [(1, 8), (1, 4096), (3, 2049), (2, 61448), (4, 131072), (16, 131072), (1, 1048576)])
+def test_factorize_workspace_takes_no_more_than_it_did(b, s, hkv, d):
+    """Programs keep a workspace of a size they once asked for: D x D partial sums of the Gram matrix for the token splits of
+    8192 waves, G, two sets of m vectors, two m x m matrices, their r chosen columns, Psi, each on 256 bytes."""
+    up = lambda n: (n * b * 8 + 255) // 256 * 256
+    for r in (8, 24, 64, 96, 160, 200, 256):
+        D = hkv * d
+        if r > D:
+            continue
+        m = min(D, r + 32)
+        even, nb = (m + 1) // 2 * 2, (D + 63) // 64
+        blocks = nb * (nb + 1) // 2 * b
+        splits = max(1, min((s + 1023) // 1024, (8192 + blocks - 1) // blocks))
+        per = ((s + splits - 1) // splits + 15) // 16 * 16
+        most = up((s + per - 1) // per * D * D) + up(D * D) + 2 * up(m * D) + 2 * up(even * even) + up(r * m) + up(r * D)
+        st = S.Params(batch=b, n_q_heads=hkv, n_kv_heads=hkv, head_dim=d, ctx_len=s, chunk_size=1, rank=r,
+                      n_outlier_chunks=0, topk_chunks=1, local_len=0).c_struct()
+        need = S.lib().shadowkv_factorize_workspace_bytes(C.addressof(st))
+        assert up(D * D) < need <= most, (b, s, hkv, d, r, need, most)
+
+
 def test_append_chunk_rejects_a_full_context_and_bad_capacity():
     lib = S.lib()
     fake = C.c_void_p(0x1000)
