@@ -423,7 +423,9 @@ __global__ __launch_bounds__(512) void jacobi_block_kernel(double* __restrict__ 
           members(t, u, pu, qu);
           const double pp = Sa[pu * P + p], pq = Sa[pu * P + q], qp = Sa[qu * P + p], qq = Sa[qu * P + q];
           double c = 1.0, sn = 0.0;
-          if (fabs(ga) > 1e-300 && ga * ga > 1e-34 * (al * be)) rotation(al, be, ga, c, sn);
+          // (roots, not squares: al and be are fourth powers of singular values, al * be need not fit in fp64)
+          if (fabs(ga) > 1e-300 && fabs(ga) > 1e-17 * (__builtin_amdgcn_sqrt(fmax(al, 0.0)) * __builtin_amdgcn_sqrt(fmax(be, 0.0))))
+            rotation(al, be, ga, c, sn);
           if (threadIdx.x < 16) cs[t & 1][sub] = make_double2(c, sn);
           const double cu = __shfl(c, u, kWave), su = __shfl(sn, u, kWave);
           const double tp = cu * pp - su * qp, tq = cu * pq - su * qq, bp = su * pp + cu * qp, bq = su * pq + cu * qq;

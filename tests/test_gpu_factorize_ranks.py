@@ -57,3 +57,28 @@ def test_factors_at_every_shape_of_the_small_algebra(b, h, d, s, r, lead):
         assert (got["B"][i].cpu().float() - want.float()).abs().max() <= 2.0 ** -8
         A = K @ psi[i].T
         assert np.abs(got["A"][i, :s].cpu().double().numpy() - A).max() <= 2.0 ** -8 * np.abs(A).max()
+
+
+@pytest.mark.parametrize("exp2", [-133, 0, 126])
+@pytest.mark.parametrize("h,d,s,r", [(1, 64, 300, 64), (2, 96, 1000, 160)])
+def test_keys_at_the_ends_of_the_storage_types_range(h, d, s, r, exp2):
+    """Keys of 0 and +-2^exp2, from the least bf16 number to nearly the largest, with as many vectors as columns, so that the
+    Ritz step alone decides.  What its rotations look at are fourth powers of singular values, and the product of two of
+    those leaves the range of fp64 at both ends."""
+    D = h * d
+    print(f"\n[case] h {h} d {d} s {s} r {r} scale 2^{exp2}", flush=True)
+    gen = torch.Generator(device="cpu").manual_seed(D)
+    K = torch.randint(-1, 2, (s, D), generator=gen).double()
+    k = (K * 2.0 ** exp2).to(torch.bfloat16)[None]
+    assert torch.equal(k[0].double() * 2.0 ** -exp2, K)
+    p = S.Params(batch=1, n_q_heads=h, n_kv_heads=h, head_dim=d, ctx_len=s, chunk_size=1, rank=r, n_outlier_chunks=0,
+                 topk_chunks=1, local_len=0)
+    got = S.factorize_keys(p, k.cuda(), want_vectors=True)
+    torch.cuda.synchronize()
+    psi, sig = got["psi"][0].cpu().numpy(), got["sigma"][0].cpu().numpy() * 2.0 ** -exp2
+    G = (K.T @ K).numpy()
+    lam = np.linalg.eigvalsh(G)[::-1]
+    # rounding only, of sums of at most a thousand terms: 1e-12 of the largest eigenvalue
+    assert np.abs(psi @ psi.T - np.eye(r)).max() < 1e-12
+    assert np.abs(sig ** 2 - lam[:r]).max() <= 1e-12 * lam[0]
+    assert np.abs(psi @ G - (sig ** 2)[:, None] * psi).max() <= 1e-12 * lam[0]
