@@ -94,13 +94,6 @@ __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int mask) {
 }
 
 // sum over the 16 lanes that share lane/16 (result in all 16)
-__device__ __forceinline__ double sum16_f64(double v) {
-  v += shfl_xor_f64(v, 8);
-  v += shfl_xor_f64(v, 4);
-  v += shfl_xor_f64(v, 2);
-  v += shfl_xor_f64(v, 1);
-  return v;
-}
 __device__ __forceinline__ float sum16_f32(float v) {
   v += __shfl_xor(v, 8, kWave);
   v += __shfl_xor(v, 4, kWave);

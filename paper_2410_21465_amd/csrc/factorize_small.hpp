@@ -11,8 +11,8 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // ---- products ---------------------------------------------------------------------------------------
 // C[i][j] = sum_k A[i][k] B(k, j), K a multiple of 16, rows of A 16-byte aligned.  BT: B is given by its columns
-// (B(k, j) = B[j][k], as A is); otherwise row-major with Kb rows (A is zero beyond).  Rows of A may be taken through a_rows.  C is written over
-// Mw x Nw, zero outside M x N.
+// (B(k, j) = B[j][k], as A is); otherwise row-major with Kb rows (A is zero beyond).  Rows of A may be taken through
+// a_rows.  C is written over Mw x Nw, zero outside M x N.
 // A workgroup is WM x WN tiles of 16 T x 16 T with the contraction cut WK ways; every operand goes from L2 straight to the
 // matrix instruction (a lane's four consecutive elements are four contraction steps), the next 16 steps requested
 // before the current ones' 16 instructions.  The products here are small (192 x 1024 x 1024 per sequence), so what
@@ -123,8 +123,10 @@ __device__ __forceinline__ double rsqrt_f64(double x) {
 // operand order, off the diagonal -L, on it the inverse of L's block (what trsm_kernel multiplies by).
 // The trailing blocks stay in the accumulators of the waves (blocks dealt out in turn, NBW per wave) for the whole
 // factorisation; only the current block column goes through LDS.  What bounds it is the chain of pivots: 16 rsqrt + updates
-// per diagonal block in one wave (60 us for 192 vectors, 79 us with the library's square root and division), which carries the unit matrix along in a second group of lanes and so ends with the
-// inverse as well.
+// per diagonal block in one wave (59 us for 192 vectors, 79 us with the library's square root and division), which carries
+// the unit matrix along in a second group of lanes and so ends with the inverse as well.  Above 192 vectors the blocks of a
+// wave no longer fit in its registers beside the rest: of 256, 19 are kept in scratch memory with NBW = 14 (224 vectors:
+// 90 us) and 161 with NBW = 22 (288 vectors: 182 us).
 // A pivot below kPivotFloor of the vector's own square is rounding: it is set to that floor, which leaves the vector's
 // remainder at a size that the next pass can work on, and nothing is projected on it; a zero vector stays zero.
 template <int NBW>
@@ -290,14 +292,15 @@ __global__ __launch_bounds__(256) void trsm_kernel(const double* __restrict__ Lp
 // step of a sweep all pairs of its 32 columns): it forms the 32 x 32 products of the columns on the matrix instruction,
 // rotates those (two-sided, in LDS, 16 disjoint rotations at a time, accumulated in J) and applies J to its columns as one
 // product.  A rotation's angle thus costs two rounds of LDS and a barrier, not a pass over the columns and a launch: a
-// sweep of 192 columns is 11 launches of 17 us where a launch per set of 96 single rotations took 191 of 4.5 us, and six
-// sweeps do (1.2 ms in all, 8.1 ms before, one sequence; 16 sequences: 1.5 ms, 11.4 ms).
+// sweep of 192 columns is 11 launches of 17 us (the first 26, those without a rotation 6) where a launch per set of 96
+// single rotations took 191 of 4.5 us, and six sweeps do (1.0 ms in all, 8.1 ms before, one sequence; 16 sequences: 1.3 ms,
+// 11.4 ms).
 // V is not needed before the end: its product with J is done by other workgroups of the next step's launch.
 // A sweep in which every cosine met was below kJacobiDone needs no successor (what is left is its square): the launches of
 // the later ones end at once.  sweep_max [batch][sweeps]: the largest cosine of each sweep (its bits; cosines are >= 0).
 constexpr float kJacobiDone = 1e-10f;
 __device__ __forceinline__ bool jacobi_active(const int32_t* sweep_max, int sweep) {
-  // (written so that a cosine that is not a number goes on)
+  // (a stored cosine that is not a number counts as not done)
   return sweep == 0 || !(__int_as_float(sweep_max[sweep - 1]) < kJacobiDone);
 }
 // (c, s) of the rotation that makes two columns with squares al, be and product ga orthogonal: tan 2 theta = 2 ga / (be - al),

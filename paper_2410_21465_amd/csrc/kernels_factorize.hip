@@ -7,8 +7,8 @@
 //      elements are exact, the sum is fp64) -- the dense contraction, 2 s D^2 flops, K streamed once per
 //      column-block pair; only blocks on and above the diagonal are formed, gram_finish sums the token
 //      splits and mirrors;
-//   2. subspace iteration on m = r + oversample vectors (X <- orth(G X), by Cholesky factorisation of the vectors' products), then one
-//      Rayleigh-Ritz step: T = X^T G X, eigenvectors of the small T by one-sided Jacobi rotations in
+//   2. subspace iteration on m = r + oversample vectors (X <- orth(G X), by Cholesky factorisation of the vectors'
+//      products), then one Rayleigh-Ritz step: T = X^T G X, eigenvectors of the small T by one-sided Jacobi rotations in
 //      blocks, the r largest kept -- all fp64, small, one launch per dependent step (factorize_small.hpp);
 //   3. sign convention (largest-magnitude component positive), B written, and project_kernel: A = K Psi on
 //      the same matrix instruction.
@@ -330,9 +330,10 @@ __global__ __launch_bounds__(64, 2) void project_kernel(const void* __restrict__
 // ---- launch sequence ----------------------------------------------------------------------------------------
 // C (Mw x Nw, zero outside M x N) = A B, see gemm64_kernel; ?.ld = elements from row to row, ?.stride = from sequence to
 // sequence.  Fewer than 64 tiles of 32 x 32 (the m x m products of one sequence): 16 x 16 tiles, the contraction cut in
-// four (192 x 192 x 1024: 11.5 us, 18.5 us on 36 tiles of 32 x 32).  Up to 1024: 32 x 32 tiles with the contraction cut eight ways (192 x 1024 x 1024 takes 18 us for one sequence, 211
-// us with a tile per workgroup on the vector unit).  More: 64 x 64 blocks cut in two (16 sequences: 177 us, 298 us on the
-// vector unit).
+// four (192 x 192 x 1024: 11.7 us, 18.5 us on 36 tiles of 32 x 32).  Up to 1024: 32 x 32 tiles with the contraction cut
+// eight ways (192 x 1024 x 1024 takes 19.6 us for one sequence, 211 us with a tile per workgroup on the vector unit).  More:
+// 64 x 64 blocks cut in two (16 sequences: 176 us, 298 us on the vector unit).  The limits lie between shapes that were
+// measured on both sides, 192 vectors of 1 and 16 sequences; those in between were not searched.
 struct Mat { const double* p; int ld; size_t stride; };
 template <bool BT>
 static hipError_t gemm64(Mat A, Mat B, double* C, int ldc, size_t strideC, int M, int N, int K, int Kb, int Mw, int Nw,
@@ -398,7 +399,10 @@ FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int
     // The token splits that cost least: 2048 waves are resident (two per SIMD) and a wave takes 245 us for 1024 tokens
     // (64 x 8 matrix instructions per 16 tokens and pair of waves, with what a large matrix reaches of the peak), a round of
     // at most one wave per SIMD 0.6 of that; every split costs its partial sums once written and once read (1.06 x 8 bytes
-    // D^2 per sequence at 4.6 TB/s).  More splits have to be worth half a per cent.
+    // D^2 per sequence at 4.6 TB/s).  More splits have to be worth half a per cent.  16 x 128K x 1024: 8 splits, 8.5 rounds
+    // (4 splits, 4.25 rounds, paid for five: 40.6 against 38.1 ms, with loads then under lane masks; 34.9 now); 1 x 32K: 15
+    // splits in one round where 32 make 2.1 (0.62 ms).  The limit costs the widest keys 1 to 3 per cent of the call: 97.1 ms
+    // at 4 x 128K x 3072 (3 splits; 96.0 with the 10 that take 3.4 GB), 43.9 at 1 x 128K x 4096 (42.6 with 3.0 GB).
     double best = 0.0;
     for (long sp = 1; sp <= std::min({max_splits, 512l, fit}); ++sp) {
       const long waves = blocks * sp, rest = waves % 2048;

@@ -18,8 +18,9 @@
 // k = which 16-byte piece of each 64-byte row segment the lane loads.  A wave covers
 // 64 rows (four 16-row tiles, all loads issued before the first MFMA), a workgroup 256.
 // Result lane 16*i + r holds the logit of head i, row r of the tile: it stores it
-// (16 consecutive floats per head) and folds the fp64 value into its running (max, sum exp),
-// from which the selection kernel forms each head's log-sum-exp.
+// (16 consecutive floats per head) and keeps the fp64 value until the wave's four tiles are
+// done, when the 64 rows' (max, sum exp) are formed at once (row16_lse) and merged over the
+// workgroup; the selection kernel makes each head's log-sum-exp of these.
 #include "kernels.hpp"
 
 namespace skv {
@@ -42,8 +43,8 @@ __device__ __forceinline__ void lse_merge(double& m, double& s, double m2, doubl
 // (max, sum exp(p - max)) over four values per lane and the 16 lanes of a row, in every lane of the row.  One maximum first,
 // then every value against it: no branches and one exponential per value (merging (m, s) pairs value by value took a
 // branch each, a third of the kernel's vector instructions with FP8 landmarks: 83 us against 77 at 16 x 128K, and 41 against
-// 32 for one sequence of 1M tokens with 16 heads per group).  A value equal to the maximum counts 1, also
-// when it is infinite; rows that do not exist carry -inf and count 0.
+// 32 for one sequence of 1M tokens with 16 heads per group).  A value equal to the maximum counts 1; rows that do not exist
+// carry -inf and count 0.  (Infinite logits end as NaN: where two waves meet the same one, lse_merge subtracts it from itself.)
 __device__ __forceinline__ void row16_lse(const double (&p)[4], double& M, double& S) {
   M = fmax(fmax(p[0], p[1]), fmax(p[2], p[3]));
   M = fmax(M, dpp_f64<0x128>(M, M));   // row_ror 8, 4, 2, 1

@@ -682,7 +682,7 @@ int shadowkv_append_chunk(const shadowkv_params* params, const shadowkv_kv* k_pr
 }
 
 constexpr int kFactorOversample = 32;  // extra vectors carried by the subspace iteration
-constexpr int kFactorSweeps = 9;       // Jacobi sweeps of the Ritz step (converged to rounding after 7-8 for m <= 288)
+constexpr int kFactorSweeps = 9;       // most Jacobi sweeps of the Ritz step (192 vectors: six; later ones end at once)
 constexpr int kFactorIters = 16;       // default number of subspace iterations
 
 size_t shadowkv_factorize_workspace_bytes(const shadowkv_params* params) {
