@@ -180,9 +180,13 @@ struct FactorizePlan {
   int m, mp;                // subspace width r + oversample (at most D), and the same rounded up to a multiple of 32
   int nb;                   // 64-column blocks of the Gram matrix
   int n_splits, tokens_per_split;
+  int nb2;                  // 128-column blocks of the digit products
+  int rest_cap;             // entries per list of what the digits miss
+  int max_lv, max_chunk, n_chunks;   // column maxima: 16-byte pieces side by side in a workgroup, tokens per chunk, chunks
   size_t part, G, Xt, Yt, S, Lp, W, V, Jbuf, idle, sweep_max, order, Psi_t, total;  // workspace offsets (bytes)
+  size_t scale, flags, rest, rest_count, by_col, col_begin;
 };
-FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int n_sweeps);
+FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int n_sweeps, int kv_bytes);
 // k_pre [b, s, h_kv*d]; A [b, s_cap, r]; B [b, h_kv, r, d]; psi_out optional [b, r, D] fp64 (right singular vectors
 // as rows, after the sign convention); sigma_out optional [b, r] fp64 (singular values, strongest first)
 hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, double* psi_out, double* sigma_out,

@@ -3,10 +3,10 @@
 // (section "High-throughput Decoding", footnote: keys are stored as K Psi and projected back with Psi^T).
 //
 // On the GPU the right singular vectors are the leading eigenvectors of the Gram matrix G = K^T K:
-//   1. gram_kernel: G in fp64 on the fp64 matrix pipe (v_mfma_f64_16x16x4f64; the products of stored
-//      elements are exact, the sum is fp64) -- the dense contraction, 2 s D^2 flops, K streamed once per
-//      column-block pair; only blocks on and above the diagonal are formed, gram_finish sums the token
-//      splits and mirrors;
+//   1. G exactly from 8-bit digits of the keys on the integer matrix instruction (factorize_gram.hpp), or, for sequences whose
+//      keys' magnitudes are too far apart for that, gram_kernel: fp64 on the fp64 matrix pipe (v_mfma_f64_16x16x4f64; the
+//      products of stored elements are exact) -- the dense contraction, 2 s D^2 operations; only blocks on and above the
+//      diagonal are formed, gram_finish sums the token splits and mirrors;
 //   2. subspace iteration on m = r + oversample vectors (X <- orth(G X), by Cholesky factorisation of the vectors'
 //      products), then one Rayleigh-Ritz step: T = X^T G X, eigenvectors of the small T by one-sided Jacobi rotations in
 //      blocks, the r largest kept -- all fp64, small, one launch per dependent step (factorize_small.hpp);
@@ -18,6 +18,7 @@
 #include <cstdlib>
 #include <type_traits>
 
+#include "factorize_gram.hpp"
 #include "factorize_small.hpp"
 #include "kernels.hpp"
 
@@ -51,11 +52,14 @@ struct Raw4 {
 // block holds columns i0 + 4 m + mt against j0 + 4 n + nt, so that a lane's four consecutive columns feed
 // four tiles and every load is 8 (or 4) contiguous bytes.  part [split][b][pair][64][64] fp64: the blocks bi <= bj packed,
 // a little over half of D x D.
+// Only for sequences whose flag is raised (gram_digits_kernel forms the others' sums).
 // Bound by the matrix pipe: 67 TFLOP/s at 16 x 128K x 1024 (a large library product reaches 73; 61 with loads under lane
 // masks, whose results the matrix instructions then waited for).
 template <int EB>
-__global__ __launch_bounds__(64, 2) void gram_kernel(const void* __restrict__ K, double* __restrict__ part, int s, int D,
-                                                  int nb, int tokens_per_split, int batch) {
+__global__ __launch_bounds__(64, 2) void gram_kernel(const void* __restrict__ K, double* __restrict__ part,
+                                                     const int32_t* __restrict__ flags, int s, int D, int nb,
+                                                     int tokens_per_split, int batch) {
+  if (!flags[blockIdx.z]) return;
   const int lane = threadIdx.x, mrow = lane & 15, kq = lane >> 4;
   // pair index -> (bi, bj), bi <= bj, row by row of the upper triangle (upper_block the other way round)
   int p = blockIdx.x, bi = 0;
@@ -120,38 +124,6 @@ __global__ __launch_bounds__(64, 2) void gram_kernel(const void* __restrict__ K,
         const int i = 4 * (4 * j + kq) + mt, x = 4 * mrow + nt;
         if (bi * 64 + i < D && bj * 64 + x < D) out[i * 64 + x] = acc[mt][nt][j];
       }
-}
-
-// index of the pair (bi, bj), bi <= bj < nb, in the order of gram_kernel's grid
-__device__ __forceinline__ int upper_block(int nb, int bi, int bj) { return bi * nb - bi * (bi - 1) / 2 + (bj - bi); }
-
-// G[b][i][j] = sum over the splits of the block that holds (i, j), written to (j, i) as well.  One 32 x 32 tile on or above
-// the diagonal per workgroup; the mirrored copy goes through LDS so that both are written in rows.  (Reading the mirrored
-// element per thread instead took 165 us for 32 splits of 1024 columns.)
-__global__ __launch_bounds__(256) void gram_finish_kernel(const double* __restrict__ part, double* __restrict__ G, int D,
-                                                          int nt, int nb, int n_splits, int batch) {
-  __shared__ double tile[32][33];
-  int p = blockIdx.x, ti = 0;   // tile index -> (ti, tj), ti <= tj, row by row of the upper triangle
-  while (p >= nt - ti) { p -= nt - ti; ++ti; }
-  const int tj = ti + p, b = blockIdx.y;
-  const int x = threadIdx.x & 31, y0 = threadIdx.x >> 5;
-  const size_t off = (size_t)b * D * D, pairs = (size_t)nb * (nb + 1) / 2;
-  double sum[4] = {0.0, 0.0, 0.0, 0.0};
-  // the tile's quarter of the 64 x 64 block that holds it
-  const double* src = part + (b * pairs + upper_block(nb, ti >> 1, tj >> 1)) * 4096 + ((ti & 1) * 32 + y0) * 64 + (tj & 1) * 32 + x;
-#pragma unroll 4
-  for (int sp = 0; sp < n_splits; ++sp)
-#pragma unroll
-    for (int u = 0; u < 4; ++u) sum[u] += src[(size_t)sp * batch * pairs * 4096 + 8 * u * 64];
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    G[off + (size_t)(ti * 32 + y0 + 8 * u) * D + tj * 32 + x] = sum[u];
-    tile[y0 + 8 * u][x] = sum[u];
-  }
-  if (ti == tj) return;
-  __syncthreads();
-#pragma unroll
-  for (int u = 0; u < 4; ++u) G[off + (size_t)(tj * 32 + y0 + 8 * u) * D + ti * 32 + x] = tile[x][y0 + 8 * u];
 }
 
 // ---- 2. small fp64 linear algebra --------------------------------------------------------------------
@@ -350,13 +322,40 @@ static hipError_t gemm64(Mat A, Mat B, double* C, int ldc, size_t strideC, int M
   return hipGetLastError();
 }
 
-FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int n_sweeps) {
+// 1. G = K^T K: the digits' products, or the fp64 kernel for sequences whose flag is raised, and the sum over the splits
+template <int EB>
+static hipError_t launch_gram(const void* K, double* part, double* G, float* scale, int32_t* flags, uint16_t* chunk_max,
+                              DigitRest* rest, int32_t* rest_count, ColumnRest* by_col, int32_t* col_begin,
+                              const FactorizePlan& pl, int batch, int s, int D, hipStream_t st) {
+  const int pieces = D * EB / 16;
+  hipLaunchKernelGGL(column_max_kernel<EB>, dim3(pl.n_chunks, batch, (pieces + pl.max_lv - 1) / pl.max_lv), dim3(256), 0, st, K,
+                     chunk_max, flags, s, D, pl.max_lv, pl.max_chunk, pl.n_chunks);
+  hipLaunchKernelGGL(column_scale_kernel<EB>, dim3(pl.nb, batch), dim3(256), 0, st, K, chunk_max, scale, flags, s, D,
+                     pl.n_chunks);
+  constexpr int kLds = 2 * 2 * 3 * 128 * 64;   // two stages of two column blocks of three digits
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gram_digits_kernel<EB>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(gram_digits_kernel<EB>, dim3((unsigned)((long)batch * pl.n_splits * (pl.nb2 * (pl.nb2 + 1) / 2))), dim3(512),
+                     kLds, st, K, scale, part, rest, rest_count, flags, s, D, pl.nb, pl.nb2, pl.tokens_per_split, pl.n_splits, batch,
+                     pl.rest_cap);
+  hipLaunchKernelGGL(gram_kernel<EB>, dim3(pl.nb * (pl.nb + 1) / 2, pl.n_splits, batch), dim3(64), 0, st, K, part, flags, s, D,
+                     pl.nb, pl.tokens_per_split, batch);
+  hipLaunchKernelGGL(rest_by_column_kernel, dim3(pl.nb2, batch), dim3(1024), 0, st, rest, rest_count, scale, flags, by_col, col_begin,
+                     D, pl.nb2, pl.n_splits, pl.rest_cap);
+  const int nt = D / 32;   // (the key width is a multiple of 32)
+  hipLaunchKernelGGL(gram_finish_kernel<EB>, dim3(nt * (nt + 1) / 2, batch), dim3(256), 0, st, part, G, K, scale, by_col, col_begin,
+                     flags, s, D, nt, pl.nb, pl.nb2, pl.n_splits, batch, pl.rest_cap);
+  return hipGetLastError();
+}
+
+FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int n_sweeps, int kv_bytes) {
   FactorizePlan p{};
   p.m = std::min(D, r + oversample);
   p.mp = (p.m + 31) / 32 * 32;
   p.nb = (D + 63) / 64;
   const long pairs = (long)p.nb * (p.nb + 1) / 2;
-  const long max_splits = (s + 1023) / 1024, blocks = pairs * batch;
+  const long blocks = pairs * batch;
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
   auto doubles = [&](size_t per_sequence) { return up(per_sequence * batch * 8); };
   auto split_tokens = [&](long splits) {
@@ -386,33 +385,62 @@ FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int
   // (SHADOWKV_GRAM_WAVES, a tuning override: waves aimed at)
   static const long target = [] { const char* e = getenv("SHADOWKV_GRAM_WAVES"); return e ? atol(e) : 0l; }();
   const long aim = target > 0 ? target : 8192l;
-  const long aim_splits = std::max(1l, std::min(max_splits, (aim + blocks - 1) / blocks));
+  const long aim_splits = std::max(1l, std::min((s + 1023l) / 1024, (aim + blocks - 1) / blocks));
   split_tokens(aim_splits);
   const size_t even = (m + 1) / 2 * 2;
   const size_t room = doubles(p.n_splits * DD) + doubles(DD) + 2 * doubles(m * D) + 2 * doubles(even * even) + doubles(r * m) +
                       doubles((size_t)r * D);
-  const long fit = std::max(1l, (long)((room - off) / split_bytes));
+  // Beside the partial sums lie what the digits need: the columns' scales, the sequences' flags and the lists of what the
+  // digits miss, in token order and by column, with room for one element in 1024 (64 at least, or what the room leaves).
+  p.nb2 = (D + 127) / 128;
+  const long tiles = (long)p.nb2 * (p.nb2 + 1) / 2;
+  auto rest_room = [&] { return std::max(64, p.tokens_per_split / 32); };   // a list: 128 columns, 16 of 64 tokens
+  auto place = [&](long splits) {
+    split_tokens(splits);
+    size_t at = off + up(p.n_splits * split_bytes);
+    const size_t lists = (size_t)batch * p.n_splits * p.nb2 * 4;
+    p.scale = at; at += up((size_t)batch * D * 4);
+    p.flags = at; at += up((size_t)batch * 4);
+    p.col_begin = at; at += up((size_t)batch * p.nb2 * 129 * 4);
+    p.rest_count = at; at += up(lists * 4);
+    const size_t left = room > at + 512 ? room - at - 512 : 0;
+    p.rest_cap = (int)std::min<size_t>(rest_room(), left / (lists * (sizeof(DigitRest) + sizeof(ColumnRest))));
+    p.rest = at; at += up(lists * p.rest_cap * sizeof(DigitRest));
+    p.by_col = at; at += up(lists * p.rest_cap * sizeof(ColumnRest));
+    return at;
+  };
   long splits = 1;
   if (target > 0) {
-    splits = std::min(aim_splits, fit);
+    splits = std::max(1l, std::min(aim_splits, (long)((room - off) / split_bytes)));
   } else {
-    // The token splits that cost least: 2048 waves are resident (two per SIMD) and a wave takes 245 us for 1024 tokens
-    // (64 x 8 matrix instructions per 16 tokens and pair of waves, with what a large matrix reaches of the peak), a round of
-    // at most one wave per SIMD 0.6 of that; every split costs its partial sums once written and once read (1.06 x 8 bytes
-    // D^2 per sequence at 4.6 TB/s).  More splits have to be worth half a per cent.  16 x 128K x 1024: 8 splits, 8.5 rounds
-    // (4 splits, 4.25 rounds, paid for five: 40.6 against 38.1 ms, with loads then under lane masks; 34.9 now); 1 x 32K: 15
-    // splits in one round where 32 make 2.1 (0.62 ms).  The limit costs the widest keys 1 to 3 per cent of the call: 97.1 ms
-    // at 4 x 128K x 3072 (3 splits; 96.0 with the 10 that take 3.4 GB), 43.9 at 1 x 128K x 4096 (42.6 with 3.0 GB).
+    // The token splits that cost least: a workgroup fills a compute unit and takes 20 ns per token; where the groups of
+    // tiles go round the XCDs evenly each XCD has 32 compute units for its share, otherwise all 256 share.  Every split
+    // costs its partial sums once written and once read (1.06 x 8 bytes D^2 per sequence at 4.6 TB/s).  A tenth of what the
+    // fp64 sums would take counts as well, so that sequences that go that way do not pay for a split that suits only the
+    // others: 2048 of their waves are resident, two per SIMD, a wave takes 245 us for 1024 tokens, a round of at most one
+    // wave per SIMD 0.6 of that.  More splits have to be worth half a per cent, and leave the lists their size.
+    // 16 x 128K x 1024: 8 splits (digits 18 rounds, fp64 8.5; with 4 splits 9 and 4.25 rounds, the latter 40.6 against
+    // 38.1 ms); 1 x 32K: 7 splits, 252 workgroups.
     double best = 0.0;
-    for (long sp = 1; sp <= std::min({max_splits, 512l, fit}); ++sp) {
-      const long waves = blocks * sp, rest = waves % 2048;
-      const double rounds = (double)(waves / 2048) + (rest == 0 ? 0.0 : rest <= 1024 ? 0.6 : 1.0);
-      const double cost = rounds * (double)((s + sp - 1) / sp) * (245.0 / 1024.0) + (double)sp * batch * D * D * (1.06 * 8.0 / 4.6e6);
+    for (long sp = 1; sp <= std::min((s + 511l) / 512, 512l); ++sp) {
+      if (sp > 1 && (place(sp) > room || p.rest_cap < rest_room())) break;
+      const long groups = sp * batch, waves = blocks * sp, rest = waves % 2048;
+      const long rounds = groups % 8 == 0 ? (groups / 8 * tiles + 31) / 32 : (groups * tiles + 255) / 256;
+      const double rounds64 = (double)(waves / 2048) + (rest == 0 ? 0.0 : rest <= 1024 ? 0.6 : 1.0);
+      const double tokens = (double)((s + sp - 1) / sp);
+      const double cost = ((double)rounds * 0.02 + 0.1 * rounds64 * (245.0 / 1024.0)) * tokens + (double)sp * batch * D * D * (1.06 * 8.0 / 4.6e6);
       if (sp == 1 || cost < best * 0.995) { best = cost; splits = sp; }
     }
   }
-  split_tokens(splits);
-  p.total = std::max(end, off + up(p.n_splits * split_bytes));
+  p.total = std::max(end, place(splits));
+  // the columns' largest elements by chunk of tokens lie where G will
+  const int ne = 16 / kv_bytes, pieces = D / ne;
+  p.max_lv = 1;
+  while (2 * p.max_lv <= std::min(pieces, 128)) p.max_lv *= 2;
+  const long column_groups = (pieces + p.max_lv - 1) / p.max_lv;
+  const long chunks = std::max(1l, std::min({(2048 + batch * column_groups - 1) / (batch * column_groups), (long)(s + 63) / 64, 4l * D}));
+  p.max_chunk = (int)((s + chunks - 1) / chunks);
+  p.n_chunks = (s + p.max_chunk - 1) / p.max_chunk;
   return p;
 }
 
@@ -437,13 +465,16 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
 #define SKV_CHECK() do { e = hipGetLastError(); if (e != hipSuccess) return e; } while (0)
   // 1. G = K^T K
   {
-    dim3 grid(pl.nb * (pl.nb + 1) / 2, pl.n_splits, batch);
-    if (kv_bytes == 1) hipLaunchKernelGGL(gram_kernel<1>, grid, dim3(64), 0, st, k_pre, part, s, D, pl.nb, pl.tokens_per_split, batch);
-    else hipLaunchKernelGGL(gram_kernel<2>, grid, dim3(64), 0, st, k_pre, part, s, D, pl.nb, pl.tokens_per_split, batch);
-    SKV_CHECK();
-    const int nt = D / 32;   // (the key width is a multiple of 32)
-    hipLaunchKernelGGL(gram_finish_kernel, dim3(nt * (nt + 1) / 2, batch), dim3(256), 0, st, part, G, D, nt, pl.nb, pl.n_splits, batch);
-    SKV_CHECK();
+    float* scale = reinterpret_cast<float*>(ws + pl.scale);
+    int32_t* flags = reinterpret_cast<int32_t*>(ws + pl.flags);
+    uint16_t* chunk_max = reinterpret_cast<uint16_t*>(ws + pl.G);
+    DigitRest* rest = reinterpret_cast<DigitRest*>(ws + pl.rest);
+    int32_t* rest_count = reinterpret_cast<int32_t*>(ws + pl.rest_count);
+    ColumnRest* by_col = reinterpret_cast<ColumnRest*>(ws + pl.by_col);
+    int32_t* col_begin = reinterpret_cast<int32_t*>(ws + pl.col_begin);
+    e = kv_bytes == 1 ? launch_gram<1>(k_pre, part, G, scale, flags, chunk_max, rest, rest_count, by_col, col_begin, pl, batch, s, D, st)
+                      : launch_gram<2>(k_pre, part, G, scale, flags, chunk_max, rest, rest_count, by_col, col_begin, pl, batch, s, D, st);
+    if (e != hipSuccess) return e;
   }
   // 2. subspace iteration: X <- orth(G X); rows of Xt are the vectors
   const size_t nx = (size_t)batch * m * D;

@@ -689,7 +689,7 @@ size_t shadowkv_factorize_workspace_bytes(const shadowkv_params* params) {
   Shape sh;
   if (check_params(params, false, &sh) != SHADOWKV_OK) return 0;
   if (params->rank < 8 || params->rank > 256 || params->rank % 8 || params->rank > sh.hkv * sh.d) return 0;
-  return plan_factorize(sh.b, sh.s, sh.hkv * sh.d, params->rank, kFactorOversample, kFactorSweeps).total;
+  return plan_factorize(sh.b, sh.s, sh.hkv * sh.d, params->rank, kFactorOversample, kFactorSweeps, sh.eb).total;
 }
 
 int shadowkv_factorize_keys(const shadowkv_params* params, const shadowkv_kv* k_pre, shadowkv_kv* A, shadowkv_kv* B,
@@ -705,7 +705,7 @@ int shadowkv_factorize_keys(const shadowkv_params* params, const shadowkv_kv* k_
   if (!k_pre || !A || !B) return fail_inval("k_pre, A and B must not be NULL");
   if (!aligned16(k_pre) || !aligned16(A) || !aligned16(B) || !aligned16(psi_out))
     return fail_inval("tensor pointers must be 16-byte aligned");
-  const FactorizePlan pl = plan_factorize(sh.b, sh.s, sh.hkv * sh.d, params->rank, kFactorOversample, kFactorSweeps);
+  const FactorizePlan pl = plan_factorize(sh.b, sh.s, sh.hkv * sh.d, params->rank, kFactorOversample, kFactorSweeps, sh.eb);
   rc = check_workspace(workspace, workspace_bytes, pl.total);
   if (rc != SHADOWKV_OK) return rc;
   hipError_t e = launch_factorize(k_pre, sh.eb, A, B, psi_out, sigma_out, static_cast<char*>(workspace), pl, sh.b, sh.hkv,

@@ -1,0 +1,66 @@
+"""The Gram matrix of shadowkv_factorize_keys (-m gpu): formed from 8-bit digits of the keys, from lists of what the digits
+leave out, or in fp64 for sequences with too much of that.  With as many vectors as the keys are wide, sigma^2 and the right
+singular vectors give the Gram matrix back, and it is compared with numpy's fp64 product of the same stored keys: at the
+edges of the 128-column blocks, of stages of 64 tokens and of the 32768 tokens summed in 32 bits, and for keys of each kind."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2410_21465_amd import shadowkv as S
+
+import parity_util as PU
+
+pytestmark = pytest.mark.gpu
+
+
+def _keys(kind, b, s, D, kd, gen):
+    k = torch.randn(b, s, D, generator=gen, device="cuda")
+    if kind == "outliers":        # a row in 500 above the rest: the lists hold several times what normal keys leave out
+        k[:, ::500] *= 6.0
+    elif kind == "spikes":        # ... far above: the others' last places lie below the digits, more than the lists hold
+        k[:, ::500] *= 3000.0
+    elif kind == "graded":        # magnitudes over 20 binades in every column: more is left out than the lists hold
+        k *= torch.exp2(-20.0 * torch.rand(b, s, D, generator=gen, device="cuda"))
+    elif kind == "columns":       # columns of very different scale, one of them zero
+        k *= torch.exp2(torch.linspace(-12, 8, D, device="cuda"))
+        k[:, :, D // 2] = 0.0
+    elif kind == "large":         # beyond 2^22: fp64 (bf16 only)
+        k *= 2.0 ** 30
+    elif kind == "mixed":         # one sequence of each route
+        k[0, ::500] *= 6.0
+        k[1] *= torch.exp2(-20.0 * torch.rand(s, D, generator=gen, device="cuda"))
+    elif kind == "ones":          # magnitudes with all leading bits set, of either sign
+        k = torch.where(k < 0, -255.0, 255.0)
+    return k.clamp(-5.0e4, 5.0e4).to(torch.float8_e5m2) if kd else k.to(torch.bfloat16)
+
+
+CASES = [(1, 1, 64, 1, "normal", 0), (1, 1, 64, 63, "normal", 0), (2, 1, 64, 65, "normal", 1), (1, 1, 96, 513, "normal", 0),
+         (1, 1, 128, 4096, "normal", 0), (3, 3, 64, 1500, "outliers", 0), (1, 2, 96, 3001, "outliers", 1),
+         (1, 2, 128, 2049, "outliers", 0), (1, 2, 128, 2000, "graded", 0), (2, 2, 64, 1200, "spikes", 0), (1, 4, 64, 1111, "graded", 1),
+         (2, 3, 64, 777, "columns", 0), (1, 2, 128, 600, "large", 0), (3, 2, 128, 1000, "mixed", 0),
+         (1, 2, 128, 5000, "ones", 0), (1, 1, 64, 70001, "outliers", 0),
+         (256, 1, 64, 33000, "normal", 0)]   # one token part of more than 32768 tokens
+
+
+@pytest.mark.parametrize("b,h,d,s,kind,kd", CASES)
+def test_gram_matrix_from_the_factors(b, h, d, s, kind, kd):
+    D = h * d
+    print(f"\n[case] b {b} h {h} d {d} s {s} {kind} kv_dtype {kd}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(7 * s + D + kd)
+    k = _keys(kind, b, s, D, kd, gen)
+    p = S.Params(batch=b, n_q_heads=h, n_kv_heads=h, head_dim=d, ctx_len=s, chunk_size=1, rank=D, n_outlier_chunks=0,
+                 topk_chunks=1, local_len=0, kv_dtype=kd)
+    got = S.factorize_keys(p, k, want_vectors=True)
+    again = S.factorize_keys(p, k, want_vectors=True)
+    torch.cuda.synchronize()
+    assert torch.equal(got["psi"], again["psi"]) and torch.equal(got["sigma"], again["sigma"])   # the same order of sums on every run
+    psi, sig = got["psi"].cpu().numpy(), got["sigma"].cpu().numpy()
+    for i in sorted({0, 1 % b, b - 1}):
+        K = PU.kv_to_f64(PU.to_bits(k[i].contiguous(), kd))
+        G = K.T @ K
+        back = (psi[i].T * sig[i] ** 2) @ psi[i]
+        # the eigenvectors' rounding: a few D units of the last place of the largest eigenvalue; directions beyond the rank of
+        # the keys are rounding as well
+        err = np.abs(back - G).max() / np.linalg.norm(G, 2)
+        print(f"[gram] sequence {i}: {err:.2e}", flush=True)
+        assert err < 32 * D * 2.0 ** -53, err
