@@ -69,21 +69,39 @@ struct Piece {
     const int sh = (int)(__float_as_uint(scale) >> 23) - 127;
     return (uint16_t)(EB == 2 ? max(134 - sh, 0) << 7 : max(17 - sh, 0) << 2);
   }
-  // element x 2^sh + kDigitMagic, rounded to an integer (nearest, ties to even): the widening is left to the instruction.
-  // bf16: the two-term product of the pair with (2^sh, 0) or (0, 2^sh) as bf16 (v_dot2_f32_bf16 rounds once and keeps the
-  // least numbers: compared with the definition for every bf16 number and scale on the box).  E5M2 is the upper byte of fp16.
-  template <int X>
-  __device__ __forceinline__ float digits(float scale) const {
-    if constexpr (EB == 2) {
-      const uint32_t s = X & 1 ? __float_as_uint(scale) : __float_as_uint(scale) >> 16;
-      return __builtin_amdgcn_fdot2_f32_bf16(*reinterpret_cast<const bf16x2*>(&w[X / 2]), *reinterpret_cast<const bf16x2*>(&s),
-                                             kDigitMagic, false);
-    } else {
-      const uint32_t p = __builtin_amdgcn_perm(0u, w[X / 4], X & 2 ? 0x030c020cu : 0x010c000cu);
-      return fmaf((float)(*reinterpret_cast<const f16x2*>(&p))[X & 1], scale, kDigitMagic);
-    }
+  // 2^sh as the products below take it: bf16 in the half of a word that meets the x-th element, or fp32 (E5M2)
+  static __device__ __forceinline__ uint32_t scale_word(int x, float scale) {
+    return EB == 2 && !(x & 1) ? __float_as_uint(scale) >> 16 : __float_as_uint(scale);
   }
 };
+// x 2^sh + kDigitMagic, rounded to an integer (nearest, ties to even), of four elements; the widening is left to the
+// instruction.  w: the words that hold them, s: their scale words (Piece::scale_word).  bf16: the two-term product of the pair
+// with (2^sh, 0) or (0, 2^sh) (v_dot2_f32_bf16 rounds once and keeps the least numbers: compared with the definition for every
+// bf16 number and scale).  The compiler has only the form that adds to its result's register, a move more per element; the
+// three idle cycles at the end are what another instruction has to wait for the result.
+__device__ __forceinline__ void scaled4_bf16(const uint32_t (&w)[4], const uint32_t (&s)[4], uint32_t (&out)[4]) {
+  asm("v_dot2_f32_bf16 %0, %4, %8, %12\n\t"
+      "v_dot2_f32_bf16 %1, %5, %9, %12\n\t"
+      "v_dot2_f32_bf16 %2, %6, %10, %12\n\t"
+      "v_dot2_f32_bf16 %3, %7, %11, %12\n\t"
+      "s_nop 2"
+      : "=&v"(out[0]), "=&v"(out[1]), "=&v"(out[2]), "=&v"(out[3])
+      : "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "v"(s[0]), "v"(s[1]), "v"(s[2]), "v"(s[3]), "s"(kDigitMagic));
+}
+// E5M2 (the upper byte of fp16): element X of the word
+template <int X>
+__device__ __forceinline__ uint32_t scaled_e5m2(uint32_t w, uint32_t s) {
+  const uint32_t p = __builtin_amdgcn_perm(0u, w, X & 2 ? 0x030c020cu : 0x010c000cu);
+  return __float_as_uint(fmaf((float)(*reinterpret_cast<const f16x2*>(&p))[X & 1], __uint_as_float(s), kDigitMagic));
+}
+// the digits of four such numbers, four bytes a digit, the most significant one first
+__device__ __forceinline__ void split_digits(const uint32_t (&w)[4], uint32_t (&d)[3]) {
+  const uint32_t lo01 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u), lo23 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
+  const uint32_t hi01 = __builtin_amdgcn_perm(w[1], w[0], 0x0c0c0602u), hi23 = __builtin_amdgcn_perm(w[3], w[2], 0x0c0c0602u);
+  d[0] = (__builtin_amdgcn_perm(hi23, hi01, 0x05040100u) + 0x40404040u) ^ 0x80808080u;
+  d[1] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u) ^ 0x80808080u;
+  d[2] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u) ^ 0x80808080u;
+}
 // what the digits of element x leave out, in units of 2^-sh: x 2^sh - v
 __device__ __forceinline__ float digit_rest(float x, float scale) {
   return fmaf(x, scale, -(fmaf(x, scale, kDigitMagic) - kDigitMagic));
@@ -224,8 +242,9 @@ struct GramTile {
   double* out;               // partial sums of this sequence and token part
   DigitRest* rest;           // diagonal: four lists of this column block and token part
   int32_t* rest_count;
+  int32_t* marks;            // [4][n_marks]: entries of each list before every 256th token
   int32_t* flag;
-  int s, D, nb, bi, bj, t_begin, t_end, rest_cap;
+  int s, D, nb, bi, bj, t_begin, t_end, rest_cap, n_marks;
 };
 // byte offset in a plane of column c (of 128), tokens 16 t16 .. + 15 (of 64)
 __device__ __forceinline__ int operand_at(int c, int t16) {
@@ -272,6 +291,7 @@ __device__ __forceinline__ void gram_digits_tile(const GramTile& g, uint8_t* lds
         for (int i = 0; i < 2 * EB; ++i) raw[u].w[i] = t0 + tok + u < g.t_end ? raw[u].w[i] : 0u;
     }
     if constexpr (DIAG) {
+      if (((t0 - g.t_begin) & 255) == 0 && lane == 0) g.marks[tq * g.n_marks + (t0 - g.t_begin) / 256] = n_rest;
       // Which elements may the digits not hold: those below their column's threshold, compared two at a time.  A pair of
       // columns where there are any (three stages of a wave in four have none where the keys are normally distributed) is
       // looked at element by element; the entries' order is that of column pair, column, token, lane.
@@ -300,16 +320,18 @@ __device__ __forceinline__ void gram_digits_tile(const GramTile& g, uint8_t* lds
     int dst = put + buf * 2 * kBlock;
     asm volatile("" : "+v"(dst));   // (the eight places are formed here and not kept through the products)
     each_of(kColumns, [&](auto x) {
-      uint32_t w[4];
+      uint32_t w[4], d[3];
+      const uint32_t sw = Piece<EB>::scale_word(x, sc[x]);
+      if constexpr (EB == 2) {
+        scaled4_bf16({raw[0].w[x / 2], raw[1].w[x / 2], raw[2].w[x / 2], raw[3].w[x / 2]}, {sw, sw, sw, sw}, w);
+      } else {
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        w[u] = __float_as_uint(raw[u].template digits<x>(sc[x]));
-      const uint32_t lo01 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u), lo23 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
-      const uint32_t hi01 = __builtin_amdgcn_perm(w[1], w[0], 0x0c0c0602u), hi23 = __builtin_amdgcn_perm(w[3], w[2], 0x0c0c0602u);
+        for (int u = 0; u < 4; ++u) w[u] = scaled_e5m2<x % 4>(raw[u].w[x / 4], sw);
+      }
+      split_digits(w, d);
       uint8_t* at = lds + (dst ^ (16 * (4 * (x & 1) + x / 2))) + 128 * (x / 2);
-      *reinterpret_cast<uint32_t*>(at) = (__builtin_amdgcn_perm(hi23, hi01, 0x05040100u) + 0x40404040u) ^ 0x80808080u;
-      *reinterpret_cast<uint32_t*>(at + kPlane) = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u) ^ 0x80808080u;
-      *reinterpret_cast<uint32_t*>(at + 2 * kPlane) = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u) ^ 0x80808080u;
+#pragma unroll
+      for (int p = 0; p < 3; ++p) *reinterpret_cast<uint32_t*>(at + p * kPlane) = d[p];
     });
   };
 
@@ -390,6 +412,7 @@ __device__ __forceinline__ void gram_digits_tile(const GramTile& g, uint8_t* lds
   }
   if (DIAG && blk == 0 && lane == 0) {
     g.rest_count[tq] = n_rest;
+    g.marks[tq * g.n_marks + (g.t_end - g.t_begin + 255) / 256] = n_rest;
     if (n_rest > g.rest_cap) __hip_atomic_store(g.flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
@@ -397,9 +420,10 @@ __device__ __forceinline__ void gram_digits_tile(const GramTile& g, uint8_t* lds
 template <int EB>
 __global__ __launch_bounds__(512, 2) void gram_digits_kernel(const void* __restrict__ K, const float* __restrict__ scale,
                                                              double* __restrict__ part, DigitRest* __restrict__ rest,
-                                                             int32_t* __restrict__ rest_count, int32_t* __restrict__ flags,
-                                                             int s, int D, int nb, int nb2, int tokens_per_split, int n_splits,
-                                                             int batch, int rest_cap) {
+                                                             int32_t* __restrict__ rest_count, int32_t* __restrict__ marks,
+                                                             int32_t* __restrict__ flags, int s, int D, int nb, int nb2,
+                                                             int tokens_per_split, int n_splits, int batch, int rest_cap,
+                                                             int n_marks) {
   extern __shared__ __align__(16) uint8_t lds[];             // [2 stages][2 column blocks][3 digits][64 pairs][128]
   __shared__ int32_t raised;
   const int tiles = nb2 * (nb2 + 1) / 2, groups = batch * n_splits;
@@ -428,6 +452,8 @@ __global__ __launch_bounds__(512, 2) void gram_digits_kernel(const void* __restr
   g.out = part + ((size_t)split * batch + b) * (nb * (nb + 1) / 2) * 4096;
   g.rest = rest + ((size_t)group * nb2 + g.bi) * 4 * rest_cap;
   g.rest_count = rest_count + ((size_t)group * nb2 + g.bi) * 4;
+  g.marks = marks + ((size_t)group * nb2 + g.bi) * 4 * n_marks;
+  g.n_marks = n_marks;
   g.flag = flags + b;
   g.s = s; g.D = D; g.nb = nb; g.rest_cap = rest_cap;
   g.t_begin = split * tokens_per_split; g.t_end = min(s, g.t_begin + tokens_per_split);

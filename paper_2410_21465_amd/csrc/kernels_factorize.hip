@@ -10,15 +10,15 @@
 //   2. subspace iteration on m = r + oversample vectors (X <- orth(G X), by Cholesky factorisation of the vectors'
 //      products), then one Rayleigh-Ritz step: T = X^T G X, eigenvectors of the small T by one-sided Jacobi rotations in
 //      blocks, the r largest kept -- all fp64, small, one launch per dependent step (factorize_small.hpp);
-//   3. sign convention (largest-magnitude component positive), B written, and project_kernel: A = K Psi on
-//      the same matrix instruction.
+//   3. sign convention (largest-magnitude component positive), B written, and A = K Psi, from digits again
+//      (factorize_project.hpp) or in fp64 (project_kernel).
 // Operand layout of v_mfma_f64_16x16x4f64 as measured on gfx950: A lane l holds (m = l % 16, k = l / 16),
 // B lane l holds (n = l % 16, k = l / 16), result register j of lane l is (m = 4 j + l / 16, n = l % 16).
 #include <algorithm>
 #include <cstdlib>
 #include <type_traits>
 
-#include "factorize_gram.hpp"
+#include "factorize_project.hpp"
 #include "factorize_small.hpp"
 #include "kernels.hpp"
 
@@ -206,6 +206,7 @@ __global__ __launch_bounds__(256) void emit_b_kernel(double* __restrict__ Psi_t,
 }
 
 // ---- 3. A = K Psi -----------------------------------------------------------------------------------------
+// For sequences whose flag is raised (project_digits_kernel takes the others), and keys wider than 32768.
 // One wave per (32 tokens, 16 NT rank columns, sequence): M = tokens (two 16-row tiles), N = rank index, contraction over
 // the key columns (a lane's four consecutive stored elements are four contraction steps).  Every fragment of Psi read
 // from L2 serves both token tiles; two tiles and not three so that two waves share a SIMD and one widens while the
@@ -214,7 +215,9 @@ __global__ __launch_bounds__(256) void emit_b_kernel(double* __restrict__ Psi_t,
 // masks, 11.4 ms now (60 TFLOP/s); one sequence of 32K 307 -> 195 us.
 template <int EB, int NT>
 __global__ __launch_bounds__(64, 2) void project_kernel(const void* __restrict__ K, const double* __restrict__ Psi_t,
-                                                     void* __restrict__ Aout, int s, int s_cap, int D, int r) {
+                                                     void* __restrict__ Aout, const int32_t* __restrict__ flags, int s,
+                                                     int s_cap, int D, int r) {
+  if (flags && !flags[blockIdx.z]) return;
   constexpr int MT = 2;
   const int lane = threadIdx.x, mrow = lane & 15, kq = lane >> 4;
   const int tok0 = blockIdx.x * (16 * MT), n0 = blockIdx.y * (16 * NT), b = blockIdx.z;
@@ -325,7 +328,7 @@ static hipError_t gemm64(Mat A, Mat B, double* C, int ldc, size_t strideC, int M
 // 1. G = K^T K: the digits' products, or the fp64 kernel for sequences whose flag is raised, and the sum over the splits
 template <int EB>
 static hipError_t launch_gram(const void* K, double* part, double* G, float* scale, int32_t* flags, uint16_t* chunk_max,
-                              DigitRest* rest, int32_t* rest_count, ColumnRest* by_col, int32_t* col_begin,
+                              DigitRest* rest, int32_t* rest_count, int32_t* marks, ColumnRest* by_col, int32_t* col_begin,
                               const FactorizePlan& pl, int batch, int s, int D, hipStream_t st) {
   const int pieces = D * EB / 16;
   hipLaunchKernelGGL(column_max_kernel<EB>, dim3(pl.n_chunks, batch, (pieces + pl.max_lv - 1) / pl.max_lv), dim3(256), 0, st, K,
@@ -337,8 +340,8 @@ static hipError_t launch_gram(const void* K, double* part, double* G, float* sca
                                      hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(gram_digits_kernel<EB>, dim3((unsigned)((long)batch * pl.n_splits * (pl.nb2 * (pl.nb2 + 1) / 2))), dim3(512),
-                     kLds, st, K, scale, part, rest, rest_count, flags, s, D, pl.nb, pl.nb2, pl.tokens_per_split, pl.n_splits, batch,
-                     pl.rest_cap);
+                     kLds, st, K, scale, part, rest, rest_count, marks, flags, s, D, pl.nb, pl.nb2, pl.tokens_per_split, pl.n_splits,
+                     batch, pl.rest_cap, pl.n_marks);
   hipLaunchKernelGGL(gram_kernel<EB>, dim3(pl.nb * (pl.nb + 1) / 2, pl.n_splits, batch), dim3(64), 0, st, K, part, flags, s, D,
                      pl.nb, pl.tokens_per_split, batch);
   hipLaunchKernelGGL(rest_by_column_kernel, dim3(pl.nb2, batch), dim3(1024), 0, st, rest, rest_count, scale, flags, by_col, col_begin,
@@ -346,6 +349,37 @@ static hipError_t launch_gram(const void* K, double* part, double* G, float* sca
   const int nt = D / 32;   // (the key width is a multiple of 32)
   hipLaunchKernelGGL(gram_finish_kernel<EB>, dim3(nt * (nt + 1) / 2, batch), dim3(256), 0, st, part, G, K, scale, by_col, col_begin,
                      flags, s, D, nt, pl.nb, pl.nb2, pl.n_splits, batch, pl.rest_cap);
+  return hipGetLastError();
+}
+
+// 3. A = K Psi: digits, or the fp64 kernel for sequences whose flag is raised
+template <int EB>
+static hipError_t launch_project(const void* K, const double* Psi_t, void* A, char* ws, const FactorizePlan& pl, int batch, int s,
+                                 int s_cap, int D, int r, hipStream_t st) {
+  const int32_t* flags = reinterpret_cast<const int32_t*>(ws + pl.flags);
+  // (32-bit sums of digits: at most 3 * 2^14 per column)
+  const bool digits = D <= 32768;
+  if (digits) {
+    const int nt = (r + 31) / 32;
+    const float* scale = reinterpret_cast<const float*>(ws + pl.scale);
+    uint8_t* psi_digits = reinterpret_cast<uint8_t*>(ws + pl.psi_digits);
+    int32_t* exps = reinterpret_cast<int32_t*>(ws + pl.psi_exps);
+    hipLaunchKernelGGL(psi_digits_kernel<EB>, dim3(32 * nt, batch), dim3(256), 0, st, Psi_t, scale, psi_digits, exps, D, r, nt);
+    const long blocks = (long)batch * pl.n_splits * (pl.n_marks - 1);
+    constexpr int kLds = 2 * kPsiDeep * kPsiStage;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&project_digits_kernel<EB>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(project_digits_kernel<EB>, dim3((unsigned)((blocks + 7) / 8 * 8 * nt)), dim3(512), kLds, st, K, psi_digits, exps,
+                       Psi_t, reinterpret_cast<const DigitRest*>(ws + pl.rest), reinterpret_cast<const int32_t*>(ws + pl.marks),
+                       flags, scale, A, s, s_cap, D, r, nt, pl.nb2, pl.tokens_per_split, pl.n_splits, batch, pl.rest_cap, pl.n_marks);
+  }
+  // up to five 16-rank tiles per wave, the tiles dealt evenly to as few waves as that takes (rank 96: 2 x 3, not 5 + 1)
+  const int tiles = (r + 15) / 16, blocks = (tiles + 4) / 5, nt = (tiles + blocks - 1) / blocks;
+  const dim3 grid((s + 31) / 32, blocks, batch);
+#define SKV_PROJECT(NT_) hipLaunchKernelGGL((project_kernel<EB, NT_>), grid, dim3(64), 0, st, K, Psi_t, A, digits ? flags : nullptr, s, s_cap, D, r)
+  if (nt == 5) SKV_PROJECT(5); else if (nt == 4) SKV_PROJECT(4); else SKV_PROJECT(3);
+#undef SKV_PROJECT
   return hipGetLastError();
 }
 
@@ -369,12 +403,14 @@ FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int
   // written), J and Psi_t that of Lp and Yt (last read by T's products; r <= m).
   p.G = p.V = 0;
   size_t off = doubles(DD);
-  p.part = p.Xt = off;
-  size_t end = off + doubles(m * D);
+  p.part = p.Xt = p.psi_digits = off;
+  const size_t vectors = (size_t)(r + 31) / 32 * 32;
+  size_t end = off + std::max(doubles(m * D), up((size_t)batch * (vectors / 32) * ((D + 63) / 64) * kPsiStage));
   p.W = p.S = end; end += doubles(mp * mp);
   p.idle = end; end += up((size_t)2 * batch * (mp / 32) * 4);
   p.sweep_max = end; end += up((size_t)batch * n_sweeps * 4);
   p.order = end; end += up((size_t)batch * r * 4);
+  p.psi_exps = end; end += up((size_t)batch * vectors * 4);
   p.Lp = p.Jbuf = p.Psi_t = end;
   p.Yt = end + doubles(nbc * (nbc + 1) / 2 * 256);
   end = std::max(p.Yt + doubles(m * D), end + doubles(2 * (mp / 32) * 1024));
@@ -390,19 +426,21 @@ FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int
   const size_t even = (m + 1) / 2 * 2;
   const size_t room = doubles(p.n_splits * DD) + doubles(DD) + 2 * doubles(m * D) + 2 * doubles(even * even) + doubles(r * m) +
                       doubles((size_t)r * D);
-  // Beside the partial sums lie what the digits need: the columns' scales, the sequences' flags and the lists of what the
+  // Behind these lies what the digits need: the columns' scales, the sequences' flags and the lists of what the
   // digits miss, in token order and by column, with room for one element in 1024 (64 at least, or what the room leaves).
   p.nb2 = (D + 127) / 128;
   const long tiles = (long)p.nb2 * (p.nb2 + 1) / 2;
   auto rest_room = [&] { return std::max(64, p.tokens_per_split / 32); };   // a list: 128 columns, 16 of 64 tokens
   auto place = [&](long splits) {
     split_tokens(splits);
-    size_t at = off + up(p.n_splits * split_bytes);
+    size_t at = std::max(off + up(p.n_splits * split_bytes), end);
     const size_t lists = (size_t)batch * p.n_splits * p.nb2 * 4;
     p.scale = at; at += up((size_t)batch * D * 4);
     p.flags = at; at += up((size_t)batch * 4);
     p.col_begin = at; at += up((size_t)batch * p.nb2 * 129 * 4);
     p.rest_count = at; at += up(lists * 4);
+    p.n_marks = (p.tokens_per_split + 255) / 256 + 1;
+    p.marks = at; at += up(lists * p.n_marks * 4);
     const size_t left = room > at + 512 ? room - at - 512 : 0;
     p.rest_cap = (int)std::min<size_t>(rest_room(), left / (lists * (sizeof(DigitRest) + sizeof(ColumnRest))));
     p.rest = at; at += up(lists * p.rest_cap * sizeof(DigitRest));
@@ -432,7 +470,7 @@ FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int
       if (sp == 1 || cost < best * 0.995) { best = cost; splits = sp; }
     }
   }
-  p.total = std::max(end, place(splits));
+  p.total = place(splits);
   // the columns' largest elements by chunk of tokens lie where G will
   const int ne = 16 / kv_bytes, pieces = D / ne;
   p.max_lv = 1;
@@ -470,10 +508,11 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
     uint16_t* chunk_max = reinterpret_cast<uint16_t*>(ws + pl.G);
     DigitRest* rest = reinterpret_cast<DigitRest*>(ws + pl.rest);
     int32_t* rest_count = reinterpret_cast<int32_t*>(ws + pl.rest_count);
+    int32_t* marks = reinterpret_cast<int32_t*>(ws + pl.marks);
     ColumnRest* by_col = reinterpret_cast<ColumnRest*>(ws + pl.by_col);
     int32_t* col_begin = reinterpret_cast<int32_t*>(ws + pl.col_begin);
-    e = kv_bytes == 1 ? launch_gram<1>(k_pre, part, G, scale, flags, chunk_max, rest, rest_count, by_col, col_begin, pl, batch, s, D, st)
-                      : launch_gram<2>(k_pre, part, G, scale, flags, chunk_max, rest, rest_count, by_col, col_begin, pl, batch, s, D, st);
+    e = kv_bytes == 1 ? launch_gram<1>(k_pre, part, G, scale, flags, chunk_max, rest, rest_count, marks, by_col, col_begin, pl, batch, s, D, st)
+                      : launch_gram<2>(k_pre, part, G, scale, flags, chunk_max, rest, rest_count, marks, by_col, col_begin, pl, batch, s, D, st);
     if (e != hipSuccess) return e;
   }
   // 2. subspace iteration: X <- orth(G X); rows of Xt are the vectors
@@ -534,19 +573,9 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
   if (kv_bytes == 1) hipLaunchKernelGGL(emit_b_kernel<1>, dim3(r, batch), dim3(256), 0, st, Psi_t, B, D, r, hkv, d);
   else hipLaunchKernelGGL(emit_b_kernel<2>, dim3(r, batch), dim3(256), 0, st, Psi_t, B, D, r, hkv, d);
   SKV_CHECK();
-  {
-    // up to five 16-rank tiles per wave, the tiles dealt evenly to as few waves as that takes (rank 96: 2 x 3, not 5 + 1)
-    const int tiles = (r + 15) / 16, blocks = (tiles + 4) / 5, nt = (tiles + blocks - 1) / blocks;
-    const dim3 grid((s + 31) / 32, blocks, batch);
-#define SKV_PROJECT(EB_, NT_) hipLaunchKernelGGL((project_kernel<EB_, NT_>), grid, dim3(64), 0, st, k_pre, Psi_t, A, s, s_cap, D, r)
-    if (kv_bytes == 1) {
-      if (nt == 5) SKV_PROJECT(1, 5); else if (nt == 4) SKV_PROJECT(1, 4); else SKV_PROJECT(1, 3);
-    } else {
-      if (nt == 5) SKV_PROJECT(2, 5); else if (nt == 4) SKV_PROJECT(2, 4); else SKV_PROJECT(2, 3);
-    }
-#undef SKV_PROJECT
-    SKV_CHECK();
-  }
+  e = kv_bytes == 1 ? launch_project<1>(k_pre, Psi_t, A, ws, pl, batch, s, s_cap, D, r, st)
+                    : launch_project<2>(k_pre, Psi_t, A, ws, pl, batch, s, s_cap, D, r, st);
+  if (e != hipSuccess) return e;
 #undef SKV_CHECK
   return hipSuccess;
 }

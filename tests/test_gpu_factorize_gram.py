@@ -1,7 +1,8 @@
-"""The Gram matrix of shadowkv_factorize_keys (-m gpu): formed from 8-bit digits of the keys, from lists of what the digits
-leave out, or in fp64 for sequences with too much of that.  With as many vectors as the keys are wide, sigma^2 and the right
-singular vectors give the Gram matrix back, and it is compared with numpy's fp64 product of the same stored keys: at the
-edges of the 128-column blocks, of stages of 64 tokens and of the 32768 tokens summed in 32 bits, and for keys of each kind."""
+"""The dense products of shadowkv_factorize_keys (-m gpu), G = K^T K and A = K Psi: formed from 8-bit digits, from lists of
+what the keys' digits leave out, or in fp64 for sequences with too much of that.  With as many vectors as the keys are wide,
+sigma^2 and the right singular vectors give G back, and it is compared with numpy's fp64 product of the same stored keys, A
+with the rounding of theirs with the vectors: at the edges of the 128-column blocks, of stages of 64 tokens, blocks of 256 and
+the 32768 tokens summed in 32 bits, and for keys of each kind."""
 import numpy as np
 import pytest
 import torch
@@ -9,6 +10,7 @@ import torch
 from paper_2410_21465_amd import shadowkv as S
 
 import parity_util as PU
+from test_gpu_factorize import ulp_distance
 
 pytestmark = pytest.mark.gpu
 
@@ -21,6 +23,11 @@ def _keys(kind, b, s, D, kd, gen):
         k[:, ::500] *= 3000.0
     elif kind == "graded":        # magnitudes over 20 binades in every column: more is left out than the lists hold
         k *= torch.exp2(-20.0 * torch.rand(b, s, D, generator=gen, device="cuda"))
+    elif kind == "faint":         # a row in 61 whose few elements are all left out by the digits
+        faint = torch.zeros(s, 1, device="cuda")
+        faint[::61] = 1.0
+        some = (torch.arange(D, device="cuda") % 16 == 3).float()
+        k = torch.where(faint > 0, k * some * 2.0 ** -17, k)
     elif kind == "columns":       # columns of very different scale, one of them zero
         k *= torch.exp2(torch.linspace(-12, 8, D, device="cuda"))
         k[:, :, D // 2] = 0.0
@@ -36,7 +43,8 @@ def _keys(kind, b, s, D, kd, gen):
 
 CASES = [(1, 1, 64, 1, "normal", 0), (1, 1, 64, 63, "normal", 0), (2, 1, 64, 65, "normal", 1), (1, 1, 96, 513, "normal", 0),
          (1, 1, 128, 4096, "normal", 0), (3, 3, 64, 1500, "outliers", 0), (1, 2, 96, 3001, "outliers", 1),
-         (1, 2, 128, 2049, "outliers", 0), (1, 2, 128, 2000, "graded", 0), (2, 2, 64, 1200, "spikes", 0), (1, 4, 64, 1111, "graded", 1),
+         (1, 2, 128, 2049, "outliers", 0), (1, 2, 128, 2000, "graded", 0), (2, 2, 64, 1200, "spikes", 0),
+         (1, 2, 128, 4000, "faint", 0), (2, 2, 96, 1000, "faint", 0), (1, 4, 64, 1111, "graded", 1),
          (2, 3, 64, 777, "columns", 0), (1, 2, 128, 600, "large", 0), (3, 2, 128, 1000, "mixed", 0),
          (1, 2, 128, 5000, "ones", 0), (1, 1, 64, 70001, "outliers", 0),
          (256, 1, 64, 33000, "normal", 0)]   # one token part of more than 32768 tokens
@@ -64,3 +72,10 @@ def test_gram_matrix_from_the_factors(b, h, d, s, kind, kd):
         err = np.abs(back - G).max() / np.linalg.norm(G, 2)
         print(f"[gram] sequence {i}: {err:.2e}", flush=True)
         assert err < 32 * D * 2.0 ** -53, err
+        # A: fp64 sums of the stored keys times these vectors, rounded once (another order of the sums moves a number across
+        # a rounding boundary with a probability of some 2^-40)
+        A = K @ psi[i].T
+        stored = torch.from_numpy(A).to(k.dtype)     # torch rounds through fp32: a unit of the last place in rare cases
+        d = ulp_distance(PU.to_bits(got["A"][i, :s].contiguous(), kd), PU.to_bits(stored, kd), kd)
+        big = np.abs(A) > 1e-9 * np.abs(K).max(axis=1, keepdims=True)    # (sums that cancel to rounding have no digits to compare)
+        assert d[big].max(initial=0) <= 1 and (d[big] > 0).mean() < 1e-4, (d[big].max(initial=0), (d[big] > 0).mean())
