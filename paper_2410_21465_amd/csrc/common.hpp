@@ -3,7 +3,13 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <utility>
+
 namespace skv {
+
+// f(0), f(1), ... with the numbers as compile-time constants
+template <int... X, class F>
+__device__ __forceinline__ void each_of(std::integer_sequence<int, X...>, F&& f) { (f(std::integral_constant<int, X>{}), ...); }
 
 typedef uint16_t bf16_t;
 constexpr int kWave = 64;

@@ -14,8 +14,6 @@
 // least bf16 number, times their column's power of two would leave bf16) raise the sequence's flag, and gram_kernel forms
 // that sequence's sums in fp64 instead.
 #pragma once
-#include <utility>
-
 #include "common.hpp"
 
 namespace skv {
@@ -106,9 +104,6 @@ __device__ __forceinline__ void split_digits(const uint32_t (&w)[4], uint32_t (&
 __device__ __forceinline__ float digit_rest(float x, float scale) {
   return fmaf(x, scale, -(fmaf(x, scale, kDigitMagic) - kDigitMagic));
 }
-template <int... X, class F>
-__device__ __forceinline__ void each_of(std::integer_sequence<int, X...>, F&& f) { (f(std::integral_constant<int, X>{}), ...); }
-
 // ---- largest magnitude of every column ------------------------------------------------------------------
 // Storage bits without the sign order like the magnitudes.  chunk_max [b][n_chunks][D]; a thread takes one 16-byte piece of
 // the rows of its chunk, 256 / LV rows of LV pieces at a time.  The first chunk's workgroup clears the sequence's flag.

@@ -119,49 +119,81 @@ __device__ __forceinline__ double rsqrt_f64(double x) {
   return y;
 }
 
-// Cholesky factor of S [m][ld] (lower triangle read), one workgroup of eight waves per sequence.  Lp: packed blocks in
-// operand order, off the diagonal -L, on it the inverse of L's block (what trsm_kernel multiplies by).
+// the first (third) row of 16 lanes in the second (fourth) as well
+__device__ __forceinline__ double even_rows_f64(double x) {
+  const uint32_t lo = (uint32_t)__double2loint(x), hi = (uint32_t)__double2hiint(x);
+  return __hiloint2double((int)__builtin_amdgcn_permlane16_swap(hi, hi, false, false)[0],
+                          (int)__builtin_amdgcn_permlane16_swap(lo, lo, false, false)[0]);
+}
+// lane J of each row of 16 in all lanes of the row
+template <int J>
+__device__ __forceinline__ double row_lane_f64(double x) {
+  return __longlong_as_double(__builtin_amdgcn_update_dpp(0ll, __double_as_longlong(x), 0x150 + J, 0xf, 0xf, true));
+}
+// One step of a 16 x 16 block's factorisation without its roots: lanes 0-15 hold its rows, lanes 16-31 the columns of the unit
+// matrix, which become those of the inverse.  Pivots below `least` (of their own lane) project nothing.  The reciprocal is the
+// hardware's estimate y (24 bits) times 1 + e + e^2, e = 1 - d y.  Bound by one wave's issue, some 40 instructions of 7 cycles
+// a pivot (a root per pivot and broadcasts through the scalar registers: 335 cycles, now 308; the next pivot's chain drawn
+// between the updates of the last: 325).
+template <int P>
+__device__ __forceinline__ void factor_step(double (&a)[16], double least, uint32_t& floored) {
+  const double d = lane_f64(a[P], P);
+  const bool skip = d < lane_f64(least, P);
+  const double y = skip ? 0.0 : __builtin_amdgcn_rcp(d), e = fma(-d, y, 1.0), g = -(a[P] * y);
+  const double f = fma(g, fma(e, e, e), g), col = even_rows_f64(a[P]);
+  each_of(std::make_integer_sequence<int, 16>{}, [&](auto j) {
+    if constexpr (j > P) a[j] = fma(f, row_lane_f64<j>(col), a[j]);
+  });
+  floored |= skip ? 1u << P : 0u;
+}
+
+// Cholesky factor of S [16 nb][16 nb] (lower triangle read; zero beyond the vectors), one workgroup of eight waves per
+// sequence.  Lp: packed blocks in operand order, off the diagonal -L, on it the inverse of L's block (what trsm_kernel
+// multiplies by).
 // The trailing blocks stay in the accumulators of the waves (blocks dealt out in turn, NBW per wave) for the whole
-// factorisation; only the current block column goes through LDS.  What bounds it is the chain of pivots: 16 rsqrt + updates
-// per diagonal block in one wave (59 us for 192 vectors, 79 us with the library's square root and division), which carries
-// the unit matrix along in a second group of lanes and so ends with the inverse as well.  Above 192 vectors the blocks of a
-// wave no longer fit in its registers beside the rest: of 256, 19 are kept in scratch memory with NBW = 14 (224 vectors:
-// 90 us) and 161 with NBW = 22 (288 vectors: 182 us).
+// factorisation; only the current block column goes through LDS.  What bounds it is the chain of pivots, 16 per diagonal block
+// in one wave, which carries the unit matrix along in a second group of lanes and so ends with the inverse as well: of 48 us
+// for 192 vectors the diagonal blocks take 25, the trailing updates 11, the block columns 9, the start 4.  (59 us before: a root
+// per pivot, and a start of 6 us, most of it fetching 25 instructions for each of its guarded loads.)  Above 192 vectors the
+// blocks of a wave no longer fit in its registers beside the rest (scratch memory: 36 bytes a lane with NBW = 14, 416 with 22).
 // A pivot below kPivotFloor of the vector's own square is rounding: it is set to that floor, which leaves the vector's
 // remainder at a size that the next pass can work on, and nothing is projected on it; a zero vector stays zero.
 template <int NBW>
-__global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S, double* __restrict__ Lp, int m, int ld,
-                                                   int nb) {
+__global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S, double* __restrict__ Lp, int nb) {
   __shared__ double col[kMaxFactorBlocks][272];   // current block column: rows at a pitch of 17, then operand order
   __shared__ double inv[256];                     // inverse of the diagonal block, rows of floored pivots zero
   __shared__ double d0[kMaxFactorBlocks * 16];    // squares of the vectors
+  __shared__ uint16_t place[8 * NBW];             // block row and column of the idx-th block (column nb: no block)
   const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int sub = lane & 15, kq = lane >> 4;
+  const int ld = 16 * nb;
   S += (size_t)blockIdx.x * ld * ld;
   Lp += (size_t)blockIdx.x * (nb * (nb + 1) / 2) * 256;
-  f64x4 acc[NBW];
+  for (int x = threadIdx.x; x < 8 * NBW; x += 512) {
+    int idx = x, k = 0;
+    while (k < nb && idx >= nb - k) { idx -= nb - k; ++k; }
+    place[x] = (uint16_t)((k + idx) << 8 | k);
+  }
+  for (int x = threadIdx.x; x < ld; x += 512) d0[x] = S[(size_t)x * (ld + 1)];
+  __syncthreads();
+  f64x4 acc[NBW];   // the negatives of the trailing blocks
   int bi[NBW], bk[NBW];
+  // (few instructions per load: this runs once, and fetching the code is what it waits for)
+  const double* Sl = S + (size_t)kq * ld + sub;
 #pragma unroll
   for (int t = 0; t < NBW; ++t) {
-    int idx = wave + 8 * t, k = 0;
-    while (k < nb && idx >= nb - k) { idx -= nb - k; ++k; }
-    bk[t] = k; bi[t] = k + idx;     // k == nb: no block
-    acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
-    if (k < nb) {
+    const int x = __builtin_amdgcn_readfirstlane(place[wave + 8 * t]);
+    bi[t] = x >> 8; bk[t] = x & 255;
+    const double* p = Sl + (bk[t] < nb ? 16 * (bi[t] * ld + bk[t]) : 0);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int r = 16 * bi[t] + 4 * j + kq, c = 16 * k + sub;
-        if (r < m && c < m) acc[t][j] = S[(size_t)r * ld + c];
-        if (r == c) d0[r] = acc[t][j];
-      }
-    }
+    for (int j = 0; j < 4; ++j) acc[t][j] = -p[4 * j * ld];
   }
   for (int k = 0; k < nb; ++k) {
 #pragma unroll
     for (int t = 0; t < NBW; ++t)
       if (bk[t] == k)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) col[bi[t]][(4 * j + kq) * 17 + sub] = acc[t][j];
+        for (int j = 0; j < 4; ++j) col[bi[t]][(4 * j + kq) * 17 + sub] = -acc[t][j];
     __syncthreads();
     double* out = Lp + (size_t)tri_block(nb, k, k) * 256;
     if (wave == 0) {
@@ -170,18 +202,16 @@ __global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S,
 #pragma unroll
       for (int j = 0; j < 16; ++j) a[j] = lane < 16 ? col[k][sub * 17 + j] : (lane < 32 && j == sub ? 1.0 : 0.0);
       const double e0 = d0[16 * k + sub];
+      const bool none = !(e0 > 1e-280);
+      const double floor = kPivotFloor * e0;
       uint32_t floored = 0;
+      each_of(std::make_integer_sequence<int, 16>{}, [&](auto p) { factor_step<p>(a, none ? INFINITY : floor, floored); });
+      // the roots of all pivots at once (lane p its own), then column p of both halves times root p
+      double d = a[0];
 #pragma unroll
-      for (int p = 0; p < 16; ++p) {
-        const double d = lane_f64(a[p], p), e = lane_f64(e0, p);
-        const bool none = !(e > 1e-280), low = !none && d < kPivotFloor * e, skip = none || low;
-        const double piv = none ? 1.0 : (low ? kPivotFloor * e : d);
-        a[p] *= rsqrt_f64(piv);
-        floored |= skip ? 1u << p : 0u;
-        const double mult = skip ? 0.0 : a[p];
-#pragma unroll
-        for (int j = p + 1; j < 16; ++j) a[j] = fma(-mult, lane_f64(mult, j), a[j]);
-      }
+      for (int p = 1; p < 16; ++p) d = sub == p ? a[p] : d;
+      const double root = even_rows_f64(rsqrt_f64(none ? 1.0 : (d < floor ? floor : d)));
+      each_of(std::make_integer_sequence<int, 16>{}, [&](auto p) { a[p] *= row_lane_f64<p>(root); });
       if (kq == 1) {
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
@@ -211,7 +241,7 @@ __global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S,
       if (bk[t] > k && bk[t] < nb) {
 #pragma unroll
         for (int x = 0; x < 4; ++x)
-          acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(-col[bi[t]][lane * 4 + x], col[bk[t]][lane * 4 + x], acc[t], 0, 0, 0);
+          acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(col[bi[t]][lane * 4 + x], col[bk[t]][lane * 4 + x], acc[t], 0, 0, 0);
       }
     __syncthreads();
   }

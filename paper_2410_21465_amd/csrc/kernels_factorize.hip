@@ -522,11 +522,11 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
   // X <- orthonormal basis of the rows of Y, each row from the ones before it (see chol_kernel)
   const int nbc = (m + 15) / 16;
   auto orthonormalise = [&](const double* Y, double* X) -> hipError_t {
-    hipError_t err = gemm64<true>({Y, D, (size_t)m * D}, {Y, D, (size_t)m * D}, S, m, (size_t)m * m, m, m, D, D, m, m, batch, st);
+    hipError_t err = gemm64<true>({Y, D, (size_t)m * D}, {Y, D, (size_t)m * D}, S, 16 * nbc, (size_t)256 * nbc * nbc, m, m, D, D, 16 * nbc, 16 * nbc, batch, st);
     if (err != hipSuccess) return err;
 #define SKV_ORTH(NBW_, NB_)                                                                                       \
   do {                                                                                                            \
-    hipLaunchKernelGGL(chol_kernel<NBW_>, dim3(batch), dim3(512), 0, st, S, Lp, m, m, nbc);                         \
+    hipLaunchKernelGGL(chol_kernel<NBW_>, dim3(batch), dim3(512), 0, st, S, Lp, nbc);                         \
     hipLaunchKernelGGL(trsm_kernel<NB_>, dim3(D / 16, batch), dim3(256), 0, st, Lp, Y, X, m, nbc, D);                \
   } while (0)
     // (blocks per wave of the eight, block rows held): up to 80, 192, 224, 288 vectors
