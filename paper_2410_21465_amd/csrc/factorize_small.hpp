@@ -17,7 +17,7 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 // matrix instruction (a lane's four consecutive elements are four contraction steps), the next 16 steps requested
 // before the current ones' 16 instructions.  The products here are small (192 x 1024 x 1024 per sequence), so what
 // bounds them is how many waves there are: for one sequence T = 2, WK = 8 gives 1536 waves of 128 steps each; with several
-// sequences the 2 x 2 x 2 form halves the L2 traffic instead; the m x m products have so few tiles that T = 1 is faster.
+// sequences T = 4 halves the L2 traffic instead; the m x m products have so few tiles that T = 1 is faster.
 template <int T, int WM, int WN, int WK, bool BT>
 __global__ __launch_bounds__(64 * WM * WN * WK) void gemm64_kernel(const double* __restrict__ A,
                                                                    const double* __restrict__ B, double* __restrict__ C,
