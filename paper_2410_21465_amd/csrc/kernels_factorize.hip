@@ -305,12 +305,12 @@ __global__ __launch_bounds__(64, 2) void project_kernel(const void* __restrict__
 // ---- launch sequence ----------------------------------------------------------------------------------------
 // C (Mw x Nw, zero outside M x N) = A B, see gemm64_kernel; ?.ld = elements from row to row, ?.stride = from sequence to
 // sequence.  Fewer than 64 tiles of 32 x 32 (the m x m products of one sequence): 16 x 16 tiles, the contraction cut in
-// four (192 x 192 x 1024: 11.7 us, 18.5 us on 36 tiles of 32 x 32).  Up to 1024: 32 x 32 tiles with the contraction cut
-// eight ways (192 x 1024 x 1024 takes 19.6 us for one sequence, 211 us with a tile per workgroup on the vector unit).  More:
-// 64 x 64 blocks, the contraction cut in four, a wave's 16 tiles of 16 x 16 in 413 registers: half the reads from L2 of 2 x 2
-// waves of 32 x 32 (16 sequences: 155 us, 185 with those; the call 25.5 -> 25.0 ms, 6 x 20K 6.0 -> 5.7, 4 x 32K x 3072 19.6 ->
-// 17.9).  B by rows (one product per call) keeps the 2 x 2 waves: 34 us against 44.  The limits lie between shapes that were
-// measured on both sides, 192 vectors of 1 and 16 sequences; those in between were not searched.
+// 16 (192 x 192 x 1024: 9.9 us, cut in four 11.7, 18.5 us on 36 tiles of 32 x 32).  Up to 1024: 32 x 32 tiles with the
+// contraction cut eight ways (192 x 1024 x 1024 takes 19.6 us for one sequence, 211 us with a tile per workgroup on the vector
+// unit).  More: 64 x 64 blocks, the contraction cut in four, a wave's 16 tiles of 16 x 16 in 413 registers: half the reads
+// from L2 of 2 x 2 waves of 32 x 32 (16 sequences: 155 us, 185 with those; the call 25.5 -> 25.0 ms, 6 x 20K 6.0 -> 5.7,
+// 4 x 32K x 3072 19.6 -> 17.9).  B by rows (one product per call) keeps the 2 x 2 waves: 34 us against 44.  The limits lie
+// between shapes that were measured on both sides, 192 vectors of 1 and 16 sequences; those in between were not searched.
 struct Mat { const double* p; int ld; size_t stride; };
 template <bool BT>
 static hipError_t gemm64(Mat A, Mat B, double* C, int ldc, size_t strideC, int M, int N, int K, int Kb, int Mw, int Nw,
@@ -320,7 +320,7 @@ static hipError_t gemm64(Mat A, Mat B, double* C, int ldc, size_t strideC, int M
   hipLaunchKernelGGL((gemm64_kernel<T_, WM_, WN_, WK_, BT>), dim3((Nw + 16 * T_ * WN_ - 1) / (16 * T_ * WN_),             \
                      (Mw + 16 * T_ * WM_ - 1) / (16 * T_ * WM_), batch), dim3(64 * WM_ * WN_ * WK_), 0, st, A.p, B.p, C, M, N, \
                      K, Kb, A.ld, B.ld, ldc, Mw, Nw, A.stride, B.stride, strideC, a_rows, a_rows_stride)
-  if (tiles < 64) SKV_GEMM(1, 1, 1, 4);
+  if (tiles < 64) SKV_GEMM(1, 1, 1, 16);
   else if (tiles < 1024) SKV_GEMM(2, 1, 1, 8);
   else if constexpr (BT) SKV_GEMM(4, 1, 1, 4);
   else SKV_GEMM(2, 2, 2, 2);
