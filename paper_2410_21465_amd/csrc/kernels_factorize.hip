@@ -360,28 +360,29 @@ template <int EB>
 static hipError_t launch_project(const void* K, const double* Psi_t, void* A, char* ws, const FactorizePlan& pl, int batch, int s,
                                  int s_cap, int D, int r, hipStream_t st) {
   const int32_t* flags = reinterpret_cast<const int32_t*>(ws + pl.flags);
-  // (32-bit sums of digits: at most 3 * 2^14 per column)
-  const bool digits = D <= 32768;
+  // 32-bit sums of digits: at most 3 * 2^14 per column; and a launch has fewer than 2^32 threads, which some 4e8 tokens of
+  // rank 160 would pass (project_kernel counts sequences in a dimension of their own)
+  const int nt = (r + 31) / 32;
+  const long blocks = (long)batch * pl.n_splits * (pl.n_marks - 1), workgroups = (blocks + 7) / 8 * 8 * nt;
+  const bool digits = D <= 32768 && workgroups < 1l << 23;
   if (digits) {
-    const int nt = (r + 31) / 32;
     const float* scale = reinterpret_cast<const float*>(ws + pl.scale);
     uint8_t* psi_digits = reinterpret_cast<uint8_t*>(ws + pl.psi_digits);
     int32_t* exps = reinterpret_cast<int32_t*>(ws + pl.psi_exps);
     hipLaunchKernelGGL(psi_digits_kernel<EB>, dim3(32 * nt, batch), dim3(256), 0, st, Psi_t, scale, psi_digits, exps, D, r, nt);
-    const long blocks = (long)batch * pl.n_splits * (pl.n_marks - 1);
     constexpr int kLds = 2 * kPsiDeep * kPsiStage;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&project_digits_kernel<EB>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(project_digits_kernel<EB>, dim3((unsigned)((blocks + 7) / 8 * 8 * nt)), dim3(512), kLds, st, K, psi_digits, exps,
+    hipLaunchKernelGGL(project_digits_kernel<EB>, dim3((unsigned)workgroups), dim3(512), kLds, st, K, psi_digits, exps,
                        Psi_t, reinterpret_cast<const DigitRest*>(ws + pl.rest), reinterpret_cast<const int32_t*>(ws + pl.marks),
                        flags, scale, A, s, s_cap, D, r, nt, pl.nb2, pl.tokens_per_split, pl.n_splits, batch, pl.rest_cap, pl.n_marks);
   }
   // up to five 16-rank tiles per wave, the tiles dealt evenly to as few waves as that takes (rank 96: 2 x 3, not 5 + 1)
-  const int tiles = (r + 15) / 16, blocks = (tiles + 4) / 5, nt = (tiles + blocks - 1) / blocks;
-  const dim3 grid((s + 31) / 32, blocks, batch);
+  const int tiles = (r + 15) / 16, waves = (tiles + 4) / 5, per_wave = (tiles + waves - 1) / waves;
+  const dim3 grid((s + 31) / 32, waves, batch);
 #define SKV_PROJECT(NT_) hipLaunchKernelGGL((project_kernel<EB, NT_>), grid, dim3(64), 0, st, K, Psi_t, A, digits ? flags : nullptr, s, s_cap, D, r)
-  if (nt == 5) SKV_PROJECT(5); else if (nt == 4) SKV_PROJECT(4); else SKV_PROJECT(3);
+  if (per_wave == 5) SKV_PROJECT(5); else if (per_wave == 4) SKV_PROJECT(4); else SKV_PROJECT(3);
 #undef SKV_PROJECT
   return hipGetLastError();
 }
