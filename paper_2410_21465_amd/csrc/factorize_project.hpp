@@ -1,8 +1,15 @@
 // A = K Psi on the 8-bit integer matrix instruction: the keys as in factorize_gram.hpp (three digits, columns scaled by powers
 // of two, lists of what the digits leave out), each right singular vector as seven 8-bit digits of Psi / (its column's power
 // of two), 54 bits below the vector's largest such number.  Every sum of products is exact; what is lost is the rounding of
-// Psi to those digits, which is less than fp64 sums lose: against 64-bit-mantissa sums 1.3e-16 to 6e-16 of the result's root
-// mean square for key widths 128 to 3072, columns of like and of graded scale, where sums in fp64 are off by 4e-16 to 1.7e-15.
+// Psi to those digits.  Measured against the result's root mean square that is less than fp64 sums lose (against
+// 64-bit-mantissa sums 1.3e-16 to 6e-16 for key widths 128 to 3072, columns of like and of graded scale, where sums in fp64
+// are off by 4e-16 to 1.7e-15).  Entry by entry it can be more: where one column is far above the others, its component of the
+// vector takes the leading bits, the other components have few or none left, and a token that is zero in that column has
+// only those.  So every entry is held against a bound of its own: an error of half a unit per component makes at most N / 2 units,
+// N the sum of the token's digit numbers.  An entry smaller than 2^kSureBits times that is summed again from the keys and the
+// vector in fp64; a wave with more than kAgain such entries raises the sequence's flag, and project_kernel forms the whole
+// sequence's A.  16 x 128K x 1024, the call: normal keys 25.08 -> 25.24 ms; one token with a key of 2^26 times the others in a
+// column that is zero elsewhere, where the entries of its vector came out wrong, 26.6 -> 31.8.
 #pragma once
 #include "factorize_gram.hpp"
 
@@ -12,6 +19,10 @@ namespace skv {
 // of 32 vectors x 64 columns in operand_at's order, then the columns' scale words.  psi_digits [b][nt][stages][kPsiStage].
 constexpr int kPsiDigits = 7, kPsiPlane = 32 * 64, kPsiScale = kPsiDigits * kPsiPlane, kPsiStage = kPsiScale + 64 * 4;
 constexpr int kPsiDeep = 4;   // stages between barriers
+constexpr int kSureBits = 24; // an entry from digits is off by less than 2^-24 of its value
+constexpr int kAgain = 16;    // entries that a wave sums again, of 1024 (not searched: keys either need hardly any or whole vectors)
+// flags[b]: the digits do not hold the sequence's keys; its entries of A need more bits of the vectors than these have
+constexpr int kFlagKeys = 1, kFlagVectors = 2;
 // One workgroup per vector (those past r are zero).  exps [b][32 nt]: the digits stand for Psi 2^(exps - sh).
 template <int EB>
 __global__ __launch_bounds__(256) void psi_digits_kernel(const double* __restrict__ Psi_t, const float* __restrict__ scale,
@@ -27,7 +38,8 @@ __global__ __launch_bounds__(256) void psi_digits_kernel(const double* __restric
   if ((threadIdx.x & 63) == 0) most[threadIdx.x >> 6] = m;
   __syncthreads();
   m = fmax(fmax(most[0], most[1]), fmax(most[2], most[3]));
-  const int e = 54 - __builtin_amdgcn_frexp_exp(m);   // every digit number is below 2^54
+  // every digit number is below 2^54 (a vector of zeros is exact: no bound on its entries)
+  const int e = m > 0.0 ? 54 - __builtin_amdgcn_frexp_exp(m) : 4096;
   if (threadIdx.x == 0) exps[(size_t)b * nt * 32 + rho] = e;
   uint8_t* out = psi_digits + ((size_t)b * nt + rho / 32) * stages * kPsiStage;
   for (int c0 = 4 * threadIdx.x; c0 < 64 * stages; c0 += 1024) {
@@ -48,7 +60,7 @@ __global__ __launch_bounds__(256) void psi_digits_kernel(const double* __restric
     if ((rho & 31) == 0)
 #pragma unroll
       for (int u = 0; u < 4; ++u)
-        reinterpret_cast<uint32_t*>(st + kPsiScale)[(c0 & 63) + u] = Piece<EB>::scale_word(u, sc[min(c0 + u, D - 1)]);
+        reinterpret_cast<uint32_t*>(st + kPsiScale)[(c0 & 63) + u] = c0 + u < D ? Piece<EB>::scale_word(u, sc[c0 + u]) : 0u;   // (digits of zeros)
   }
 }
 
@@ -64,7 +76,7 @@ template <int EB>
 __global__ __launch_bounds__(512, 2) void project_digits_kernel(const void* __restrict__ K, const uint8_t* __restrict__ psi_digits,
                                                                 const int32_t* __restrict__ exps, const double* __restrict__ Psi_t,
                                                                 const DigitRest* __restrict__ rest, const int32_t* __restrict__ marks,
-                                                                const int32_t* __restrict__ flags, const float* __restrict__ scale,
+                                                                int32_t* __restrict__ flags, const float* __restrict__ scale,
                                                                 void* __restrict__ Aout, int s, int s_cap, int D, int r, int nt,
                                                                 int nb2, int tokens_per_split, int n_splits, int batch,
                                                                 int rest_cap, int n_marks) {
@@ -74,10 +86,14 @@ __global__ __launch_bounds__(512, 2) void project_digits_kernel(const void* __re
   __shared__ int32_t columns[kEntries];
   __shared__ double products[kEntries][32];
   __shared__ int32_t list_n[512];
+  __shared__ int32_t raised;
   const int per_split = n_marks - 1, j = blockIdx.x >> 3, n = j % nt, block = (j / nt) * 8 + (blockIdx.x & 7);
   if (block >= batch * n_splits * per_split) return;
   const int group = block / per_split, in_split = block % per_split, b = group / n_splits, split = group % n_splits;
-  if (flags[b]) return;
+  // (another workgroup may raise kFlagVectors at any time, kFlagKeys is settled)
+  const int flag = __hip_atomic_load(&flags[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (flag == kFlagKeys) return;
+  if (threadIdx.x == 0) raised = flag;
   const int t_begin = split * tokens_per_split + in_split * 256;
   const int t_end = min(min(s, (split + 1) * tokens_per_split), t_begin + 256);
   if (t_begin >= t_end) return;
@@ -100,7 +116,7 @@ __global__ __launch_bounds__(512, 2) void project_digits_kernel(const void* __re
   };
   using Raw = Piece<EB>[2][2];
   Raw raw0, raw1;   // this lane's keys of the stage at hand and the next
-  auto request_k = [&](Raw& raw, int st) {   // (columns past the end repeat the last ones: their digits of Psi are zero)
+  auto request_k = [&](Raw& raw, int st) {   // (columns past the end repeat the last ones: scaled by zero, and their digits of Psi are zero)
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
@@ -126,6 +142,7 @@ __global__ __launch_bounds__(512, 2) void project_digits_kernel(const void* __re
 #pragma unroll 1
   for (int st = 0; st < kPsiDeep; ++st) { request_b(st); put_b(st); }
   __syncthreads();
+  if (raised) return;
   auto stage = [&](const Raw& raw, Raw& next, int st) {
     const uint8_t* plane = lds + st % (2 * kPsiDeep) * kPsiStage;
     request_b(st + kPsiDeep);
@@ -211,6 +228,73 @@ __global__ __launch_bounds__(512, 2) void project_digits_kernel(const void* __re
         const double x = products[i][sub];
 #pragma unroll
         for (int y = 0; y < 16; ++y) v[y] += (token & 31) == 8 * (y >> 2) + 4 * half + (y & 3) ? x : 0.0;
+      }
+    }
+  }
+  // Entries that their bound does not vouch for: held against the most that a token can have first, and where that leaves many
+  // (a token of zeros is exact, and a faint one has less), against what each token has.  (Summing the magnitudes along with
+  // the products took 3 % of the kernel.)
+  const double unit = ldexp(1.0, kSureBits - 1 - e);
+  uint32_t unsure = 0;
+  int n_unsure = 0;
+  auto look = [&](auto&& bound) {   // bound(x): N of the wave's token x
+    unsure = 0; n_unsure = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int x = 8 * (i >> 2) + 4 * half + (i & 3);
+      const bool low = fabs(v[i]) < unit * (double)bound(x) && rho < r && t_begin + 32 * wave + x < t_end;
+      unsure |= low ? 1u << i : 0u;
+      n_unsure += __popcll(__ballot(low));
+    }
+  };
+  look([&](int) { return 4194304.0f * (float)D; });
+  if (n_unsure > kAgain) {
+    const uint8_t* first_row = static_cast<const uint8_t*>(K) + (size_t)b * s * D * EB;
+    uint32_t present = 0;   // tokens that are not all zeros
+    for (int x0 = 0; x0 < 32; x0 += 8)
+      for (int c0 = 0; c0 < D; c0 += 8 * kWave) {
+        Piece<EB> p[8];
+#pragma unroll
+        for (int x = 0; x < 8; ++x)
+          p[x].load(first_row + ((size_t)min(t_begin + 32 * wave + x0 + x, s - 1) * D + min(c0 + 8 * lane, D - 8)) * EB);
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+          uint32_t any = 0;
+#pragma unroll
+          for (int i = 0; i < 2 * EB; ++i) any |= p[x].w[i] & (EB == 2 ? 0x7fff7fffu : 0x7f7f7f7fu);
+          present |= __any(any != 0) ? 1u << (x0 + x) : 0u;
+        }
+      }
+    look([&](int x) { return present >> x & 1 ? 4194304.0f * (float)D : 0.0f; });
+    if (n_unsure > kAgain) {
+      float sum = 0.0f;   // of half of token `sub`
+#pragma unroll 4
+      for (int c = half * (D / 2); c < (half + 1) * (D / 2); c += 8) {
+        Piece<EB> p;
+        p.load(row + (size_t)c * EB);
+        const float* sc = scale + (size_t)b * D + c;
+        each_of(std::make_integer_sequence<int, 8>{}, [&](auto x) { sum += fabsf(fmaf(p.template elem<x>(), sc[x], kDigitMagic) - kDigitMagic); });
+      }
+      sum += __shfl_xor(sum, 32, kWave);
+      look([&](int x) { return __shfl(sum, x, kWave); });
+    }
+  }
+  if (n_unsure > kAgain) {
+    if (lane == 0) __hip_atomic_store(&flags[b], kFlagVectors, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  } else if (n_unsure) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      uint64_t which = __ballot(unsure >> i & 1);
+      while (which) {
+        const int l = __ffsll((unsigned long long)which) - 1;
+        which &= which - 1;
+        const size_t t = (size_t)b * s + t_begin + 32 * wave + 8 * (i >> 2) + 4 * (l >> 5) + (i & 3);
+        const double* psi = Psi_t + ((size_t)b * r + 32 * n + (l & 31)) * D;
+        double sum = 0.0;
+#pragma unroll 4
+        for (int x = lane; x < D; x += kWave) sum = fma((double)kv_elem<EB>(K, t * D + x), psi[x], sum);
+        sum = wave_sum_f64(sum);
+        v[i] = lane == l ? sum : v[i];
       }
     }
   }

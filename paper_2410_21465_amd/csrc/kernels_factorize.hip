@@ -359,7 +359,7 @@ static hipError_t launch_gram(const void* K, double* part, double* G, float* sca
 template <int EB>
 static hipError_t launch_project(const void* K, const double* Psi_t, void* A, char* ws, const FactorizePlan& pl, int batch, int s,
                                  int s_cap, int D, int r, hipStream_t st) {
-  const int32_t* flags = reinterpret_cast<const int32_t*>(ws + pl.flags);
+  int32_t* flags = reinterpret_cast<int32_t*>(ws + pl.flags);
   // 32-bit sums of digits: at most 3 * 2^14 per column; and a launch has fewer than 2^32 threads, which some 4e8 tokens of
   // rank 160 would pass (project_kernel counts sequences in a dimension of their own)
   const int nt = (r + 31) / 32;

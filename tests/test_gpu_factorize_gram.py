@@ -36,6 +36,14 @@ def _keys(kind, b, s, D, kd, gen):
     elif kind == "mixed":         # one sequence of each route
         k[0, ::500] *= 6.0
         k[1] *= torch.exp2(-20.0 * torch.rand(s, D, generator=gen, device="cuda"))
+    elif kind == "absent":        # a column far above the others that some tokens do not have: of theirs the weak entries of its
+        k *= 2.0 ** (-9 if kd else -4)                           # vectors are all there is
+        k[:, :, 3] *= 2.0 ** (20 if kd else 22)
+        k[:, ::61, 3] = 0.0
+    elif kind == "lone":          # a column that one token has
+        k *= 2.0 ** -6
+        k[:, :, 5] = 0.0
+        k[:, s // 2, 5] = 2.0 ** (15 if kd else 20)
     elif kind == "ones":          # magnitudes with all leading bits set, of either sign
         k = torch.where(k < 0, -255.0, 255.0)
     return k.clamp(-5.0e4, 5.0e4).to(torch.float8_e5m2) if kd else k.to(torch.bfloat16)
@@ -46,6 +54,7 @@ CASES = [(1, 1, 64, 1, "normal", 0), (1, 1, 64, 63, "normal", 0), (2, 1, 64, 65,
          (1, 2, 128, 2049, "outliers", 0), (1, 2, 128, 2000, "graded", 0), (2, 2, 64, 1200, "spikes", 0),
          (1, 2, 128, 4000, "faint", 0), (2, 2, 96, 1000, "faint", 0), (1, 4, 64, 1111, "graded", 1),
          (2, 3, 64, 777, "columns", 0), (1, 2, 128, 600, "large", 0), (3, 2, 128, 1000, "mixed", 0),
+         (1, 1, 128, 4000, "absent", 0), (2, 2, 96, 3000, "absent", 1), (1, 2, 128, 2000, "lone", 0), (2, 3, 64, 1000, "lone", 1),
          (1, 2, 128, 5000, "ones", 0), (1, 1, 64, 70001, "outliers", 0),
          (256, 1, 64, 33000, "normal", 0)]   # one token part of more than 32768 tokens
 
