@@ -275,6 +275,17 @@ int shadowkv_factorize_keys(const shadowkv_params *params, const shadowkv_kv *k_
                             void *workspace, size_t workspace_bytes, void *stream);
 size_t shadowkv_factorize_workspace_bytes(const shadowkv_params *params);
 
+/*
+ * How shadowkv_factorize_keys of this shape is laid out on the GPU, and where it leaves which way each sequence went (for
+ * tests and profiling).  Writes 4 values to `plan` (host):
+ *   [0] token parts of the Gram matrix; [1] tokens per part; [2] entries that a list of a part has room for (lists hold what
+ *       the keys' digits leave out: one per 128 columns and quarter of a part's tokens);
+ *   [3] byte offset in the workspace of an int32 per sequence, valid after the call: 0 Gram matrix and A from digits,
+ *       1 both from fp64 sums, 2 the Gram matrix from digits and A from fp64 sums.
+ * Returns SHADOWKV_OK or SHADOWKV_EINVAL (bad params / plan NULL).
+ */
+int shadowkv_factorize_plan(const shadowkv_params *params, int64_t *plan);
+
 /* Bytes of `value_cache` for the given shape and slot count (0 if either is invalid). */
 size_t shadowkv_value_cache_bytes(const shadowkv_params *params, int32_t cache_slots);
 

@@ -692,6 +692,18 @@ size_t shadowkv_factorize_workspace_bytes(const shadowkv_params* params) {
   return plan_factorize(sh.b, sh.s, sh.hkv * sh.d, params->rank, kFactorOversample, kFactorSweeps, sh.eb).total;
 }
 
+int shadowkv_factorize_plan(const shadowkv_params* params, int64_t* plan) {
+  Shape sh;
+  int rc = check_params(params, false, &sh);
+  if (rc != SHADOWKV_OK) return rc;
+  if (params->rank < 8 || params->rank > 256 || params->rank % 8 || params->rank > sh.hkv * sh.d)
+    return fail_inval("rank must be a multiple of 8 in [8, 256] and at most h_kv * d");
+  if (!plan) return fail_inval("plan is NULL");
+  const FactorizePlan pl = plan_factorize(sh.b, sh.s, sh.hkv * sh.d, params->rank, kFactorOversample, kFactorSweeps, sh.eb);
+  plan[0] = pl.n_splits; plan[1] = pl.tokens_per_split; plan[2] = pl.rest_cap; plan[3] = (int64_t)pl.flags;
+  return SHADOWKV_OK;
+}
+
 int shadowkv_factorize_keys(const shadowkv_params* params, const shadowkv_kv* k_pre, shadowkv_kv* A, shadowkv_kv* B,
                             double* psi_out, double* sigma_out, int32_t n_iter, void* workspace, size_t workspace_bytes,
                             void* stream) {

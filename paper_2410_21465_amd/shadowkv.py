@@ -29,7 +29,7 @@ EXPORTS = (
     "shadowkv_profile_begin", "shadowkv_profile_end", "shadowkv_decode_step_cached", "shadowkv_value_cache_bytes",
     "shadowkv_value_cache_reset", "shadowkv_append_chunk", "shadowkv_argtopk", "shadowkv_argtopk_workspace_bytes",
     "shadowkv_factorize_keys", "shadowkv_factorize_workspace_bytes", "shadowkv_decode_step_static",
-    "shadowkv_static_scratch_bytes", "shadowkv_decode_plan",
+    "shadowkv_static_scratch_bytes", "shadowkv_decode_plan", "shadowkv_factorize_plan",
 )
 STAGES = ("score", "select", "gather_values", "attention")
 
@@ -89,6 +89,8 @@ def lib() -> C.CDLL:
         L.shadowkv_factorize_keys.argtypes = [vp] * 6 + [i32, vp, sz, vp]
         L.shadowkv_factorize_workspace_bytes.restype = sz
         L.shadowkv_factorize_workspace_bytes.argtypes = [vp]
+        L.shadowkv_factorize_plan.restype = i32
+        L.shadowkv_factorize_plan.argtypes = [vp, vp]
         L.shadowkv_build_workspace_bytes.restype = sz
         L.shadowkv_build_workspace_bytes.argtypes = [vp]
         L.shadowkv_decode_workspace_bytes.restype = sz
@@ -312,6 +314,21 @@ def decode_step_static(p: Params, q, A, B, landmarks, landmark_chunk_ids, k_outl
                                              _ptr(landmark_chunk_ids), _ptr(k_outlier), _ptr(v_outlier),
                                              _ptr(k_local), _ptr(v_local), _ptr(value_store), _ptr(pos_offset),
                                              _ptr(out), _ptr(out_chunk_ids), _stream_ptr(stream)))
+
+
+def factorize_plan(p: "Params") -> dict:
+    """shadowkv_factorize_plan: how the keys of this shape are factored on the GPU."""
+    st = p.c_struct()
+    plan = (C.c_int64 * 4)()
+    _check(lib().shadowkv_factorize_plan(C.addressof(st), plan))
+    return {"parts": plan[0], "tokens_per_part": plan[1], "entries_per_list": plan[2], "routes_offset": plan[3]}
+
+
+def factorize_routes(p: "Params", workspace: torch.Tensor) -> torch.Tensor:
+    """Which way each sequence of the last ``factorize_keys`` went, int32 [b] aliasing ``workspace``: 0 Gram matrix and A from
+    digits, 1 both from fp64 sums, 2 the Gram matrix from digits and A from fp64 sums."""
+    off = factorize_plan(p)["routes_offset"]
+    return workspace[off:off + 4 * p.batch].view(torch.int32)
 
 
 def append_chunk(p: Params, k_pre, k_rope, v, B, A, landmarks, landmark_chunk_ids, value_store, stream=None) -> None:

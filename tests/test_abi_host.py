@@ -162,6 +162,21 @@ def test_factorize_workspace_takes_no_more_than_it_did(b, s, hkv, d):
         assert up(D * D) < need <= most, (b, s, hkv, d, r, need, most)
 
 
+def test_factorize_plan_lies_in_the_workspace():
+    for b, s, hkv, d in [(1, 8, 1, 64), (3, 2049, 3, 64), (1, 32768, 8, 128), (16, 131072, 8, 128), (1024, 33000, 3, 64)]:
+        p = S.Params(batch=b, n_q_heads=hkv, n_kv_heads=hkv, head_dim=d, ctx_len=s, chunk_size=1, rank=64, n_outlier_chunks=0,
+                     topk_chunks=1, local_len=0)
+        st = p.c_struct()
+        plan = S.factorize_plan(p)
+        assert plan["parts"] * plan["tokens_per_part"] >= s > (plan["parts"] - 1) * plan["tokens_per_part"]
+        assert plan["tokens_per_part"] % 16 == 0 and plan["entries_per_list"] > 0
+        assert plan["routes_offset"] % 256 == 0
+        assert plan["routes_offset"] + 4 * b <= S.lib().shadowkv_factorize_workspace_bytes(C.addressof(st))
+        assert S.lib().shadowkv_factorize_plan(C.addressof(st), None) == S.EINVAL
+    bad = S.Params(**{**GOOD, "rank": 264}).c_struct()
+    assert S.lib().shadowkv_factorize_plan(C.addressof(bad), (C.c_int64 * 4)()) == S.EINVAL
+
+
 def test_append_chunk_rejects_a_full_context_and_bad_capacity():
     lib = S.lib()
     fake = C.c_void_p(0x1000)
