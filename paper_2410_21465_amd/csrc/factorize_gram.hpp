@@ -167,7 +167,7 @@ __global__ __launch_bounds__(256) void column_max_kernel(const void* __restrict_
 
 // scale[b][j] = 2^sh_j, 1 <= scale <= 2^126; 64 columns per workgroup, four threads each.  The flag of the sequence is raised
 // by a column with an element beyond 2^22 (or not finite), and where more than one in 512 of the workgroup's elements in 256
-// tokens (evenly spaced) is not held by its digits: twice what the lists have room for.  (Found out only by full lists, keys
+// tokens (evenly spaced over the sequence; all of them, once each, of a shorter one) is not held by its digits: twice what the lists have room for.  (Found out only by full lists, keys
 // with a row in 500 of 3000 times the others' size took 68.0 ms at 16 x 128K x 1024 where the fp64 sums alone take 53.5.)
 template <int EB>
 __global__ __launch_bounds__(256) void column_scale_kernel(const void* __restrict__ K, const uint16_t* __restrict__ chunk_max,
@@ -197,20 +197,22 @@ __global__ __launch_bounds__(256) void column_scale_kernel(const void* __restric
   }
   __syncthreads();
   // eight columns of a token per thread, 32 tokens at a time
-  const int c8 = 8 * (threadIdx.x & 7), step = max(s / kSample, 1), n = min(kSample, s);
+  const int c8 = 8 * (threadIdx.x & 7), n = min(kSample, s);
   Piece<EB> v[kSample / 32];
 #pragma unroll
   for (int i = 0; i < kSample / 32; ++i) {
-    const int t = min((int)(threadIdx.x >> 3) + 32 * i, n - 1) * step;
+    const int t = (int)((int64_t)min((int)(threadIdx.x >> 3) + 32 * i, n - 1) * s / n);
     v[i].load(static_cast<const uint8_t*>(K) + (((size_t)b * s + t) * D + min(col0 + c8, D - 8)) * EB);
   }
   int mine = 0;
 #pragma unroll
-  for (int i = 0; i < kSample / 32; ++i)
+  for (int i = 0; i < kSample / 32; ++i) {
+    if ((int)(threadIdx.x >> 3) + 32 * i >= n) continue;
     each_of(std::make_integer_sequence<int, 8>{}, [&](auto e) { mine += digit_rest(v[i].template elem<e>(), sc[c8 + e]) != 0.0f ? 1 : 0; });
+  }
   if (col0 + c8 < D && mine) atomicAdd(&missed, mine);
   __syncthreads();
-  if (threadIdx.x == 0 && missed > kSample * 64 / 512) flags[b] = 1;
+  if (threadIdx.x == 0 && 512 * missed > n * min(64, D - col0)) flags[b] = 1;
 }
 
 // ---- the digits' products ---------------------------------------------------------------------------------

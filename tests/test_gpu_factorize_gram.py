@@ -36,6 +36,8 @@ def _keys(kind, b, s, D, kd, gen):
     elif kind == "unseen":        # as graded, in tokens that the sample of evenly spaced ones skips: found by full lists
         k[:, s // 4 + 1:s // 4 + 513:2] *= torch.exp2(-20.0 * torch.rand(n, 256, D, generator=gen, device="cuda"))
         k *= 2.0 ** (12 if kd else 0)
+    elif kind == "last":          # one element that its digits do not hold, in the last token of a short sequence
+        k[:, -1, 3] = 1.125 * 2.0 ** -21
     elif kind == "large":         # beyond 2^22: fp64 (bf16 only)
         k *= 2.0 ** 30
     elif kind == "mixed":         # one sequence of each route
@@ -63,7 +65,7 @@ CASES = [(1, 1, 64, 1, "normal", 0, 2), (1, 1, 64, 63, "normal", 0, 2), (2, 1, 6
          (2, 2, 64, 1200, "spikes", 0, 1), (1, 2, 128, 4000, "faint", 0, 0), (2, 2, 96, 1000, "faint", 0, 0),
          (1, 4, 64, 1111, "graded", 1, 1), (1, 2, 128, 2500, "faint", 1, 0), (2, 3, 64, 777, "columns", 0, 0),
          (1, 2, 128, 600, "large", 0, 1), (3, 2, 128, 1000, "mixed", 0, (0, 1, 0)), (2, 3, 64, 4096, "unseen", 0, 1),
-         (1, 2, 96, 8192, "unseen", 1, 1), (1, 1, 128, 4000, "absent", 0, 0), (2, 2, 96, 3000, "absent", 1, 0),
+         (1, 2, 96, 8192, "unseen", 1, 1), (1, 1, 64, 100, "last", 0, 0), (1, 1, 128, 4000, "absent", 0, 0), (2, 2, 96, 3000, "absent", 1, 0),
          (1, 2, 128, 2000, "lone", 0, 2), (2, 3, 64, 1000, "lone", 1, 2), (1, 2, 128, 5000, "ones", 0, 0),
          (1, 1, 64, 70001, "outliers", 0, 0),
          (256, 1, 64, 33000, "normal", 0, 0),
