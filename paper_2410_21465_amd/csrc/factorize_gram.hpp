@@ -9,7 +9,7 @@
 // one's is such an integer itself; of normally distributed keys one in ten thousand is not.  What rounding leaves of those,
 // r = x - v 2^-sh, goes on a list, and gram_finish_kernel adds what the digits miss: with Y = K - R,
 //   K^T K = Y^T Y + H + H^T,  H = R^T (K - R / 2),
-// in fp64.  The list of a part of the tokens and columns has room for one element in 1024; keys that need more (a few rows
+// in fp64.  The list of a part of the tokens and columns has room for one element in 768; keys that need more (a few rows
 // far above the rest, columns next to the least bf16 numbers) and keys that are infinite, NaN or beyond 2^22 (2^-133, the
 // least bf16 number, times their column's power of two would leave bf16) raise the sequence's flag, and gram_kernel forms
 // that sequence's sums in fp64 instead.
@@ -165,27 +165,33 @@ __global__ __launch_bounds__(256) void column_max_kernel(const void* __restrict_
   }
 }
 
-// scale[b][j] = 2^sh_j, 1 <= scale <= 2^126; 64 columns per workgroup, four threads each.  The flag of the sequence is raised
-// by a column with an element beyond 2^22 (or not finite), and where more than one in 512 of the workgroup's elements in 256
-// tokens (evenly spaced over the sequence; all of them, once each, of a shorter one) is not held by its digits: twice what the lists have room for.  (Found out only by full lists, keys
-// with a row in 500 of 3000 times the others' size took 68.0 ms at 16 x 128K x 1024 where the fp64 sums alone take 53.5.)
+// scale[b][j] = 2^sh_j, 1 <= scale <= 2^126; 64 columns per workgroup, sixteen threads each.  The flag of the sequence is raised
+// by a column with an element beyond 2^22 (or not finite), and where a sample of kSample tokens (evenly spaced over the
+// sequence; all of a shorter one) says that the lists will not do: more than `share` of the workgroup's elements are not held
+// by their digits, or several times that in one token part.  `share` is what the lists have room for, less three standard
+// deviations of such a list's length, and the sample is large enough to tell that from three quarters of it: with 256 tokens and
+// twice the lists' room, keys with 1 % of their chunks 10 to 16 times the others' size went through the digits' products, filled
+// their lists and were summed in fp64 after all, 64.2 ms at 16 x 128K x 1024 where the fp64 sums alone take 53.9; now 40.8 to 54.0.
 template <int EB>
-__global__ __launch_bounds__(256) void column_scale_kernel(const void* __restrict__ K, const uint16_t* __restrict__ chunk_max,
-                                                           float* __restrict__ scale, int32_t* __restrict__ flags, int s, int D,
-                                                           int n_chunks) {
-  constexpr int kSample = 256;
-  __shared__ uint32_t red[4][64];
+__global__ __launch_bounds__(1024) void column_scale_kernel(const void* __restrict__ K, const uint16_t* __restrict__ chunk_max,
+                                                            float* __restrict__ scale, int32_t* __restrict__ flags, int s, int D,
+                                                            int n_chunks, int tokens_per_split, float share) {
+  constexpr int kSample = 2048, kRows = 1024 / 64, kPass = 1024 / 8, kParts = 512;
+  __shared__ uint32_t red[kRows][64];
   __shared__ float sc[64];
-  __shared__ int32_t missed;
+  __shared__ int32_t taken[kParts], missed[kParts];   // tokens of the sample, and their elements that are not held, per token part
+  __shared__ int32_t all_missed;
   const int b = blockIdx.y, x = threadIdx.x & 63, y = threadIdx.x >> 6, col0 = blockIdx.x * 64, col = min(col0 + x, D - 1);
   uint32_t m = 0;
 #pragma unroll 8
-  for (int c = y; c < n_chunks; c += 4) m = max(m, (uint32_t)chunk_max[((size_t)b * n_chunks + c) * D + col]);
+  for (int c = y; c < n_chunks; c += kRows) m = max(m, (uint32_t)chunk_max[((size_t)b * n_chunks + c) * D + col]);
   red[y][x] = m;
-  if (threadIdx.x == 0) missed = 0;
+  if (threadIdx.x < kParts) taken[threadIdx.x] = missed[threadIdx.x] = 0;
+  if (threadIdx.x == 0) all_missed = 0;
   __syncthreads();
   if (y == 0) {
-    m = max(max(red[0][x], red[1][x]), max(red[2][x], red[3][x]));
+#pragma unroll
+    for (int i = 1; i < kRows; ++i) m = max(m, red[i][x]);
     // exponent of the largest element, biased as in fp32; one more where the leading bits are all ones (two more units of
     // the last place of bf16 carry into it), since 2^22 itself is out of kDigitMagic's reach
     const uint32_t f = EB == 2 ? m << 16 : __float_as_uint(e5m2_to_f32((uint8_t)m));
@@ -196,23 +202,33 @@ __global__ __launch_bounds__(256) void column_scale_kernel(const void* __restric
     if (col0 + x < D) scale[(size_t)b * D + col] = sc[x];
   }
   __syncthreads();
-  // eight columns of a token per thread, 32 tokens at a time
+  // eight columns of a token per thread, kPass tokens at a time
   const int c8 = 8 * (threadIdx.x & 7), n = min(kSample, s);
-  Piece<EB> v[kSample / 32];
+  const uint64_t step = ((uint64_t)s << 32) / (uint32_t)n;
+  auto token = [&](int i) { return (int)((uint64_t)i * step >> 32); };
+#pragma unroll 1
+  for (int i0 = threadIdx.x >> 3; i0 < n; i0 += 8 * kPass) {
+    Piece<EB> v[8];
 #pragma unroll
-  for (int i = 0; i < kSample / 32; ++i) {
-    const int t = (int)((int64_t)min((int)(threadIdx.x >> 3) + 32 * i, n - 1) * s / n);
-    v[i].load(static_cast<const uint8_t*>(K) + (((size_t)b * s + t) * D + min(col0 + c8, D - 8)) * EB);
-  }
-  int mine = 0;
+    for (int i = 0; i < 8; ++i) {
+      const int t = token(min(i0 + kPass * i, n - 1));
+      v[i].load(static_cast<const uint8_t*>(K) + (((size_t)b * s + t) * D + min(col0 + c8, D - 8)) * EB);
+    }
 #pragma unroll
-  for (int i = 0; i < kSample / 32; ++i) {
-    if ((int)(threadIdx.x >> 3) + 32 * i >= n) continue;
-    each_of(std::make_integer_sequence<int, 8>{}, [&](auto e) { mine += digit_rest(v[i].template elem<e>(), sc[c8 + e]) != 0.0f ? 1 : 0; });
+    for (int i = 0; i < 8; ++i) {
+      if (i0 + kPass * i >= n) continue;
+      const int part = min(token(i0 + kPass * i) / tokens_per_split, kParts - 1);
+      if (c8 == 0) atomicAdd(&taken[part], 1);
+      int mine = 0;
+      each_of(std::make_integer_sequence<int, 8>{}, [&](auto e) { mine += digit_rest(v[i].template elem<e>(), sc[c8 + e]) != 0.0f ? 1 : 0; });
+      if (col0 + c8 < D && mine) { atomicAdd(&missed[part], mine); atomicAdd(&all_missed, mine); }
+    }
   }
-  if (col0 + c8 < D && mine) atomicAdd(&missed, mine);
   __syncthreads();
-  if (threadIdx.x == 0 && 512 * missed > n * min(64, D - col0)) flags[b] = 1;
+  // (eight elements fill no list)
+  const float room = share * (float)min(64, D - col0);
+  if (threadIdx.x < kParts && (float)missed[threadIdx.x] > 2.0f * room * (float)taken[threadIdx.x] + 8.0f) flags[b] = 1;
+  if (threadIdx.x == 0 && (float)all_missed > fmaxf(room * (float)n, 8.0f)) flags[b] = 1;
 }
 
 // ---- the digits' products ---------------------------------------------------------------------------------
@@ -288,7 +304,10 @@ __device__ __forceinline__ void gram_digits_tile(const GramTile& g, uint8_t* lds
         for (int i = 0; i < 2 * EB; ++i) raw[u].w[i] = t0 + tok + u < g.t_end ? raw[u].w[i] : 0u;
     }
     if constexpr (DIAG) {
-      if (((t0 - g.t_begin) & 255) == 0 && lane == 0) g.marks[tq * g.n_marks + (t0 - g.t_begin) / 256] = n_rest;
+      if (((t0 - g.t_begin) & 255) == 0 && lane == 0) {
+        g.marks[tq * g.n_marks + (t0 - g.t_begin) / 256] = n_rest;
+        if (n_rest > g.rest_cap) __hip_atomic_store(g.flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
       // Which elements may the digits not hold: those below their column's threshold, compared two at a time.  A pair of
       // columns where there are any (three stages of a wave in four have none where the keys are normally distributed) is
       // looked at element by element; the entries' order is that of column pair, column, token, lane.
@@ -460,27 +479,26 @@ __global__ __launch_bounds__(512, 2) void gram_digits_kernel(const void* __restr
 
 // ---- what the digits miss, by column ---------------------------------------------------------------------
 // The lists of one block of 128 columns (four of each token part) as one, sorted by column; within a column the order is
-// that of the walk below, the same on every run, and so is that of the sums.  by_col [b][nb2][n_lists * rest_cap]; col_begin
-// [b][nb2][129].  32 lists at a time, 64 entries of each, go through LDS; eight threads per column, each with four of the 32
-// lists, count their entries and then place them.  (A thread per column for all lists: 250 us at 16 x 128K x 1024, 80 at
-// 1 x 32K.)
-struct ColumnRest { uint32_t token; float rest; };   // rest = x - v 2^-sh
+// that of the walk below, the same on every run, and so is that of the sums.  by_col [b][nb2][n_lists * rest_cap]: places in the
+// sequence's lists; col_begin [b][nb2][129].  32 lists at a time, 64 entries of each, go through LDS; eight threads per column,
+// each with four of the 32 lists, count their entries and then place them.  (A thread per column for all lists: 250 us at
+// 16 x 128K x 1024, 80 at 1 x 32K.)
 __global__ __launch_bounds__(1024) void rest_by_column_kernel(const DigitRest* __restrict__ rest, const int32_t* __restrict__ rest_count,
-                                                              const float* __restrict__ scale, const int32_t* __restrict__ flags,
-                                                              ColumnRest* __restrict__ by_col, int32_t* __restrict__ col_begin,
-                                                              int D, int nb2, int n_splits, int rest_cap) {
+                                                              const int32_t* __restrict__ flags, uint32_t* __restrict__ by_col,
+                                                              int32_t* __restrict__ col_begin, int nb2, int n_splits, int rest_cap) {
   constexpr int kLists = 32, kTake = 64, kShare = kLists / 8;
-  __shared__ DigitRest buf[kLists][kTake];
+  __shared__ uint8_t buf[kLists][kTake];
   __shared__ int32_t have[kLists];
   __shared__ int32_t counts[8][128];
   const int bi = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, c = tid & 127, share = tid >> 7;
   const int n_lists = 4 * n_splits;
   if (flags[b]) return;
-  auto list_of = [&](int l) { return (((size_t)b * n_splits + (l >> 2)) * nb2 + bi) * 4 + (l & 3); };
+  const size_t first_list = (size_t)b * n_splits * nb2 * 4;   // of the sequence
+  auto list_of = [&](int l) { return (((size_t)(l >> 2)) * nb2 + bi) * 4 + (l & 3); };
   auto walk = [&](auto&& each) {
     for (int l0 = 0; l0 < n_lists; l0 += kLists) {
       __syncthreads();
-      if (tid < kLists) have[tid] = l0 + tid < n_lists ? min(rest_count[list_of(l0 + tid)], rest_cap) : 0;
+      if (tid < kLists) have[tid] = l0 + tid < n_lists ? min(rest_count[first_list + list_of(l0 + tid)], rest_cap) : 0;
       __syncthreads();
       int most = 0;
       for (int l = 0; l < kLists; ++l) most = max(most, have[l]);
@@ -488,18 +506,18 @@ __global__ __launch_bounds__(1024) void rest_by_column_kernel(const DigitRest* _
         if (p0) __syncthreads();
         const int l = tid >> 5, n = min(have[l] - p0, kTake);   // 32 threads copy a list
         if (n > 0) {
-          const DigitRest* src = rest + list_of(l0 + l) * rest_cap + p0;
-          for (int i = tid & 31; i < n; i += 32) buf[l][i] = src[i];
+          const DigitRest* src = rest + (first_list + list_of(l0 + l)) * rest_cap + p0;
+          for (int i = tid & 31; i < n; i += 32) buf[l][i] = (uint8_t)src[i].col;
         }
         __syncthreads();
         for (int m = kShare * share; m < kShare * share + kShare; ++m)
           for (int i = 0; i < min(have[m] - p0, kTake); ++i)
-            if (buf[m][i].col == c) each(buf[m][i]);
+            if (buf[m][i] == c) each(l0 + m, p0 + i);
       }
     }
   };
   int n = 0;
-  walk([&](const DigitRest&) { ++n; });
+  walk([&](int, int) { ++n; });
   counts[share][c] = n;
   __syncthreads();
   int at = 0;   // entries of the columns before this one, then of this column's shares before this one
@@ -510,9 +528,8 @@ __global__ __launch_bounds__(1024) void rest_by_column_kernel(const DigitRest* _
   if (share == 0) begin[c] = at;
   for (int x = 0; x < share; ++x) at += counts[x][c];
   if (tid == 1023) begin[128] = at + n;
-  const float inv = 1.0f / scale[(size_t)b * D + min(bi * 128 + c, D - 1)];
-  ColumnRest* dst = by_col + ((size_t)b * nb2 + bi) * n_lists * rest_cap;
-  walk([&](const DigitRest& e) { dst[at++] = ColumnRest{e.token, __uint_as_float((uint32_t)e.rest << 16) * inv}; });
+  uint32_t* dst = by_col + ((size_t)b * nb2 + bi) * n_lists * rest_cap;
+  walk([&](int l, int i) { dst[at++] = (uint32_t)(list_of(l) * rest_cap + i); });
 }
 
 // G[b][i][j] = sum over the splits of the block that holds (i, j), plus what the digits miss, written to (j, i) as well.  One
@@ -521,10 +538,14 @@ __global__ __launch_bounds__(1024) void rest_by_column_kernel(const DigitRest* _
 template <int EB>
 __global__ __launch_bounds__(256) void gram_finish_kernel(const double* __restrict__ part, double* __restrict__ G,
                                                           const void* __restrict__ K, const float* __restrict__ scale,
-                                                          const ColumnRest* __restrict__ by_col, const int32_t* __restrict__ col_begin,
+                                                          const DigitRest* __restrict__ rest, const uint32_t* __restrict__ by_col,
+                                                          const int32_t* __restrict__ col_begin,
                                                           const int32_t* __restrict__ flags, int s, int D, int nt, int nb, int nb2,
                                                           int n_splits, int batch, int rest_cap) {
+  constexpr int kStrip = 512;   // entries in LDS at a time
   __shared__ double tile[32][33];
+  __shared__ uint32_t strip_token[kStrip];
+  __shared__ float strip_rest[kStrip];
   int p = blockIdx.x, ti = 0;   // tile index -> (ti, tj), ti <= tj, row by row of the upper triangle
   while (p >= nt - ti) { p -= nt - ti; ++ti; }
   const int tj = ti + p, b = blockIdx.y;
@@ -539,21 +560,39 @@ __global__ __launch_bounds__(256) void gram_finish_kernel(const double* __restri
     for (int u = 0; u < 4; ++u) sum[u] += src[(size_t)sp * batch * pairs * 4096 + 8 * u * 64];
   if (!flags[b]) {
     // h[u] = H(row, col) = sum over the listed elements (t, row) of r_t,row (K - R / 2)(t, col): rows y0 + 8 u of strip sr,
-    // column x of strip sc
+    // column x of strip sc.  The strip's entries go through LDS, so that only the keys are waited for: 300 us at
+    // 16 x 128K x 1024, 519 with each thread following its column's places in the lists by itself.
     auto missed = [&](int sr, int sc, double (&h)[4]) {
       const float sx = scale[(size_t)b * D + sc * 32 + x];
       const double inv = 0.5 / (double)sx;
-      const ColumnRest* list = by_col + ((size_t)b * nb2 + (sr >> 2)) * 4 * n_splits * rest_cap;
+      const uint32_t* list = by_col + ((size_t)b * nb2 + (sr >> 2)) * 4 * n_splits * rest_cap;
+      const size_t first = (size_t)b * n_splits * nb2 * 4 * rest_cap;   // entry of the sequence's lists
       const int32_t* begin = col_begin + ((size_t)b * nb2 + (sr >> 2)) * 129 + (sr & 3) * 32;
+      const int last = begin[32];
+      int e[4], e1[4];
+      float inv_row[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int e0 = begin[y0 + 8 * u], e1 = begin[y0 + 8 * u + 1];
+        e[u] = begin[y0 + 8 * u]; e1[u] = begin[y0 + 8 * u + 1];
+        inv_row[u] = 1.0f / scale[(size_t)b * D + sr * 32 + y0 + 8 * u];
         h[u] = 0.0;
+      }
+      for (int c0 = begin[0]; c0 < last; c0 += kStrip) {
+        const int c1 = min(c0 + kStrip, last);
+        __syncthreads();
+        for (int i = c0 + (int)threadIdx.x; i < c1; i += 256) {
+          const DigitRest r = rest[first + list[i]];
+          strip_token[i - c0] = r.token;
+          strip_rest[i - c0] = bf16_to_f32(r.rest);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
 #pragma unroll 4
-        for (int e = e0; e < e1; ++e) {
-          const ColumnRest c = list[e];
-          const float k = kv_elem<EB>(K, ((size_t)b * s + c.token) * D + sc * 32 + x);
-          h[u] = fma((double)c.rest, (double)k - inv * (double)digit_rest(k, sx), h[u]);
+          for (; e[u] < min(e1[u], c1); ++e[u]) {
+            const float k = kv_elem<EB>(K, ((size_t)b * s + strip_token[e[u] - c0]) * D + sc * 32 + x);
+            h[u] = fma((double)(strip_rest[e[u] - c0] * inv_row[u]), (double)k - inv * (double)digit_rest(k, sx), h[u]);
+          }
         }
       }
     };

@@ -247,7 +247,10 @@ __global__ __launch_bounds__(512, 2) void project_digits_kernel(const void* __re
       n_unsure += __popcll(__ballot(low));
     }
   };
-  look([&](int) { return 4194304.0f * (float)D; });
+  double least = fabs(v[0]);
+#pragma unroll
+  for (int i = 1; i < 16; ++i) least = fmin(least, fabs(v[i]));
+  if (__any(least < unit * (double)(4194304.0f * (float)D))) look([&](int) { return 4194304.0f * (float)D; });
   if (n_unsure > kAgain) {
     const uint8_t* first_row = static_cast<const uint8_t*>(K) + (size_t)b * s * D * EB;
     uint32_t present = 0;   // tokens that are not all zeros

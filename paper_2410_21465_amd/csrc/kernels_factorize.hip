@@ -15,6 +15,7 @@
 // Operand layout of v_mfma_f64_16x16x4f64 as measured on gfx950: A lane l holds (m = l % 16, k = l / 16),
 // B lane l holds (n = l % 16, k = l / 16), result register j of lane l is (m = 4 j + l / 16, n = l % 16).
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <type_traits>
 
@@ -331,13 +332,13 @@ static hipError_t gemm64(Mat A, Mat B, double* C, int ldc, size_t strideC, int M
 // 1. G = K^T K: the digits' products, or the fp64 kernel for sequences whose flag is raised, and the sum over the splits
 template <int EB>
 static hipError_t launch_gram(const void* K, double* part, double* G, float* scale, int32_t* flags, uint16_t* chunk_max,
-                              DigitRest* rest, int32_t* rest_count, int32_t* marks, ColumnRest* by_col, int32_t* col_begin,
+                              DigitRest* rest, int32_t* rest_count, int32_t* marks, uint32_t* by_col, int32_t* col_begin,
                               const FactorizePlan& pl, int batch, int s, int D, hipStream_t st) {
   const int pieces = D * EB / 16;
   hipLaunchKernelGGL(column_max_kernel<EB>, dim3(pl.n_chunks, batch, (pieces + pl.max_lv - 1) / pl.max_lv), dim3(256), 0, st, K,
                      chunk_max, flags, s, D, pl.max_lv, pl.max_chunk, pl.n_chunks);
-  hipLaunchKernelGGL(column_scale_kernel<EB>, dim3(pl.nb, batch), dim3(256), 0, st, K, chunk_max, scale, flags, s, D,
-                     pl.n_chunks);
+  hipLaunchKernelGGL(column_scale_kernel<EB>, dim3(pl.nb, batch), dim3(1024), 0, st, K, chunk_max, scale, flags, s, D,
+                     pl.n_chunks, pl.tokens_per_split, pl.rest_share);
   constexpr int kLds = 2 * 2 * 3 * 128 * 64;   // two stages of two column blocks of three digits
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gram_digits_kernel<EB>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
@@ -347,10 +348,10 @@ static hipError_t launch_gram(const void* K, double* part, double* G, float* sca
                      batch, pl.rest_cap, pl.n_marks);
   hipLaunchKernelGGL(gram_kernel<EB>, dim3(pl.nb * (pl.nb + 1) / 2, pl.n_splits, batch), dim3(64), 0, st, K, part, flags, s, D,
                      pl.nb, pl.tokens_per_split, batch);
-  hipLaunchKernelGGL(rest_by_column_kernel, dim3(pl.nb2, batch), dim3(1024), 0, st, rest, rest_count, scale, flags, by_col, col_begin,
-                     D, pl.nb2, pl.n_splits, pl.rest_cap);
+  hipLaunchKernelGGL(rest_by_column_kernel, dim3(pl.nb2, batch), dim3(1024), 0, st, rest, rest_count, flags, by_col, col_begin, pl.nb2,
+                     pl.n_splits, pl.rest_cap);
   const int nt = D / 32;   // (the key width is a multiple of 32)
-  hipLaunchKernelGGL(gram_finish_kernel<EB>, dim3(nt * (nt + 1) / 2, batch), dim3(256), 0, st, part, G, K, scale, by_col, col_begin,
+  hipLaunchKernelGGL(gram_finish_kernel<EB>, dim3(nt * (nt + 1) / 2, batch), dim3(256), 0, st, part, G, K, scale, rest, by_col, col_begin,
                      flags, s, D, nt, pl.nb, pl.nb2, pl.n_splits, batch, pl.rest_cap);
   return hipGetLastError();
 }
@@ -431,10 +432,10 @@ FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int
   const size_t room = doubles(p.n_splits * DD) + doubles(DD) + 2 * doubles(m * D) + 2 * doubles(even * even) + doubles(r * m) +
                       doubles((size_t)r * D);
   // Behind these lies what the digits need: the columns' scales, the sequences' flags and the lists of what the
-  // digits miss, in token order and by column, with room for one element in 1024 (64 at least, or what the room leaves).
+  // digits miss, in token order and by column, with room for one element in 768 (85 at least, or what the room leaves).
   p.nb2 = (D + 127) / 128;
   const long tiles = (long)p.nb2 * (p.nb2 + 1) / 2;
-  auto rest_room = [&] { return std::max(64, p.tokens_per_split / 32); };   // a list: 128 columns, 16 of 64 tokens
+  auto rest_room = [&] { return std::max(64, p.tokens_per_split / 32) * 4 / 3; };   // of 32 elements a token: 128 columns, 16 of 64 tokens
   auto place = [&](long splits) {
     split_tokens(splits);
     size_t at = std::max(off + up(p.n_splits * split_bytes), end);
@@ -446,9 +447,10 @@ FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int
     p.n_marks = (p.tokens_per_split + 255) / 256 + 1;
     p.marks = at; at += up(lists * p.n_marks * 4);
     const size_t left = room > at + 512 ? room - at - 512 : 0;
-    p.rest_cap = (int)std::min<size_t>(rest_room(), left / (lists * (sizeof(DigitRest) + sizeof(ColumnRest))));
-    p.rest = at; at += up(lists * p.rest_cap * sizeof(DigitRest));
-    p.by_col = at; at += up(lists * p.rest_cap * sizeof(ColumnRest));
+    // (12 bytes an entry, four of them its place in the order by column)
+    p.rest_cap = (int)std::min<size_t>(std::max(64, p.tokens_per_split / 32), left / (lists * 16)) * 4 / 3;
+    p.rest = at; p.by_col = p.rest + lists * p.rest_cap * sizeof(DigitRest);
+    at += up(lists * p.rest_cap * 12);
     return at;
   };
   long splits = 1;
@@ -475,6 +477,7 @@ FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int
     }
   }
   p.total = place(splits);
+  p.rest_share = std::min(1.0f / 512.0f, std::max(0.0f, (float)p.rest_cap - 3.0f * std::sqrt((float)p.rest_cap)) / (32.0f * (float)p.tokens_per_split));
   // the columns' largest elements by chunk of tokens lie where G will
   const int ne = 16 / kv_bytes, pieces = D / ne;
   p.max_lv = 1;
@@ -513,7 +516,7 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
     DigitRest* rest = reinterpret_cast<DigitRest*>(ws + pl.rest);
     int32_t* rest_count = reinterpret_cast<int32_t*>(ws + pl.rest_count);
     int32_t* marks = reinterpret_cast<int32_t*>(ws + pl.marks);
-    ColumnRest* by_col = reinterpret_cast<ColumnRest*>(ws + pl.by_col);
+    uint32_t* by_col = reinterpret_cast<uint32_t*>(ws + pl.by_col);
     int32_t* col_begin = reinterpret_cast<int32_t*>(ws + pl.col_begin);
     e = kv_bytes == 1 ? launch_gram<1>(k_pre, part, G, scale, flags, chunk_max, rest, rest_count, marks, by_col, col_begin, pl, batch, s, D, st)
                       : launch_gram<2>(k_pre, part, G, scale, flags, chunk_max, rest, rest_count, marks, by_col, col_begin, pl, batch, s, D, st);

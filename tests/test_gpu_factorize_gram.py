@@ -21,6 +21,8 @@ def _keys(kind, b, s, D, kd, gen):
     k = torch.randn(n, s, D, generator=gen, device="cuda")
     if kind == "outliers":        # a row in 500 above the rest: the lists hold several times what normal keys leave out
         k[:, ::500] *= 128.0 if kd else 6.0
+    elif kind == "crowded":       # ... more above: one element in 1024 is left out, three quarters of what the lists hold
+        k[:, ::500] *= 15.0
     elif kind == "spikes":        # ... far above: the others' last places lie below the digits, more than the lists hold
         k[:, ::500] *= 3000.0
     elif kind == "graded":        # magnitudes over 20 binades in every column: more is left out than the lists hold
@@ -70,7 +72,7 @@ CASES = [(1, 1, 64, 1, "normal", 0, 2), (1, 1, 64, 63, "normal", 0, 2), (2, 1, 6
          (1, 1, 64, 70001, "outliers", 0, 0),
          (256, 1, 64, 33000, "normal", 0, 0),
          # one token part of more than the 32768 tokens summed in 32 bits, off the diagonal too
-         (1024, 3, 64, 33000, "outliers", 0, 0), (2048, 1, 64, 33000, "outliers", 1, 0)]
+         (1024, 3, 64, 33000, "crowded", 0, 0), (2048, 1, 64, 33000, "outliers", 1, 0)]
 
 
 def _left_out(K):
@@ -92,12 +94,13 @@ def test_gram_matrix_from_the_factors(b, h, d, s, kind, kd, route):
     torch.cuda.synchronize()
     assert torch.equal(got["psi"], again["psi"]) and torch.equal(got["sigma"], again["sigma"])   # the same order of sums on every run
     routes, plan = S.factorize_routes(p, got["workspace"]).tolist(), S.factorize_plan(p)
-    assert routes == ([route] * b if isinstance(route, int) else list(route)), routes
+    others = [(i, x) for i, x in enumerate(routes) if x != (route if isinstance(route, int) else route[i])]
+    assert not others[:8]
     assert plan["parts"] * plan["tokens_per_part"] >= s and (plan["tokens_per_part"] > 32768) == (b >= 1024), plan
     psi, sig = got["psi"].cpu().numpy(), got["sigma"].cpu().numpy()
     for i in sorted({0, 1 % b, b - 1}):
         K = PU.kv_to_f64(PU.to_bits(k[i].contiguous(), kd))
-        if kind in ("outliers", "faint"):
+        if kind in ("outliers", "crowded", "faint"):
             assert _left_out(K) > 0
         G = K.T @ K
         back = (psi[i].T * sig[i] ** 2) @ psi[i]
