@@ -182,6 +182,7 @@ struct FactorizePlan {
   int n_splits, tokens_per_split;
   int nb2;                  // 128-column blocks of the digit products
   int rest_cap;             // entries per list of what the digits miss
+  int waves64;              // waves per block and token part of the fp64 sums
   float rest_share;         // share of the elements that the lists surely have room for
   int n_marks;              // places in a list that are kept: before every 256th token, and its end
   int max_lv, max_chunk, n_chunks;   // column maxima: 16-byte pieces side by side in a workgroup, tokens per chunk, chunks

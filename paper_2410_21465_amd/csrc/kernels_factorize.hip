@@ -49,19 +49,22 @@ struct Raw4 {
 };
 
 // ---- 1. Gram matrix ---------------------------------------------------------------------------------
-// One wave per (pair of 64-column blocks bi <= bj, token split, sequence).  Tile (mt, nt) of the 64 x 64
+// WK waves per (pair of 64-column blocks bi <= bj, token split, sequence), which take 16 tokens in turn and add their sums up
+// through LDS: the splits suit the digits' products, a sequence of these needs more waves.  Tile (mt, nt) of the 64 x 64
 // block holds columns i0 + 4 m + mt against j0 + 4 n + nt, so that a lane's four consecutive columns feed
 // four tiles and every load is 8 (or 4) contiguous bytes.  part [split][b][pair][64][64] fp64: the blocks bi <= bj packed,
 // a little over half of D x D.
 // Only for sequences whose flag is raised (gram_digits_kernel forms the others' sums).
 // Bound by the matrix pipe: 67 TFLOP/s at 16 x 128K x 1024 (a large library product reaches 73; 61 with loads under lane
 // masks, whose results the matrix instructions then waited for).
-template <int EB>
-__global__ __launch_bounds__(64, 2) void gram_kernel(const void* __restrict__ K, double* __restrict__ part,
+template <int EB, int WK>
+__global__ __launch_bounds__(64 * WK, 2) void gram_kernel(const void* __restrict__ K, double* __restrict__ part,
                                                      const int32_t* __restrict__ flags, int s, int D, int nb,
                                                      int tokens_per_split, int batch) {
+  __shared__ double red[WK > 1 ? WK / 2 : 1][WK > 1 ? 64 : 1][64];   // [wave][register][lane]
   if (!flags[blockIdx.z]) return;
-  const int lane = threadIdx.x, mrow = lane & 15, kq = lane >> 4;
+  const int wk = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int lane = threadIdx.x & (kWave - 1), mrow = lane & 15, kq = lane >> 4;
   // pair index -> (bi, bj), bi <= bj, row by row of the upper triangle (upper_block the other way round)
   int p = blockIdx.x, bi = 0;
   while (p >= nb - bi) { p -= nb - bi; ++bi; }
@@ -90,12 +93,12 @@ __global__ __launch_bounds__(64, 2) void gram_kernel(const void* __restrict__ K,
       bn[u].load(row + cj * EB);
     }
   };
-  request(t_begin);
-  for (int t0 = t_begin; t0 < t_end; t0 += 4 * PF) {
+  request(t_begin + 4 * PF * wk);
+  for (int t0 = t_begin + 4 * PF * wk; t0 < t_end; t0 += 4 * PF * WK) {
     Raw4<EB> ac[PF], bc[PF];
 #pragma unroll
     for (int u = 0; u < PF; ++u) { ac[u] = an[u]; bc[u] = bn[u]; }
-    request(t0 + 4 * PF);
+    request(t0 + 4 * PF * WK);
     if (t0 + 4 * PF > t_end) {   // fewer than 16 tokens left: the ones past the end count as zero
 #pragma unroll
       for (int u = 0; u < PF; ++u)
@@ -115,6 +118,19 @@ __global__ __launch_bounds__(64, 2) void gram_kernel(const void* __restrict__ K,
           acc[mt][nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[mt], bb[nt], acc[mt][nt], 0, 0, 0);
     }
   }
+  // the upper half of the waves hands its sums to the lower half, until one is left
+#pragma unroll
+  for (int w = WK / 2; w >= 1; w /= 2) {
+    if (wk >= w && wk < 2 * w)
+#pragma unroll
+      for (int x = 0; x < 64; ++x) red[wk - w][x][lane] = acc[x >> 4][x >> 2 & 3][x & 3];
+    __syncthreads();
+    if (wk < w)
+#pragma unroll
+      for (int x = 0; x < 64; ++x) acc[x >> 4][x >> 2 & 3][x & 3] += red[wk][x][lane];
+    if (w > 1) __syncthreads();
+  }
+  if (wk > 0) return;
   double* out = part + (((size_t)split * batch + b) * gridDim.x + blockIdx.x) * 4096;
 #pragma unroll
   for (int mt = 0; mt < 4; ++mt)
@@ -346,8 +362,11 @@ static hipError_t launch_gram(const void* K, double* part, double* G, float* sca
   hipLaunchKernelGGL(gram_digits_kernel<EB>, dim3((unsigned)((long)batch * pl.n_splits * (pl.nb2 * (pl.nb2 + 1) / 2))), dim3(512),
                      kLds, st, K, scale, part, rest, rest_count, marks, flags, s, D, pl.nb, pl.nb2, pl.tokens_per_split, pl.n_splits,
                      batch, pl.rest_cap, pl.n_marks);
-  hipLaunchKernelGGL(gram_kernel<EB>, dim3(pl.nb * (pl.nb + 1) / 2, pl.n_splits, batch), dim3(64), 0, st, K, part, flags, s, D,
-                     pl.nb, pl.tokens_per_split, batch);
+#define SKV_GRAM64(WK_)                                                                                                  \
+  hipLaunchKernelGGL((gram_kernel<EB, WK_>), dim3(pl.nb * (pl.nb + 1) / 2, pl.n_splits, batch), dim3(64 * WK_), 0, st, K, part, \
+                     flags, s, D, pl.nb, pl.tokens_per_split, batch)
+  if (pl.waves64 == 8) SKV_GRAM64(8); else if (pl.waves64 == 4) SKV_GRAM64(4); else if (pl.waves64 == 2) SKV_GRAM64(2); else SKV_GRAM64(1);
+#undef SKV_GRAM64
   hipLaunchKernelGGL(rest_by_column_kernel, dim3(pl.nb2, batch), dim3(1024), 0, st, rest, rest_count, flags, by_col, col_begin, pl.nb2,
                      pl.n_splits, pl.rest_cap);
   const int nt = D / 32;   // (the key width is a multiple of 32)
@@ -453,6 +472,11 @@ FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int
     at += up(lists * p.rest_cap * 12);
     return at;
   };
+  // rounds of fp64 workgroups of so many waves: two waves a SIMD, or one, which takes 0.6 of the time
+  auto rounds64 = [](long workgroups, int waves) {
+    const long resident = 2048 / waves, rest = workgroups % resident;
+    return (double)(workgroups / resident) + (rest == 0 ? 0.0 : rest <= resident / 2 && waves < 8 ? 0.6 : 1.0);
+  };
   long splits = 1;
   if (target > 0) {
     splits = std::max(1l, std::min(aim_splits, (long)((room - off) / split_bytes)));
@@ -468,15 +492,21 @@ FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int
     double best = 0.0;
     for (long sp = 1; sp <= std::min((s + 511l) / 512, 512l); ++sp) {
       if (sp > 1 && (place(sp) > room || p.rest_cap < rest_room())) break;
-      const long groups = sp * batch, waves = blocks * sp, rest = waves % 2048;
+      const long groups = sp * batch;
       const long rounds = groups % 8 == 0 ? (groups / 8 * tiles + 31) / 32 : (groups * tiles + 255) / 256;
-      const double rounds64 = (double)(waves / 2048) + (rest == 0 ? 0.0 : rest <= 1024 ? 0.6 : 1.0);
       const double tokens = (double)((s + sp - 1) / sp);
-      const double cost = ((double)rounds * 0.02 + 0.1 * rounds64 * (245.0 / 1024.0)) * tokens + (double)sp * batch * D * D * (1.06 * 8.0 / 4.6e6);
+      const double cost = ((double)rounds * 0.02 + 0.1 * rounds64(blocks * sp, 1) * (245.0 / 1024.0)) * tokens + (double)sp * batch * D * D * (1.06 * 8.0 / 4.6e6);
       if (sp == 1 || cost < best * 0.995) { best = cost; splits = sp; }
     }
   }
   p.total = place(splits);
+  // Waves that share an fp64 block of a part, for the least rounds times tokens of a wave.  With one wave each, as many splits as
+  // suit the digits left half of the chip idle: 1 x 32K x 1024 624 us with the 15 splits that the fp64 sums would choose, 1,214
+  // with 7 splits and one wave, 648 with two; 2 x 32K x 512 344, 717 and 379; 3 x 8K x 1024 460, 566 and 549.
+  p.waves64 = 1;
+  auto time64 = [&](int w) { return rounds64(blocks * p.n_splits, w) * ((p.tokens_per_split + 16 * w - 1) / (16 * w)); };
+  for (int w = 2; w <= 8; w *= 2)
+    if (time64(w) < 0.95 * time64(p.waves64)) p.waves64 = w;
   p.rest_share = std::min(1.0f / 512.0f, std::max(0.0f, (float)p.rest_cap - 3.0f * std::sqrt((float)p.rest_cap)) / (32.0f * (float)p.tokens_per_split));
   // the columns' largest elements by chunk of tokens lie where G will
   const int ne = 16 / kv_bytes, pieces = D / ne;

@@ -700,7 +700,7 @@ int shadowkv_factorize_plan(const shadowkv_params* params, int64_t* plan) {
     return fail_inval("rank must be a multiple of 8 in [8, 256] and at most h_kv * d");
   if (!plan) return fail_inval("plan is NULL");
   const FactorizePlan pl = plan_factorize(sh.b, sh.s, sh.hkv * sh.d, params->rank, kFactorOversample, kFactorSweeps, sh.eb);
-  plan[0] = pl.n_splits; plan[1] = pl.tokens_per_split; plan[2] = pl.rest_cap; plan[3] = (int64_t)pl.flags;
+  plan[0] = pl.n_splits; plan[1] = pl.tokens_per_split; plan[2] = pl.rest_cap; plan[3] = (int64_t)pl.flags; plan[4] = pl.waves64;
   return SHADOWKV_OK;
 }
 

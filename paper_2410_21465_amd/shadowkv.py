@@ -319,9 +319,10 @@ def decode_step_static(p: Params, q, A, B, landmarks, landmark_chunk_ids, k_outl
 def factorize_plan(p: "Params") -> dict:
     """shadowkv_factorize_plan: how the keys of this shape are factored on the GPU."""
     st = p.c_struct()
-    plan = (C.c_int64 * 4)()
+    plan = (C.c_int64 * 5)()
     _check(lib().shadowkv_factorize_plan(C.addressof(st), plan))
-    return {"parts": plan[0], "tokens_per_part": plan[1], "entries_per_list": plan[2], "routes_offset": plan[3]}
+    return {"parts": plan[0], "tokens_per_part": plan[1], "entries_per_list": plan[2], "routes_offset": plan[3],
+            "fp64_waves": plan[4]}
 
 
 def factorize_routes(p: "Params", workspace: torch.Tensor) -> torch.Tensor:

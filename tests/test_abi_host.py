@@ -174,7 +174,19 @@ def test_factorize_plan_lies_in_the_workspace():
         assert plan["routes_offset"] + 4 * b <= S.lib().shadowkv_factorize_workspace_bytes(C.addressof(st))
         assert S.lib().shadowkv_factorize_plan(C.addressof(st), None) == S.EINVAL
     bad = S.Params(**{**GOOD, "rank": 264}).c_struct()
-    assert S.lib().shadowkv_factorize_plan(C.addressof(bad), (C.c_int64 * 4)()) == S.EINVAL
+    assert S.lib().shadowkv_factorize_plan(C.addressof(bad), (C.c_int64 * 5)()) == S.EINVAL
+
+
+@pytest.mark.parametrize("b,s,hkv,d", [(1, 32768, 8, 128), (2, 32768, 4, 128), (3, 8192, 8, 128), (1, 4096, 8, 128), (4, 20000, 4, 64),
+                                       (16, 131072, 8, 128), (1, 8192, 1, 64)])
+def test_fp64_sums_have_a_wave_for_every_simd(b, s, hkv, d):
+    """The token parts suit the digits' products; sequences that are summed in fp64 share a part's blocks between waves, so that
+    more than one of the 1024 SIMDs in two has one, or a wave no more than 256 tokens."""
+    plan = S.factorize_plan(S.Params(batch=b, n_q_heads=hkv, n_kv_heads=hkv, head_dim=d, ctx_len=s, chunk_size=1, rank=64,
+                                     n_outlier_chunks=0, topk_chunks=1, local_len=0))
+    nb = (hkv * d + 63) // 64
+    waves = b * plan["parts"] * (nb * (nb + 1) // 2) * plan["fp64_waves"]
+    assert waves > 1024 or plan["tokens_per_part"] <= 256 * plan["fp64_waves"], (waves, plan)
 
 
 def test_append_chunk_rejects_a_full_context_and_bad_capacity():
