@@ -542,10 +542,11 @@ __global__ __launch_bounds__(256) void gram_finish_kernel(const double* __restri
                                                           const int32_t* __restrict__ col_begin,
                                                           const int32_t* __restrict__ flags, int s, int D, int nt, int nb, int nb2,
                                                           int n_splits, int batch, int rest_cap) {
-  constexpr int kStrip = 512;   // entries in LDS at a time
+  constexpr int kDeep = 16;
   __shared__ double tile[32][33];
-  __shared__ uint32_t strip_token[kStrip];
-  __shared__ float strip_rest[kStrip];
+  __shared__ int32_t strip_begin[33];
+  __shared__ uint32_t strip_token[32 * kDeep];
+  __shared__ float strip_rest[32 * kDeep];
   int p = blockIdx.x, ti = 0;   // tile index -> (ti, tj), ti <= tj, row by row of the upper triangle
   while (p >= nt - ti) { p -= nt - ti; ++ti; }
   const int tj = ti + p, b = blockIdx.y;
@@ -560,38 +561,45 @@ __global__ __launch_bounds__(256) void gram_finish_kernel(const double* __restri
     for (int u = 0; u < 4; ++u) sum[u] += src[(size_t)sp * batch * pairs * 4096 + 8 * u * 64];
   if (!flags[b]) {
     // h[u] = H(row, col) = sum over the listed elements (t, row) of r_t,row (K - R / 2)(t, col): rows y0 + 8 u of strip sr,
-    // column x of strip sc.  The strip's entries go through LDS, so that only the keys are waited for: 300 us at
-    // 16 x 128K x 1024, 519 with each thread following its column's places in the lists by itself.
+    // column x of strip sc.  The strip's entries go through LDS, kDeep of each row at a time, so that only the keys are waited
+    // for: 311 us at 16 x 128K x 1024, 519 with each thread following its column's places in the lists by itself; 437 at
+    // 3 x 1M x 1024, 710 with the strip's entries in order, where a column's many leave the other rows idle.
     auto missed = [&](int sr, int sc, double (&h)[4]) {
       const float sx = scale[(size_t)b * D + sc * 32 + x];
       const double inv = 0.5 / (double)sx;
       const uint32_t* list = by_col + ((size_t)b * nb2 + (sr >> 2)) * 4 * n_splits * rest_cap;
       const size_t first = (size_t)b * n_splits * nb2 * 4 * rest_cap;   // entry of the sequence's lists
       const int32_t* begin = col_begin + ((size_t)b * nb2 + (sr >> 2)) * 129 + (sr & 3) * 32;
-      const int last = begin[32];
-      int e[4], e1[4];
+      __syncthreads();
+      if (threadIdx.x < 33) strip_begin[threadIdx.x] = begin[threadIdx.x];
+      __syncthreads();
+      int most = strip_begin[(threadIdx.x & 31) + 1] - strip_begin[threadIdx.x & 31];
+#pragma unroll
+      for (int m = 16; m >= 1; m >>= 1) most = max(most, __shfl_xor(most, m, kWave));
       float inv_row[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        e[u] = begin[y0 + 8 * u]; e1[u] = begin[y0 + 8 * u + 1];
         inv_row[u] = 1.0f / scale[(size_t)b * D + sr * 32 + y0 + 8 * u];
         h[u] = 0.0;
       }
-      for (int c0 = begin[0]; c0 < last; c0 += kStrip) {
-        const int c1 = min(c0 + kStrip, last);
-        __syncthreads();
-        for (int i = c0 + (int)threadIdx.x; i < c1; i += 256) {
-          const DigitRest r = rest[first + list[i]];
-          strip_token[i - c0] = r.token;
-          strip_rest[i - c0] = bf16_to_f32(r.rest);
+      for (int k0 = 0; k0 < most; k0 += kDeep) {
+        if (k0) __syncthreads();
+        for (int i = threadIdx.x; i < 32 * kDeep; i += 256) {
+          const int at = strip_begin[i / kDeep] + k0 + i % kDeep;
+          if (at < strip_begin[i / kDeep + 1]) {
+            const DigitRest r = rest[first + list[at]];
+            strip_token[i] = r.token;
+            strip_rest[i] = bf16_to_f32(r.rest);
+          }
         }
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
+          const int row = y0 + 8 * u, n = min(kDeep, strip_begin[row + 1] - strip_begin[row] - k0);
 #pragma unroll 4
-          for (; e[u] < min(e1[u], c1); ++e[u]) {
-            const float k = kv_elem<EB>(K, ((size_t)b * s + strip_token[e[u] - c0]) * D + sc * 32 + x);
-            h[u] = fma((double)(strip_rest[e[u] - c0] * inv_row[u]), (double)k - inv * (double)digit_rest(k, sx), h[u]);
+          for (int i = 0; i < n; ++i) {
+            const float k = kv_elem<EB>(K, ((size_t)b * s + strip_token[row * kDeep + i]) * D + sc * 32 + x);
+            h[u] = fma((double)(strip_rest[row * kDeep + i] * inv_row[u]), (double)k - inv * (double)digit_rest(k, sx), h[u]);
           }
         }
       }

@@ -91,9 +91,8 @@ __global__ __launch_bounds__(512, 2) void project_digits_kernel(const void* __re
   if (block >= batch * n_splits * per_split) return;
   const int group = block / per_split, in_split = block % per_split, b = group / n_splits, split = group % n_splits;
   // (another workgroup may raise kFlagVectors at any time, kFlagKeys is settled)
-  const int flag = __hip_atomic_load(&flags[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (flag == kFlagKeys) return;
-  if (threadIdx.x == 0) raised = flag;
+  if (flags[b] == kFlagKeys) return;
+  const int flag = threadIdx.x == 0 ? __hip_atomic_load(&flags[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
   const int t_begin = split * tokens_per_split + in_split * 256;
   const int t_end = min(min(s, (split + 1) * tokens_per_split), t_begin + 256);
   if (t_begin >= t_end) return;
@@ -141,6 +140,7 @@ __global__ __launch_bounds__(512, 2) void project_digits_kernel(const void* __re
   find(0);
 #pragma unroll 1
   for (int st = 0; st < kPsiDeep; ++st) { request_b(st); put_b(st); }
+  if (threadIdx.x == 0) raised = flag;
   __syncthreads();
   if (raised) return;
   auto stage = [&](const Raw& raw, Raw& next, int st) {
