@@ -257,12 +257,14 @@ int shadowkv_append_chunk(const shadowkv_params *params, const shadowkv_kv *k_pr
  * singular values: B = Psi^T (reshaped [h_kv, r, d]: B[h, rho, x] = Psi[h*d + x, rho]) and A = K Psi = Phi Sigma
  * (the low-rank states of section "High-throughput Decoding": keys are kept as K Psi and projected back with Psi^T).
  * Singular vectors are defined up to sign; the convention here makes the component of largest magnitude of every
- * right singular vector positive (ties: lowest index).  Computed from the Gram matrix K^T K (fp64) by subspace
- * iteration with `n_iter` steps (0 => 16) on r + 32 vectors and a Rayleigh-Ritz step; accurate when sigma_r and
- * sigma_(r+33) are apart (the convergence factor per step is (sigma_(r+33) / sigma_r)^2).
+ * right singular vector positive (ties: lowest index).  Computed from the Gram matrix K^T K (stored as fp64; its
+ * products are exact, its sums exact or fp64) by subspace iteration with `n_iter` steps (0 => 16) on r + 32 vectors
+ * and a Rayleigh-Ritz step; accurate when sigma_r and sigma_(r+33) are apart (the convergence factor per step is
+ * (sigma_(r+33) / sigma_r)^2).
  *
  *   k_pre      dev      [b, s, h_kv*d] kv   pre-RoPE keys, heads side by side
- *   A          dev out  [b, cap, r] kv      rows 0 .. s-1 written (fp64 accumulate, rounded once)
+ *   A          dev out  [b, cap, r] kv      rows 0 .. s-1 written: sums good to 2^-24 of each entry, or fp64 sums where an
+ *                                           entry is too small beside its row for that; rounded once to storage
  *   B          dev out  [b, h_kv, r, d] kv
  *   psi_out    dev out  [b, r, h_kv*d] fp64 optional (NULL): the right singular vectors before rounding, as rows
  *   sigma_out  dev out  [b, r] fp64         optional (NULL): singular values, largest first

@@ -1,4 +1,4 @@
-// Gram matrix G = K^T K of the stored keys on the 8-bit integer matrix instruction, exact: the keys of a column are taken
+// Gram matrix G = K^T K of the stored keys on the 8-bit integer matrix instruction, exact but for the last additions: the keys of a column are taken
 // as multiples of one power of two, cut into three signed 8-bit digits, and the digits' products are summed in 32-bit
 // integers, which lose nothing.  (v_mfma_i32_32x32x32_i8: A lane l holds row l % 32, contraction elements 16 (l / 32) .. + 15,
 // B the same of its columns, result register j of lane l is (row = 8 (j / 4) + 4 (l / 32) + j % 4, column = l % 32); measured

@@ -1,15 +1,17 @@
 // A = K Psi on the 8-bit integer matrix instruction: the keys as in factorize_gram.hpp (three digits, columns scaled by powers
 // of two, lists of what the digits leave out), each right singular vector as seven 8-bit digits of Psi / (its column's power
-// of two), 54 bits below the vector's largest such number.  Every sum of products is exact; what is lost is the rounding of
-// Psi to those digits.  Measured against the result's root mean square that is less than fp64 sums lose (against
-// 64-bit-mantissa sums 1.3e-16 to 6e-16 for key widths 128 to 3072, columns of like and of graded scale, where sums in fp64
-// are off by 4e-16 to 1.7e-15).  Entry by entry it can be more: where one column is far above the others, its component of the
-// vector takes the leading bits, the other components have few or none left, and a token that is zero in that column has
-// only those.  So every entry is held against a bound of its own: an error of half a unit per component makes at most N / 2 units,
-// N the sum of the token's digit numbers.  An entry smaller than 2^kSureBits times that is summed again from the keys and the
-// vector in fp64; a wave with more than kAgain such entries raises the sequence's flag, and project_kernel forms the whole
-// sequence's A.  16 x 128K x 1024, the call: normal keys 25.08 -> 25.24 ms; one token with a key of 2^26 times the others in a
-// column that is zero elsewhere, where the entries of its vector came out wrong, 26.6 -> 31.8.
+// of two), 54 bits below the vector's largest such number.  (Cutting the operands of a product into integers whose products
+// and sums are exact is the splitting of Ozaki, Ogita, Oishi and Rump, 2012.)  Every sum of digit products is exact; what is
+// lost is the rounding of Psi to those digits, and that of adding the sums and what the lists hold in fp64.  Measured against
+// the result's root mean square that is less than fp64 sums lose: against 64-bit-mantissa sums 1.3e-16 to 6e-16 for key widths
+// 128 to 3072, columns of like and of graded scale, where sums in fp64 are off by 4e-16 to 1.7e-15.
+// Entry by entry it can be more: where one column is far above the others, its component of the vector takes the leading
+// bits, the other components have few or none left, and a token that is zero in that column has only those.  So every entry is
+// held against a bound of its own: an error of half a unit per component makes at most N / 2 units, N the sum of the token's
+// digit numbers.  An entry smaller than 2^kSureBits times that is summed again from the keys and the vector in fp64; a wave
+// with more than kAgain such entries raises the sequence's flag, and project_kernel forms the whole sequence's A.
+// 16 x 128K x 1024, the call: normal keys 25.08 -> 25.24 ms; one token with a key of 2^26 times the others in a column that
+// is zero elsewhere, where the entries of its vector came out wrong, 26.6 -> 31.8.
 #pragma once
 #include "factorize_gram.hpp"
 
@@ -39,7 +41,7 @@ __global__ __launch_bounds__(256) void psi_digits_kernel(const double* __restric
   __syncthreads();
   m = fmax(fmax(most[0], most[1]), fmax(most[2], most[3]));
   // every digit number is below 2^54 (a vector of zeros is exact: no bound on its entries)
-  const int e = m > 0.0 ? 54 - __builtin_amdgcn_frexp_exp(m) : 4096;
+  const int e = rho < r && m > 0.0 ? 54 - __builtin_amdgcn_frexp_exp(m) : 4096;
   if (threadIdx.x == 0) exps[(size_t)b * nt * 32 + rho] = e;
   uint8_t* out = psi_digits + ((size_t)b * nt + rho / 32) * stages * kPsiStage;
   for (int c0 = 4 * threadIdx.x; c0 < 64 * stages; c0 += 1024) {
@@ -188,7 +190,8 @@ __global__ __launch_bounds__(512, 2) void project_digits_kernel(const void* __re
   __syncthreads();
   const int rho = 32 * n + sub;
   const int e = exps[(size_t)b * nt * 32 + rho];
-  // the nine sums from the most significant one down: the first four steps are exact, the others round once each
+  // the nine sums from the most significant one down: the first three steps are exact (below 2^53 for every width), the others
+  // round once each
   double v[16];
 #pragma unroll
   for (int i = 0; i < 16; ++i) {

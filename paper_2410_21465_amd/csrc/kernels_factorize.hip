@@ -3,15 +3,15 @@
 // (section "High-throughput Decoding", footnote: keys are stored as K Psi and projected back with Psi^T).
 //
 // On the GPU the right singular vectors are the leading eigenvectors of the Gram matrix G = K^T K:
-//   1. G exactly from 8-bit digits of the keys on the integer matrix instruction (factorize_gram.hpp), or, for sequences whose
-//      keys' magnitudes are too far apart for that, gram_kernel: fp64 on the fp64 matrix pipe (v_mfma_f64_16x16x4f64; the
+//   1. G from 8-bit digits of the keys on the integer matrix instruction, products exact (factorize_gram.hpp), or, for
+//      sequences whose keys' magnitudes are too far apart for that, gram_kernel: fp64 on the fp64 matrix pipe (v_mfma_f64_16x16x4f64; the
 //      products of stored elements are exact) -- the dense contraction, 2 s D^2 operations; only blocks on and above the
 //      diagonal are formed, gram_finish sums the token splits and mirrors;
 //   2. subspace iteration on m = r + oversample vectors (X <- orth(G X), by Cholesky factorisation of the vectors'
 //      products), then one Rayleigh-Ritz step: T = X^T G X, eigenvectors of the small T by one-sided Jacobi rotations in
 //      blocks, the r largest kept -- all fp64, small, one launch per dependent step (factorize_small.hpp);
-//   3. sign convention (largest-magnitude component positive), B written, and A = K Psi, from digits again
-//      (factorize_project.hpp) or in fp64 (project_kernel).
+//   3. sign convention (largest-magnitude component positive), B written, and A = K Psi, from digits again, entries that
+//      these do not hold to 24 bits in fp64 (factorize_project.hpp), or all of a sequence in fp64 (project_kernel).
 // Operand layout of v_mfma_f64_16x16x4f64 as measured on gfx950: A lane l holds (m = l % 16, k = l / 16),
 // B lane l holds (n = l % 16, k = l / 16), result register j of lane l is (m = 4 j + l / 16, n = l % 16).
 #include <algorithm>
