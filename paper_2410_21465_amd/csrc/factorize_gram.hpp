@@ -9,7 +9,7 @@
 // one's is such an integer itself; of normally distributed keys one in ten thousand is not.  What rounding leaves of those,
 // r = x - v 2^-sh, goes on a list, and gram_finish_kernel adds what the digits miss: with Y = K - R,
 //   K^T K = Y^T Y + H + H^T,  H = R^T (K - R / 2),
-// in fp64.  The list of a part of the tokens and columns has room for one element in 768; keys that need more (a few rows
+// in fp64.  The list of a part of the tokens and columns has room for three elements in 2048; keys that need more (a few rows
 // far above the rest, columns next to the least bf16 numbers) and keys that are infinite, NaN or beyond 2^22 (2^-133, the
 // least bf16 number, times their column's power of two would leave bf16) raise the sequence's flag, and gram_kernel forms
 // that sequence's sums in fp64 instead.
@@ -30,11 +30,13 @@ constexpr int kDigitStage = 64;            // tokens in LDS at a time
 // pattern, 0x408080 + v; the bytes of that are d0 + 64, d1 + 128 and d2 + 128
 constexpr float kDigitMagic = 12615808.0f;
 
-// one element that its digits do not hold: what they miss, in units of 2^-sh of its column, has at most 8 significant bits
-struct DigitRest {
-  uint32_t token;
-  uint16_t col;    // inside the block of 128 columns
-  uint16_t rest;   // bf16
+// Lists of the elements that their digits do not hold: where (token << 7 | column in the block of 128) and what the digits miss,
+// as bf16 in units of 2^-sh of the column (it has at most 8 significant bits).  Six bytes an entry, and four for its place in
+// the order by column: a workspace has room for few.
+constexpr int kRestTokens = 1 << 25;       // tokens that an entry can name; longer sequences are summed in fp64
+struct RestLists {
+  uint32_t* where;
+  uint16_t* rest;
 };
 // eight stored columns of a token as they lie in memory, and one of them as fp32
 template <int EB>
@@ -168,10 +170,10 @@ __global__ __launch_bounds__(256) void column_max_kernel(const void* __restrict_
 // scale[b][j] = 2^sh_j, 1 <= scale <= 2^126; 64 columns per workgroup, sixteen threads each.  The flag of the sequence is raised
 // by a column with an element beyond 2^22 (or not finite), and where a sample of kSample tokens (evenly spaced over the
 // sequence; all of a shorter one) says that the lists will not do: more than `share` of the workgroup's elements are not held
-// by their digits, or several times that in one token part.  `share` is what the lists have room for, less three standard
+// by their digits, or several times that in one token part.  `share` is what the lists have room for, less four standard
 // deviations of such a list's length, and the sample is large enough to tell that from three quarters of it: with 256 tokens and
 // twice the lists' room, keys with 1 % of their chunks 10 to 16 times the others' size went through the digits' products, filled
-// their lists and were summed in fp64 after all, 64.2 ms at 16 x 128K x 1024 where the fp64 sums alone take 53.9; now 40.8 to 54.0.
+// their lists and were summed in fp64 after all, 64.2 ms at 16 x 128K x 1024 where the fp64 sums alone take 53.9; now 33.0 to 54.0.
 template <int EB>
 __global__ __launch_bounds__(1024) void column_scale_kernel(const void* __restrict__ K, const uint16_t* __restrict__ chunk_max,
                                                             float* __restrict__ scale, int32_t* __restrict__ flags, int s, int D,
@@ -196,7 +198,7 @@ __global__ __launch_bounds__(1024) void column_scale_kernel(const void* __restri
     // the last place of bf16 carry into it), since 2^22 itself is out of kDigitMagic's reach
     const uint32_t f = EB == 2 ? m << 16 : __float_as_uint(e5m2_to_f32((uint8_t)m));
     const int e = (int)((f + 0x20000u) >> 23);
-    if (e > 148) flags[b] = 1;
+    if (e > 148 || s > kRestTokens) flags[b] = 1;
     // |x| <= (1 - 3 / 256) 2^(e - 126): 2^(148 - e) |x| <= 0x3f4000
     sc[x] = __uint_as_float((uint32_t)(127 + 148 - min(max(e, 22), 148)) << 23);
     if (col0 + x < D) scale[(size_t)b * D + col] = sc[x];
@@ -253,7 +255,7 @@ struct GramTile {
   const uint8_t* K;          // the sequence's keys
   const float* scale;        // [D]
   double* out;               // partial sums of this sequence and token part
-  DigitRest* rest;           // diagonal: four lists of this column block and token part
+  RestLists rest;            // diagonal: four lists of this column block and token part
   int32_t* rest_count;
   int32_t* marks;            // [4][n_marks]: entries of each list before every 256th token
   int32_t* flag;
@@ -324,8 +326,10 @@ __device__ __forceinline__ void gram_digits_tile(const GramTile& g, uint8_t* lds
               const uint64_t mask = __ballot(have);
               if (mask) {
                 const int at = n_rest + __popcll(mask & ((1ull << lane) - 1ull));
-                if (have && at < g.rest_cap)
-                  g.rest[tq * g.rest_cap + at] = DigitRest{(uint32_t)(t0 + tok + u), (uint16_t)(cl + x), (uint16_t)(__float_as_uint(r) >> 16)};
+                if (have && at < g.rest_cap) {
+                  g.rest.where[tq * g.rest_cap + at] = (uint32_t)(t0 + tok + u) << 7 | (uint32_t)(cl + x);
+                  g.rest.rest[tq * g.rest_cap + at] = (uint16_t)(__float_as_uint(r) >> 16);
+                }
                 n_rest += __popcll(mask);
               }
             }
@@ -435,7 +439,7 @@ __device__ __forceinline__ void gram_digits_tile(const GramTile& g, uint8_t* lds
 
 template <int EB>
 __global__ __launch_bounds__(512, 2) void gram_digits_kernel(const void* __restrict__ K, const float* __restrict__ scale,
-                                                             double* __restrict__ part, DigitRest* __restrict__ rest,
+                                                             double* __restrict__ part, RestLists rest,
                                                              int32_t* __restrict__ rest_count, int32_t* __restrict__ marks,
                                                              int32_t* __restrict__ flags, int s, int D, int nb, int nb2,
                                                              int tokens_per_split, int n_splits, int batch, int rest_cap,
@@ -466,7 +470,8 @@ __global__ __launch_bounds__(512, 2) void gram_digits_kernel(const void* __restr
   g.K = static_cast<const uint8_t*>(K) + (size_t)b * s * D * EB;
   g.scale = scale + (size_t)b * D;
   g.out = part + ((size_t)split * batch + b) * (nb * (nb + 1) / 2) * 4096;
-  g.rest = rest + ((size_t)group * nb2 + g.bi) * 4 * rest_cap;
+  const size_t lists = ((size_t)group * nb2 + g.bi) * 4 * rest_cap;
+  g.rest = RestLists{rest.where + lists, rest.rest + lists};
   g.rest_count = rest_count + ((size_t)group * nb2 + g.bi) * 4;
   g.marks = marks + ((size_t)group * nb2 + g.bi) * 4 * n_marks;
   g.n_marks = n_marks;
@@ -483,7 +488,7 @@ __global__ __launch_bounds__(512, 2) void gram_digits_kernel(const void* __restr
 // sequence's lists; col_begin [b][nb2][129].  32 lists at a time, 64 entries of each, go through LDS; eight threads per column,
 // each with four of the 32 lists, count their entries and then place them.  (A thread per column for all lists: 250 us at
 // 16 x 128K x 1024, 80 at 1 x 32K.)
-__global__ __launch_bounds__(1024) void rest_by_column_kernel(const DigitRest* __restrict__ rest, const int32_t* __restrict__ rest_count,
+__global__ __launch_bounds__(1024) void rest_by_column_kernel(const uint32_t* __restrict__ where, const int32_t* __restrict__ rest_count,
                                                               const int32_t* __restrict__ flags, uint32_t* __restrict__ by_col,
                                                               int32_t* __restrict__ col_begin, int nb2, int n_splits, int rest_cap) {
   constexpr int kLists = 32, kTake = 64, kShare = kLists / 8;
@@ -506,8 +511,8 @@ __global__ __launch_bounds__(1024) void rest_by_column_kernel(const DigitRest* _
         if (p0) __syncthreads();
         const int l = tid >> 5, n = min(have[l] - p0, kTake);   // 32 threads copy a list
         if (n > 0) {
-          const DigitRest* src = rest + (first_list + list_of(l0 + l)) * rest_cap + p0;
-          for (int i = tid & 31; i < n; i += 32) buf[l][i] = (uint8_t)src[i].col;
+          const uint32_t* src = where + (first_list + list_of(l0 + l)) * rest_cap + p0;
+          for (int i = tid & 31; i < n; i += 32) buf[l][i] = (uint8_t)(src[i] & 127u);
         }
         __syncthreads();
         for (int m = kShare * share; m < kShare * share + kShare; ++m)
@@ -538,7 +543,7 @@ __global__ __launch_bounds__(1024) void rest_by_column_kernel(const DigitRest* _
 template <int EB>
 __global__ __launch_bounds__(256) void gram_finish_kernel(const double* __restrict__ part, double* __restrict__ G,
                                                           const void* __restrict__ K, const float* __restrict__ scale,
-                                                          const DigitRest* __restrict__ rest, const uint32_t* __restrict__ by_col,
+                                                          RestLists rest, const uint32_t* __restrict__ by_col,
                                                           const int32_t* __restrict__ col_begin,
                                                           const int32_t* __restrict__ flags, int s, int D, int nt, int nb, int nb2,
                                                           int n_splits, int batch, int rest_cap) {
@@ -587,9 +592,9 @@ __global__ __launch_bounds__(256) void gram_finish_kernel(const double* __restri
         for (int i = threadIdx.x; i < 32 * kDeep; i += 256) {
           const int at = strip_begin[i / kDeep] + k0 + i % kDeep;
           if (at < strip_begin[i / kDeep + 1]) {
-            const DigitRest r = rest[first + list[at]];
-            strip_token[i] = r.token;
-            strip_rest[i] = bf16_to_f32(r.rest);
+            const size_t place = first + list[at];
+            strip_token[i] = rest.where[place] >> 7;
+            strip_rest[i] = bf16_to_f32(rest.rest[place]);
           }
         }
         __syncthreads();

@@ -77,14 +77,15 @@ __global__ __launch_bounds__(256) void psi_digits_kernel(const double* __restric
 template <int EB>
 __global__ __launch_bounds__(512, 2) void project_digits_kernel(const void* __restrict__ K, const uint8_t* __restrict__ psi_digits,
                                                                 const int32_t* __restrict__ exps, const double* __restrict__ Psi_t,
-                                                                const DigitRest* __restrict__ rest, const int32_t* __restrict__ marks,
+                                                                RestLists rest, const int32_t* __restrict__ marks,
                                                                 int32_t* __restrict__ flags, const float* __restrict__ scale,
                                                                 void* __restrict__ Aout, int s, int s_cap, int D, int r, int nt,
                                                                 int nb2, int tokens_per_split, int n_splits, int batch,
                                                                 int rest_cap, int n_marks) {
   constexpr int kPieces = kPsiStage / 16, kEntries = 64;
   extern __shared__ __align__(16) uint8_t lds[];   // [2][kPsiDeep][kPsiStage]
-  __shared__ DigitRest entries[kEntries];
+  struct Entry { uint32_t where, rest; };   // as in the lists
+  __shared__ Entry entries[kEntries];
   __shared__ int32_t columns[kEntries];
   __shared__ double products[kEntries][32];
   __shared__ int32_t list_n[512];
@@ -131,12 +132,12 @@ __global__ __launch_bounds__(512, 2) void project_digits_kernel(const void* __re
   // this thread's list of what the digits left out: its part for these tokens, and the first entry of that
   const int n_lists = 4 * nb2;
   int from = 0, to = 0;
-  DigitRest first{};
+  Entry first{};
   auto find = [&](int l0) {
     const size_t list = (size_t)group * n_lists + min(l0 + (int)threadIdx.x, n_lists - 1);
     from = marks[list * n_marks + in_split];
     to = l0 + (int)threadIdx.x < n_lists ? marks[list * n_marks + in_split + 1] : from;
-    if (from < to) first = rest[list * rest_cap + from];
+    if (from < to) first = Entry{rest.where[list * rest_cap + from], rest.rest[list * rest_cap + from]};
   };
   request_k(raw0, 0);
   find(0);
@@ -213,20 +214,21 @@ __global__ __launch_bounds__(512, 2) void project_digits_kernel(const void* __re
       if (c0) __syncthreads();
       for (int i = max(from, from + c0 - at); i < min(to, from + c0 + kEntries - at); ++i) {
         const int l = l0 + threadIdx.x;
-        entries[at + (i - from) - c0] = i == from ? first : rest[((size_t)group * n_lists + l) * rest_cap + i];
+        const size_t place = ((size_t)group * n_lists + l) * rest_cap + i;
+        entries[at + (i - from) - c0] = i == from ? first : Entry{rest.where[place], rest.rest[place]};
         columns[at + (i - from) - c0] = (l >> 2) * 128;
       }
       __syncthreads();
       const int here = min(kEntries, total - c0);
       for (int i = threadIdx.x; i < 32 * here; i += 512) {
-        const DigitRest x = entries[i >> 5];
-        const int col = columns[i >> 5] + x.col;
+        const Entry x = entries[i >> 5];
+        const int col = columns[i >> 5] + (int)(x.where & 127u);
         const double psi = Psi_t[((size_t)b * r + min(32 * n + (i & 31), r - 1)) * D + col], sc = (double)scale[(size_t)b * D + col];
-        products[i >> 5][i & 31] = (double)__uint_as_float((uint32_t)x.rest << 16) / sc * psi;
+        products[i >> 5][i & 31] = (double)__uint_as_float(x.rest << 16) / sc * psi;
       }
       __syncthreads();
       for (int i = 0; i < here; ++i) {
-        const int token = __builtin_amdgcn_readfirstlane((int)entries[i].token) - t_begin;
+        const int token = __builtin_amdgcn_readfirstlane((int)(entries[i].where >> 7)) - t_begin;
         if (token >> 5 != wave) continue;
         const double x = products[i][sub];
 #pragma unroll

@@ -187,7 +187,7 @@ struct FactorizePlan {
   int n_marks;              // places in a list that are kept: before every 256th token, and its end
   int max_lv, max_chunk, n_chunks;   // column maxima: 16-byte pieces side by side in a workgroup, tokens per chunk, chunks
   size_t part, G, Xt, Yt, S, Lp, W, V, Jbuf, idle, sweep_max, order, Psi_t, total;  // workspace offsets (bytes)
-  size_t scale, flags, rest, rest_count, marks, by_col, col_begin, psi_digits, psi_exps;
+  size_t scale, flags, rest_where, rest, rest_count, marks, by_col, col_begin, psi_digits, psi_exps;
 };
 FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int n_sweeps, int kv_bytes);
 // k_pre [b, s, h_kv*d]; A [b, s_cap, r]; B [b, h_kv, r, d]; psi_out optional [b, r, D] fp64 (right singular vectors

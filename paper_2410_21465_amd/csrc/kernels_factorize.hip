@@ -345,10 +345,14 @@ static hipError_t gemm64(Mat A, Mat B, double* C, int ldc, size_t strideC, int M
   return hipGetLastError();
 }
 
+static RestLists rest_lists(char* ws, const FactorizePlan& pl) {
+  return {reinterpret_cast<uint32_t*>(ws + pl.rest_where), reinterpret_cast<uint16_t*>(ws + pl.rest)};
+}
+
 // 1. G = K^T K: the digits' products, or the fp64 kernel for sequences whose flag is raised, and the sum over the splits
 template <int EB>
 static hipError_t launch_gram(const void* K, double* part, double* G, float* scale, int32_t* flags, uint16_t* chunk_max,
-                              DigitRest* rest, int32_t* rest_count, int32_t* marks, uint32_t* by_col, int32_t* col_begin,
+                              RestLists rest, int32_t* rest_count, int32_t* marks, uint32_t* by_col, int32_t* col_begin,
                               const FactorizePlan& pl, int batch, int s, int D, hipStream_t st) {
   const int pieces = D * EB / 16;
   hipLaunchKernelGGL(column_max_kernel<EB>, dim3(pl.n_chunks, batch, (pieces + pl.max_lv - 1) / pl.max_lv), dim3(256), 0, st, K,
@@ -367,7 +371,7 @@ static hipError_t launch_gram(const void* K, double* part, double* G, float* sca
                      flags, s, D, pl.nb, pl.tokens_per_split, batch)
   if (pl.waves64 == 8) SKV_GRAM64(8); else if (pl.waves64 == 4) SKV_GRAM64(4); else if (pl.waves64 == 2) SKV_GRAM64(2); else SKV_GRAM64(1);
 #undef SKV_GRAM64
-  hipLaunchKernelGGL(rest_by_column_kernel, dim3(pl.nb2, batch), dim3(1024), 0, st, rest, rest_count, flags, by_col, col_begin, pl.nb2,
+  hipLaunchKernelGGL(rest_by_column_kernel, dim3(pl.nb2, batch), dim3(1024), 0, st, rest.where, rest_count, flags, by_col, col_begin, pl.nb2,
                      pl.n_splits, pl.rest_cap);
   const int nt = D / 32;   // (the key width is a multiple of 32)
   hipLaunchKernelGGL(gram_finish_kernel<EB>, dim3(nt * (nt + 1) / 2, batch), dim3(256), 0, st, part, G, K, scale, rest, by_col, col_begin,
@@ -395,7 +399,7 @@ static hipError_t launch_project(const void* K, const double* Psi_t, void* A, ch
                                        hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(project_digits_kernel<EB>, dim3((unsigned)workgroups), dim3(512), kLds, st, K, psi_digits, exps,
-                       Psi_t, reinterpret_cast<const DigitRest*>(ws + pl.rest), reinterpret_cast<const int32_t*>(ws + pl.marks),
+                       Psi_t, rest_lists(ws, pl), reinterpret_cast<const int32_t*>(ws + pl.marks),
                        flags, scale, A, s, s_cap, D, r, nt, pl.nb2, pl.tokens_per_split, pl.n_splits, batch, pl.rest_cap, pl.n_marks);
   }
   // up to five 16-rank tiles per wave, the tiles dealt evenly to as few waves as that takes (rank 96: 2 x 3, not 5 + 1)
@@ -451,10 +455,10 @@ FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int
   const size_t room = doubles(p.n_splits * DD) + doubles(DD) + 2 * doubles(m * D) + 2 * doubles(even * even) + doubles(r * m) +
                       doubles((size_t)r * D);
   // Behind these lies what the digits need: the columns' scales, the sequences' flags and the lists of what the
-  // digits miss, in token order and by column, with room for one element in 768 (85 at least, or what the room leaves).
+  // digits miss, in token order and by column, with room for three elements in 2048 (96 at least, or what the room leaves).
   p.nb2 = (D + 127) / 128;
   const long tiles = (long)p.nb2 * (p.nb2 + 1) / 2;
-  auto rest_room = [&] { return std::max(64, p.tokens_per_split / 32) * 4 / 3; };   // of 32 elements a token: 128 columns, 16 of 64 tokens
+  auto rest_room = [&] { return std::max(64, p.tokens_per_split / 32) * 3 / 2; };   // of 32 elements a token: 128 columns, 16 of 64 tokens
   auto place = [&](long splits) {
     split_tokens(splits);
     size_t at = std::max(off + up(p.n_splits * split_bytes), end);
@@ -466,10 +470,10 @@ FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int
     p.n_marks = (p.tokens_per_split + 255) / 256 + 1;
     p.marks = at; at += up(lists * p.n_marks * 4);
     const size_t left = room > at + 512 ? room - at - 512 : 0;
-    // (12 bytes an entry, four of them its place in the order by column)
-    p.rest_cap = (int)std::min<size_t>(std::max(64, p.tokens_per_split / 32), left / (lists * 16)) * 4 / 3;
-    p.rest = at; p.by_col = p.rest + lists * p.rest_cap * sizeof(DigitRest);
-    at += up(lists * p.rest_cap * 12);
+    // (10 bytes an entry, four of them its place in the order by column; 16 of what is left for three halves of one)
+    p.rest_cap = (int)std::min<size_t>(std::max(64, p.tokens_per_split / 32), left / (lists * 16)) * 3 / 2;
+    p.rest_where = at; p.by_col = p.rest_where + lists * p.rest_cap * 4; p.rest = p.by_col + lists * p.rest_cap * 4;
+    at += up(lists * p.rest_cap * 10);
     return at;
   };
   // rounds of fp64 workgroups of so many waves: two waves a SIMD, or one, which takes 0.6 of the time
@@ -507,7 +511,7 @@ FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int
   auto time64 = [&](int w) { return rounds64(blocks * p.n_splits, w) * ((p.tokens_per_split + 16 * w - 1) / (16 * w)); };
   for (int w = 2; w <= 8; w *= 2)
     if (time64(w) < 0.95 * time64(p.waves64)) p.waves64 = w;
-  p.rest_share = std::min(1.0f / 512.0f, std::max(0.0f, (float)p.rest_cap - 3.0f * std::sqrt((float)p.rest_cap)) / (32.0f * (float)p.tokens_per_split));
+  p.rest_share = std::min(1.0f / 512.0f, std::max(0.0f, (float)p.rest_cap - 4.0f * std::sqrt((float)p.rest_cap)) / (32.0f * (float)p.tokens_per_split));
   // the columns' largest elements by chunk of tokens lie where G will
   const int ne = 16 / kv_bytes, pieces = D / ne;
   p.max_lv = 1;
@@ -543,7 +547,7 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
     float* scale = reinterpret_cast<float*>(ws + pl.scale);
     int32_t* flags = reinterpret_cast<int32_t*>(ws + pl.flags);
     uint16_t* chunk_max = reinterpret_cast<uint16_t*>(ws + pl.G);
-    DigitRest* rest = reinterpret_cast<DigitRest*>(ws + pl.rest);
+    const RestLists rest = rest_lists(ws, pl);
     int32_t* rest_count = reinterpret_cast<int32_t*>(ws + pl.rest_count);
     int32_t* marks = reinterpret_cast<int32_t*>(ws + pl.marks);
     uint32_t* by_col = reinterpret_cast<uint32_t*>(ws + pl.by_col);
