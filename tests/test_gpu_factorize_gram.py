@@ -123,3 +123,31 @@ def test_gram_matrix_from_the_factors(b, h, d, s, kind, kd, route):
         d = ulp_distance(PU.to_bits(got["A"][i, :s].contiguous(), kd), PU.to_bits(stored, kd), kd)
         big = np.abs(A) > 1e-9 * np.abs(K).max(axis=1, keepdims=True)    # (sums that cancel to rounding have no digits to compare)
         assert d[big].max(initial=0) <= 1 and (d[big] > 0).mean() < 1e-4, (d[big].max(initial=0), (d[big] > 0).mean())
+
+
+@pytest.mark.parametrize("s,route", [(2 ** 25, 0), (2 ** 25 + 16, 1)])
+def test_as_many_tokens_as_a_list_entry_can_name(s, route):
+    """An entry of the digits' lists has 25 bits for its token; a longer sequence is summed in fp64."""
+    D = 64
+    print(f"\n[case] s {s}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(s % 1000)
+    k = torch.empty(1, s, D, dtype=torch.bfloat16, device="cuda")
+    for part in k[0].split(2 ** 22):
+        part.copy_(torch.randn(part.shape, generator=gen, device="cuda"))
+    p = S.Params(batch=1, n_q_heads=1, n_kv_heads=1, head_dim=D, ctx_len=s, chunk_size=1, rank=D, n_outlier_chunks=0,
+                 topk_chunks=1, local_len=0)
+    got = S.factorize_keys(p, k, want_vectors=True)
+    assert S.factorize_routes(p, got["workspace"]).tolist() == [route]
+    G = torch.zeros(D, D, dtype=torch.float64, device="cuda")
+    for part in k[0].split(2 ** 21):
+        x = part.double()
+        G += x.t().contiguous() @ x
+    psi, sig = got["psi"][0].cpu().numpy(), got["sigma"][0].cpu().numpy()
+    G = G.cpu().numpy()
+    err = np.abs((psi.T * sig ** 2) @ psi - G).max() / np.linalg.norm(G, 2)
+    # the eigenvectors' rounding as above; the reference adds 2^21 products at a time in fp64: a random walk of 2^-53 each
+    assert err < (32 * D + 2 ** 11) * 2.0 ** -53, err
+    for rows in (slice(0, 1000), slice(s - 1000, s)):
+        A = PU.kv_to_f64(PU.to_bits(k[0, rows].contiguous(), 0)) @ psi.T
+        d = ulp_distance(PU.to_bits(got["A"][0, rows].contiguous(), 0), PU.to_bits(torch.from_numpy(A).to(k.dtype), 0), 0)
+        assert d.max() <= 1 and (d > 0).mean() < 1e-3
