@@ -168,27 +168,29 @@ __global__ __launch_bounds__(256) void column_max_kernel(const void* __restrict_
 }
 
 // scale[b][j] = 2^sh_j, 1 <= scale <= 2^126; 64 columns per workgroup, sixteen threads each.  The flag of the sequence is raised
-// by a column with an element beyond 2^22 (or not finite), and where a sample of kSample tokens (evenly spaced over the
-// sequence; all of a shorter one) says that the lists will not do: more than `share` of the workgroup's elements are not held
-// by their digits, or several times that in one token part.  `share` is what the lists have room for, less four standard
-// deviations of such a list's length, and the sample is large enough to tell that from three quarters of it: with 256 tokens and
-// twice the lists' room, keys with 1 % of their chunks 10 to 16 times the others' size went through the digits' products, filled
-// their lists and were summed in fp64 after all, 64.2 ms at 16 x 128K x 1024 where the fp64 sums alone take 53.9; now 33.0 to 54.0.
+// by a column with an element beyond 2^22 (or not finite), and where a sample of kSample tokens (spaced evenly over the
+// sequence, step 2^-32 tokens apart; all of a shorter one) says that the lists will not do: more than `share` of the workgroup's
+// elements are not held by their digits, or several times that in one token part.  `share` is what the lists have room for,
+// less four standard deviations of such a list's length, and the sample is large enough to tell that from three quarters of it:
+// with 256 tokens and twice the lists' room, keys with 1 % of their chunks 10 to 16 times the others' size went through the
+// digits' products, filled their lists and were summed in fp64 after all, 64.2 ms at 16 x 128K x 1024 where the fp64 sums alone
+// take 53.9; now 33.0 to 54.0.  The sample takes 2 us of 11 for one sequence, 12 of 19 for 16.
+constexpr int kSample = 2048;
 template <int EB>
 __global__ __launch_bounds__(1024) void column_scale_kernel(const void* __restrict__ K, const uint16_t* __restrict__ chunk_max,
                                                             float* __restrict__ scale, int32_t* __restrict__ flags, int s, int D,
-                                                            int n_chunks, int tokens_per_split, float share) {
-  constexpr int kSample = 2048, kRows = 1024 / 64, kPass = 1024 / 8, kParts = 512;
+                                                            int n_chunks, int tokens_per_split, uint64_t step, float share) {
+  constexpr int kRows = 1024 / 64, kPass = 1024 / 8, kParts = 512;
   __shared__ uint32_t red[kRows][64];
   __shared__ float sc[64];
-  __shared__ int32_t taken[kParts], missed[kParts];   // tokens of the sample, and their elements that are not held, per token part
+  __shared__ int32_t missed[kParts];   // elements of the sample that are not held, per token part
   __shared__ int32_t all_missed;
   const int b = blockIdx.y, x = threadIdx.x & 63, y = threadIdx.x >> 6, col0 = blockIdx.x * 64, col = min(col0 + x, D - 1);
   uint32_t m = 0;
 #pragma unroll 8
   for (int c = y; c < n_chunks; c += kRows) m = max(m, (uint32_t)chunk_max[((size_t)b * n_chunks + c) * D + col]);
   red[y][x] = m;
-  if (threadIdx.x < kParts) taken[threadIdx.x] = missed[threadIdx.x] = 0;
+  if (threadIdx.x < kParts) missed[threadIdx.x] = 0;
   if (threadIdx.x == 0) all_missed = 0;
   __syncthreads();
   if (y == 0) {
@@ -206,7 +208,6 @@ __global__ __launch_bounds__(1024) void column_scale_kernel(const void* __restri
   __syncthreads();
   // eight columns of a token per thread, kPass tokens at a time
   const int c8 = 8 * (threadIdx.x & 7), n = min(kSample, s);
-  const uint64_t step = ((uint64_t)s << 32) / (uint32_t)n;
   auto token = [&](int i) { return (int)((uint64_t)i * step >> 32); };
 #pragma unroll 1
   for (int i0 = threadIdx.x >> 3; i0 < n; i0 += 8 * kPass) {
@@ -219,17 +220,18 @@ __global__ __launch_bounds__(1024) void column_scale_kernel(const void* __restri
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       if (i0 + kPass * i >= n) continue;
-      const int part = min(token(i0 + kPass * i) / tokens_per_split, kParts - 1);
-      if (c8 == 0) atomicAdd(&taken[part], 1);
       int mine = 0;
       each_of(std::make_integer_sequence<int, 8>{}, [&](auto e) { mine += digit_rest(v[i].template elem<e>(), sc[c8 + e]) != 0.0f ? 1 : 0; });
-      if (col0 + c8 < D && mine) { atomicAdd(&missed[part], mine); atomicAdd(&all_missed, mine); }
+      if (col0 + c8 < D && mine) {
+        atomicAdd(&missed[min(token(i0 + kPass * i) / tokens_per_split, kParts - 1)], mine);
+        atomicAdd(&all_missed, mine);
+      }
     }
   }
   __syncthreads();
   // (eight elements fill no list)
-  const float room = share * (float)min(64, D - col0);
-  if (threadIdx.x < kParts && (float)missed[threadIdx.x] > 2.0f * room * (float)taken[threadIdx.x] + 8.0f) flags[b] = 1;
+  const float room = share * (float)min(64, D - col0), taken = (float)n * (float)min(s, tokens_per_split) / (float)s;   // of a part
+  if (threadIdx.x < kParts && (float)missed[threadIdx.x] > 2.0f * room * taken + 8.0f) flags[b] = 1;
   if (threadIdx.x == 0 && (float)all_missed > fmaxf(room * (float)n, 8.0f)) flags[b] = 1;
 }
 

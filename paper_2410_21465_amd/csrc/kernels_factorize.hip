@@ -358,7 +358,7 @@ static hipError_t launch_gram(const void* K, double* part, double* G, float* sca
   hipLaunchKernelGGL(column_max_kernel<EB>, dim3(pl.n_chunks, batch, (pieces + pl.max_lv - 1) / pl.max_lv), dim3(256), 0, st, K,
                      chunk_max, flags, s, D, pl.max_lv, pl.max_chunk, pl.n_chunks);
   hipLaunchKernelGGL(column_scale_kernel<EB>, dim3(pl.nb, batch), dim3(1024), 0, st, K, chunk_max, scale, flags, s, D,
-                     pl.n_chunks, pl.tokens_per_split, pl.rest_share);
+                     pl.n_chunks, pl.tokens_per_split, ((uint64_t)s << 32) / (uint32_t)std::min(s, kSample), pl.rest_share);
   constexpr int kLds = 2 * 2 * 3 * 128 * 64;   // two stages of two column blocks of three digits
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gram_digits_kernel<EB>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
