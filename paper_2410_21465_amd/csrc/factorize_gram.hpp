@@ -174,7 +174,7 @@ __global__ __launch_bounds__(256) void column_max_kernel(const void* __restrict_
 // less four standard deviations of such a list's length, and the sample is large enough to tell that from three quarters of it:
 // with 256 tokens and twice the lists' room, keys with 1 % of their chunks 10 to 16 times the others' size went through the
 // digits' products, filled their lists and were summed in fp64 after all, 64.2 ms at 16 x 128K x 1024 where the fp64 sums alone
-// take 53.9; now 33.0 to 54.0.  The sample takes 2 us of 11 for one sequence, 12 of 19 for 16.
+// take 53.9; now 32.5 to 54.0.  The sample takes 2 us of 11 for one sequence, 12 of 19 for 16.
 constexpr int kSample = 2048;
 template <int EB>
 __global__ __launch_bounds__(1024) void column_scale_kernel(const void* __restrict__ K, const uint16_t* __restrict__ chunk_max,

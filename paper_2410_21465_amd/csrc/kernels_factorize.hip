@@ -506,11 +506,13 @@ FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int
   p.total = place(splits);
   // Waves that share an fp64 block of a part, for the least rounds times tokens of a wave.  With one wave each, as many splits as
   // suit the digits left half of the chip idle: 1 x 32K x 1024 624 us with the 15 splits that the fp64 sums would choose, 1,214
-  // with 7 splits and one wave, 648 with two; 2 x 32K x 512 344, 717 and 379; 3 x 8K x 1024 460, 566 and 549.
+  // with 7 splits and one wave, 648 with two, 636 with four; 2 x 32K x 512 344, 717, 379 and 376; 3 x 8K x 1024 460, 566, 549 and
+  // 543.  Four rather than fewer where they are equal: a few sequences of a batch fill more of the chip (two of which one is
+  // summed in fp64, 2 x 32K x 512: the call 4.21 ms with two waves, 4.04 with four).
   p.waves64 = 1;
   auto time64 = [&](int w) { return rounds64(blocks * p.n_splits, w) * ((p.tokens_per_split + 16 * w - 1) / (16 * w)); };
   for (int w = 2; w <= 8; w *= 2)
-    if (time64(w) < 0.95 * time64(p.waves64)) p.waves64 = w;
+    if (time64(w) < (w < 8 ? 1.02 : 0.95) * time64(p.waves64)) p.waves64 = w;
   p.rest_share = std::min(1.0f / 512.0f, std::max(0.0f, (float)p.rest_cap - 4.0f * std::sqrt((float)p.rest_cap)) / (32.0f * (float)p.tokens_per_split));
   // the columns' largest elements by chunk of tokens lie where G will
   const int ne = 16 / kv_bytes, pieces = D / ne;

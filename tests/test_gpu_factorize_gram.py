@@ -69,7 +69,8 @@ CASES = [(1, 1, 64, 1, "normal", 0, 2), (1, 1, 64, 63, "normal", 0, 2), (2, 1, 6
          (1, 2, 128, 600, "large", 0, 1), (3, 2, 128, 1000, "mixed", 0, (0, 1, 0)), (2, 3, 64, 4096, "unseen", 0, 1),
          (1, 2, 96, 8192, "unseen", 1, 1), (1, 1, 64, 100, "last", 0, 0), (1, 1, 128, 4000, "absent", 0, 0), (2, 2, 96, 3000, "absent", 1, 0),
          (1, 2, 128, 2000, "lone", 0, 2), (2, 3, 64, 1000, "lone", 1, 2), (1, 2, 128, 5000, "ones", 0, 0),
-         (1, 1, 64, 70001, "outliers", 0, 0), (40, 4, 64, 600, "graded", 0, 1), (180, 4, 64, 520, "graded", 1, 1),
+         (1, 1, 64, 70001, "outliers", 0, 0), (40, 4, 64, 600, "graded", 0, 1), (80, 4, 64, 600, "graded", 0, 1),
+         (180, 4, 64, 520, "graded", 1, 1),
          (256, 1, 64, 33000, "normal", 0, 0),
          # one token part of more than the 32768 tokens summed in 32 bits, off the diagonal too
          (1024, 3, 64, 33000, "crowded", 0, 0), (2048, 1, 64, 33000, "outliers", 1, 0)]
