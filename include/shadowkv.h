@@ -283,7 +283,7 @@ size_t shadowkv_factorize_workspace_bytes(const shadowkv_params *params);
  *   [0] token parts of the Gram matrix; [1] tokens per part; [2] entries that a list of a part has room for (lists hold what
  *       the keys' digits leave out: one per 128 columns and quarter of a part's tokens);
  *   [3] byte offset in the workspace of an int32 per sequence, valid after the call: 0 Gram matrix and A from digits,
- *       1 both from fp64 sums, 2 the Gram matrix from digits and A from fp64 sums;
+ *       1 both from fp64 sums, 2 the Gram matrix from digits and A from fp64 sums (A always is where h_kv*d is beyond 32768);
  *   [4] waves that share a 64 x 64 block of a part's fp64 sums (1, 2, 4 or 8).
  * Returns SHADOWKV_OK or SHADOWKV_EINVAL (bad params / plan NULL).
  */
