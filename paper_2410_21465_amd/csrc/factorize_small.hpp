@@ -119,110 +119,202 @@ __device__ __forceinline__ double rsqrt_f64(double x) {
   return y;
 }
 
-// the first (third) row of 16 lanes in the second (fourth) as well
-__device__ __forceinline__ double even_rows_f64(double x) {
-  const uint32_t lo = (uint32_t)__double2loint(x), hi = (uint32_t)__double2hiint(x);
-  return __hiloint2double((int)__builtin_amdgcn_permlane16_swap(hi, hi, false, false)[0],
-                          (int)__builtin_amdgcn_permlane16_swap(lo, lo, false, false)[0]);
-}
-// lane J of each row of 16 in all lanes of the row
-template <int J>
-__device__ __forceinline__ double row_lane_f64(double x) {
-  return __longlong_as_double(__builtin_amdgcn_update_dpp(0ll, __double_as_longlong(x), 0x150 + J, 0xf, 0xf, true));
-}
-// One step of a 16 x 16 block's factorisation without its roots: lanes 0-15 hold its rows, lanes 16-31 the columns of the unit
-// matrix, which become those of the inverse.  Pivots below `least` (of their own lane) project nothing.  The reciprocal is the
-// hardware's estimate y (24 bits) times 1 + e + e^2, e = 1 - d y.  Bound by one wave's issue, some 40 instructions of 7 cycles
-// a pivot (a root per pivot and broadcasts through the scalar registers: 335 cycles, now 308; the next pivot's chain drawn
-// between the updates of the last: 325).
-template <int P>
-__device__ __forceinline__ void factor_step(double (&a)[16], double least, uint32_t& floored) {
-  const double d = lane_f64(a[P], P);
-  const bool skip = d < lane_f64(least, P);
-  const double y = skip ? 0.0 : __builtin_amdgcn_rcp(d), e = fma(-d, y, 1.0), g = -(a[P] * y);
-  const double f = fma(g, fma(e, e, e), g), col = even_rows_f64(a[P]);
-  each_of(std::make_integer_sequence<int, 16>{}, [&](auto j) {
-    if constexpr (j > P) a[j] = fma(f, row_lane_f64<j>(col), a[j]);
+// Factorisation of a 16 x 16 diagonal block by one wave, four pivots at a time on the matrix instruction.  Register j of lane
+// (sub, kq) holds entry (4 j + kq, sub), by symmetry also (sub, 4 j + kq): register j is the operand of a contraction over
+// columns 4 j .. 4 j + 3 as it stands.  Per panel: the reciprocals r of the 4 x 4 block's pivots and the inverse N of its unit
+// lower factor in every lane alike; U = N times the panel's rows; the rest of the block less U^T diag(r) U; and the unit matrix
+// carried along the same way, of which N times rows 4 j .. 4 j + 3 are, up to the roots of the pivots, rows of the inverse.
+// f, d: of rows 4 j + kq these rows (column sub), and the pivots.  CHECK: pivots below `least` (of their row) project nothing.
+template <bool CHECK>
+__device__ __forceinline__ void factor_panels(f64x4 a, const double (&least)[4], double (&f)[4], double (&d)[4]) {
+  const int lane = threadIdx.x & (kWave - 1), sub = lane & 15, kq = lane >> 4, at = 4 * (sub & 3) + kq;
+  const bool k1 = kq == 1, k2 = kq == 2, k3 = kq == 3;
+  f64x4 e;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) e[j] = 4 * j + kq == sub ? 1.0 : 0.0;
+  each_of(std::make_integer_sequence<int, 4>{}, [&](auto jc) {
+    constexpr int J = jc;
+    double r[4], l[4][4], s[4][4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int p = q; p < 4; ++p) s[p][q] = lane_f64(a[J], 4 * J + p + 16 * q);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      // the hardware's estimate y (24 bits) times 1 + g + g^2, g = 1 - d y
+      double y = __builtin_amdgcn_rcp(s[p][p]);
+      if constexpr (CHECK) y = s[p][p] < lane_f64(least[J], 16 * p) ? 0.0 : y;
+      const double g = fma(-s[p][p], y, 1.0), h = fma(g, g, g);
+      r[p] = fma(y, h, y);
+#pragma unroll
+      for (int i = p + 1; i < 4; ++i) {
+        const double t = s[i][p] * y;
+        l[i][p] = fma(t, h, t);
+#pragma unroll
+        for (int q = p + 1; q <= i; ++q) s[i][q] = fma(-l[i][p], s[q][p], s[i][q]);
+      }
+    }
+    // (computed by all lanes: not to be drawn into branches of the selections below)
+    asm volatile("" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]));
+    const double n10 = -l[1][0], n21 = -l[2][1], n32 = -l[3][2];
+    const double n20 = fma(n21, n10, -l[2][0]), n31 = fma(n32, n21, -l[3][1]);
+    const double n30 = fma(n32, n20, fma(-l[3][1], n10, -l[3][0]));
+    // N as the left operand of four 4 x 4 x 4 products side by side (lane: row sub % 4, column kq)
+    double nv = (sub & 3) == kq ? 1.0 : 0.0;
+    nv = at == 4 ? n10 : nv; nv = at == 9 ? n21 : nv; nv = at == 8 ? n20 : nv;
+    nv = at == 14 ? n32 : nv; nv = at == 13 ? n31 : nv; nv = at == 12 ? n30 : nv;
+    d[J] = k1 ? s[1][1] : s[0][0];
+    d[J] = k2 ? s[2][2] : d[J];
+    d[J] = k3 ? s[3][3] : d[J];
+    if constexpr (J < 3) {
+      double rk = k1 ? r[1] : r[0];
+      rk = k2 ? r[2] : rk;
+      rk = k3 ? r[3] : rk;
+      rk = sub >= 4 * (J + 1) ? -rk : 0.0;   // rows below the panel
+      const double u = __builtin_amdgcn_mfma_f64_4x4x4f64(nv, a[J], 0.0, 0, 0, 0);   // row kq, column sub
+      const double w = rk * u;
+      a = __builtin_amdgcn_mfma_f64_16x16x4f64(w, u, a, 0, 0, 0);
+      f[J] = __builtin_amdgcn_mfma_f64_4x4x4f64(nv, e[J], 0.0, 0, 0, 0);
+      e = __builtin_amdgcn_mfma_f64_16x16x4f64(w, f[J], e, 0, 0, 0);
+    } else {
+      f[J] = __builtin_amdgcn_mfma_f64_4x4x4f64(nv, e[J], 0.0, 0, 0, 0);
+    }
   });
-  floored |= skip ? 1u << P : 0u;
+}
+
+// The block's inverse factor.  Pivots below kPivotFloor times their vector's square (e0[j], row 4 j + kq) project nothing and
+// count as that (see chol_kernel); a block that has one is taken again with the checks.
+// out: the inverse in operand order; inv: the same, rows of floored pivots zero; returns the least pivot of the lane's rows.
+__device__ __forceinline__ double factor_block(f64x4 a, const double (&e0)[4], double* __restrict__ out, double* __restrict__ inv) {
+  const int lane = threadIdx.x & (kWave - 1), sub = lane & 15, kq = lane >> 4;
+  double f[4], d[4], least[4];
+  bool bad = false;
+  factor_panels<false>(a, least, f, d);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    least[j] = e0[j] > 1e-280 ? kPivotFloor * e0[j] : INFINITY;
+    bad |= d[j] < least[j];
+  }
+  if (__builtin_expect(__any(bad), 0)) factor_panels<true>(a, least, f, d);
+  double smallest = INFINITY;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const bool none = least[j] == INFINITY, floored = d[j] < least[j];
+    const double piv = none ? 1.0 : (floored ? least[j] : d[j]), x = f[j] * rsqrt_f64(piv);
+    smallest = none ? smallest : fmin(smallest, piv);
+    out[op_index(4 * j + kq, sub)] = x;
+    inv[op_index(4 * j + kq, sub)] = floored ? 0.0 : x;
+  }
+  return smallest;
 }
 
 // Cholesky factor of S [16 nb][16 nb] (lower triangle read; zero beyond the vectors), one workgroup of eight waves per
 // sequence.  Lp: packed blocks in operand order, off the diagonal -L, on it the inverse of L's block (what trsm_kernel
 // multiplies by).
-// The trailing blocks stay in the accumulators of the waves (blocks dealt out in turn, NBW per wave) for the whole
-// factorisation; only the current block column goes through LDS.  What bounds it is the chain of pivots, 16 per diagonal block
-// in one wave, which carries the unit matrix along in a second group of lanes and so ends with the inverse as well: of 48 us
-// for 192 vectors the diagonal blocks take 25, the trailing updates 11, the block columns 9, the start 4.  (59 us before: a root
-// per pivot, and a start of 6 us, most of it fetching 25 instructions for each of its guarded loads.)  Above 192 vectors the
-// blocks of a wave no longer fit in its registers beside the rest (scratch memory: 36 bytes a lane with NBW = 14, 416 with 22).
+// Wave 0 has the chain: it takes block (k + 1, k) of column k, the next diagonal block and that block's pivots, while the
+// others finish column k and keep the trailing blocks in their accumulators (dealt out in turn by columns, NBW per wave) up
+// to date; of those, the next block column and the diagonal block after the next go through LDS.
+// What bounds it is that chain: for 192 vectors a step takes 5,000 cycles, 3,300 of them the pivots (panels of four on the
+// matrix instruction; a column at a time with broadcasts along the rows 5,000) and 750 the next block, the first three steps
+// half as much again for the others' matrix instructions; the start 6,000.  33 us in all, where one wave after the other,
+// pivots, column, trailing blocks with four barriers a step, took 49.  Above 192 vectors a wave's blocks fill its registers.
 // A pivot below kPivotFloor of the vector's own square is rounding: it is set to that floor, which leaves the vector's
 // remainder at a size that the next pass can work on, and nothing is projected on it; a zero vector stays zero.
 template <int NBW>
 __global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S, double* __restrict__ Lp, int nb) {
-  __shared__ double col[kMaxFactorBlocks][272];   // current block column: rows at a pitch of 17, then operand order
+  __shared__ double col[kMaxFactorBlocks][272];   // current block column, rows at a pitch of 17
+  __shared__ double sol[kMaxFactorBlocks][256];   // the same times the diagonal block's inverse, operand order
   __shared__ double inv[256];                     // inverse of the diagonal block, rows of floored pivots zero
-  __shared__ double d0[kMaxFactorBlocks * 16];    // squares of the vectors
-  __shared__ uint16_t place[8 * NBW];             // block row and column of the idx-th block (column nb: no block)
+  __shared__ double next[4][kWave];               // the diagonal block after the next, as in the accumulators
+  __shared__ uint16_t place[7][NBW];              // block row and column of the blocks of waves 1 .. 7 (column nb: no block)
   const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int sub = lane & 15, kq = lane >> 4;
   const int ld = 16 * nb;
   S += (size_t)blockIdx.x * ld * ld;
   Lp += (size_t)blockIdx.x * (nb * (nb + 1) / 2) * 256;
-  for (int x = threadIdx.x; x < 8 * NBW; x += 512) {
-    int idx = x, k = 0;
+  const double* Sl = S + (size_t)kq * ld + sub;
+  // trailing blocks: columns 1 .. nb - 1 from the diagonal down, without (1, 1); wave 4, which shares wave 0's SIMD, takes part
+  // in the first quarter of the columns only
+  const int c7 = NBW == 11 ? nb / 4 : nb, n7 = c7 * nb - c7 * (c7 + 1) / 2 - 1, t7 = (max(n7, 0) + 6) / 7;
+  for (int x = threadIdx.x; x < 7 * NBW; x += 512) {
+    const int w = x % 7, t = x / 7;
+    int idx = t < t7 ? (x < n7 ? x + 1 : 1 << 20) : w == 3 ? 1 << 20 : n7 + 1 + (t - t7) * 6 + w - (w > 3 ? 1 : 0), k = 1;
     while (k < nb && idx >= nb - k) { idx -= nb - k; ++k; }
-    place[x] = (uint16_t)((k + idx) << 8 | k);
+    place[w][t] = k < nb ? (uint16_t)((k + idx) << 8 | k) : (uint16_t)nb;
   }
-  for (int x = threadIdx.x; x < ld; x += 512) d0[x] = S[(size_t)x * (ld + 1)];
+  for (int x = threadIdx.x; x < (nb - 1) * 256; x += 512) {
+    const int i = 1 + (x >> 8), r = (x >> 4) & 15, c = x & 15;
+    col[i][r * 17 + c] = S[(size_t)(16 * i + r) * ld + c];
+  }
   __syncthreads();
+  if (wave == 0) {
+    f64x4 d;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) d[j] = Sl[4 * j * ld];
+    f64x4 a = d;
+    if (nb > 1)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) d[j] = -Sl[(16 + 4 * j) * ld + 16];
+    __builtin_amdgcn_s_setprio(3);
+    double e1[4];   // squares of the next block's vectors 4 j + kq, ahead of their use
+#pragma unroll
+    for (int j = 0; j < 4; ++j) e1[j] = S[(size_t)(4 * j + kq) * (ld + 1)];
+    for (int k = 0;; ++k) {
+      double e0[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        e0[j] = e1[j];
+        e1[j] = S[(size_t)(16 * min(k + 1, nb - 1) + 4 * j + kq) * (ld + 1)];
+      }
+      factor_block(a, e0, Lp + (size_t)tri_block(nb, k, k) * 256, inv);
+      __syncthreads();   // B: the inverse, column k and the next diagonal block are in LDS
+      if (k + 1 >= nb) break;
+      if (k > 0)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) d[j] = next[j][lane];
+      double x4[4], iv[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) { x4[t] = col[k + 1][sub * 17 + 4 * t + kq]; iv[t] = inv[lane * 4 + t]; }
+      f64x4 x = {0.0, 0.0, 0.0, 0.0}, y = {0.0, 0.0, 0.0, 0.0};
+      x = __builtin_amdgcn_mfma_f64_16x16x4f64(x4[0], iv[0], x, 0, 0, 0);
+      y = __builtin_amdgcn_mfma_f64_16x16x4f64(x4[1], iv[1], y, 0, 0, 0);
+      x = __builtin_amdgcn_mfma_f64_16x16x4f64(x4[2], iv[2], x, 0, 0, 0);
+      y = __builtin_amdgcn_mfma_f64_16x16x4f64(x4[3], iv[3], y, 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) sol[k + 1][op_index(4 * j + kq, sub)] = x[j] + y[j];
+      __syncthreads();   // A: column k times the inverse is in LDS
+      double l4[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) l4[t] = sol[k + 1][lane * 4 + t];
+      y = f64x4{0.0, 0.0, 0.0, 0.0};
+      d = __builtin_amdgcn_mfma_f64_16x16x4f64(l4[0], l4[0], d, 0, 0, 0);
+      y = __builtin_amdgcn_mfma_f64_16x16x4f64(l4[1], l4[1], y, 0, 0, 0);
+      d = __builtin_amdgcn_mfma_f64_16x16x4f64(l4[2], l4[2], d, 0, 0, 0);
+      y = __builtin_amdgcn_mfma_f64_16x16x4f64(l4[3], l4[3], y, 0, 0, 0);
+      double* dst = Lp + (size_t)tri_block(nb, k + 1, k) * 256 + lane * 4;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) dst[t] = -l4[t];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) a[j] = -(d[j] + y[j]);
+    }
+    return;
+  }
   f64x4 acc[NBW];   // the negatives of the trailing blocks
   int bi[NBW], bk[NBW];
   // (few instructions per load: this runs once, and fetching the code is what it waits for)
-  const double* Sl = S + (size_t)kq * ld + sub;
 #pragma unroll
   for (int t = 0; t < NBW; ++t) {
-    const int x = __builtin_amdgcn_readfirstlane(place[wave + 8 * t]);
+    const int x = __builtin_amdgcn_readfirstlane(place[wave - 1][t]);
     bi[t] = x >> 8; bk[t] = x & 255;
     const double* p = Sl + (bk[t] < nb ? 16 * (bi[t] * ld + bk[t]) : 0);
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[t][j] = -p[4 * j * ld];
   }
-  for (int k = 0; k < nb; ++k) {
-#pragma unroll
-    for (int t = 0; t < NBW; ++t)
-      if (bk[t] == k)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) col[bi[t]][(4 * j + kq) * 17 + sub] = -acc[t][j];
-    __syncthreads();
-    double* out = Lp + (size_t)tri_block(nb, k, k) * 256;
-    if (wave == 0) {
-      // lanes 0-15: rows of the block; lanes 16-31: columns of the unit matrix, which become those of the inverse
-      double a[16];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) a[j] = lane < 16 ? col[k][sub * 17 + j] : (lane < 32 && j == sub ? 1.0 : 0.0);
-      const double e0 = d0[16 * k + sub];
-      const bool none = !(e0 > 1e-280);
-      const double floor = kPivotFloor * e0;
-      uint32_t floored = 0;
-      each_of(std::make_integer_sequence<int, 16>{}, [&](auto p) { factor_step<p>(a, none ? INFINITY : floor, floored); });
-      // the roots of all pivots at once (lane p its own), then column p of both halves times root p
-      double d = a[0];
-#pragma unroll
-      for (int p = 1; p < 16; ++p) d = sub == p ? a[p] : d;
-      const double root = even_rows_f64(rsqrt_f64(none ? 1.0 : (d < floor ? floor : d)));
-      each_of(std::make_integer_sequence<int, 16>{}, [&](auto p) { a[p] *= row_lane_f64<p>(root); });
-      if (kq == 1) {
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          out[op_index(j, sub)] = a[j];
-          inv[op_index(j, sub)] = (floored >> j) & 1 ? 0.0 : a[j];
-        }
-      }
-    }
-    __syncthreads();
+  for (int k = 0;; ++k) {
+    __syncthreads();   // B
+    if (k + 1 >= nb) break;
     // L(i, k) = A(i, k) inv^T
-    for (int i = k + 1 + wave; i < nb; i += 8) {
+    for (int i = k + 1 + wave; i < nb; i += 7) {
       double a[4];
 #pragma unroll
       for (int t = 0; t < 4; ++t) a[t] = col[i][sub * 17 + 4 * t + kq];
@@ -230,20 +322,25 @@ __global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S,
 #pragma unroll
       for (int t = 0; t < 4; ++t) x = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], inv[lane * 4 + t], x, 0, 0, 0);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) col[i][op_index(4 * j + kq, sub)] = x[j];
+      for (int j = 0; j < 4; ++j) sol[i][op_index(4 * j + kq, sub)] = x[j];
       double* dst = Lp + (size_t)tri_block(nb, i, k) * 256;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) dst[lane * 4 + t] = -col[i][lane * 4 + t];
+      for (int t = 0; t < 4; ++t) dst[lane * 4 + t] = -sol[i][lane * 4 + t];
     }
-    __syncthreads();
+    __syncthreads();   // A
 #pragma unroll
     for (int t = 0; t < NBW; ++t)
       if (bk[t] > k && bk[t] < nb) {
 #pragma unroll
         for (int x = 0; x < 4; ++x)
-          acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(col[bi[t]][lane * 4 + x], col[bk[t]][lane * 4 + x], acc[t], 0, 0, 0);
+          acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(sol[bi[t]][lane * 4 + x], sol[bk[t]][lane * 4 + x], acc[t], 0, 0, 0);
+        if (bk[t] == k + 1 && bi[t] > k + 1)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) col[bi[t]][(4 * j + kq) * 17 + sub] = -acc[t][j];
+        if (bk[t] == k + 2 && bi[t] == k + 2)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) next[j][lane] = acc[t][j];
       }
-    __syncthreads();
   }
 }
 

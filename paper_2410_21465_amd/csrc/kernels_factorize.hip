@@ -574,7 +574,7 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
   } while (0)
     // (blocks per wave of the eight, block rows held): up to 80, 192, 224, 288 vectors
     if (nbc <= 5) SKV_ORTH(2, 5);
-    else if (nbc <= 12) SKV_ORTH(10, 12);
+    else if (nbc <= 12) SKV_ORTH(11, 12);
     else if (nbc <= 14) SKV_ORTH(14, 14);
     else SKV_ORTH(22, kMaxFactorBlocks);
 #undef SKV_ORTH
