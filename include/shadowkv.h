@@ -258,9 +258,10 @@ int shadowkv_append_chunk(const shadowkv_params *params, const shadowkv_kv *k_pr
  * (the low-rank states of section "High-throughput Decoding": keys are kept as K Psi and projected back with Psi^T).
  * Singular vectors are defined up to sign; the convention here makes the component of largest magnitude of every
  * right singular vector positive (ties: lowest index).  Computed from the Gram matrix K^T K (stored as fp64; its
- * products are exact, its sums exact or fp64) by subspace iteration with `n_iter` steps (0 => 16) on r + 32 vectors
- * and a Rayleigh-Ritz step; accurate when sigma_r and sigma_(r+33) are apart (the convergence factor per step is
- * (sigma_(r+33) / sigma_r)^2).
+ * products are exact, its sums exact or fp64) by subspace iteration with `n_iter` steps on r + 32 vectors and a
+ * Rayleigh-Ritz step; accurate when sigma_r and sigma_(r+33) are apart (the convergence factor per step is
+ * (sigma_(r+33) / sigma_r)^2).  n_iter = 0, the default, takes thirteen steps of which the last nine are shifted; they
+ * come at least as close as sixteen plain ones.
  *
  *   k_pre      dev      [b, s, h_kv*d] kv   pre-RoPE keys, heads side by side
  *   A          dev out  [b, cap, r] kv      rows 0 .. s-1 written: sums good to 2^-24 of each entry, or fp64 sums where an
@@ -269,7 +270,7 @@ int shadowkv_append_chunk(const shadowkv_params *params, const shadowkv_kv *k_pr
  *   psi_out    dev out  [b, r, h_kv*d] fp64 optional (NULL): the right singular vectors before rounding, as rows
  *   sigma_out  dev out  [b, r] fp64         optional (NULL): singular values, largest first
  *   workspace  dev      >= shadowkv_factorize_workspace_bytes(), 256-byte aligned
- * Needs rank <= h_kv*d.  topk_chunks, local_len, n_outlier_chunks are ignored.  Enqueues some 180 launches at rank
+ * Needs rank <= h_kv*d.  topk_chunks, local_len, n_outlier_chunks are ignored.  Enqueues some 170 launches at rank
  * 160, most of them small (one per dependent step of the orthogonalisation and of the Jacobi sweeps).
  */
 int shadowkv_factorize_keys(const shadowkv_params *params, const shadowkv_kv *k_pre, shadowkv_kv *A,

@@ -12,7 +12,7 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 // ---- products ---------------------------------------------------------------------------------------
 // C[i][j] = sum_k A[i][k] B(k, j), K a multiple of 16, rows of A 16-byte aligned.  BT: B is given by its columns
 // (B(k, j) = B[j][k], as A is); otherwise row-major with Kb rows (A is zero beyond).  Rows of A may be taken through
-// a_rows.  C is written over Mw x Nw, zero outside M x N.
+// a_rows.  C is written over Mw x Nw, zero outside M x N.  With `shift` (one number per sequence; N = K): C = A (B - node shift).
 // A workgroup is WM x WN tiles of 16 T x 16 T with the contraction cut WK ways; every operand goes from L2 straight to the
 // matrix instruction (a lane's four consecutive elements are four contraction steps), the next 16 steps requested
 // before the current ones' 16 instructions.  The products here are small (192 x 1024 x 1024 per sequence), so what
@@ -23,7 +23,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm64_kernel(const double*
                                                                    const double* __restrict__ B, double* __restrict__ C,
                                                                    int M, int N, int K, int Kb, int lda, int ldb, int ldc,
                                                                    int Mw, int Nw, size_t strideA, size_t strideB, size_t strideC,
-                                                                   const int32_t* __restrict__ a_rows, int a_rows_stride) {
+                                                                   const int32_t* __restrict__ a_rows, int a_rows_stride,
+                                                                   const double* __restrict__ shift, double node) {
   __shared__ double red[WM * WN][WK][4 * T * T][kWave];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int sub = lane & 15, kq = lane >> 4;
@@ -82,6 +83,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm64_kernel(const double*
 #pragma unroll
       for (int j = 0; j < 4; ++j) red[wt][wk][(x * T + y) * 4 + j][lane] = acc[x][y][j];
   __syncthreads();
+  const double theta = shift ? node * shift[blockIdx.z] : 0.0;
   // the WK waves of a tile add up its 4 T T registers in turn
 #pragma unroll
   for (int reg = wk; reg < 4 * T * T; reg += WK) {
@@ -90,6 +92,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm64_kernel(const double*
 #pragma unroll
     for (int w = 0; w < WK; ++w) sum += red[wt][w][reg][lane];
     const int i = i0 + 16 * (tile / T) + 4 * (reg & 3) + kq, j = j0 + 16 * (tile % T) + sub;
+    if (shift && i < M && j < N) sum = fma(-theta, A[(size_t)i * lda + j], sum);
     if (i < Mw && j < Nw) C[(size_t)i * ldc + j] = (i < M && j < N) ? sum : 0.0;
   }
 }
@@ -184,7 +187,8 @@ __device__ __forceinline__ void factor_panels(f64x4 a, const double (&least)[4],
 
 // The block's inverse factor.  Pivots below kPivotFloor times their vector's square (e0[j], row 4 j + kq) project nothing and
 // count as that (see chol_kernel); a block that has one is taken again with the checks.
-// out: the inverse in operand order; inv: the same, rows of floored pivots zero; returns the least pivot of the lane's rows.
+// out: the inverse in operand order; inv: the same, rows of floored pivots zero; returns the least pivot of the lane's rows, 0 if
+// one of them was floored, infinity for zero vectors.
 __device__ __forceinline__ double factor_block(f64x4 a, const double (&e0)[4], double* __restrict__ out, double* __restrict__ inv) {
   const int lane = threadIdx.x & (kWave - 1), sub = lane & 15, kq = lane >> 4;
   double f[4], d[4], least[4];
@@ -201,7 +205,7 @@ __device__ __forceinline__ double factor_block(f64x4 a, const double (&e0)[4], d
   for (int j = 0; j < 4; ++j) {
     const bool none = least[j] == INFINITY, floored = d[j] < least[j];
     const double piv = none ? 1.0 : (floored ? least[j] : d[j]), x = f[j] * rsqrt_f64(piv);
-    smallest = none ? smallest : fmin(smallest, piv);
+    smallest = none ? smallest : fmin(smallest, floored ? 0.0 : piv);
     out[op_index(4 * j + kq, sub)] = x;
     inv[op_index(4 * j + kq, sub)] = floored ? 0.0 : x;
   }
@@ -220,8 +224,10 @@ __device__ __forceinline__ double factor_block(f64x4 a, const double (&e0)[4], d
 // pivots, column, trailing blocks with four barriers a step, took 49.  Above 192 vectors a wave's blocks fill its registers.
 // A pivot below kPivotFloor of the vector's own square is rounding: it is set to that floor, which leaves the vector's
 // remainder at a size that the next pass can work on, and nothing is projected on it; a zero vector stays zero.
+// smallest (may be NULL): the least entry of L's diagonal of each sequence, 0 where a pivot was set to its floor.
 template <int NBW>
-__global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S, double* __restrict__ Lp, int nb) {
+__global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S, double* __restrict__ Lp, int nb,
+                                                   double* __restrict__ smallest) {
   __shared__ double col[kMaxFactorBlocks][272];   // current block column, rows at a pitch of 17
   __shared__ double sol[kMaxFactorBlocks][256];   // the same times the diagonal block's inverse, operand order
   __shared__ double inv[256];                     // inverse of the diagonal block, rows of floored pivots zero
@@ -256,6 +262,7 @@ __global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S,
 #pragma unroll
       for (int j = 0; j < 4; ++j) d[j] = -Sl[(16 + 4 * j) * ld + 16];
     __builtin_amdgcn_s_setprio(3);
+    double least = INFINITY;
     double e1[4];   // squares of the next block's vectors 4 j + kq, ahead of their use
 #pragma unroll
     for (int j = 0; j < 4; ++j) e1[j] = S[(size_t)(4 * j + kq) * (ld + 1)];
@@ -266,7 +273,7 @@ __global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S,
         e0[j] = e1[j];
         e1[j] = S[(size_t)(16 * min(k + 1, nb - 1) + 4 * j + kq) * (ld + 1)];
       }
-      factor_block(a, e0, Lp + (size_t)tri_block(nb, k, k) * 256, inv);
+      least = fmin(least, factor_block(a, e0, Lp + (size_t)tri_block(nb, k, k) * 256, inv));
       __syncthreads();   // B: the inverse, column k and the next diagonal block are in LDS
       if (k + 1 >= nb) break;
       if (k > 0)
@@ -296,6 +303,11 @@ __global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S,
       for (int t = 0; t < 4; ++t) dst[t] = -l4[t];
 #pragma unroll
       for (int j = 0; j < 4; ++j) a[j] = -(d[j] + y[j]);
+    }
+    if (smallest) {
+      least = fmin(least, shfl_xor_f64(least, 16));
+      least = fmin(least, shfl_xor_f64(least, 32));
+      if (lane == 0) smallest[blockIdx.x] = least < INFINITY ? sqrt(least) : 0.0;
     }
     return;
   }

@@ -186,12 +186,13 @@ struct FactorizePlan {
   float rest_share;         // share of the elements that the lists surely have room for
   int n_marks;              // places in a list that are kept: before every 256th token, and its end
   int max_lv, max_chunk, n_chunks;   // column maxima: 16-byte pieces side by side in a workgroup, tokens per chunk, chunks
-  size_t part, G, Xt, Yt, S, Lp, W, V, Jbuf, idle, sweep_max, order, Psi_t, total;  // workspace offsets (bytes)
+  size_t part, G, Xt, Yt, S, Lp, W, V, Jbuf, idle, shift, sweep_max, order, Psi_t, total;  // workspace offsets (bytes)
   size_t scale, flags, rest_where, rest, rest_count, marks, by_col, col_begin, psi_digits, psi_exps;
 };
 FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int n_sweeps, int kv_bytes);
 // k_pre [b, s, h_kv*d]; A [b, s_cap, r]; B [b, h_kv, r, d]; psi_out optional [b, r, D] fp64 (right singular vectors
-// as rows, after the sign convention); sigma_out optional [b, r] fp64 (singular values, strongest first)
+// as rows, after the sign convention); sigma_out optional [b, r] fp64 (singular values, strongest first); n_iter: subspace
+// steps, 0 for the default schedule
 hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, double* psi_out, double* sigma_out,
                             char* ws, const FactorizePlan& pl, int batch, int hkv, int d, int s, int s_cap, int r,
                             int n_iter, int n_sweeps, hipStream_t st);

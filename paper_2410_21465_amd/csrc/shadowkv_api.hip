@@ -683,7 +683,6 @@ int shadowkv_append_chunk(const shadowkv_params* params, const shadowkv_kv* k_pr
 
 constexpr int kFactorOversample = 32;  // extra vectors carried by the subspace iteration
 constexpr int kFactorSweeps = 9;       // most Jacobi sweeps of the Ritz step (192 vectors: six; later ones end at once)
-constexpr int kFactorIters = 16;       // default number of subspace iterations
 
 size_t shadowkv_factorize_workspace_bytes(const shadowkv_params* params) {
   Shape sh;
@@ -721,7 +720,7 @@ int shadowkv_factorize_keys(const shadowkv_params* params, const shadowkv_kv* k_
   rc = check_workspace(workspace, workspace_bytes, pl.total);
   if (rc != SHADOWKV_OK) return rc;
   hipError_t e = launch_factorize(k_pre, sh.eb, A, B, psi_out, sigma_out, static_cast<char*>(workspace), pl, sh.b, sh.hkv,
-                                  sh.d, sh.s, sh.cap, params->rank, n_iter ? n_iter : kFactorIters, kFactorSweeps,
+                                  sh.d, sh.s, sh.cap, params->rank, n_iter, kFactorSweeps,
                                   static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return fail_hip("factorize keys", e);
   return SHADOWKV_OK;

@@ -1,0 +1,60 @@
+"""The default schedule of shadowkv_factorize_keys (plain steps, then shifted ones) against sixteen plain steps asked for with
+n_iter, on spectra that converge slowly, fast, after a few strong directions, or not at all (-m gpu)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2410_21465_amd import shadowkv as S
+
+import parity_util as PU
+
+pytestmark = pytest.mark.gpu
+
+
+def _scales(kind, D):
+    x = torch.arange(D, dtype=torch.float64)
+    if kind == "flat":
+        return torch.ones(D, dtype=torch.float64)
+    if kind == "harmonic":
+        return 1.0 / (1.0 + x)
+    if kind == "exp60":
+        return torch.exp(-x / 60.0)
+    if kind == "exp20":
+        return torch.exp(-x / 20.0)
+    out = torch.exp(-x / 100.0)
+    out[:3] *= {"lead": 3e3, "far lead": 1e5}[kind]
+    return out
+
+
+# (spectrum, KV heads, head_dim, tokens, rank): more columns than vectors, from one more to eight times as many
+CASES = [("flat", 8, 64, 2048, 160), ("harmonic", 4, 128, 1500, 160), ("exp60", 3, 128, 1500, 48), ("exp20", 4, 64, 900, 96),
+         ("lead", 4, 128, 2048, 160), ("far lead", 4, 96, 1200, 48), ("exp60", 2, 64, 1000, 88), ("harmonic", 2, 96, 1000, 152),
+         ("flat", 1, 64, 500, 24)]
+
+
+@pytest.mark.parametrize("kind,h,d,s,r", CASES)
+def test_default_steps_come_as_close_as_sixteen_plain_ones(kind, h, d, s, r):
+    D = h * d
+    print(f"\n[case] {kind} h {h} d {d} s {s} r {r}", flush=True)
+    gen = torch.Generator(device="cpu").manual_seed(D + r)
+    scale = _scales(kind, D)[torch.randperm(D, generator=gen)]
+    k = (torch.randn(2, s, D, generator=gen, dtype=torch.float64) * scale).to(torch.bfloat16)
+    p = S.Params(batch=2, n_q_heads=h, n_kv_heads=h, head_dim=d, ctx_len=s, chunk_size=1, rank=r, n_outlier_chunks=0,
+                 topk_chunks=1, local_len=0)
+    out = {n: S.factorize_keys(p, k.cuda(), want_vectors=True, n_iter=n) for n in (0, 16)}
+    torch.cuda.synchronize()
+    for i in range(2):
+        K = k[i].double().numpy()
+        G = K.T @ K
+        lam = np.linalg.eigvalsh(G)[::-1]
+        res, miss = {}, {}
+        for n, got in out.items():
+            psi, sig = got["psi"][i].cpu().numpy(), got["sigma"][i].cpu().numpy()
+            assert np.abs(psi @ psi.T - np.eye(r)).max() < 1e-12
+            res[n] = np.linalg.norm(psi @ G - (sig ** 2)[:, None] * psi)
+            miss[n] = lam[:r].sum() - np.einsum("ij,ij->", psi @ G, psi)   # energy that the best subspace has more
+        print(f"[steps] residual / lam_1 {res[0] / lam[0]:.1e} (16: {res[16] / lam[0]:.1e}), energy {miss[0] / lam[0]:.1e} "
+              f"({miss[16] / lam[0]:.1e}), lam_(m+1) / lam_r {lam[min(r + 32, D - 1)] / lam[r - 1]:.2f}", flush=True)
+        # rounding: 1e-12 of the largest eigenvalue for sums of a few hundred terms
+        assert res[0] <= res[16] + 1e-12 * lam[0]
+        assert miss[0] <= miss[16] + 1e-12 * lam[0]
