@@ -448,20 +448,28 @@ __device__ __forceinline__ bool jacobi_active(const int32_t* sweep_max, int swee
   // (a stored cosine that is not a number counts as not done)
   return sweep == 0 || !(__int_as_float(sweep_max[sweep - 1]) < kJacobiDone);
 }
-// (c, s) of the rotation that makes two columns with squares al, be and product ga orthogonal: tan 2 theta = 2 ga / (be - al),
-// |theta| <= pi / 4, through cos 2 theta and two reciprocal square roots; the exponent is taken out first.
+// (c, s) of a rotation that makes two columns with squares al, be and product ga nearly orthogonal: t = tan theta with
+// tan 2 theta = 2 ga / (be - al), |theta| <= pi / 4, in fp32 with the exponent taken out first, which leaves 2^-22 of ga; then
+// c = 1 / sqrt(1 + t^2) and s = t c to fp64, so that the columns' lengths and what is accumulated lose nothing.  The angle in
+// fp64 takes the same number of sweeps; a round is a chain of latencies that begins with this.
 __device__ __forceinline__ void rotation(double al, double be, double ga, double& c, double& s) {
-  double d = be - al, g = 2.0 * ga;
+  const double d = be - al, g = 2.0 * ga;
   const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(d), fabs(g)));
-  d = ldexp(d, ex); g = ldexp(g, ex);
-  const double r = rsqrt_f64(fma(d, d, g * g));
-  const double c2 = fma(0.5 * fabs(d), r, 0.5), rc = rsqrt_f64(c2);
-  c = c2 * rc;
-  s = 0.5 * g * r * rc;
-  if (d < 0.0) s = -s;
+  const float df = (float)__builtin_amdgcn_ldexp(d, ex), gf = (float)__builtin_amdgcn_ldexp(g, ex);   // the larger in [1/2, 1], or both 0
+  const float den = fmaxf(fabsf(df) + __builtin_amdgcn_sqrtf(fmaf(df, df, gf * gf)), 0.25f);
+  const float tf = gf * __builtin_amdgcn_rcpf(den);
+  const double t = (double)(df < 0.0f ? -tf : tf);
+  c = rsqrt_f64(fma(t, t, 1.0));
+  s = t * c;
+}
+// lane J of each row of 16 in all lanes of the row
+template <int J>
+__device__ __forceinline__ double row_lane_f64(double x) {
+  return __longlong_as_double(__builtin_amdgcn_update_dpp(0ll, __double_as_longlong(x), 0x150 + J, 0xf, 0xf, true));
 }
 // step = sweep * (nb - 1) + st.  Workgroups [0, nb/2): step `step` on W (none when step == n_steps); [nb/2, nb): the step
 // before, on V.  J and idle (whether its J is the identity) alternate between two halves from step to step.
+// A round in which every pair is orthogonal to rounding at the start of the step is left out.
 __global__ __launch_bounds__(512) void jacobi_block_kernel(double* __restrict__ W, double* __restrict__ V,
                                                            double* __restrict__ Jbuf, int32_t* __restrict__ idle,
                                                            int32_t* __restrict__ sweep_max, int mp, int step, int n_steps,
@@ -469,9 +477,9 @@ __global__ __launch_bounds__(512) void jacobi_block_kernel(double* __restrict__ 
   constexpr int P = 33;                     // pitch of the 32 x 32 matrices in LDS
   __shared__ double red[8 * 3 * 256];       // partial products of the waves; then the second copy of S, and J
   __shared__ double S0[32 * P];
-  __shared__ float wmax[8];
+  __shared__ uint2 found[8];                // largest cosine and rounds of each wave's pairs
   __shared__ double2 cs[2][16];             // rotations of the last two rounds
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int sub = lane & 15, kq = lane >> 4;
   const int nb = mp / 16, np = nb / 2, b = blockIdx.y, batch = gridDim.y;
   const bool on_v = (int)blockIdx.x >= np;
@@ -487,33 +495,46 @@ __global__ __launch_bounds__(512) void jacobi_block_kernel(double* __restrict__ 
   else { pb = (st + pair) % (nb - 1); qb = (st - pair + (nb - 1)) % (nb - 1); }
   double* M = (on_v ? V : W) + (size_t)b * mp * mp;
   auto row = [&](int i) { return M + (size_t)((i < 16 ? pb * 16 : qb * 16 - 16) + i) * mp; };
-  const double* Js;                         // J, row p, column q at Js[p * pitch + q]
-  int pitch;
-  if (on_v) {
-    if (idle[slot]) return;
-    Js = Jg; pitch = 32;
-  } else {
-    // products of the 32 columns: tiles (0,0), (0,1), (1,1), the contraction dealt to the waves 16 at a time
+  if (on_v && idle[slot]) return;
+  // what J will be applied to: 16 entries of the 32 columns per wave at a time, the first two pieces requested ahead
+  double xa[2][8];
+  auto request = [&](double (&x)[8], int c0) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) x[t] = row(4 * t + kq)[c0 + sub];
+  };
+  const double* Js = Jg;                    // J, row p, column q at Js[p * pitch + q]
+  int pitch = 32;
+  if (!on_v) {
+    // products of the 32 columns: tiles (0,0), (0,1), (1,1), the contraction dealt to the waves 8 at a time, all requested at once
+    constexpr int NP = (kMaxFactorBlocks * 2 + 7) / 8;
     f64x4 g[3];
 #pragma unroll
     for (int t = 0; t < 3; ++t) g[t] = f64x4{0.0, 0.0, 0.0, 0.0};
-    const double* r0 = row(sub) + 4 * kq;
-    const double* r1 = row(16 + sub) + 4 * kq;
-    for (int k0 = 16 * wave; k0 < mp; k0 += 16 * 8) {
-      const double2 a0 = *reinterpret_cast<const double2*>(r0 + k0), a1 = *reinterpret_cast<const double2*>(r0 + k0 + 2);
-      const double2 c0 = *reinterpret_cast<const double2*>(r1 + k0), c1 = *reinterpret_cast<const double2*>(r1 + k0 + 2);
-      const double x[4] = {a0.x, a0.y, a1.x, a1.y}, y[4] = {c0.x, c0.y, c1.x, c1.y};
+    const double* r0 = row(sub) + 2 * kq + 8 * wave;
+    const double* r1 = row(16 + sub) + 2 * kq + 8 * wave;
+    double2 x[NP], y[NP];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        g[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[e], x[e], g[0], 0, 0, 0);
-        g[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[e], y[e], g[1], 0, 0, 0);
-        g[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(y[e], y[e], g[2], 0, 0, 0);
+    for (int i = 0; i < NP; ++i)
+      if (8 * (wave + 8 * i) < mp) {
+        x[i] = *reinterpret_cast<const double2*>(r0 + 64 * i);
+        y[i] = *reinterpret_cast<const double2*>(r1 + 64 * i);
       }
-    }
+#pragma unroll
+    for (int i = 0; i < NP; ++i)
+      if (8 * (wave + 8 * i) < mp) {
+        g[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i].x, x[i].x, g[0], 0, 0, 0);
+        g[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i].x, y[i].x, g[1], 0, 0, 0);
+        g[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(y[i].x, y[i].x, g[2], 0, 0, 0);
+        g[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i].y, x[i].y, g[0], 0, 0, 0);
+        g[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i].y, y[i].y, g[1], 0, 0, 0);
+        g[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(y[i].y, y[i].y, g[2], 0, 0, 0);
+      }
 #pragma unroll
     for (int t = 0; t < 3; ++t)
 #pragma unroll
       for (int j = 0; j < 4; ++j) red[(wave * 3 + t) * 256 + (4 * j + kq) * 16 + sub] = g[t][j];
+    if (16 * wave < mp) request(xa[0], 16 * wave);
+    if (16 * (wave + 8) < mp) request(xa[1], 16 * (wave + 8));
     __syncthreads();
     for (int i = threadIdx.x; i < 3 * 256; i += 512) {
       double v = 0.0;
@@ -525,97 +546,126 @@ __global__ __launch_bounds__(512) void jacobi_block_kernel(double* __restrict__ 
       if (t == 2) S0[(16 + r) * P + 16 + c] = v;
     }
     __syncthreads();
-    // largest cosine among the pairs this step is about
-    float big = 0.0f;
+    // largest cosine among the pairs this step is about (its reciprocal roots from the hardware's estimates: a few parts in
+    // 10^7, as it only says whether to go on), and the rounds in which there is something to rotate
+    uint32_t big = 0, rounds = 0;           // (cosines are >= 0: their bits are in their order, not-a-numbers above all)
     for (int i = threadIdx.x; i < 1024; i += 512) {
       const int r = i >> 5, c = i & 31;
-      if (r < c && (st == 0 || (r < 16 && c >= 16))) {
-        const double ga = fabs(S0[r * P + c]), n2 = sqrt(fmax(S0[r * P + r], 0.0)) * sqrt(fmax(S0[c * P + c], 0.0));
-        if (!(ga <= 1e-300)) { const float x = (float)(ga / n2); big = !(x <= big) ? x : big; }
+      const double ga = fabs(S0[r * P + c]), al = S0[r * P + r], be = S0[c * P + c];
+      if (r < c && (st == 0 || (r < 16 && c >= 16)) && !(ga <= 1e-300)) {
+        const float x = (float)(ga * __builtin_amdgcn_rsq(al) * __builtin_amdgcn_rsq(be));
+        big = max(big, __float_as_uint(x));
+        // (the round of a pair, see members below: (c - r) mod 16, or with 31 the other one, else half the sum mod 31)
+        if (!(x <= 2e-16f)) rounds |= 1u << (st != 0 ? (c - r) & 15 : c == 31 ? r : (r + c) * 16 % 31);
       }
     }
-#pragma unroll
-    for (int x = 32; x >= 1; x >>= 1) { const float o = __shfl_xor(big, x, kWave); big = !(o <= big) ? o : big; }
-    if (lane == 0) wmax[wave] = big;
+    big = wave_max_u32(big);
+    rounds = wave_or_u32(rounds);
+    if (lane == 0) found[wave] = make_uint2(big, rounds);
     double* S1 = red;                      // (the partial products have been read)
     double* J = red + 32 * P;
     for (int i = threadIdx.x; i < 32 * P; i += 512) J[i] = i / P == i % P ? 1.0 : 0.0;
     __syncthreads();
-    big = wmax[0];
 #pragma unroll
-    for (int w = 1; w < 8; ++w) big = !(wmax[w] <= big) ? wmax[w] : big;
-    const bool rest = big <= 2e-16f;       // what the rounding of the products leaves: nothing to rotate
+    for (int w = 0; w < 8; ++w) { const uint2 f = found[w]; big = max(big, f.x); rounds |= f.y; }
+    rounds = (uint32_t)__builtin_amdgcn_readfirstlane((int)rounds);
     if (threadIdx.x == 0) {
-      atomicMax(&sweep_max[sweep], __float_as_int(big));
-      idle[slot] = rest ? 1 : 0;
+      atomicMax(&sweep_max[sweep], (int)big);
+      idle[slot] = rounds ? 0 : 1;
     }
-    if (rest) return;
-    const int rounds = st == 0 ? 31 : 16;
-    double *Sa = S0, *Sb = S1;
-    // waves 0-3 rotate S, each lane forming the rotation of its column's pair (one such wave per SIMD); waves 4-7 apply
-    // the rotations of the round before to J, taken from LDS
-    for (int t = 0; t <= rounds; ++t) {
-      // the 16 disjoint pairs of round u: across the two blocks, or the circle method over all 32 columns
-      auto members = [&](int u, int i, int& p, int& q) {
-        if (st != 0) { p = i; q = 16 + ((i + u) & 15); }
-        else if (i == 0) { p = 31; q = u; }
-        else { p = u + i; p -= p >= 31 ? 31 : 0; q = u - i; q += q < 0 ? 31 : 0; }
+    if (!rounds) return;
+    // the 16 disjoint pairs of round u: across the two blocks, or the circle method over all 32 columns
+    auto members = [&](int u, int i, int& p, int& q) {
+      if (st != 0) { p = i; q = 16 + ((i + u) & 15); }
+      else if (i == 0) { p = 31; q = u; }
+      else { p = u + i; p -= p >= 31 ? 31 : 0; q = u - i; q += q < 0 ? 31 : 0; }
+    };
+    if (wave < 4) {
+      // waves 0-3 (one per SIMD) rotate S: 16 lanes take the rows of pair pu, each with the columns of another pair, the first
+      // with its own, so that the rows' rotation is what lane 0 of the 16 has formed for its columns
+      const int pu = wave * 4 + kq, pc = (pu + sub) & 15;
+      int o[7];   // places of the pair's three products and of the four entries
+      auto places = [&](int u) {
+        int p, q, r, t;
+        members(u, pc, p, q);
+        members(u, pu, r, t);
+        o[0] = p * P + p; o[1] = q * P + q; o[2] = p * P + q;
+        o[3] = r * P + p; o[4] = r * P + q; o[5] = t * P + p; o[6] = t * P + q;
       };
-      int p, q;
-      if (wave < 4) {
-        if (t < rounds) {
-          members(t, sub, p, q);
-          const double al = Sa[p * P + p], be = Sa[q * P + q], ga = Sa[p * P + q];
-          const int u = wave * 4 + kq;      // this lane: rows of pair u, columns of pair sub
-          int pu, qu;
-          members(t, u, pu, qu);
-          const double pp = Sa[pu * P + p], pq = Sa[pu * P + q], qp = Sa[qu * P + p], qq = Sa[qu * P + q];
-          double c = 1.0, sn = 0.0;
-          // (roots, not squares: al and be are fourth powers of singular values, al * be need not fit in fp64)
-          if (fabs(ga) > 1e-300 && fabs(ga) > 1e-17 * (__builtin_amdgcn_sqrt(fmax(al, 0.0)) * __builtin_amdgcn_sqrt(fmax(be, 0.0))))
-            rotation(al, be, ga, c, sn);
-          if (threadIdx.x < 16) cs[t & 1][sub] = make_double2(c, sn);
-          const double cu = __shfl(c, u, kWave), su = __shfl(sn, u, kWave);
-          const double tp = cu * pp - su * qp, tq = cu * pq - su * qq, bp = su * pp + cu * qp, bq = su * pq + cu * qq;
-          const bool own = u == sub && sn != 0.0;   // (the rotated pair itself: zero by construction)
-          Sb[pu * P + p] = c * tp - sn * tq; Sb[pu * P + q] = own ? 0.0 : sn * tp + c * tq;
-          Sb[qu * P + p] = own ? 0.0 : c * bp - sn * bq; Sb[qu * P + q] = sn * bp + c * bq;
-        }
-      } else if (t > 0) {                  // J: columns of pair sub, eight rows per wave
-        members(t - 1, sub, p, q);
-        const double2 r = cs[(t - 1) & 1][sub];
+      places(__ffs(rounds) - 1);
+      const double* Sa = S0;
+      double* Sb = S1;
+      for (int t = 0; rounds; ++t) {
+        rounds &= rounds - 1;
+        const double al = Sa[o[0]], be = Sa[o[1]], ga = Sa[o[2]];
+        const double pp = Sa[o[3]], pq = Sa[o[4]], qp = Sa[o[5]], qq = Sa[o[6]];
+        double c, sn;
+        rotation(al, be, ga, c, sn);
+        if (wave == 0 && kq == 0) cs[t & 1][pc] = make_double2(c, sn);
+        const double cu = row_lane_f64<0>(c), su = row_lane_f64<0>(sn);
+        const double tp = cu * pp - su * qp, tq = cu * pq - su * qq, bp = su * pp + cu * qp, bq = su * pq + cu * qq;
+        Sb[o[3]] = c * tp - sn * tq; Sb[o[4]] = sn * tp + c * tq;
+        Sb[o[5]] = c * bp - sn * bq; Sb[o[6]] = sn * bp + c * bq;
+        places((__ffs(rounds) - 1) & 31);
+        __syncthreads();
+        double* tmp = const_cast<double*>(Sa); Sa = Sb; Sb = tmp;
+      }
+    } else {
+      // waves 4-7 apply the rotations of the round before to J: columns of pair sub, eight rows per wave
+      double* jr = J + ((wave - 4) * 8 + kq * 2) * P;
+      __syncthreads();
+      for (int t = 0; rounds; ++t) {
+        int p, q;
+        members(__ffs(rounds) - 1, sub, p, q);
+        rounds &= rounds - 1;
+        const double2 r = cs[t & 1][sub];
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
-          double* jr = J + ((wave - 4) * 8 + kq * 2 + e) * P;
-          const double x = jr[p], y = jr[q];
-          jr[p] = r.x * x - r.y * y; jr[q] = r.y * x + r.x * y;
+          const double x = jr[e * P + p], y = jr[e * P + q];
+          jr[e * P + p] = r.x * x - r.y * y; jr[e * P + q] = r.y * x + r.x * y;
         }
+        if (rounds) __syncthreads();
       }
-      __syncthreads();
-      double* tmp = Sa; Sa = Sb; Sb = tmp;
     }
-    for (int i = threadIdx.x; i < 1024; i += 512) Jg[i] = J[(i >> 5) * P + (i & 31)];
+    __syncthreads();
     Js = J; pitch = P;
+  } else {
+    if (16 * wave < mp) request(xa[0], 16 * wave);
+    if (16 * (wave + 8) < mp) request(xa[1], 16 * (wave + 8));
   }
-  // new column q = sum_p J[p][q] column p, 16 entries of the 32 columns per wave at a time
+  // new column q = sum_p J[p][q] column p
   double ja[2][8];
 #pragma unroll
   for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
     for (int t = 0; t < 8; ++t) ja[mt][t] = Js[(4 * t + kq) * pitch + 16 * mt + sub];
-  for (int c0 = 16 * wave; c0 < mp; c0 += 16 * 8) {
-    double x[8];
+  auto apply = [&](int c0, bool two) {      // one piece, or two, 128 entries apart
+    f64x4 y[2][2];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) x[t] = row(4 * t + kq)[c0 + sub];
+    for (int mt = 0; mt < 2; ++mt) y[0][mt] = y[1][mt] = f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
-      f64x4 y = {0.0, 0.0, 0.0, 0.0};
+    for (int t = 0; t < 8; ++t)
 #pragma unroll
-      for (int t = 0; t < 8; ++t) y = __builtin_amdgcn_mfma_f64_16x16x4f64(ja[mt][t], x[t], y, 0, 0, 0);
+      for (int mt = 0; mt < 2; ++mt) {
+        y[0][mt] = __builtin_amdgcn_mfma_f64_16x16x4f64(ja[mt][t], xa[0][t], y[0][mt], 0, 0, 0);
+        if (two) y[1][mt] = __builtin_amdgcn_mfma_f64_16x16x4f64(ja[mt][t], xa[1][t], y[1][mt], 0, 0, 0);
+      }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) row(16 * mt + 4 * j + kq)[c0 + sub] = y[j];
-    }
+    for (int x = 0; x < 2; ++x)
+      if (x == 0 || two)
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) row(16 * mt + 4 * j + kq)[c0 + 128 * x + sub] = y[x][mt][j];
+  };
+  if (16 * (wave + 8) < mp) apply(16 * wave, true);
+  else if (16 * wave < mp) apply(16 * wave, false);
+  if (16 * (wave + 16) < mp) {              // more than 256 vectors
+    request(xa[0], 16 * (wave + 16));
+    apply(16 * (wave + 16), false);
   }
+  if (!on_v)
+    for (int i = threadIdx.x; i < 1024; i += 512) Jg[i] = Js[(i >> 5) * P + (i & 31)];
 }
 
 }  // namespace skv
