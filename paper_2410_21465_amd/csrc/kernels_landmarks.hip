@@ -4,7 +4,7 @@
 // (ascending chunk order) and the gather of the outlier chunks' keys and values.
 //
 // chunk_stats: 16 lanes own one chunk (d/16 columns each, all c rows), so the mean needs
-// no cross-lane traffic.  For c <= 8 the rows stay in registers (one pass over HBM).  The
+// no cross-lane traffic.  For c <= 8 and c = 16 the rows stay in registers (one pass over HBM).  The
 // per-row dot products <mean, k_t> and squared norms are partial sums over a lane's columns;
 // a transposed butterfly over the 16 lanes (DPP pairings xor 8, 7, 2, 1) leaves row t's dot
 // in lane t and its squared norm in lane t+8, so each cosine -- an fp64 sqrt and divide -- is
@@ -61,15 +61,60 @@ __device__ __forceinline__ double reduce_scatter16_f64(const double (&v)[16], in
   return d[0];
 }
 
-// REG: the chunk's rows are kept in registers (c <= 8); otherwise they are read twice, eight at a time.
-// EB: bytes per stored element (2 = bf16, 1 = FP8 E5M2); the means are written in the same type.
-template <int D, bool REG, int EB>
+// The same of 8 values: lane i gets the sum of v[i % 8].
+__device__ __forceinline__ double reduce_scatter8_f64(const double (&v)[8], int sub) {
+  double a[8], b[4], c[2], d[1];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a[i] = v[i] + dpp_f64<kDppXor8>(v[i]);
+  scatter_stage<8, kDppXor7>(a, b, (sub & 4) != 0);
+  scatter_stage<4, kDppXor2>(b, c, (sub & 2) != 0);
+  scatter_stage<2, kDppXor1>(c, d, (sub & 1) != 0);
+  return d[0];
+}
+
+// EPL means rounded once to the storage type, as pack_kv does it.  Where all of a wave's are normal numbers of the type, in the
+// upper words of the fp64 numbers: add just below half a unit of the last place, one more if that place is odd or anything
+// stands in the lower word, and move the exponent (a carry into the exponent, up to infinity, is the right result).
+template <int EPL, int EB>
+__device__ __forceinline__ void pack_means(const double (&x)[EPL], uint32_t (&w)[RawWords<EPL, EB>::n]) {
+  constexpr int DROP = EB == 2 ? 13 : 18;                                    // bits of the upper word below the last place
+  constexpr uint32_t BIAS = (uint32_t)(EB == 2 ? 1023 - 127 : 1023 - 15) << 20;
+  constexpr uint32_t LO = BIAS + (1u << 20), HI = BIAS + ((EB == 2 ? 255u : 31u) << 20);   // normal numbers: [LO, HI)
+  uint32_t least = 0xffffffffu, most = 0;
+#pragma unroll
+  for (int e = 0; e < EPL; ++e) {
+    const uint32_t m = (uint32_t)__double2hiint(x[e]) & 0x7fffffffu;
+    least = min(least, m);
+    most = max(most, m);
+  }
+  if (__builtin_expect(__any(least < LO || most >= HI), 0)) { pack_kv<EPL, EB>(x, w); return; }
+#pragma unroll
+  for (int i = 0; i < RawWords<EPL, EB>::n; ++i) w[i] = 0u;
+#pragma unroll
+  for (int e = 0; e < EPL; ++e) {
+    const uint32_t hi = (uint32_t)__double2hiint(x[e]);
+    const uint32_t up = ((hi >> DROP) & 1u) | (__double2loint(x[e]) != 0 ? 1u : 0u);
+    const uint32_t t = hi + ((1u << (DROP - 1)) - 1u - BIAS) + up;
+    const uint32_t code = ((t >> DROP) & (EB == 2 ? 0x7fffu : 0x7fu)) | ((hi >> (EB == 2 ? 16 : 24)) & (EB == 2 ? 0x8000u : 0x80u));
+    w[e * EB / 4] |= code << (8 * EB * (e % (4 / EB)));
+  }
+}
+
+// R > 0: chunks of R rows (4, 8, 16), kept in registers; R = 0: up to 8 rows in registers; R < 0: any number, read twice, eight
+// at a time.  EB: bytes per stored element (2 = bf16, 1 = FP8 E5M2); the means are written in the same type.
+// FP8 keys are bound by the vector instructions (some 850 a wave of four chunks with rows guarded and rounded one at a time:
+// 75 us for 3 x 61K tokens, 8 KV heads of 128), bf16 keys by HBM and these together.
+template <int D, int R, int EB>
 __global__ __launch_bounds__(256) void chunk_stats_kernel(const uint8_t* __restrict__ k_rope,
                                                           uint8_t* __restrict__ chunk_mean,
-                                                          double* __restrict__ chunk_min_cos, int s, int c,
-                                                          int n_ch) {
+                                                          double* __restrict__ chunk_min_cos, int s, int c_any,
+                                                          int n_ch, double inv_c) {
   constexpr int EPL = D / 16;
   constexpr int RW = RawWords<EPL, EB>::n;
+  constexpr bool EXACT = R > 0, REG = R >= 0;
+  constexpr int HELD = EXACT ? R : 8;            // rows held in registers
+  constexpr int GROUP = R == 4 ? 4 : 8;          // rows whose cosines are formed together
+  const int c = EXACT ? R : c_any;
   const int unit = blockIdx.y;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int sub = lane & 15, cg = lane >> 4;
@@ -77,74 +122,80 @@ __global__ __launch_bounds__(256) void chunk_stats_kernel(const uint8_t* __restr
   const bool ok = j < n_ch;
   const uint8_t* base = k_rope + (((size_t)unit * s + (size_t)(ok ? j : 0) * c) * D + sub * EPL) * EB;
 
-  uint32_t raw[8][RW];
+  uint32_t raw[HELD][RW];
   double mean[EPL];
 #pragma unroll
   for (int e = 0; e < EPL; ++e) mean[e] = 0.0;
-  auto load_rows = [&](int t0) {   // rows t0 .. t0 + 7 of the chunk; beyond its end zeros (0.0 in either type)
+  auto load_rows = [&](int t0) {   // rows t0 .. t0 + HELD - 1 of the chunk; beyond its end zeros (0.0 in either type)
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
+    for (int t = 0; t < HELD; ++t) {
+      if constexpr (EXACT) {
+        load_raw<EPL, EB>(base + (size_t)t * D * EB, raw[t]);
+      } else {
 #pragma unroll
-      for (int e = 0; e < RW; ++e) raw[t][e] = 0u;
-      if (t0 + t < c) load_raw<EPL, EB>(base + (size_t)(t0 + t) * D * EB, raw[t]);
+        for (int e = 0; e < RW; ++e) raw[t][e] = 0u;
+        if (t0 + t < c) load_raw<EPL, EB>(base + (size_t)(t0 + t) * D * EB, raw[t]);
+      }
     }
   };
-  for (int t0 = 0; t0 < (REG ? 8 : c); t0 += 8) {
+  for (int t0 = 0; t0 < (REG ? 1 : c); t0 += 8) {
     load_rows(t0);
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
+    for (int t = 0; t < HELD; ++t) {
       float x[EPL];
       unpack_kv<EPL, EB>(raw[t], x);
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) mean[e] += (double)x[e];
+      for (int e = 0; e < EPL; ++e) mean[e] = EXACT && t == 0 ? (double)x[e] : mean[e] + (double)x[e];
     }
   }
   // sum / c: the multiplication by 1/c is exact (and identical to the division) when c is a power of two
-  const bool pow2 = (c & (c - 1)) == 0;
-  const double inv_c = 1.0 / (double)c;
+  const bool pow2 = EXACT || (c & (c - 1)) == 0;
   double cn2 = 0.0;
 #pragma unroll
   for (int e = 0; e < EPL; ++e) {
-    mean[e] = pow2 ? mean[e] * inv_c : mean[e] / (double)c;
-    cn2 = fma(mean[e], mean[e], cn2);
+    mean[e] = pow2 ? fma(mean[e], inv_c, 0.0) : mean[e] / (double)c;   // (a sum of negative zeros is a positive one)
+    cn2 = e == 0 ? mean[e] * mean[e] : fma(mean[e], mean[e], cn2);
   }
   const double cn = fmax(sqrt(allsum16_f64(cn2)), 1e-8);
 
   double mn = INFINITY;
-  for (int t0 = 0; t0 < (REG ? 8 : c); t0 += 8) {
-    if constexpr (!REG) {
-      load_rows(t0);
-    } else if constexpr (EB == 1) {
-      // FP8 rows are widened again here: kept as fp64 they take 128 registers, and with half the bytes per row it is waves
-      // in flight that the loads need (3 x 61K tokens, 8 KV heads of 128: 84 -> 76 us; bf16 rows, whose loads fill the
-      // memory system from two waves per SIMD, lose: 937 -> 960 us at 16 x 128K)
+  if constexpr (REG && (EB == 1 || R == 16)) {
+    // FP8 rows are widened again here: kept as fp64 they take 128 registers, and with half the bytes per row it is waves
+    // in flight that the loads need (3 x 61K tokens, 8 KV heads of 128: 84 -> 76 us; bf16 rows, whose loads fill the
+    // memory system from two waves per SIMD, lose: 937 -> 960 us at 16 x 128K)
 #pragma unroll
-      for (int t = 0; t < 8; ++t)
+    for (int t = 0; t < HELD; ++t)
 #pragma unroll
-        for (int e = 0; e < RW; ++e) asm volatile("" : "+v"(raw[t][e]));
-    }
-    double v[16];  // v[t] = partial <mean, k_t>, v[8 + t] = partial |k_t|^2
+      for (int e = 0; e < RW; ++e) asm volatile("" : "+v"(raw[t][e]));
+  }
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
+  for (int t0 = 0; t0 < (REG ? HELD : c); t0 += GROUP) {
+    if constexpr (!REG) load_rows(t0);
+    double v[2 * GROUP];  // v[t] = partial <mean, k_t>, v[GROUP + t] = partial |k_t|^2
+#pragma unroll
+    for (int t = 0; t < GROUP; ++t) {
       double dot = 0.0, kn2 = 0.0;
       float x[EPL];
-      unpack_kv<EPL, EB>(raw[t], x);
+      unpack_kv<EPL, EB>(raw[REG ? t0 + t : t], x);
 #pragma unroll
       for (int e = 0; e < EPL; ++e) {
         const double xd = (double)x[e];
-        dot = fma(mean[e], xd, dot);
-        kn2 = fma(xd, xd, kn2);
+        dot = e == 0 ? mean[e] * xd : fma(mean[e], xd, dot);
+        kn2 = e == 0 ? xd * xd : fma(xd, xd, kn2);
       }
-      v[t] = dot; v[8 + t] = kn2;
+      v[t] = dot; v[GROUP + t] = kn2;
     }
-    const double mine = reduce_scatter16_f64(v, sub);   // lane t: dot of row t0 + t, lane 8 + t: its squared norm
-    const double kn2 = dpp_f64<kDppXor8>(mine);
-    if (sub < min(8, c - t0)) mn = fmin(mn, mine / (cn * fmax(sqrt(kn2), 1e-8)));
+    // lane t: dot of row t0 + t, lane GROUP + t: its squared norm (groups of four: the same again eight lanes on)
+    double mine, kn2;
+    if constexpr (GROUP == 8) { mine = reduce_scatter16_f64(v, sub); kn2 = dpp_f64<kDppXor8>(mine); }
+    else { mine = reduce_scatter8_f64(v, sub); kn2 = dpp_f64<0x124>(mine); }   // row_ror:4
+    if ((sub & (2 * GROUP - 1)) < (EXACT ? GROUP : min(8, c - t0))) mn = fmin(mn, mine / (cn * fmax(sqrt(kn2), 1e-8)));
   }
   mn = allmin16_f64(mn);
   if (ok) {
     uint32_t hm[RW];
-    pack_kv<EPL, EB>(mean, hm);
+    if constexpr (D * EB < 256) pack_means<EPL, EB>(mean, hm);
+    else pack_kv<EPL, EB>(mean, hm);   // (bound by memory; 16 x 128K, c = 8: 1146 us against 1154)
     store_raw<EPL, EB>(chunk_mean + (((size_t)unit * n_ch + j) * D + sub * EPL) * EB, hm);
     if (sub == 0) chunk_min_cos[(size_t)unit * n_ch + j] = mn;
   }
@@ -205,10 +256,20 @@ hipError_t launch_chunk_stats(const void* k_rope, int kv_bytes, void* chunk_mean
   dim3 grid((n_ch + 15) / 16, units), block(256);
   const uint8_t* kr = static_cast<const uint8_t*>(k_rope);
   uint8_t* cm = static_cast<uint8_t*>(chunk_mean);
-#define SKV_STATS(D_, EB_)                                                                                         \
-  do {                                                                                                             \
-    if (c <= 8) hipLaunchKernelGGL((chunk_stats_kernel<D_, true, EB_>), grid, block, 0, st, kr, cm, chunk_min_cos, s, c, n_ch); \
-    else hipLaunchKernelGGL((chunk_stats_kernel<D_, false, EB_>), grid, block, 0, st, kr, cm, chunk_min_cos, s, c, n_ch);       \
+  const double inv_c = 1.0 / (double)c;
+  // Rows counted by the compiler need no guards and chunks of four no work for eight (16 x 128K of 128: 1725 -> 1395 us for the
+  // whole call, FP8 476 -> 390; c = 16, read once instead of twice: 4 x 128K 367 -> 295).  Chunks of eight gain in FP8 (3 x 61K
+  // 97 -> 93) and heads of 96 (4 x 128K 256 -> 247); bf16 rows of 256 bytes, all requested at once, lose (16 x 128K 1145 ->
+  // 1158: the memory system is full either way) and stay with the guarded form.
+#define SKV_STATS_R(D_, R_, EB_)                                                                                  \
+  hipLaunchKernelGGL((chunk_stats_kernel<D_, R_, EB_>), grid, block, 0, st, kr, cm, chunk_min_cos, s, c, n_ch, inv_c)
+#define SKV_STATS(D_, EB_)                                                                                        \
+  do {                                                                                                            \
+    if (c == 8 && D_ * EB_ < 256) SKV_STATS_R(D_, 8, EB_);\
+    else if (c == 4) SKV_STATS_R(D_, 4, EB_);                                                                     \
+    else if (c == 16) SKV_STATS_R(D_, 16, EB_);                                                                   \
+    else if (c <= 8) SKV_STATS_R(D_, 0, EB_);                                                                     \
+    else SKV_STATS_R(D_, -1, EB_);                                                                                \
   } while (0)
   switch (d * 4 + kv_bytes) {
     case 64 * 4 + 2: SKV_STATS(64, 2); break;
@@ -220,6 +281,7 @@ hipError_t launch_chunk_stats(const void* k_rope, int kv_bytes, void* chunk_mean
     default: return hipErrorInvalidValue;
   }
 #undef SKV_STATS
+#undef SKV_STATS_R
   return hipGetLastError();
 }
 
