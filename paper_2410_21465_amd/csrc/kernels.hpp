@@ -9,7 +9,9 @@
 namespace skv {
 
 constexpr int kMaxHalfDim = 64;   // head_dim <= 128
-constexpr int kScoreTile = 256;   // landmark rows per scoring workgroup
+constexpr int kScoreTile = 256;   // landmark rows per scoring workgroup, at most
+// workgroups of four waves with `tiles` tiles of 16 rows each, for n_c landmark rows
+inline int score_tile_count(int n_c, int tiles) { return (n_c + 64 * tiles - 1) / (64 * tiles); }
 
 // Rotary frequencies, in revolutions per position (inv_freq / 2 pi), fp64, by value.
 struct RopeFreqs {
@@ -21,8 +23,11 @@ struct RopeFreqs {
 // per tile, fp64.
 // landmarks [units, nc_stride, d]: n_c valid rows per unit.
 // kv_bytes (here and below): bytes per element of the KV-cache tensors, 2 = bf16, 1 = FP8 E5M2.
+// tiles: 16-row tiles per wave (1, 2 or 4; a workgroup of four waves makes one pair of partials per head, n_tiles =
+// score_tile_count(n_c, tiles)); score_tiles: how many the sizes call for.
+int score_tiles(int units, int G, int n_c, int kv_bytes);
 hipError_t launch_score(const bf16_t* q, const void* landmarks, int kv_bytes, float* logits, int ld, double2* partials,
-                        int batch, int hq, int hkv, int d, int n_c, int nc_stride, double scale, hipStream_t st);
+                        int batch, int hq, int hkv, int d, int n_c, int nc_stride, double scale, int tiles, hipStream_t st);
 
 // ---- ArgTopK -------------------------------------------------------------------
 // Attention over the resident rows [outliers ; recent] of every unit, done by extra workgroups of the selection's

@@ -16,10 +16,11 @@
 // = 16*k + 4*block + (i for A | j for B), result lane = 16*i + 4*block + j.
 // Here i = query head (4), j = landmark row inside the block (4 blocks = 16 rows),
 // k = which 16-byte piece of each 64-byte row segment the lane loads.  A wave covers
-// 64 rows (four 16-row tiles, all loads issued before the first MFMA), a workgroup 256.
+// NT 16-row tiles (one, two or four, see score_tiles; all loads issued before the first MFMA), a workgroup
+// four times as many.
 // Result lane 16*i + r holds the logit of head i, row r of the tile: it stores it
-// (16 consecutive floats per head) and keeps the fp64 value until the wave's four tiles are
-// done, when the 64 rows' (max, sum exp) are formed at once (row16_lse) and merged over the
+// (16 consecutive floats per head) and keeps the fp64 value until the wave's tiles are
+// done, when its rows' (max, sum exp) are formed at once (row16_lse) and merged over the
 // workgroup; the selection kernel makes each head's log-sum-exp of these.
 #include "kernels.hpp"
 
@@ -40,20 +41,23 @@ __device__ __forceinline__ void lse_merge(double& m, double& s, double m2, doubl
   if (m2 > m) { s = s * e + s2; m = m2; } else { s += s2 * e; }
 }
 
-// (max, sum exp(p - max)) over four values per lane and the 16 lanes of a row, in every lane of the row.  One maximum first,
+// (max, sum exp(p - max)) over NT values per lane and the 16 lanes of a row, in every lane of the row.  One maximum first,
 // then every value against it: no branches and one exponential per value (merging (m, s) pairs value by value took a
 // branch each, a third of the kernel's vector instructions with FP8 landmarks: 83 us against 77 at 16 x 128K, and 41 against
 // 32 for one sequence of 1M tokens with 16 heads per group).  A value equal to the maximum counts 1; rows that do not exist
 // carry -inf and count 0.  (Infinite logits end as NaN: where two waves meet the same one, lse_merge subtracts it from itself.)
-__device__ __forceinline__ void row16_lse(const double (&p)[4], double& M, double& S) {
-  M = fmax(fmax(p[0], p[1]), fmax(p[2], p[3]));
+template <int NT>
+__device__ __forceinline__ void row16_lse(const double (&p)[NT], double& M, double& S) {
+  M = p[0];
+  if constexpr (NT >= 2) M = fmax(M, p[1]);
+  if constexpr (NT == 4) M = fmax(M, fmax(p[2], p[3]));
   M = fmax(M, dpp_f64<0x128>(M, M));   // row_ror 8, 4, 2, 1
   M = fmax(M, dpp_f64<0x124>(M, M));
   M = fmax(M, dpp_f64<0x122>(M, M));
   M = fmax(M, dpp_f64<0x121>(M, M));
   S = 0.0;
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
+  for (int t = 0; t < NT; ++t) {
     const double e = exp_neg(p[t] - M);
     S += p[t] == M ? (M == -INFINITY ? 0.0 : 1.0) : e;
   }
@@ -68,7 +72,7 @@ __device__ __forceinline__ void row16_lse(const double (&p)[4], double& M, doubl
 // HG = groups of four heads per landmark element: 1, or 2 for 5 to 8 query heads per KV head.  With HG = 2 every
 // widened landmark element feeds two instructions (heads 0-3, heads 4-7; two accumulators per tile), so the
 // landmarks are read and converted once for all eight heads.  The queries live in LDS as fp64.
-template <int D, int EB, int HG>
+template <int D, int EB, int HG, int NT>
 __global__ __launch_bounds__(256) void score_kernel(const bf16_t* __restrict__ q, const uint8_t* __restrict__ L,
                                                     float* __restrict__ logits, double2* __restrict__ partials,
                                                     int hq, int hkv, int G, int n_c, int ld, int nc_stride, int n_tiles,
@@ -88,14 +92,14 @@ __global__ __launch_bounds__(256) void score_kernel(const bf16_t* __restrict__ q
   const size_t head0 = (size_t)b * hq + (size_t)h * G + g0;
 
   const uint8_t* Lu = L + (size_t)unit * nc_stride * D * EB;  // the landmark array may have room to grow
-  const int row0 = tile * kScoreTile + wave * kWave;
+  const int row0 = (tile * 4 + wave) * (16 * NT);
   // requested before q: the landmark rows are the long-latency loads.  FP8 rows past the end repeat the last one and count
   // as -inf below: a clamped index costs less than a lane mask around every load (step of 16 x 128K 129.5 -> 126.1 us; in
   // the 16-head kernel, 1M tokens, 104.8 -> 103 us); bf16 rows are bound by the memory system and lose by it (168.4 ->
   // 169.5 us).
-  uint32_t w[4][NI][PW];
+  uint32_t w[NT][NI][PW];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
+  for (int t = 0; t < NT; ++t) {
     const int r = row0 + t * 16 + blk * 4 + ij;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
@@ -122,9 +126,9 @@ __global__ __launch_bounds__(256) void score_kernel(const bf16_t* __restrict__ q
   }
   __syncthreads();
 
-  double p[HG][4];   // logits of heads g0 + 4 hg + lane / 16
+  double p[HG][NT];   // logits of heads g0 + 4 hg + lane / 16
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
+  for (int t = 0; t < NT; ++t) {
     double acc[HG];
 #pragma unroll
     for (int hg = 0; hg < HG; ++hg) acc[hg] = 0.0;
@@ -159,7 +163,7 @@ __global__ __launch_bounds__(256) void score_kernel(const bf16_t* __restrict__ q
     }
   }
 
-  // (max, sum) of each head over the workgroup's 256 rows
+  // (max, sum) of each head over the workgroup's rows
 #pragma unroll
   for (int hg = 0; hg < HG; ++hg) {
     double m, s;
@@ -181,7 +185,7 @@ __global__ __launch_bounds__(256) void score_kernel(const bf16_t* __restrict__ q
 // of lane l = (head 4 j + l / 16, row l % 16); measured on gfx950), so every landmark element is loaded and widened
 // once instead of once per four heads.  Same tiles, same logits (exact products, fp64 sum) and partials as above.
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
-template <int D, int EB>
+template <int D, int EB, int NT>
 __global__ __launch_bounds__(256) void score_kernel_g16(const bf16_t* __restrict__ q, const uint8_t* __restrict__ L,
                                                         float* __restrict__ logits, double2* __restrict__ partials,
                                                         int hq, int hkv, int G, int n_c, int ld, int nc_stride,
@@ -195,10 +199,10 @@ __global__ __launch_bounds__(256) void score_kernel_g16(const bf16_t* __restrict
   const int kq = lane >> 4, rl = lane & 15;
   const size_t head0 = (size_t)b * hq + (size_t)h * G + g0;
   const uint8_t* Lu = L + (size_t)unit * nc_stride * D * EB;
-  const int row0 = tile * kScoreTile + wave * kWave;
-  uint32_t w[4][NI][PW];
+  const int row0 = (tile * 4 + wave) * (16 * NT);
+  uint32_t w[NT][NI][PW];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
+  for (int t = 0; t < NT; ++t) {
     const uint8_t* row = Lu + (size_t)min(row0 + t * 16 + rl, n_c - 1) * D * EB + PE * kq * EB;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
@@ -226,38 +230,38 @@ __global__ __launch_bounds__(256) void score_kernel_g16(const bf16_t* __restrict
         for (int e = 0; e < 8; ++e) qa[i][8 * e8 + e] = hv ? (double)x[e] : 0.0;
       }
   }
-  // the four 16-row tiles of the wave take turns on the matrix pipe: consecutive instructions are independent,
-  // a tile's own chain comes round every fourth one
-  f64x4_t acc[4];
+  // the 16-row tiles of the wave take turns on the matrix pipe: consecutive instructions are independent where there are
+  // several
+  f64x4_t acc[NT];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) acc[t] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+  for (int t = 0; t < NT; ++t) acc[t] = f64x4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
   for (int i = 0; i < NI; ++i)
 #pragma unroll
     for (int x = 0; x < PW; ++x) {
       if constexpr (EB == 2) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int t = 0; t < NT; ++t)
           acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[i][2 * x], (double)bf16_lo(w[t][i][x]), acc[t], 0, 0, 0);
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int t = 0; t < NT; ++t)
           acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[i][2 * x + 1], (double)bf16_hi(w[t][i][x]), acc[t], 0, 0, 0);
       } else {
-        float f[4][4];
+        float f[NT][4];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) e5m2x4_to_f32(w[t][i][x], f[t]);
+        for (int t = 0; t < NT; ++t) e5m2x4_to_f32(w[t][i][x], f[t]);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
-          for (int t = 0; t < 4; ++t)
+          for (int t = 0; t < NT; ++t)
             acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[i][4 * x + e], (double)f[t][e], acc[t], 0, 0, 0);
       }
     }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {   // heads g0 + 4 j + kq
-    double p[4], m, s;
+    double p[NT], m, s;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < NT; ++t) {
       const int r = row0 + t * 16 + rl;
       p[t] = r < n_c ? acc[t][j] * scale : -INFINITY;   // the logit: exact products, fp64 sum
       if (r < n_c && g0 + 4 * j + kq < G) logits[(head0 + 4 * j + kq) * ld + r] = (float)p[t];
@@ -275,23 +279,41 @@ __global__ __launch_bounds__(256) void score_kernel_g16(const bf16_t* __restrict
   }
 }
 
+// 16-row tiles per wave.  Many waves of few rows start and end evenly and fill a chip that few workgroups would leave idle;
+// where there is enough of both, fewer workgroups stage the queries less often and leave fewer pairs to merge.  In workgroups of
+// 256 rows, us with four / two / one tiles per wave, and where the limits lie:
+//   up to four heads: 16 (1 x 4K) 9.4 / 7.3 / 6.7; 512 (4 x 32K) 16.5 / 13.9 / 12.8; 1024 (8 x 32K) 21.6 / 19.1 / 19.6;
+//     4096 (16 x 64K) 57.1 / 56.6 / 64.9; 8192 107.9 / 107.7 / 123.7; FP8: 1024 17.1 / 15.9 / 17.8, 2048 24.3 / 25.8 / 28.0
+//   five to eight: 360 (3 x 61K) 16.4 / 13.4 / 13.8; 1440 33.2 / 32.8 / 36.9; FP8: 1024 23.5 / 22.9 / 24.6
+//   sixteen: 32 (1 x 32K) 12.1 / 8.8 / 7.4; 128 12.4 / 9.2 / 9.5; 512 18.8 / 18.9 / 20.7
+int score_tiles(int units, int G, int n_c, int kv_bytes) {
+  const long z = G > 8 ? (G + 15) / 16 : 1, wgs = units * z * score_tile_count(n_c, 4);
+  const long one = G > 8 ? 64 : G > 4 ? 256 : 512, two = G > 8 ? 256 : kv_bytes == 1 ? 1024 : 4096;
+  return wgs <= one ? 1 : wgs <= two ? 2 : 4;
+}
+
 hipError_t launch_score(const bf16_t* q, const void* landmarks, int kv_bytes, float* logits, int ld, double2* partials,
-                        int batch, int hq, int hkv, int d, int n_c, int nc_stride, double scale, hipStream_t st) {
+                        int batch, int hq, int hkv, int d, int n_c, int nc_stride, double scale, int tiles, hipStream_t st) {
   const int G = hq / hkv;
-  const int n_tiles = (n_c + kScoreTile - 1) / kScoreTile;
+  const int n_tiles = score_tile_count(n_c, tiles);
   // up to four heads per KV head: score_kernel<.., 1>; five to eight: score_kernel<.., 2>; more: one pass per 16
   // heads on the 16x16x4 instruction (heads past the group are zero rows of its operand)
   const bool g16 = G > 8;
   dim3 grid(n_tiles, batch * hkv, g16 ? (G + 15) / 16 : 1), block(256);
   const uint8_t* L = static_cast<const uint8_t*>(landmarks);
+#define SKV_LAUNCH(KERNEL_) hipLaunchKernelGGL(KERNEL_, grid, block, 0, st, q, L, logits, partials, hq, hkv, G, n_c, ld, nc_stride, n_tiles, scale)
+#define SKV_SCORE_NT(D_, EB_, NT_)                                                                                    \
+  do {                                                                                                                \
+    if (g16) SKV_LAUNCH((score_kernel_g16<D_, EB_, NT_>));                                                            \
+    else if (G > 4) SKV_LAUNCH((score_kernel<D_, EB_, 2, NT_>));                                                      \
+    else SKV_LAUNCH((score_kernel<D_, EB_, 1, NT_>));                                                                 \
+  } while (0)
 #define SKV_SCORE(D_, EB_)                                                                                            \
   do {                                                                                                                \
-    if (g16) hipLaunchKernelGGL((score_kernel_g16<D_, EB_>), grid, block, 0, st, q, L, logits, partials, hq, hkv, G,   \
-                                n_c, ld, nc_stride, n_tiles, scale);                                                  \
-    else if (G > 4) hipLaunchKernelGGL((score_kernel<D_, EB_, 2>), grid, block, 0, st, q, L, logits, partials, hq,     \
-                                       hkv, G, n_c, ld, nc_stride, n_tiles, scale);                                  \
-    else hipLaunchKernelGGL((score_kernel<D_, EB_, 1>), grid, block, 0, st, q, L, logits, partials, hq, hkv, G, n_c,   \
-                            ld, nc_stride, n_tiles, scale);                                                           \
+    if (tiles == 1) SKV_SCORE_NT(D_, EB_, 1);                                                                         \
+    else if (tiles == 2) SKV_SCORE_NT(D_, EB_, 2);                                                                    \
+    else if (tiles == 4) SKV_SCORE_NT(D_, EB_, 4);                                                                    \
+    else return hipErrorInvalidValue;                                                                                 \
   } while (0)
   switch (d * 4 + kv_bytes) {
     case 64 * 4 + 2: SKV_SCORE(64, 2); break;
@@ -303,6 +325,8 @@ hipError_t launch_score(const bf16_t* q, const void* landmarks, int kv_bytes, fl
     default: return hipErrorInvalidValue;
   }
 #undef SKV_SCORE
+#undef SKV_SCORE_NT
+#undef SKV_LAUNCH
   return hipGetLastError();
 }
 

@@ -144,7 +144,7 @@ DecodeLayout decode_layout(const Shape& sh) {
   DecodeLayout L{};
   plan_select(sh.n_c, sh.k, kSrcLogits, sh.units, &L.sel);
   L.attn = plan_attention(sh);
-  L.n_tiles = (sh.n_c + kScoreTile - 1) / kScoreTile;
+  L.n_tiles = score_tile_count(sh.n_c, 4);
   const size_t heads = (size_t)sh.b * sh.hq, rows = (size_t)sh.units * sh.k * sh.c;
   size_t off = 0;
   L.ld = (sh.n_c + 3) / 4 * 4;
@@ -487,12 +487,17 @@ static int decode_impl(const shadowkv_params* params, const shadowkv_bf16* q, co
   const int pstep = (g_prof.on && g_prof.n_steps < g_prof.max_steps) ? g_prof.n_steps++ : -1;
   prof_mark(st, pstep, 0);
   // 1. P = Q L^T / sqrt(d), per-tile softmax statistics
-  hipError_t e = launch_score(q, landmarks, sh.eb, logits, L.ld, partials, sh.b, sh.hq, sh.hkv, sh.d, sh.n_c, sh.nc_cap, scale, st);
+  //    (smaller tiles leave more pairs than the workspace's place for them holds: they go where the selected rows' logits
+  //    of the two-phase path will, as far as they fit)
+  int tiles = score_tiles(sh.units, sh.G, sh.n_c, sh.eb);
+  while (tiles < 4 && (size_t)score_tile_count(sh.n_c, tiles) * sizeof(double2) > (size_t)sh.k * sh.c * sizeof(float)) tiles *= 2;
+  if (tiles < 4) partials = reinterpret_cast<double2*>(ws + L.logit_buf);
+  hipError_t e = launch_score(q, landmarks, sh.eb, logits, L.ld, partials, sh.b, sh.hq, sh.hkv, sh.d, sh.n_c, sh.nc_cap, scale, tiles, st);
   if (e != hipSuccess) return fail_hip("score", e);
   prof_mark(st, pstep, 1);
   // 2. softmax normaliser per head, max over the group, ArgTopK -> true chunk ids
   SelectArgs a{};
-  a.logits = logits; a.partials = partials; a.n_tiles = L.n_tiles; a.G = sh.G; a.ld = L.ld;
+  a.logits = logits; a.partials = partials; a.n_tiles = score_tile_count(sh.n_c, tiles); a.G = sh.G; a.ld = L.ld;
   a.q = q; a.landmarks = landmarks; a.d = sh.d; a.kv_bytes = sh.eb; a.nc_stride = sh.nc_cap; a.scale = scale;
   a.lse_out = reinterpret_cast<double*>(ws + L.lse);
   a.key_top_out = reinterpret_cast<uint32_t*>(ws + L.key_top);
