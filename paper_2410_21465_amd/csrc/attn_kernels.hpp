@@ -85,6 +85,55 @@ struct AFrag<1> {
   }
 };
 
+// B^T of a KV head in LDS as bf16: element (n, kk) = B[kk][n] (zero beyond rank r) at n rp + kk.  A thread takes four rank rows
+// of eight columns and writes them as eight pieces of four neighbouring kk.  (As 16-bit pieces, a piece of one row per thread,
+// the writes were four times as many: 3 x 61K 25.1 -> 23.7 us for the attention, 1 x 4K 14.6 -> 13.8, 16 x 128K FP8 37.7 -> 37.1,
+// bf16 40.8 -> 40.6.  Turning the rows so that the pieces written together fall into different banks sped up the small ones
+// no further and slowed the operand reads of the large ones: 41.5, 38.2.)
+template <int D, int KSMAX, int EB, int NT>
+struct BStage {
+  static constexpr int N = (KSMAX * 8 * (D / 8) + NT - 1) / NT;
+  AFrag<EB> raw[N][4];
+  // (threads past the last piece repeat it: same values to the same place, no branch)
+  static __device__ __forceinline__ void place(const AttnArgs& a, int it, int& n8, int& kk) {
+    const int idx = min((int)threadIdx.x + it * NT, a.r32 / 4 * (D / 8) - 1), four = idx / a.r32;
+    n8 = (idx & 3) + 4 * four;
+    kk = ((idx - four * a.r32) >> 2) * 4;
+  }
+  __device__ __forceinline__ void request(const AttnArgs& a, int unit) {
+    const uint8_t* Bu = static_cast<const uint8_t*>(a.B) + (size_t)unit * a.r * D * EB;
+#pragma unroll
+    for (int it = 0; it < N; ++it) {
+      int n8, kk;
+      place(a, it, n8, kk);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) raw[it][j].load(Bu + ((size_t)(min(kk, a.r - 4) + j) * D + n8 * 8) * EB);
+    }
+  }
+  __device__ __forceinline__ void put(const AttnArgs& a, bf16_t* Bt) const {
+#pragma unroll
+    for (int it = 0; it < N; ++it) {
+      int n8, kk;
+      place(a, it, n8, kk);
+      uint32_t w[4][4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const bf16x8 x = raw[it][j].operand(kk >= a.r);
+        const uint4 v = *reinterpret_cast<const uint4*>(&x);
+        w[j][0] = v.x; w[j][1] = v.y; w[j][2] = v.z; w[j][3] = v.w;
+      }
+      bf16_t* dst = Bt + n8 * 8 * a.rp + kk;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        *reinterpret_cast<uint2*>(dst + (2 * i) * a.rp) =
+            make_uint2(__builtin_amdgcn_perm(w[1][i], w[0][i], 0x05040100u), __builtin_amdgcn_perm(w[3][i], w[2][i], 0x05040100u));
+        *reinterpret_cast<uint2*>(dst + (2 * i + 1) * a.rp) =
+            make_uint2(__builtin_amdgcn_perm(w[1][i], w[0][i], 0x07060302u), __builtin_amdgcn_perm(w[3][i], w[2][i], 0x07060302u));
+      }
+    }
+  }
+};
+
 // Online-softmax state of one lane: NR rows at a time are folded in with one rescale per head.
 template <int GH, int EPL, int EB>
 struct OnlineSoftmax {
@@ -277,7 +326,7 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_kernel(AttnArgs a) {
   constexpr int EPL = D / 16, NB = D / 16, HB = NB / 2;
   constexpr int RW = RawWords<EPL, EB>::n;
   constexpr int NT = FAST4 ? 1 : 4;  // token positions a lane keeps per block (FAST4: the first of 4 consecutive)
-  extern __shared__ __align__(16) bf16_t Bt[];  // [D][rp], element (n, kk) = B[kk][n]; then int tokb[]
+  extern __shared__ __align__(16) bf16_t Bt[];  // B^T, see BStage; then int tokb[]
   __shared__ float sm_acc[4][GH][D];
   __shared__ float sm_m[4][GH], sm_l[4][GH];
   // KEYS_ONLY: a flat grid, the gather's workgroups first (they are dispatched first), then (split, unit, head block)
@@ -389,45 +438,11 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_kernel(AttnArgs a) {
   bool okN[NT];
   if (s_begin < s_end) load_block(s_begin + wave * 16, afN, vN, tokN, okN);
 
-  // ---- B^T of this KV head into LDS (zero beyond rank r).  A wave reads 16 rank rows x 64 bytes
-  //      per load and scatters them as 16-bit LDS writes.
+  // ---- B^T of this KV head into LDS
   {
-    constexpr int NBI = (KSMAX * 32 * (D / 8) + 255) / 256;  // 16-byte pieces per thread
-    const uint8_t* Bu = static_cast<const uint8_t*>(a.B) + (size_t)unit * r * D * EB;
-    const int pieces = r32 * (D / 8);
-    uint4 bw[NBI];
-    int dst[NBI];
-#pragma unroll
-    for (int it = 0; it < NBI; ++it) {
-      const int idx = min((int)threadIdx.x + it * 256, pieces - 1);
-      const int n8 = (idx & 3) + 4 * (idx / (4 * r32)), kk = (idx >> 2) % r32;
-      const uint8_t* src = Bu + ((size_t)min(kk, r - 1) * D + n8 * 8) * EB;
-      if constexpr (EB == 2) {
-        bw[it] = *reinterpret_cast<const uint4*>(src);
-      } else {   // 8 bytes -> the same 8 elements as bf16 bit patterns
-        const uint2 v = *reinterpret_cast<const uint2*>(src);
-        bw[it] = make_uint4(v.x, v.y, 0u, 0u);
-      }
-      dst[it] = kk < r ? n8 * 8 * rp + kk : -(n8 * 8 * rp + kk) - 1;  // negative: store zeros
-    }
-    if constexpr (EB == 1) {
-#pragma unroll
-      for (int it = 0; it < NBI; ++it)
-        bw[it] = make_uint4(e5m2x2_to_bf16x2<0>(bw[it].x), e5m2x2_to_bf16x2<1>(bw[it].x), e5m2x2_to_bf16x2<0>(bw[it].y),
-                            e5m2x2_to_bf16x2<1>(bw[it].y));
-    }
-#pragma unroll
-    for (int it = 0; it < NBI; ++it) {
-      // (threads past the last piece repeat it: same values to the same place, no branch)
-      const bool real = dst[it] >= 0;
-      const int at = real ? dst[it] : -(dst[it] + 1);
-      const uint32_t w4[4] = {real ? bw[it].x : 0u, real ? bw[it].y : 0u, real ? bw[it].z : 0u, real ? bw[it].w : 0u};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        Bt[at + (2 * i) * rp] = (bf16_t)(w4[i] & 0xffffu);
-        Bt[at + (2 * i + 1) * rp] = (bf16_t)(w4[i] >> 16);
-      }
-    }
+    BStage<D, KSMAX, EB, 256> bt;
+    bt.request(a, unit);
+    bt.put(a, Bt);
   }
 
   OnlineSoftmax<GH, EPL, EB> st;
@@ -693,7 +708,7 @@ __global__ __launch_bounds__(64 * (NKW + NVW), 4) void sparse_attn_roles_kernel(
   constexpr int RW = RawWords<EPL, EB>::n;
   constexpr int NT = 64 * (NKW + NVW), RPS = 16 * NKW, BPV = NKW / NVW;   // threads; rows per step; blocks per value wave and step
   static_assert(NKW % NVW == 0, "every value wave takes the same number of blocks per step");
-  extern __shared__ __align__(16) bf16_t Bt[];  // [D][rp], element (n, kk) = B[kk][n]; then int tokb[], vrowb[]
+  extern __shared__ __align__(16) bf16_t Bt[];  // B^T, see BStage; then int tokb[], vrowb[]
   __shared__ __align__(16) float lgs[2][RPS][GH]; // logits (log2 units) of the rows of one step, -inf past the end
   __shared__ __align__(16) float qs[GH][D];       // the block's queries, scaled to log2 units
   __shared__ double frev_s[D / 2];                // rotary frequencies in revolutions per position
@@ -716,6 +731,9 @@ __global__ __launch_bounds__(64 * (NKW + NVW), 4) void sparse_attn_roles_kernel(
   const int ch_begin = chunk_of(s_begin);
   const int n_it = (s_end - s_begin + RPS - 1) / RPS;
 
+  // ---- B^T of this KV head into LDS, by all the waves: requested ahead of the tables
+  BStage<D, KSMAX, EB, NT> bt;
+  bt.request(a, unit);
   int* tokb = reinterpret_cast<int*>(Bt + (size_t)D * rp);
   int* vrowb = tokb + (a.sparse_split_len / a.c + 2);
   const uint8_t* vbase = a.v_sparse ? static_cast<const uint8_t*>(a.v_sparse) + (size_t)unit * a.v_unit_rows * D * EB
@@ -747,44 +765,7 @@ __global__ __launch_bounds__(64 * (NKW + NVW), 4) void sparse_attn_roles_kernel(
     cd_s[threadIdx.x] = __builtin_amdgcn_cosf((float)rv);
     sd_s[threadIdx.x] = __builtin_amdgcn_sinf((float)rv);
   }
-  // ---- B^T of this KV head into LDS (zero beyond rank r), by all the waves
-  {
-    constexpr int NBI = (KSMAX * 32 * (D / 8) + NT - 1) / NT;  // 16-byte pieces per thread
-    const uint8_t* Bu = static_cast<const uint8_t*>(a.B) + (size_t)unit * r * D * EB;
-    const int pieces = r32 * (D / 8);
-    uint4 bw[NBI];
-    int dst[NBI];
-#pragma unroll
-    for (int it = 0; it < NBI; ++it) {
-      const int idx = min((int)threadIdx.x + it * NT, pieces - 1);
-      const int n8 = (idx & 3) + 4 * (idx / (4 * r32)), kk = (idx >> 2) % r32;
-      const uint8_t* src = Bu + ((size_t)min(kk, r - 1) * D + n8 * 8) * EB;
-      if constexpr (EB == 2) {
-        bw[it] = *reinterpret_cast<const uint4*>(src);
-      } else {
-        const uint2 v = *reinterpret_cast<const uint2*>(src);
-        bw[it] = make_uint4(v.x, v.y, 0u, 0u);
-      }
-      dst[it] = kk < r ? n8 * 8 * rp + kk : -(n8 * 8 * rp + kk) - 1;  // negative: store zeros
-    }
-    if constexpr (EB == 1) {
-#pragma unroll
-      for (int it = 0; it < NBI; ++it)
-        bw[it] = make_uint4(e5m2x2_to_bf16x2<0>(bw[it].x), e5m2x2_to_bf16x2<1>(bw[it].x), e5m2x2_to_bf16x2<0>(bw[it].y),
-                            e5m2x2_to_bf16x2<1>(bw[it].y));
-    }
-#pragma unroll
-    for (int it = 0; it < NBI; ++it) {
-      const bool real = dst[it] >= 0;
-      const int at = real ? dst[it] : -(dst[it] + 1);
-      const uint32_t w4[4] = {real ? bw[it].x : 0u, real ? bw[it].y : 0u, real ? bw[it].z : 0u, real ? bw[it].w : 0u};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        Bt[at + (2 * i) * rp] = (bf16_t)(w4[i] & 0xffffu);
-        Bt[at + (2 * i + 1) * rp] = (bf16_t)(w4[i] >> 16);
-      }
-    }
-  }
+  bt.put(a, Bt);
   __syncthreads();   // tables, queries and B^T are in place
 
   if (wave < NKW) {
