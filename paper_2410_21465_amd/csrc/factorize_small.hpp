@@ -9,10 +9,15 @@ namespace skv {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
+// Of the steps 1, 2, ... a sequence takes every every[sequence]-th (all of them without `every`).
+struct Every { const int32_t* every; int step; };
+__device__ __forceinline__ bool step_left_out(Every e, int sequence) { return e.every && e.step % e.every[sequence] != 0; }
+
 // ---- products ---------------------------------------------------------------------------------------
 // C[i][j] = sum_k A[i][k] B(k, j), K a multiple of 16, rows of A 16-byte aligned.  BT: B is given by its columns
 // (B(k, j) = B[j][k], as A is); otherwise row-major with Kb rows (A is zero beyond).  Rows of A may be taken through
 // a_rows.  C is written over Mw x Nw, zero outside M x N.  With `shift` (one number per sequence; N = K): C = A (B - node shift).
+// With `every`, see step_left_out.
 // A workgroup is WM x WN tiles of 16 T x 16 T with the contraction cut WK ways; every operand goes from L2 straight to the
 // matrix instruction (a lane's four consecutive elements are four contraction steps), the next 16 steps requested
 // before the current ones' 16 instructions.  The products here are small (192 x 1024 x 1024 per sequence), so what
@@ -24,7 +29,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm64_kernel(const double*
                                                                    int M, int N, int K, int Kb, int lda, int ldb, int ldc,
                                                                    int Mw, int Nw, size_t strideA, size_t strideB, size_t strideC,
                                                                    const int32_t* __restrict__ a_rows, int a_rows_stride,
-                                                                   const double* __restrict__ shift, double node) {
+                                                                   const double* __restrict__ shift, double node, Every every) {
+  if (step_left_out(every, blockIdx.z)) return;
   __shared__ double red[WM * WN][WK][4 * T * T][kWave];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int sub = lane & 15, kq = lane >> 4;
@@ -224,10 +230,14 @@ __device__ __forceinline__ double factor_block(f64x4 a, const double (&e0)[4], d
 // pivots, column, trailing blocks with four barriers a step, took 49.  Above 192 vectors a wave's blocks fill its registers.
 // A pivot below kPivotFloor of the vector's own square is rounding: it is set to that floor, which leaves the vector's
 // remainder at a size that the next pass can work on, and nothing is projected on it; a zero vector stays zero.
-// smallest (may be NULL): the least entry of L's diagonal of each sequence, 0 where a pivot was set to its floor.
+// smallest (may be NULL): the least entry of L's diagonal of each sequence, 0 where a pivot was set to its floor; and
+// `pause`: how many of the steps that follow may go without an orthonormalisation in between, one more than that.  What an
+// earlier vector leaves in a later one by rounding (1e-16) grows by the ratio of their eigenvalues in every step; up to three
+// steps, as long as the largest ratio (that of the longest vector and the least entry) to their number is below 1e13.
 template <int NBW>
 __global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S, double* __restrict__ Lp, int nb,
-                                                   double* __restrict__ smallest) {
+                                                   double* __restrict__ smallest, int32_t* __restrict__ pause, Every every) {
+  if (step_left_out(every, blockIdx.x)) return;
   __shared__ double col[kMaxFactorBlocks][272];   // current block column, rows at a pitch of 17
   __shared__ double sol[kMaxFactorBlocks][256];   // the same times the diagonal block's inverse, operand order
   __shared__ double inv[256];                     // inverse of the diagonal block, rows of floored pivots zero
@@ -307,7 +317,14 @@ __global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S,
     if (smallest) {
       least = fmin(least, shfl_xor_f64(least, 16));
       least = fmin(least, shfl_xor_f64(least, 32));
-      if (lane == 0) smallest[blockIdx.x] = least < INFINITY ? sqrt(least) : 0.0;
+      double longest = 0.0;
+      for (int i = lane; i < ld; i += kWave) longest = fmax(longest, S[(size_t)i * (ld + 1)]);
+      longest = wave_max_f64(longest);
+      if (lane == 0) {
+        smallest[blockIdx.x] = least < INFINITY ? sqrt(least) : 0.0;
+        const double x = longest / least;   // squared ratio (without pivots, and where one was floored: one step at a time)
+        pause[blockIdx.x] = least > 0.0 && x * x * x <= 1e26 ? 3 : least > 0.0 && x * x <= 1e26 ? 2 : 1;
+      }
     }
     return;
   }
@@ -363,7 +380,13 @@ __global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S,
 // 192 vectors of 1024 columns: 12.5 us (one wave for all rows, 312 matrix instructions in a row: 18.5 us).
 template <int NB>
 __global__ __launch_bounds__(256) void trsm_kernel(const double* __restrict__ Lp, const double* __restrict__ Y,
-                                                   double* __restrict__ X, int m, int nb, int D) {
+                                                   double* __restrict__ X, int m, int nb, int D, Every every) {
+  if (step_left_out(every, blockIdx.y)) {   // X <- Y
+    const size_t at = (size_t)blockIdx.y * m * D + blockIdx.x * 16 + (threadIdx.x & 15);
+#pragma unroll 8
+    for (int r = threadIdx.x >> 4; r < m; r += 16) X[at + (size_t)r * D] = Y[at + (size_t)r * D];
+    return;
+  }
   constexpr int NR = (NB + 3) / 4;           // block rows per wave
   __shared__ double xs[2][kWave][4];
   const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);

@@ -332,13 +332,13 @@ struct Mat { const double* p; int ld; size_t stride; };
 template <bool BT>
 static hipError_t gemm64(Mat A, Mat B, double* C, int ldc, size_t strideC, int M, int N, int K, int Kb, int Mw, int Nw,
                          int batch, hipStream_t st, const int32_t* a_rows = nullptr, int a_rows_stride = 0,
-                         const double* shift = nullptr, double node = 0.0) {
+                         const double* shift = nullptr, double node = 0.0, Every every = {nullptr, 0}) {
   const long tiles = (long)((Mw + 31) / 32) * ((Nw + 31) / 32) * batch;
 #define SKV_GEMM(T_, WM_, WN_, WK_)                                                                                       \
   hipLaunchKernelGGL((gemm64_kernel<T_, WM_, WN_, WK_, BT>), dim3((Nw + 16 * T_ * WN_ - 1) / (16 * T_ * WN_),             \
                      (Mw + 16 * T_ * WM_ - 1) / (16 * T_ * WM_), batch), dim3(64 * WM_ * WN_ * WK_), 0, st, A.p, B.p, C, M, N, \
                      K, Kb, A.ld, B.ld, ldc, Mw, Nw, A.stride, B.stride, strideC, a_rows, a_rows_stride, \
-                     shift, node)
+                     shift, node, every)
   if (tiles < 64) SKV_GEMM(1, 1, 1, 16);
   else if (tiles < 1024) SKV_GEMM(2, 1, 1, 8);
   else if constexpr (BT) SKV_GEMM(4, 1, 1, 4);
@@ -566,13 +566,16 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
   SKV_CHECK();
   // X <- orthonormal basis of the rows of Y, each row from the ones before it (see chol_kernel)
   const int nbc = (m + 15) / 16;
-  auto orthonormalise = [&](const double* Y, double* X, double* smallest = nullptr) -> hipError_t {
-    hipError_t err = gemm64<true>({Y, D, (size_t)m * D}, {Y, D, (size_t)m * D}, S, 16 * nbc, (size_t)256 * nbc * nbc, m, m, D, D, 16 * nbc, 16 * nbc, batch, st);
+  // (with `every` for those sequences whose turn it is, X <- Y for the others)
+  auto orthonormalise = [&](const double* Y, double* X, double* smallest = nullptr, int32_t* pause = nullptr,
+                            Every every = {nullptr, 0}) -> hipError_t {
+    hipError_t err = gemm64<true>({Y, D, (size_t)m * D}, {Y, D, (size_t)m * D}, S, 16 * nbc, (size_t)256 * nbc * nbc, m, m, D, D, 16 * nbc, 16 * nbc, batch, st,
+                                  nullptr, 0, nullptr, 0.0, every);
     if (err != hipSuccess) return err;
 #define SKV_ORTH(NBW_, NB_)                                                                                       \
   do {                                                                                                            \
-    hipLaunchKernelGGL(chol_kernel<NBW_>, dim3(batch), dim3(512), 0, st, S, Lp, nbc, smallest);               \
-    hipLaunchKernelGGL(trsm_kernel<NB_>, dim3(D / 16, batch), dim3(256), 0, st, Lp, Y, X, m, nbc, D);                \
+    hipLaunchKernelGGL(chol_kernel<NBW_>, dim3(batch), dim3(512), 0, st, S, Lp, nbc, smallest, pause, every); \
+    hipLaunchKernelGGL(trsm_kernel<NB_>, dim3(D / 16, batch), dim3(256), 0, st, Lp, Y, X, m, nbc, D, every);         \
   } while (0)
     // (blocks per wave of the eight, block rows held): up to 80, 192, 224, 288 vectors
     if (nbc <= 5) SKV_ORTH(2, 5);
@@ -590,17 +593,22 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
   // nine of G - theta_j with theta_j the Chebyshev points of [0, b], b the least entry of the fourth factor's diagonal: 0.8 to
   // 1.2 lam_m on every spectrum tried, at which the nine damp like 1 / T_9(2 lam_r / b - 1).  On spectra with lam_(m+1) / lam_r
   // from 0.9 to 0.15 the r vectors come out 5 to 1000 times closer than after 16 steps of G, below that alike to rounding (numpy
-  // model, keys of 30 kinds).  Where a pivot was rounding b is 0.  Each step is orthonormalised, so that the order of the points
-  // matters to rounding only; large and small ones take turns.
+  // model, keys of 30 kinds).  Where a pivot was rounding b is 0.  Of the nine every third, or second, is followed by an
+  // orthonormalisation where the eigenvalues lie close enough (see chol_kernel), and the last: after four steps the vectors are
+  // near enough to single eigenvectors that another step mostly scales them.  (Same model, 25 kinds,
+  // eigenvalues from alike to 1e30 apart: the same residuals to two digits.  1 x 32K: 56 us each, now 10.)  So the order of the points matters to rounding only; large and
+  // small ones take turns.
   constexpr int kPlain = 4, kPoints = 9;
   const bool shifted = n_iter == 0 && m < D;
   double* shift = reinterpret_cast<double*>(ws + pl.shift);
+  int32_t* pause = order;   // (the order is found after these steps)
   const int steps = n_iter ? n_iter : shifted ? kPlain + kPoints : 16;
   for (int it = 0; it < steps; ++it) {
     const int j = shifted ? it - kPlain : -1;
     const double node = 0.5 - 0.5 * std::cos(3.14159265358979323846 * (2 * (4 * j % kPoints) + 1) / (2 * kPoints));
     if ((e = j < 0 ? times_gram(Xt, Yt) : times_gram(Xt, Yt, shift, node)) != hipSuccess) return e;
-    if ((e = orthonormalise(Yt, Xt, j == -1 && shifted ? shift : nullptr)) != hipSuccess) return e;
+    const bool pauses = j >= 0 && it + 1 < steps;
+    if ((e = orthonormalise(Yt, Xt, j == -1 && shifted ? shift : nullptr, pause, {pauses ? pause : nullptr, j + 1})) != hipSuccess) return e;
   }
   // twice more before the Ritz step: the first brings the basis to the rounding unit, the second does the same for
   // vectors whose pivots were rounding in the one before

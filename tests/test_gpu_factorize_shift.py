@@ -58,3 +58,32 @@ def test_default_steps_come_as_close_as_sixteen_plain_ones(kind, h, d, s, r):
         # rounding: 1e-12 of the largest eigenvalue for sums of a few hundred terms
         assert res[0] <= res[16] + 1e-12 * lam[0]
         assert miss[0] <= miss[16] + 1e-12 * lam[0]
+
+
+def test_sequences_of_a_batch_pause_by_themselves():
+    """Sequences whose shifted steps go without orthonormalisation two at a time, one at a time and not at all, in one batch:
+    each as close as after sixteen plain steps (the bounds as above), the first also alone (sums in another order)."""
+    h, d, s, r = 4, 128, 1200, 160
+    D = h * d
+    gen = torch.Generator(device="cpu").manual_seed(7)
+    x = torch.arange(D, dtype=torch.float64)
+    scales = [torch.exp(-x / 100.0), torch.exp(-x / 14.0), torch.exp(-x / 30.0), torch.ones(D, dtype=torch.float64)]
+    k = torch.stack([torch.randn(s, D, generator=gen, dtype=torch.float64) * c for c in scales]).to(torch.bfloat16)
+
+    def run(keys, n):
+        p = S.Params(batch=len(keys), n_q_heads=h, n_kv_heads=h, head_dim=d, ctx_len=s, chunk_size=1, rank=r, n_outlier_chunks=0,
+                     topk_chunks=1, local_len=0)
+        got = S.factorize_keys(p, keys.cuda(), want_vectors=True, n_iter=n)
+        return got["psi"].cpu().numpy(), got["sigma"].cpu().numpy()
+
+    many, plain, alone = run(k, 0), run(k, 16), run(k[:1], 0)
+    for i in range(len(scales)):
+        K = k[i].double().numpy()
+        G = K.T @ K
+        top = np.linalg.eigvalsh(G)[-1]
+        residual = [np.linalg.norm(psi[i] @ G - (sig[i] ** 2)[:, None] * psi[i]) for psi, sig in (many, plain)]
+        print(f"[case] sequence {i}: residual / lam_1 {residual[0] / top:.1e} (16: {residual[1] / top:.1e})", flush=True)
+        assert np.abs(many[0][i] @ many[0][i].T - np.eye(r)).max() < 1e-12
+        assert residual[0] <= residual[1] + 1e-12 * top
+    # singular values to rounding: 1e-12 of the largest squared one, as the residuals
+    assert np.abs(alone[1][0] ** 2 - many[1][0] ** 2).max() <= 1e-12 * many[1][0][0] ** 2
