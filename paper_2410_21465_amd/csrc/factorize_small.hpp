@@ -17,7 +17,7 @@ __device__ __forceinline__ bool step_left_out(Every e, int sequence) { return e.
 // C[i][j] = sum_k A[i][k] B(k, j), K a multiple of 16, rows of A 16-byte aligned.  BT: B is given by its columns
 // (B(k, j) = B[j][k], as A is); otherwise row-major with Kb rows (A is zero beyond).  Rows of A may be taken through
 // a_rows.  C is written over Mw x Nw, zero outside M x N.  With `shift` (one number per sequence; N = K): C = A (B - node shift).
-// With `every`, see step_left_out.
+// With `every`, see step_left_out; with `lower` blocks above the diagonal are left as they were.
 // A workgroup is WM x WN tiles of 16 T x 16 T with the contraction cut WK ways; every operand goes from L2 straight to the
 // matrix instruction (a lane's four consecutive elements are four contraction steps), the next 16 steps requested
 // before the current ones' 16 instructions.  The products here are small (192 x 1024 x 1024 per sequence), so what
@@ -29,8 +29,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm64_kernel(const double*
                                                                    int M, int N, int K, int Kb, int lda, int ldb, int ldc,
                                                                    int Mw, int Nw, size_t strideA, size_t strideB, size_t strideC,
                                                                    const int32_t* __restrict__ a_rows, int a_rows_stride,
-                                                                   const double* __restrict__ shift, double node, Every every) {
-  if (step_left_out(every, blockIdx.z)) return;
+                                                                   const double* __restrict__ shift, double node, Every every,
+                                                                   bool lower) {
+  if (step_left_out(every, blockIdx.z) || (lower && blockIdx.x * WN >= (blockIdx.y + 1) * WM)) return;
   __shared__ double red[WM * WN][WK][4 * T * T][kWave];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int sub = lane & 15, kq = lane >> 4;

@@ -332,13 +332,13 @@ struct Mat { const double* p; int ld; size_t stride; };
 template <bool BT>
 static hipError_t gemm64(Mat A, Mat B, double* C, int ldc, size_t strideC, int M, int N, int K, int Kb, int Mw, int Nw,
                          int batch, hipStream_t st, const int32_t* a_rows = nullptr, int a_rows_stride = 0,
-                         const double* shift = nullptr, double node = 0.0, Every every = {nullptr, 0}) {
+                         const double* shift = nullptr, double node = 0.0, Every every = {nullptr, 0}, bool lower = false) {
   const long tiles = (long)((Mw + 31) / 32) * ((Nw + 31) / 32) * batch;
 #define SKV_GEMM(T_, WM_, WN_, WK_)                                                                                       \
   hipLaunchKernelGGL((gemm64_kernel<T_, WM_, WN_, WK_, BT>), dim3((Nw + 16 * T_ * WN_ - 1) / (16 * T_ * WN_),             \
                      (Mw + 16 * T_ * WM_ - 1) / (16 * T_ * WM_), batch), dim3(64 * WM_ * WN_ * WK_), 0, st, A.p, B.p, C, M, N, \
                      K, Kb, A.ld, B.ld, ldc, Mw, Nw, A.stride, B.stride, strideC, a_rows, a_rows_stride, \
-                     shift, node, every)
+                     shift, node, every, lower)
   if (tiles < 64) SKV_GEMM(1, 1, 1, 16);
   else if (tiles < 1024) SKV_GEMM(2, 1, 1, 8);
   else if constexpr (BT) SKV_GEMM(4, 1, 1, 4);
@@ -570,7 +570,7 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
   auto orthonormalise = [&](const double* Y, double* X, double* smallest = nullptr, int32_t* pause = nullptr,
                             Every every = {nullptr, 0}) -> hipError_t {
     hipError_t err = gemm64<true>({Y, D, (size_t)m * D}, {Y, D, (size_t)m * D}, S, 16 * nbc, (size_t)256 * nbc * nbc, m, m, D, D, 16 * nbc, 16 * nbc, batch, st,
-                                  nullptr, 0, nullptr, 0.0, every);
+                                  nullptr, 0, nullptr, 0.0, every, true);
     if (err != hipSuccess) return err;
 #define SKV_ORTH(NBW_, NB_)                                                                                       \
   do {                                                                                                            \
