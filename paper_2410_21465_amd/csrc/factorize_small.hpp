@@ -458,7 +458,7 @@ __global__ __launch_bounds__(256) void trsm_kernel(const double* __restrict__ Lp
 // rotations accumulated in V: then the norms of W's columns are the eigenvalues of T and the columns of V its eigenvectors.
 // The columns are taken as nb = mp / 16 blocks; a step pairs the blocks up (circle method: (nb-1, st), ((st+i) mod (nb-1),
 // (st-i) mod (nb-1))), and a workgroup makes the 16 x 16 pairs of columns between its two blocks orthogonal (in the first
-// step of a sweep all pairs of its 32 columns): it forms the 32 x 32 products of the columns on the matrix instruction,
+// step of a sweep and ahead of the sweeps all pairs of its 32 columns): it forms the 32 x 32 products of the columns on the matrix instruction,
 // rotates those (two-sided, in LDS, 16 disjoint rotations at a time, accumulated in J) and applies J to its columns as one
 // product.  A rotation's angle thus costs two rounds of LDS and a barrier, not a pass over the columns and a launch: a
 // sweep of 192 columns is 11 launches of 17 us (the first 26, those without a rotation 6) where a launch per set of 96
@@ -491,13 +491,23 @@ template <int J>
 __device__ __forceinline__ double row_lane_f64(double x) {
   return __longlong_as_double(__builtin_amdgcn_update_dpp(0ll, __double_as_longlong(x), 0x150 + J, 0xf, 0xf, true));
 }
-// step = sweep * (nb - 1) + st.  Workgroups [0, nb/2): step `step` on W (none when step == n_steps); [nb/2, nb): the step
-// before, on V.  J and idle (whether its J is the identity) alternate between two halves from step to step.
+// Ahead of the sweeps come passes over neighbouring blocks only, all pairs of 32 columns each, in two steps a pass: after
+// the subspace iteration T is a matrix whose entries fall off fast from the diagonal, so these settle most of it and spare more
+// sweeps (of nb - 1 steps) than they cost.  Launch by launch, in numpy, keys of the spectra exp(-i / 40), exp(-i / 100), 1 / i
+// and one with a gap, us without, with two, with three passes: 192 vectors 844 / 668 / 638, 974 / 792 / 780, 973 / 757 / 793,
+// 1109 / 993 / 938; 288 vectors 1238 / 898 / 830 ..; 128: 578 / 509 / 509, 639 / 584 / 591; 96 446 / 433 / 444, 491 / 477 /
+// 483; 64 317 / 356 / 383.  After a first pass without a cosine above kLocalWorth (flat spectra, which take nine sweeps either
+// way) the others are left out.
+constexpr float kLocalWorth = 1e-3f;
+__host__ __device__ __forceinline__ int local_steps(int nb) { return nb >= 10 ? 6 : nb >= 8 ? 4 : 0; }
+// local_max [batch]: the largest cosine of the first of them, as in sweep_max.
+// step = local step, then local_steps(nb) + sweep * (nb - 1) + st.  Workgroups [0, nb/2): step `step` on W (none when step ==
+// n_steps); [nb/2, nb): the step before, on V.  J and idle (whether its J is the identity) alternate between two halves from step to step.
 // A round in which every pair is orthogonal to rounding at the start of the step is left out.
 __global__ __launch_bounds__(512) void jacobi_block_kernel(double* __restrict__ W, double* __restrict__ V,
                                                            double* __restrict__ Jbuf, int32_t* __restrict__ idle,
-                                                           int32_t* __restrict__ sweep_max, int mp, int step, int n_steps,
-                                                           int n_sweeps) {
+                                                           int32_t* __restrict__ sweep_max, int32_t* __restrict__ local_max,
+                                                           int mp, int step, int n_steps, int n_sweeps) {
   constexpr int P = 33;                     // pitch of the 32 x 32 matrices in LDS
   __shared__ double red[8 * 3 * 256];       // partial products of the waves; then the second copy of S, and J
   __shared__ double S0[32 * P];
@@ -509,13 +519,22 @@ __global__ __launch_bounds__(512) void jacobi_block_kernel(double* __restrict__ 
   const bool on_v = (int)blockIdx.x >= np;
   const int mine = on_v ? step - 1 : step, pair = on_v ? blockIdx.x - np : blockIdx.x;
   if (mine < 0 || mine >= n_steps) return;
-  const int sweep = mine / (nb - 1), st = mine - sweep * (nb - 1);
+  const int n_local = local_steps(nb);
+  const bool local = mine < n_local;
+  const int sweep = local ? 0 : (mine - n_local) / (nb - 1), st = local ? 0 : mine - n_local - sweep * (nb - 1);
   sweep_max += (size_t)b * n_sweeps;
-  if (!jacobi_active(sweep_max, sweep)) return;
+  if (local) {
+    // (a stored cosine that is not a number counts as worth it)
+    if (mine >= 2 && __int_as_float(local_max[b]) <= kLocalWorth) return;
+    if (2 * pair + (mine & 1) + 1 >= nb) return;
+  } else if (!jacobi_active(sweep_max, sweep)) {
+    return;
+  }
   const int slot = ((mine & 1) * batch + b) * np + pair;
   double* Jg = Jbuf + (size_t)slot * 1024;
   int pb, qb;
-  if (pair == 0) { pb = nb - 1; qb = st; }
+  if (local) { pb = 2 * pair + (mine & 1); qb = pb + 1; }
+  else if (pair == 0) { pb = nb - 1; qb = st; }
   else { pb = (st + pair) % (nb - 1); qb = (st - pair + (nb - 1)) % (nb - 1); }
   double* M = (on_v ? V : W) + (size_t)b * mp * mp;
   auto row = [&](int i) { return M + (size_t)((i < 16 ? pb * 16 : qb * 16 - 16) + i) * mp; };
@@ -594,7 +613,8 @@ __global__ __launch_bounds__(512) void jacobi_block_kernel(double* __restrict__ 
     for (int w = 0; w < 8; ++w) { const uint2 f = found[w]; big = max(big, f.x); rounds |= f.y; }
     rounds = (uint32_t)__builtin_amdgcn_readfirstlane((int)rounds);
     if (threadIdx.x == 0) {
-      atomicMax(&sweep_max[sweep], (int)big);
+      if (!local) atomicMax(&sweep_max[sweep], (int)big);
+      else if (mine < 2) atomicMax(&local_max[b], (int)big);
       idle[slot] = rounds ? 0 : 1;
     }
     if (!rounds) return;

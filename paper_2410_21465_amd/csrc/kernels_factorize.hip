@@ -156,10 +156,11 @@ __global__ __launch_bounds__(256) void subspace_init_kernel(double* __restrict__
 }
 
 // before the Jacobi sweeps: V <- identity (mp x mp per sequence), the largest cosine of every sweep <- 0
-__global__ __launch_bounds__(256) void jacobi_init_kernel(double* __restrict__ V, int32_t* __restrict__ sweep_max, int mp,
-                                                          int n_sweeps) {
+__global__ __launch_bounds__(256) void jacobi_init_kernel(double* __restrict__ V, int32_t* __restrict__ sweep_max,
+                                                          int32_t* __restrict__ local_max, int mp, int n_sweeps) {
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (i < (size_t)n_sweeps) sweep_max[(size_t)blockIdx.y * n_sweeps + i] = 0;
+  if (i == 0) local_max[blockIdx.y] = 0;
   if (i >= (size_t)mp * mp) return;
   V[(size_t)blockIdx.y * mp * mp + i] = (i / mp == i % mp) ? 1.0 : 0.0;
 }
@@ -620,13 +621,14 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
     // W [mp x mp]: T(i, j) = sum_x Xt[i][x] Yt[j][x], zero outside the leading m x m block
     if ((e = gemm64<true>({Xt, D, (size_t)m * D}, {Yt, D, (size_t)m * D}, W, mp, (size_t)mp * mp, m, m, D, D, mp, mp, batch, st)) != hipSuccess)
       return e;
+    int32_t* local_max = order;   // (the order is found after the sweeps)
     hipLaunchKernelGGL(jacobi_init_kernel, dim3((unsigned)(((size_t)mp * mp + 255) / 256), batch), dim3(256), 0, st, V, sweep_max,
-                       mp, n_sweeps);
+                       local_max, mp, n_sweeps);
     SKV_CHECK();
-    const int nbj = mp / 16, n_steps = n_sweeps * (nbj - 1);
+    const int nbj = mp / 16, n_steps = local_steps(nbj) + n_sweeps * (nbj - 1);
     for (int step = 0; step <= n_steps; ++step)   // (the last launch only brings V up to date)
-      hipLaunchKernelGGL(jacobi_block_kernel, dim3(nbj, batch), dim3(512), 0, st, W, V, Jbuf, idle, sweep_max, mp, step, n_steps,
-                         n_sweeps);
+      hipLaunchKernelGGL(jacobi_block_kernel, dim3(nbj, batch), dim3(512), 0, st, W, V, Jbuf, idle, sweep_max, local_max, mp, step,
+                         n_steps, n_sweeps);
     SKV_CHECK();
     hipLaunchKernelGGL(ritz_select_kernel, dim3(batch), dim3(1024), (size_t)m * sizeof(double), st, W, order, sigma_out, mp, m, r);
     SKV_CHECK();
