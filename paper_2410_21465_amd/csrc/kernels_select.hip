@@ -205,16 +205,11 @@ __global__ __launch_bounds__(NT) void select_logits_kernel(SelectArgs a, Residen
   for (int e = 0; e < E; ++e) key[e] = j0 + e < a.n ? score_key32((double)zf[e]) : 0u;
 
   // reported ids of the selected slots (single slice): requested as soon as the selection is known
-  int id[E];
+  auto ids = selected_ids([&](int e) { return a.id_map ? a.id_map[(size_t)unit * a.id_stride + j0 + e] : j0 + e; });
   bool have_ids = false;
   auto request_ids = [&](uint32_t m) {
     have_ids = true;
-    if (a.n_slices != 1) return;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      id[e] = j0 + e;
-      if ((m & (1u << e)) && a.id_map) id[e] = a.id_map[(size_t)unit * a.id_stride + j0 + e];
-    }
+    if (a.n_slices == 1) ids.request(m);
   };
   uint32_t sel; int pos;
   const ExactOperands xo = exact_operands(a, unit);
@@ -224,13 +219,10 @@ __global__ __launch_bounds__(NT) void select_logits_kernel(SelectArgs a, Residen
   if (!have_ids) request_ids(sel);
 
   if (a.n_slices == 1) {
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-      if ((sel & (1u << e)) && pos < k_here) {
-        a.out_ids[(size_t)unit * a.k + pos] = id[e];
-        if (a.out_ids2) a.out_ids2[(size_t)unit * a.k + pos] = id[e];
-        ++pos;
-      }
+    ids.put(sel, pos, k_here, [&](int at, int id) {
+      a.out_ids[(size_t)unit * a.k + at] = id;
+      if (a.out_ids2) a.out_ids2[(size_t)unit * a.k + at] = id;
+    });
   } else {
     const size_t off = (size_t)unit * a.cand_stride + (size_t)slice * min(a.k, a.slice_len);
     uint32_t* ck = reinterpret_cast<uint32_t*>(a.cand_key);
@@ -282,16 +274,14 @@ __global__ __launch_bounds__(NT) void merge_logits_kernel(SelectArgs a) {
   double lmax = 0.0;
   for (int g = 0; g < a.G; ++g) lmax = fmax(lmax, fabs(lse_sm[g]));
 
-  int id[E];
+  auto ids = selected_ids([&](int e) {
+    const int j = ci[threadIdx.x * E + e];
+    return a.id_map ? a.id_map[(size_t)unit * a.id_stride + j] : j;
+  });
   bool have_ids = false;
   auto request_ids = [&](uint32_t m) {
     have_ids = true;
-    if (MID) return;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      id[e] = idx[e];
-      if ((m & (1u << e)) && a.id_map) id[e] = a.id_map[(size_t)unit * a.id_stride + idx[e]];
-    }
+    if (!MID) ids.request(m);
   };
   uint32_t sel; int pos;
   const ExactOperands xo = exact_operands(a, unit);
@@ -312,13 +302,10 @@ __global__ __launch_bounds__(NT) void merge_logits_kernel(SelectArgs a) {
   } else {
     // survivors are in ascending index within a slice / group and slices / groups are in order, so the
     // output is in ascending index here as well
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-      if ((sel & (1u << e)) && pos < a.k) {
-        a.out_ids[(size_t)unit * a.k + pos] = id[e];
-        if (a.out_ids2) a.out_ids2[(size_t)unit * a.k + pos] = id[e];
-        ++pos;
-      }
+    ids.put(sel, pos, a.k, [&](int at, int id) {
+      a.out_ids[(size_t)unit * a.k + at] = id;
+      if (a.out_ids2) a.out_ids2[(size_t)unit * a.k + at] = id;
+    });
   }
 }
 

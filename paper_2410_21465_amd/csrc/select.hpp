@@ -36,6 +36,16 @@ __device__ __forceinline__ int key_clz(K v) {   // v != 0
   else return __clz((int)v);
 }
 
+// Sum of the entries of tot[NW] before the wave's own: one read and a scan over the lanes (read one after the other by every
+// wave, sixteen of them took 0.3 us).
+template <int NW>
+__device__ __forceinline__ uint32_t waves_before(const uint32_t* tot, int wave) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const uint32_t t = lane < NW ? tot[lane] : 0u;
+  const uint32_t incl = wave_incl_scan_u32(t);
+  return (uint32_t)__builtin_amdgcn_readlane((int)(incl - t), __builtin_amdgcn_readfirstlane(wave));
+}
+
 // Exclusive prefix sum of `v` over the workgroup in thread order; needs sm.wave_tot.
 template <int NT>
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, SelectSmem<NT>& sm) {
@@ -44,12 +54,9 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, SelectSmem<
   const uint32_t incl = wave_incl_scan_u32(v);
   if (lane == kWave - 1) sm.wave_tot[wave] = incl;
   __syncthreads();
-  uint32_t base = 0;
-#pragma unroll
-  for (int w = 0; w < NW; ++w)
-    if (w < wave) base += sm.wave_tot[w];
+  const uint32_t before = waves_before<NW>(sm.wave_tot, wave);
   __syncthreads();
-  return base + incl - v;
+  return before + incl - v;
 }
 
 // Value of an order-preserving key (inverse of f64_key).
@@ -164,9 +171,11 @@ __device__ __forceinline__ void place_selected(uint32_t gt, uint32_t eq, uint32_
   const uint32_t pre_g = excl >> 16, pre_e = excl & 0xffffu;
   out_pos = (int)(pre_g + (pre_e < need ? pre_e : need));
   uint32_t sel = gt, rank = pre_e;
+  if (__any(eq != 0u)) {   // (seldom: elements that the search could not tell apart)
 #pragma unroll
-  for (int e = 0; e < E; ++e)
-    if (eq & (1u << e)) { if (rank < need) sel |= 1u << e; ++rank; }
+    for (int e = 0; e < E; ++e)
+      if (eq & (1u << e)) { if (rank < need) sel |= 1u << e; ++rank; }
+  }
   sel_mask = sel;
 }
 
@@ -219,14 +228,14 @@ __device__ __forceinline__ uint32_t score_key32(double z) {
 __device__ __forceinline__ double score_from_key32(uint32_t key) { return (double)key / kKeyScale - kKeyOffset; }
 
 // ---- threshold search on 32-bit score keys: one histogram pass, then the boundary bin ranked from a list ----
-// The histogram's 2048 bins count down from `key_top`, a key no element exceeds (the largest score of the unit):
-// the upper 1024 bins are 2^19 key units wide (1/64 in the score) and cover the 16 below the top, where the
-// threshold of a softmax that is not extremely peaked lies; the lower 1024 are 2^22 wide (1/8) and cover the rest
-// of the key range.  Wave 0 walks the histogram from the top to the bin that straddles the k-th position.  The few
+// The histogram's 2048 bins count down from `key_top`, a key no element exceeds (the largest score of the unit), bin 0 first:
+// the first 1024 are 2^19 key units wide (1/64 in the score) and cover the 16 below the top, where the
+// threshold of a softmax that is not extremely peaked lies; 896 more are 2^22 wide (1/8) and cover the rest
+// of the key range.  All waves walk the histogram together to the bin that straddles the k-th position.  The few
 // keys in that bin are put on a list and ranked against each other (larger key first, equal keys by order
 // index): no further passes.  A boundary bin with more keys than the list holds falls back to radix passes among
 // them.
-constexpr int kHistBins = 2048, kFineShift = 19, kCoarseShift = 22;
+constexpr int kHistBins = 2048, kFineBins = 1024, kFineShift = 19, kCoarse = 3;   // (a coarse bin: 2^kCoarse fine ones)
 constexpr int kListCap = 512;
 template <int NT>
 struct Select32Smem {
@@ -247,19 +256,15 @@ __device__ __forceinline__ void threshold32_prepare(Select32Smem<NT>& sm) {
   if (threadIdx.x == 0) sm.list_n = 0u;
 }
 __device__ __forceinline__ uint32_t hist_bin(uint32_t key, uint32_t key_top) {
-  const uint32_t d = key < key_top ? key_top - key : 0u;            // distance below the top
-  const uint32_t fine = (uint32_t)(kHistBins / 2) << kFineShift;    // 2^29: the part the fine bins cover
-  if (d < fine) return (uint32_t)kHistBins - 1u - (d >> kFineShift);
-  const uint32_t c = (d - fine) >> kCoarseShift;                    // at most (2^32 - 2^29) >> 22 = 896
-  return (uint32_t)(kHistBins / 2) - 1u - c;
+  const uint32_t f = (key_top - min(key, key_top)) >> kFineShift;   // below 2^13
+  // (the smaller one: they meet at f = kFineBins)
+  return min(f, (f >> kCoarse) + (uint32_t)(kFineBins - (kFineBins >> kCoarse)));
 }
 
 // smallest key that falls into `bin` (inverse of hist_bin at the bin's lower edge; 0 when the edge is below every key)
 __device__ __forceinline__ uint32_t hist_bin_floor(uint32_t bin, uint32_t key_top) {
-  const uint32_t fine = (uint32_t)(kHistBins / 2) << kFineShift;
-  uint64_t d_max;   // largest distance below the top that still maps to `bin`
-  if (bin >= (uint32_t)(kHistBins / 2)) d_max = (((uint64_t)kHistBins - bin) << kFineShift) - 1u;
-  else d_max = (uint64_t)fine + ((((uint64_t)(kHistBins / 2) - bin)) << kCoarseShift) - 1u;
+  const uint32_t f = bin < (uint32_t)kFineBins ? bin + 1u : (bin + 1u - (uint32_t)(kFineBins - (kFineBins >> kCoarse))) << kCoarse;
+  const uint64_t d_max = ((uint64_t)f << kFineShift) - 1u;   // largest distance below the top that still maps to `bin`
   return d_max >= key_top ? 0u : key_top - (uint32_t)d_max;
 }
 
@@ -279,24 +284,26 @@ __device__ bool threshold32(const uint32_t (&key)[E], uint32_t k, uint32_t key_t
     if (key[e]) atomicAdd(&sm.hist[bins[e]], 1u);
   }
   __syncthreads();
-  if (wave == 0) {
-    // lane l owns the 32 bins from hi = 2047 - 32 l downwards
-    constexpr int PER = kHistBins / kWave;
-    const int hi = kHistBins - 1 - PER * lane;
+  // thread t owns PER bins.  (One wave with 32 bins a lane, which all lie in the same banks, took 1.1 to 1.8 us; this 0.4.)
+  {
+    constexpr int PER = kHistBins / NT, NW = NT / kWave;
     uint32_t c[PER], tot = 0;
 #pragma unroll
-    for (int j = 0; j < PER / 4; ++j) {
-      const uint4 v = *reinterpret_cast<const uint4*>(&sm.hist[hi - 3 - 4 * j]);
-      c[4 * j] = v.w; c[4 * j + 1] = v.z; c[4 * j + 2] = v.y; c[4 * j + 3] = v.x;   // descending bins
-      tot += v.x + v.y + v.z + v.w;
+    for (int j = 0; j < PER; j += 2) {
+      const uint2 v = *reinterpret_cast<const uint2*>(&sm.hist[PER * threadIdx.x + j]);
+      c[j] = v.x; c[j + 1] = v.y;
+      tot += v.x + v.y;
     }
-    const uint32_t incl = wave_incl_scan_u32(tot), excl = incl - tot;
-    if (excl < k && k <= incl) {
-      uint32_t run = excl;
+    const uint32_t incl = wave_incl_scan_u32(tot);
+    if (lane == kWave - 1) sm.red[wave] = incl;
+    __syncthreads();
+    const uint32_t last = waves_before<NW>(sm.red, wave) + incl;
+    if (last - tot < k && k <= last) {
+      uint32_t run = last - tot;
       bool found = false;
 #pragma unroll
       for (int i = 0; i < PER; ++i) {
-        if (!found && k <= run + c[i]) { sm.bin = (uint32_t)(hi - i); sm.above = run; sm.cnt = c[i]; found = true; }
+        if (!found && k <= run + c[i]) { sm.bin = (uint32_t)(PER * threadIdx.x + i); sm.above = run; sm.cnt = c[i]; found = true; }
         run += c[i];
       }
     }
@@ -308,20 +315,23 @@ __device__ bool threshold32(const uint32_t (&key)[E], uint32_t k, uint32_t key_t
   gt = 0; eq = 0;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
-    const bool present = key[e] != 0u;
-    gt |= (uint32_t)(present & (bins[e] > bin)) << e;
-    cand |= (uint32_t)(present & (bins[e] == bin)) << e;
+    // (key 0, absent, lies in no bin before that of a key)
+    gt |= (uint32_t)(bins[e] < bin) << e;
+    cand |= (uint32_t)((key[e] != 0u) & (bins[e] == bin)) << e;
   }
+  const bool have_cand = __any(cand != 0u);   // (a wave: few have one)
   tu_known = false;
   if (cnt > (uint32_t)kWave && cnt == need) { eq = cand; return true; }      // the whole bin is wanted
   if (cnt <= (uint32_t)kListCap) {
+    if (have_cand) {
 #pragma unroll
-    for (int e = 0; e < E; ++e)
-      if (cand & (1u << e)) {
-        const uint32_t slot = atomicAdd(&sm.list_n, 1u);
-        sm.list_key[slot] = key[e];
-        sm.list_ord[slot] = threadIdx.x * E + e;
-      }
+      for (int e = 0; e < E; ++e)
+        if (cand & (1u << e)) {
+          const uint32_t slot = atomicAdd(&sm.list_n, 1u);
+          sm.list_key[slot] = key[e];
+          sm.list_ord[slot] = threadIdx.x * E + e;
+        }
+    }
     __syncthreads();
     if (cnt <= (uint32_t)kWave) {
       // every wave ranks the list in its registers: lane i holds entry i and counts the entries ahead of it
@@ -342,10 +352,12 @@ __device__ bool threshold32(const uint32_t (&key)[E], uint32_t k, uint32_t key_t
         u_key = fl > 1u ? fl - 1u : 0u;
       }
       tu_known = true;
+      if (have_cand) {
 #pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const bool in = (key[e] > t_key) | ((key[e] == t_key) & (threadIdx.x * E + e <= t_ord));
-        gt |= (uint32_t)(((cand >> e) & 1u) & in) << e;
+        for (int e = 0; e < E; ++e) {
+          const bool in = (key[e] > t_key) | ((key[e] == t_key) & (threadIdx.x * E + e <= t_ord));
+          gt |= (uint32_t)(((cand >> e) & 1u) & in) << e;
+        }
       }
       need = 0;
       return true;
@@ -353,7 +365,7 @@ __device__ bool threshold32(const uint32_t (&key)[E], uint32_t k, uint32_t key_t
     // a longer list: every thread walks it once (broadcast reads) and counts, for each of its own candidates, the
     // entries ahead of it.  Equal keys on both sides of the boundary are ranked by order index here; the caller sees them
     // as a taken and a left-out element with the same key and settles them on exact scores.
-    if (__builtin_amdgcn_readfirstlane(__any(cand != 0u))) {
+    if (have_cand) {
       uint32_t ahead[E];
 #pragma unroll
       for (int e = 0; e < E; ++e) ahead[e] = 0u;
@@ -379,6 +391,35 @@ __device__ bool threshold32(const uint32_t (&key)[E], uint32_t k, uint32_t key_t
   classify<E, uint32_t>(k2, det_val, det_mask, gt, eq);
   return all_wanted;
 }
+
+// Reported ids of a thread's selected elements, the first kFetched of them requested ahead of their use (of 16 elements
+// seldom more than two are selected; a branch for each of the 16 took longer than the whole of this).
+constexpr int kFetched = 3;
+template <class IdOf>
+struct SelectedIds {
+  IdOf id_of;   // id_of(e): the id of the thread's element e, from memory
+  int id[kFetched];
+  __device__ __forceinline__ void request(uint32_t m) {
+#pragma unroll
+    for (int u = 0; u < kFetched; ++u) {
+      if (m) id[u] = id_of(__ffs((int)m) - 1);
+      m &= m - 1u;   // (0 stays 0)
+    }
+  }
+  // write(pos, id) for the elements of m, which `request` was given, at pos, pos + 1, ... below `end`
+  template <class Write>
+  __device__ __forceinline__ void put(uint32_t m, int pos, int end, Write write) const {
+#pragma unroll
+    for (int u = 0; u < kFetched; ++u) {
+      if (m && pos < end) write(pos, id[u]);
+      pos += m ? 1 : 0;
+      m &= m - 1u;
+    }
+    for (; m && pos < end; ++pos, m &= m - 1u) write(pos, id_of(__ffs((int)m) - 1));
+  }
+};
+template <class IdOf>
+__device__ __forceinline__ SelectedIds<IdOf> selected_ids(IdOf id_of) { return SelectedIds<IdOf>{id_of, {}}; }
 
 // The k largest of the exact scores z, found through 32-bit keys of approximate scores z~ (key = score_key32(z~)):
 //   |z~ - z| <= u_rel * (|z~| + lmax)  for every element, where lmax bounds the magnitude of what was subtracted
