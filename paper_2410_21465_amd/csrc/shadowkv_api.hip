@@ -109,6 +109,7 @@ int check_params(const shadowkv_params* p, bool decode, Shape* sh) {
 // rows (outliers + recent tokens).
 struct AttnPlan {
   int res_split_len, sparse_split_len, n_splits, z;
+  int room_splits;                // splits that workspaces have room for
   int pv_split_len, n_pv_splits;  // second phase of the two-phase path (values gathered meanwhile)
 };
 AttnPlan plan_attention(const Shape& sh, bool with_cache = false) {
@@ -116,18 +117,39 @@ AttnPlan plan_attention(const Shape& sh, bool with_cache = false) {
   ap.z = (sh.G + attention_heads_per_group(sh.G) - 1) / attention_heads_per_group(sh.G);
   const long groups = (long)sh.units * ap.z;
   const long kc = (long)sh.k * sh.c, n_res = (long)sh.o * sh.c + sh.w;
-  // the largest split (fewest B^T stagings) that still gives >= 512 workgroups; the kernel with key and value
-  // waves runs one 1024-thread workgroup per compute unit: 256 of them fill the chip
-  const bool roles = attention_has_roles(sh.G, sh.c, sh.k, sh.keep_keys, sh.stage || with_cache);
-  const long want = roles ? 256 : 512;
+  const bool gathers = sh.stage || with_cache, roles = attention_has_roles(sh.G, sh.c, sh.k, sh.keep_keys, gathers);
+  // What workspaces have room for: the largest power of two of rows that gives 256 workgroups with key and value waves, 512 of
+  // the others.
   long len = 32;
-  for (long cand : {1024l, 512l, 256l, 128l, 64l}) if (kc * groups / cand >= want) { len = cand; break; }
+  for (long cand : {1024l, 512l, 256l, 128l, 64l}) if (kc * groups / cand >= (roles ? 256 : 512)) { len = cand; break; }
+  while ((kc + len - 1) / len > 65535) len *= 2;   // the splits are a grid dimension
+  const long room = (kc + len - 1) / len;
+  if (roles) {
+    // One 1024-thread workgroup per compute unit: what a step takes is the rounds of 256 workgroups times a split's rows and some
+    // 320 rows' worth of staging and merging.  The splits that fill one to eight rounds are compared.  Attention with all
+    // the room and so (us, workgroups): 3 x 61K with seven heads 23.9 (288) and 17.4 (192), 5 x 32K 32.1 (320) and 23.2 (240),
+    // 6 x 64K FP8 of 120 chunks 26.3 (384) and 19.0 (240), 12 x 61K 43.9 (384) and 38.3 (192).
+    const long fewest = (kc + 1023) / 1024;
+    long best = 0;
+    for (long rounds = 1; rounds <= 8; ++rounds) {
+      const long splits = std::max(fewest, std::min(room, 256 * rounds / groups));
+      const long rows = ((kc + splits - 1) / splits + 31) / 32 * 32, wgs = groups * ((kc + rows - 1) / rows);
+      const long cost = (wgs + 255) / 256 * (rows + 320);
+      if (rounds == 1 || cost < best) { best = cost; len = rows; }
+    }
+  } else {
+    // Two workgroups or more per compute unit: the largest split (fewest B^T stagings) that still gives >= 512 workgroups, but
+    // no fewer rows than the four waves take at a time (1 x 32K without groups, 100 chunks: 19.1 us with 32, 14.6 with 64),
+    // and beside a gather, which wants compute units of its own, twice that (1 x 1M 49.7 us with 32, 48.5 with 64, 40.7).
+    len = std::max(len, gathers ? 128l : 64l);
+  }
   // tuning override: rows per split (read once)
   static const long forced = [] { const char* ov = std::getenv("SHADOWKV_SPARSE_SPLIT"); return ov ? std::atol(ov) : 0l; }();
   if (forced >= 32 && forced <= 1024 && forced % 32 == 0) len = forced;
-  while ((kc + len - 1) / len > 65535) len *= 2;   // the splits are a grid dimension
+  while ((kc + len - 1) / len > 65535) len *= 2;
   ap.sparse_split_len = (int)len;
   ap.n_splits = (int)((kc + len - 1) / len);
+  ap.room_splits = std::max((int)room, ap.n_splits);
   ap.res_split_len = (int)((n_res + ap.n_splits - 1) / ap.n_splits);
   ap.pv_split_len = 256;
   ap.n_pv_splits = (int)((kc + ap.pv_split_len - 1) / ap.pv_split_len);
@@ -164,7 +186,7 @@ DecodeLayout decode_layout(const Shape& sh) {
   L.v_sparse = off; off += sh.stage ? up(rows * sh.d * sh.eb) : 0;
   // (a step with a value cache plans its splits for the two-phase kernels: room for whichever has more)
   const AttnPlan cached = plan_attention(sh, true);
-  const size_t n_part = (size_t)std::max(L.attn.n_splits, cached.n_splits) + L.attn.n_pv_splits;
+  const size_t n_part = (size_t)std::max(L.attn.room_splits, cached.room_splits) + L.attn.n_pv_splits;
   L.part_acc = off; off += up(heads * n_part * sh.d * sizeof(float));
   L.part_ml = off; off += up(heads * n_part * sizeof(float2));
   L.total = off;

@@ -1,0 +1,28 @@
+"""Decode steps whose selected rows are cut into splits that are no power of two: parts of a step of 192 rows, several steps with a
+rest, a last split that is shorter than the others, against the oracle (the bounds of every decode test)."""
+import pytest
+
+from paper_2410_21465_amd import shadowkv as S
+from workloads import Workload
+
+import parity_util as PU
+
+pytestmark = pytest.mark.gpu
+
+
+# (batch, query heads, KV heads, head_dim, selected chunks of 8, rank, rows per split)
+@pytest.mark.parametrize("b,hq,hkv,d,k,r,rows", [(8, 8, 2, 64, 189, 56, 96), (6, 14, 2, 128, 189, 136, 160), (10, 14, 2, 64, 300, 64, 416),
+                                                  (6, 4, 4, 64, 33, 32, 64)])
+@pytest.mark.parametrize("kd", [0, 1])
+def test_odd_splits(b, hq, hkv, d, k, r, rows, kd):
+    wl = Workload("splits", batch=b, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, ctx_len=3200, chunk_size=8, rank=r,
+                  n_outlier_chunks=3, topk_chunks=k, local_len=7, rope_theta=1e4, seed=17, n_queries=1)
+    plan = S.decode_plan(S.Params.from_workload(wl, kv_dtype=kd))
+    print(f"[case] {wl} kv_dtype {kd} {plan}", flush=True)
+    assert plan["rows_per_split"] == rows
+    t = PU.draw(wl)
+    if kd:
+        from workloads import to_fp8_storage
+        t = to_fp8_storage(t)
+    ref_b, _ = PU.run_build_parity(wl, t, kv_dtype=kd)
+    PU.run_decode_parity(wl, t, ref_b, check_keys=False, kv_dtype=kd)
