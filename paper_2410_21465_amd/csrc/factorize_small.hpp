@@ -458,12 +458,12 @@ __global__ __launch_bounds__(256) void trsm_kernel(const double* __restrict__ Lp
 // rotations accumulated in V: then the norms of W's columns are the eigenvalues of T and the columns of V its eigenvectors.
 // The columns are taken as nb = mp / 16 blocks; a step pairs the blocks up (circle method: (nb-1, st), ((st+i) mod (nb-1),
 // (st-i) mod (nb-1))), and a workgroup makes the 16 x 16 pairs of columns between its two blocks orthogonal (in the first
-// step of a sweep and ahead of the sweeps all pairs of its 32 columns): it forms the 32 x 32 products of the columns on the matrix instruction,
-// rotates those (two-sided, in LDS, 16 disjoint rotations at a time, accumulated in J) and applies J to its columns as one
-// product.  A rotation's angle thus costs two rounds of LDS and a barrier, not a pass over the columns and a launch: a
-// sweep of 192 columns is 11 launches of 17 us (the first 26, those without a rotation 6) where a launch per set of 96
-// single rotations took 191 of 4.5 us, and six sweeps do (1.0 ms in all, 8.1 ms before, one sequence; 16 sequences: 1.3 ms,
-// 11.4 ms).
+// step of a sweep and ahead of the sweeps all pairs of its 32 columns): it forms the 32 x 32 products of the columns on the
+// matrix instruction, rotates those (two-sided, in LDS, 16 disjoint rotations at a time, accumulated in J) and applies J to
+// its columns as one product.  A rotation's angle thus costs two rounds of LDS and a barrier, not a pass over the columns and
+// a launch: a sweep of 192 columns is 11 launches of 14 us (the first 21, those without a rotation 6) where a launch per set of
+// 96 single rotations took 191 of 4.5 us.  In all 0.67 ms for one sequence, 1.0 with six sweeps and no passes ahead of them, 8.1
+// with single rotations.
 // V is not needed before the end: its product with J is done by other workgroups of the next step's launch.
 // A sweep in which every cosine met was below kJacobiDone needs no successor (what is left is its square): the launches of
 // the later ones end at once.  sweep_max [batch][sweeps]: the largest cosine of each sweep (its bits; cosines are >= 0).

@@ -709,7 +709,7 @@ int shadowkv_append_chunk(const shadowkv_params* params, const shadowkv_kv* k_pr
 }
 
 constexpr int kFactorOversample = 32;  // extra vectors carried by the subspace iteration
-constexpr int kFactorSweeps = 9;       // most Jacobi sweeps of the Ritz step (192 vectors: six; later ones end at once)
+constexpr int kFactorSweeps = 9;       // most Jacobi sweeps of the Ritz step (192 vectors: three, six without the passes ahead of them; later ones end at once)
 
 size_t shadowkv_factorize_workspace_bytes(const shadowkv_params* params) {
   Shape sh;
