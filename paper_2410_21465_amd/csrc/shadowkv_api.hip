@@ -109,7 +109,7 @@ int check_params(const shadowkv_params* p, bool decode, Shape* sh) {
 // rows (outliers + recent tokens).
 struct AttnPlan {
   int res_split_len, sparse_split_len, n_splits, z;
-  int room_splits;                // splits that workspaces have room for
+  int room_splits;                // parts (of both phases) that workspaces have room for
   int pv_split_len, n_pv_splits;  // second phase of the two-phase path (values gathered meanwhile)
 };
 AttnPlan plan_attention(const Shape& sh, bool with_cache = false) {
@@ -153,6 +153,14 @@ AttnPlan plan_attention(const Shape& sh, bool with_cache = false) {
   ap.res_split_len = (int)((n_res + ap.n_splits - 1) / ap.n_splits);
   ap.pv_split_len = 256;
   ap.n_pv_splits = (int)((kc + ap.pv_split_len - 1) / ap.pv_split_len);
+  ap.room_splits += ap.n_pv_splits;
+  // Half of that where the first phase leaves room for twice as many parts: its workgroups are chains of dependent loads, four
+  // times 64 rows or twice (values and merge of 1 x 1M 16.2 -> 13.2 us, 5 x 32K 17.9 -> 15.5, 3 x 32K with seven heads 16.5 ->
+  // 14.2; with 64 rows 13.0, 18.0 and 16.6).
+  if (ap.n_splits + (kc + 127) / 128 <= ap.room_splits) {
+    ap.pv_split_len = 128;
+    ap.n_pv_splits = (int)((kc + 127) / 128);
+  }
   return ap;
 }
 
@@ -186,7 +194,7 @@ DecodeLayout decode_layout(const Shape& sh) {
   L.v_sparse = off; off += sh.stage ? up(rows * sh.d * sh.eb) : 0;
   // (a step with a value cache plans its splits for the two-phase kernels: room for whichever has more)
   const AttnPlan cached = plan_attention(sh, true);
-  const size_t n_part = (size_t)std::max(L.attn.room_splits, cached.room_splits) + L.attn.n_pv_splits;
+  const size_t n_part = (size_t)std::max(L.attn.room_splits, cached.room_splits);
   L.part_acc = off; off += up(heads * n_part * sh.d * sizeof(float));
   L.part_ml = off; off += up(heads * n_part * sizeof(float2));
   L.total = off;
