@@ -13,10 +13,14 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 struct Every { const int32_t* every; int step; };
 __device__ __forceinline__ bool step_left_out(Every e, int sequence) { return e.every && e.step % e.every[sequence] != 0; }
 
+// What a factor says of the shifted steps of its sequence: b, of whose shares the shifts are, and a power of two that brings the
+// longest vector of a step between 1/2 and 1 (see chol_kernel).
+struct Shift { double b, scale; };
+
 // ---- products ---------------------------------------------------------------------------------------
 // C[i][j] = sum_k A[i][k] B(k, j), K a multiple of 16, rows of A 16-byte aligned.  BT: B is given by its columns
 // (B(k, j) = B[j][k], as A is); otherwise row-major with Kb rows (A is zero beyond).  Rows of A may be taken through
-// a_rows.  C is written over Mw x Nw, zero outside M x N.  With `shift` (one number per sequence; N = K): C = A (B - node shift).
+// a_rows.  C is written over Mw x Nw, zero outside M x N.  With `shift` (one per sequence; N = K): C = A (B - node b) scale.
 // With `every`, see step_left_out; with `lower` blocks above the diagonal are left as they were.
 // A workgroup is WM x WN tiles of 16 T x 16 T with the contraction cut WK ways; every operand goes from L2 straight to the
 // matrix instruction (a lane's four consecutive elements are four contraction steps), the next 16 steps requested
@@ -29,7 +33,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm64_kernel(const double*
                                                                    int M, int N, int K, int Kb, int lda, int ldb, int ldc,
                                                                    int Mw, int Nw, size_t strideA, size_t strideB, size_t strideC,
                                                                    const int32_t* __restrict__ a_rows, int a_rows_stride,
-                                                                   const double* __restrict__ shift, double node, Every every,
+                                                                   const Shift* __restrict__ shift, double node, Every every,
                                                                    bool lower) {
   if (step_left_out(every, blockIdx.z) || (lower && blockIdx.x * WN >= (blockIdx.y + 1) * WM)) return;
   __shared__ double red[WM * WN][WK][4 * T * T][kWave];
@@ -90,7 +94,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm64_kernel(const double*
 #pragma unroll
       for (int j = 0; j < 4; ++j) red[wt][wk][(x * T + y) * 4 + j][lane] = acc[x][y][j];
   __syncthreads();
-  const double theta = shift ? node * shift[blockIdx.z] : 0.0;
+  const double theta = shift ? node * shift[blockIdx.z].b : 0.0, scale = shift ? shift[blockIdx.z].scale : 1.0;
   // the WK waves of a tile add up its 4 T T registers in turn
 #pragma unroll
   for (int reg = wk; reg < 4 * T * T; reg += WK) {
@@ -99,7 +103,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm64_kernel(const double*
 #pragma unroll
     for (int w = 0; w < WK; ++w) sum += red[wt][w][reg][lane];
     const int i = i0 + 16 * (tile / T) + 4 * (reg & 3) + kq, j = j0 + 16 * (tile % T) + sub;
-    if (shift && i < M && j < N) sum = fma(-theta, A[(size_t)i * lda + j], sum);
+    if (shift && i < M && j < N) sum = fma(-theta, A[(size_t)i * lda + j], sum) * scale;
     if (i < Mw && j < Nw) C[(size_t)i * ldc + j] = (i < M && j < N) ? sum : 0.0;
   }
 }
@@ -231,13 +235,16 @@ __device__ __forceinline__ double factor_block(f64x4 a, const double (&e0)[4], d
 // pivots, column, trailing blocks with four barriers a step, took 49.  Above 192 vectors a wave's blocks fill its registers.
 // A pivot below kPivotFloor of the vector's own square is rounding: it is set to that floor, which leaves the vector's
 // remainder at a size that the next pass can work on, and nothing is projected on it; a zero vector stays zero.
-// smallest (may be NULL): the least entry of L's diagonal of each sequence, 0 where a pivot was set to its floor; and
-// `pause`: how many of the steps that follow may go without an orthonormalisation in between, one more than that.  What an
-// earlier vector leaves in a later one by rounding (1e-16) grows by the ratio of their eigenvalues in every step; up to three
-// steps, as long as the largest ratio (that of the longest vector and the least entry) to their number is below 1e13.
+// shift (may be NULL): of each sequence b, the least entry of L's diagonal, 0 where a pivot was set to its floor, and the power
+// of two that brings the longest vector between 1/2 and 1; and `pause`: how many of the steps that follow may go without an
+// orthonormalisation in between, one more than that.  What an earlier vector leaves in a later one by rounding (1e-16) grows by
+// the ratio of their eigenvalues in every step; up to three steps, as long as the largest ratio (that of the longest vector and
+// the least entry) to their number is below 1e13.  The products of vectors three steps apart from orthonormal ones are sixth
+// powers of eigenvalues, twelfth powers of singular values: without the power of two those of keys beyond 2^82 leave fp64, and
+// those of keys below 2^-82 fall under what counts as a zero vector.
 template <int NBW>
 __global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S, double* __restrict__ Lp, int nb,
-                                                   double* __restrict__ smallest, int32_t* __restrict__ pause, Every every) {
+                                                   Shift* __restrict__ shift, int32_t* __restrict__ pause, Every every) {
   if (step_left_out(every, blockIdx.x)) return;
   __shared__ double col[kMaxFactorBlocks][272];   // current block column, rows at a pitch of 17
   __shared__ double sol[kMaxFactorBlocks][256];   // the same times the diagonal block's inverse, operand order
@@ -315,14 +322,17 @@ __global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S,
 #pragma unroll
       for (int j = 0; j < 4; ++j) a[j] = -(d[j] + y[j]);
     }
-    if (smallest) {
+    if (shift) {
       least = fmin(least, shfl_xor_f64(least, 16));
       least = fmin(least, shfl_xor_f64(least, 32));
       double longest = 0.0;
       for (int i = lane; i < ld; i += kWave) longest = fmax(longest, S[(size_t)i * (ld + 1)]);
       longest = wave_max_f64(longest);
       if (lane == 0) {
-        smallest[blockIdx.x] = least < INFINITY ? sqrt(least) : 0.0;
+        // (the root first: its exponent is the vector's; zeros and what is not finite are left as they are)
+        const bool finite = longest > 0.0 && longest < INFINITY;
+        shift[blockIdx.x] = {least < INFINITY ? sqrt(least) : 0.0,
+                             finite ? ldexp(1.0, -__builtin_amdgcn_frexp_exp(sqrt(longest))) : 1.0};
         const double x = longest / least;   // squared ratio (without pivots, and where one was floored: one step at a time)
         pause[blockIdx.x] = least > 0.0 && x * x * x <= 1e26 ? 3 : least > 0.0 && x * x <= 1e26 ? 2 : 1;
       }

@@ -333,7 +333,7 @@ struct Mat { const double* p; int ld; size_t stride; };
 template <bool BT>
 static hipError_t gemm64(Mat A, Mat B, double* C, int ldc, size_t strideC, int M, int N, int K, int Kb, int Mw, int Nw,
                          int batch, hipStream_t st, const int32_t* a_rows = nullptr, int a_rows_stride = 0,
-                         const double* shift = nullptr, double node = 0.0, Every every = {nullptr, 0}, bool lower = false) {
+                         const Shift* shift = nullptr, double node = 0.0, Every every = {nullptr, 0}, bool lower = false) {
   const long tiles = (long)((Mw + 31) / 32) * ((Nw + 31) / 32) * batch;
 #define SKV_GEMM(T_, WM_, WN_, WK_)                                                                                       \
   hipLaunchKernelGGL((gemm64_kernel<T_, WM_, WN_, WK_, BT>), dim3((Nw + 16 * T_ * WN_ - 1) / (16 * T_ * WN_),             \
@@ -438,7 +438,8 @@ FactorizePlan plan_factorize(int batch, int s, int D, int r, int oversample, int
   const size_t vectors = (size_t)(r + 31) / 32 * 32;
   size_t end = off + std::max(doubles(m * D), up((size_t)batch * (vectors / 32) * ((D + 63) / 64) * kPsiStage));
   p.W = p.S = end; end += doubles(mp * mp);
-  p.idle = p.shift = end; end += up((size_t)2 * batch * (mp / 32) * 4);   // (the shift is last read before the sweeps)
+  // (the shifts are last read before the sweeps)
+  p.idle = p.shift = end; end += up(std::max((size_t)2 * batch * (mp / 32) * 4, m < (size_t)D ? batch * sizeof(Shift) : 0));
   p.sweep_max = end; end += up((size_t)batch * n_sweeps * 4);
   p.order = end; end += up((size_t)batch * r * 4);
   p.psi_exps = end; end += up((size_t)batch * vectors * 4);
@@ -568,14 +569,14 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
   // X <- orthonormal basis of the rows of Y, each row from the ones before it (see chol_kernel)
   const int nbc = (m + 15) / 16;
   // (with `every` for those sequences whose turn it is, X <- Y for the others)
-  auto orthonormalise = [&](const double* Y, double* X, double* smallest = nullptr, int32_t* pause = nullptr,
+  auto orthonormalise = [&](const double* Y, double* X, Shift* shift = nullptr, int32_t* pause = nullptr,
                             Every every = {nullptr, 0}) -> hipError_t {
     hipError_t err = gemm64<true>({Y, D, (size_t)m * D}, {Y, D, (size_t)m * D}, S, 16 * nbc, (size_t)256 * nbc * nbc, m, m, D, D, 16 * nbc, 16 * nbc, batch, st,
                                   nullptr, 0, nullptr, 0.0, every, true);
     if (err != hipSuccess) return err;
 #define SKV_ORTH(NBW_, NB_)                                                                                       \
   do {                                                                                                            \
-    hipLaunchKernelGGL(chol_kernel<NBW_>, dim3(batch), dim3(512), 0, st, S, Lp, nbc, smallest, pause, every); \
+    hipLaunchKernelGGL(chol_kernel<NBW_>, dim3(batch), dim3(512), 0, st, S, Lp, nbc, shift, pause, every); \
     hipLaunchKernelGGL(trsm_kernel<NB_>, dim3(D / 16, batch), dim3(256), 0, st, Lp, Y, X, m, nbc, D, every);         \
   } while (0)
     // (blocks per wave of the eight, block rows held): up to 80, 192, 224, 288 vectors
@@ -587,7 +588,7 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
     return hipGetLastError();
   };
   // Y = X (G - node shift); G is symmetric, so its rows are its columns
-  auto times_gram = [&](const double* X, double* Y, const double* by = nullptr, double node = 0.0) {
+  auto times_gram = [&](const double* X, double* Y, const Shift* by = nullptr, double node = 0.0) {
     return gemm64<true>({X, D, (size_t)m * D}, {G, D, (size_t)D * D}, Y, D, (size_t)m * D, m, D, D, D, m, D, batch, st, nullptr, 0, by, node);
   };
   // Steps of G alone damp what lies beyond the m vectors by lam_(m+1) / lam_r each.  By default four of these are followed by
@@ -601,7 +602,7 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
   // small ones take turns.
   constexpr int kPlain = 4, kPoints = 9;
   const bool shifted = n_iter == 0 && m < D;
-  double* shift = reinterpret_cast<double*>(ws + pl.shift);
+  Shift* shift = reinterpret_cast<Shift*>(ws + pl.shift);
   int32_t* pause = order;   // (the order is found after these steps)
   const int steps = n_iter ? n_iter : shifted ? kPlain + kPoints : 16;
   for (int it = 0; it < steps; ++it) {

@@ -94,3 +94,44 @@ def test_keys_at_the_ends_of_the_storage_types_range(h, d, s, r, exp2):
     assert np.abs(psi @ psi.T - np.eye(r)).max() < 1e-12
     assert np.abs(sig ** 2 - lam[:r]).max() <= 1e-12 * lam[0]
     assert np.abs(psi @ G - (sig ** 2)[:, None] * psi).max() <= 1e-12 * lam[0]
+
+
+# Exponent of column x's scale.  The largest eigenvalue over that of the last vector decides after how many shifted steps vectors
+# are made orthonormal again: three up to 10^(13/3), two up to 10^6.5, each beyond.
+GRADED = {
+    3: lambda x: -min(8, max(0, (x - 128) // 16)),
+    2: lambda x: -min(12, x // 20),
+    1: lambda x: -min(20, x // 12),
+}
+
+
+@pytest.mark.parametrize("pause", [0, 1, 2, 3])
+@pytest.mark.parametrize("end", ["least", -90, 0, 90, "most"])
+def test_keys_at_the_ends_of_the_range_with_fewer_vectors_than_columns(pause, end):
+    """Keys of 0 and +-2^e with graded (pause > 0) and equal columns, 192 vectors of 512: the steps that follow each other without
+    an orthonormalisation take eigenvalues to their third power and the products of vectors to the sixth."""
+    h, d, s, r = 4, 128, 1000, 160
+    D = h * d
+    exps = torch.tensor([GRADED[pause](x) if pause else 0 for x in range(D)], dtype=torch.float64)
+    exp2 = {"least": -133 - int(exps.min()), "most": 126}.get(end, end)
+    print(f"\n[case] pause {pause} scale 2^{exp2}", flush=True)
+    gen = torch.Generator(device="cpu").manual_seed(D + pause)
+    K = torch.randint(-1, 2, (s, D), generator=gen).double() * torch.exp2(exps)[torch.randperm(D, generator=gen)]
+    k = (K * 2.0 ** exp2).to(torch.bfloat16)[None]
+    assert torch.equal(k[0].double() * 2.0 ** -exp2, K)
+    p = S.Params(batch=1, n_q_heads=h, n_kv_heads=h, head_dim=d, ctx_len=s, chunk_size=1, rank=r, n_outlier_chunks=0,
+                 topk_chunks=1, local_len=0)
+    got = {n: S.factorize_keys(p, k.cuda(), want_vectors=True, n_iter=n) for n in (0, 16)}
+    torch.cuda.synchronize()
+    G = (K.T @ K).numpy()
+    lam = np.linalg.eigvalsh(G)[::-1]
+    ratio = lam[0] / lam[r + 31]
+    assert {3: 1.0, 2: 1e13 ** (1 / 3), 1: 1e6 * 10 ** 0.5}.get(pause, 0.0) < ratio < {3: 1e13 ** (1 / 3), 2: 1e6 * 10 ** 0.5}.get(pause, np.inf)
+    res = {}
+    for n, g in got.items():
+        psi, sig = g["psi"][0].cpu().numpy(), g["sigma"][0].cpu().numpy() * 2.0 ** -exp2
+        assert np.abs(psi @ psi.T - np.eye(r)).max() < 1e-12
+        res[n] = np.linalg.norm(psi @ G - (sig ** 2)[:, None] * psi)
+    print(f"[ends] residual / lam_1 {res[0] / lam[0]:.1e} (16 plain steps {res[16] / lam[0]:.1e})", flush=True)
+    # rounding, of sums of at most a thousand terms: 1e-12 of the largest eigenvalue
+    assert res[0] <= res[16] + 1e-12 * lam[0]
