@@ -588,29 +588,35 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
     return hipGetLastError();
   };
   // Y = X (G - node shift); G is symmetric, so its rows are its columns
-  auto times_gram = [&](const double* X, double* Y, const Shift* by = nullptr, double node = 0.0) {
-    return gemm64<true>({X, D, (size_t)m * D}, {G, D, (size_t)D * D}, Y, D, (size_t)m * D, m, D, D, D, m, D, batch, st, nullptr, 0, by, node);
+  auto times_gram = [&](const double* X, double* Y, const Shift* by = nullptr, double node = 0.0, Every every = {nullptr, 0}) {
+    return gemm64<true>({X, D, (size_t)m * D}, {G, D, (size_t)D * D}, Y, D, (size_t)m * D, m, D, D, D, m, D, batch, st, nullptr, 0, by,
+                        node, every);
   };
   // Steps of G alone damp what lies beyond the m vectors by lam_(m+1) / lam_r each.  By default four of these are followed by
   // nine of G - theta_j with theta_j the Chebyshev points of [0, b], b the least entry of the fourth factor's diagonal: 0.8 to
   // 1.2 lam_m on every spectrum tried, at which the nine damp like 1 / T_9(2 lam_r / b - 1).  On spectra with lam_(m+1) / lam_r
   // from 0.9 to 0.15 the r vectors come out 5 to 1000 times closer than after 16 steps of G, below that alike to rounding (numpy
-  // model, keys of 30 kinds).  Where a pivot was rounding b is 0.  Of the nine every third, or second, is followed by an
+  // model, keys of 30 kinds).  Where a pivot was rounding b is 0, nothing is shifted, and three steps more make sixteen plain
+  // ones.  Of the nine every third, or second, is followed by an
   // orthonormalisation where the eigenvalues lie close enough (see chol_kernel), and the last: after four steps the vectors are
   // near enough to single eigenvectors that another step mostly scales them.  (Same model, 25 kinds,
   // eigenvalues from alike to 1e30 apart: the same residuals to two digits.  1 x 32K: 56 us each, now 10.)  So the order of the points matters to rounding only; large and
   // small ones take turns.
-  constexpr int kPlain = 4, kPoints = 9;
+  constexpr int kPlain = 4, kPoints = 9, kMost = 16;
   const bool shifted = n_iter == 0 && m < D;
   Shift* shift = reinterpret_cast<Shift*>(ws + pl.shift);
   int32_t* pause = order;   // (the order is found after these steps)
-  const int steps = n_iter ? n_iter : shifted ? kPlain + kPoints : 16;
+  const int steps = n_iter ? n_iter : shifted ? kPlain + kPoints : kMost;
   for (int it = 0; it < steps; ++it) {
     const int j = shifted ? it - kPlain : -1;
     const double node = 0.5 - 0.5 * std::cos(3.14159265358979323846 * (2 * (4 * j % kPoints) + 1) / (2 * kPoints));
     if ((e = j < 0 ? times_gram(Xt, Yt) : times_gram(Xt, Yt, shift, node)) != hipSuccess) return e;
     const bool pauses = j >= 0 && it + 1 < steps;
     if ((e = orthonormalise(Yt, Xt, j == -1 && shifted ? shift : nullptr, pause, {pauses ? pause : nullptr, j + 1})) != hipSuccess) return e;
+  }
+  for (int it = steps; shifted && it < kMost; ++it) {   // sequences without a shift
+    if ((e = times_gram(Xt, Yt, nullptr, 0.0, {pause, 0})) != hipSuccess) return e;
+    if ((e = orthonormalise(Yt, Xt, nullptr, nullptr, {pause, 0})) != hipSuccess) return e;
   }
   // twice more before the Ritz step: the first brings the basis to the rounding unit, the second does the same for
   // vectors whose pivots were rounding in the one before

@@ -87,3 +87,26 @@ def test_sequences_of_a_batch_pause_by_themselves():
         assert residual[0] <= residual[1] + 1e-12 * top
     # singular values to rounding: 1e-12 of the largest squared one, as the residuals
     assert np.abs(alone[1][0] ** 2 - many[1][0] ** 2).max() <= 1e-12 * many[1][0][0] ** 2
+
+
+def _factored(k, h, d, r):
+    p = S.Params(batch=len(k), n_q_heads=h, n_kv_heads=h, head_dim=d, ctx_len=k.shape[1], chunk_size=1, rank=r, n_outlier_chunks=0,
+                 topk_chunks=1, local_len=0)
+    out = {n: S.factorize_keys(p, k.cuda(), want_vectors=True, n_iter=n) for n in (0, 16)}
+    torch.cuda.synchronize()
+    return out
+
+
+@pytest.mark.parametrize("lead", [1e6, 1e8])
+def test_sequences_whose_weakest_pivots_are_rounding_take_sixteen_plain_steps(lead):
+    """One direction so far above the others that what it leaves in the last vectors after a step is more than their own length: there
+    is no shift to go by, and the default is what n_iter = 16 asks for, bit for bit (the same products in the same order)."""
+    h, d, s, r = 4, 128, 1500, 160
+    print(f"\n[case] lead {lead}", flush=True)
+    gen = torch.Generator(device="cpu").manual_seed(int(np.log10(lead)))
+    scale = torch.exp(-torch.arange(h * d, dtype=torch.float64) / 100.0)
+    scale[0] *= lead
+    k = (torch.randn(1, s, h * d, generator=gen, dtype=torch.float64) * scale).to(torch.bfloat16)
+    out = _factored(k, h, d, r)
+    for name in ("psi", "sigma", "A", "B"):
+        assert torch.equal(out[0][name].cpu(), out[16][name].cpu()), name
