@@ -260,8 +260,9 @@ int shadowkv_append_chunk(const shadowkv_params *params, const shadowkv_kv *k_pr
  * right singular vector positive (ties: lowest index).  Computed from the Gram matrix K^T K (stored as fp64; its
  * products are exact, its sums exact or fp64) by subspace iteration with `n_iter` steps on r + 32 vectors and a
  * Rayleigh-Ritz step; accurate when sigma_r and sigma_(r+33) are apart (the convergence factor per step is
- * (sigma_(r+33) / sigma_r)^2).  n_iter = 0, the default, takes thirteen steps of which the last nine are shifted; they
- * come at least as close as sixteen plain ones.
+ * (sigma_(r+33) / sigma_r)^2).  n_iter = 0, the default, stands for sixteen steps.  Where r + 32 < h_kv*d and the r-th
+ * eigenvalue of K^T K as the fourth step sees it is at least four times the (r+32)-th, it takes thirteen, the last nine of
+ * them shifted, which come as close to within D rounding units of the largest eigenvalue.
  *
  *   k_pre      dev      [b, s, h_kv*d] kv   pre-RoPE keys, heads side by side
  *   A          dev out  [b, cap, r] kv      rows 0 .. s-1 written: sums good to 2^-24 of each entry, or fp64 sums where an

@@ -123,6 +123,7 @@ __device__ __forceinline__ int op_index(int row, int col) { return (row + 16 * (
 __device__ __forceinline__ int tri_block(int nb, int i, int k) { return k * nb - k * (k - 1) / 2 + (i - k); }
 constexpr int kMaxFactorBlocks = 18;       // 288 = 256 + 32 vectors
 constexpr double kPivotFloor = 1e-13;      // share of a vector's square below which its remainder is rounding
+constexpr double kShiftRatio = 4.0;        // r-th eigenvalue over the last that the vectors hold, from which steps are shifted
 
 __device__ __forceinline__ double lane_f64(double x, int l) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l), __builtin_amdgcn_readlane(__double2loint(x), l));
@@ -202,9 +203,10 @@ __device__ __forceinline__ void factor_panels(f64x4 a, const double (&least)[4],
 
 // The block's inverse factor.  Pivots below kPivotFloor times their vector's square (e0[j], row 4 j + kq) project nothing and
 // count as that (see chol_kernel); a block that has one is taken again with the checks.
-// out: the inverse in operand order; inv: the same, rows of floored pivots zero; returns the least pivot of the lane's rows, 0 if
-// one of them was floored, infinity for zero vectors.
-__device__ __forceinline__ double factor_block(f64x4 a, const double (&e0)[4], double* __restrict__ out, double* __restrict__ inv) {
+// out: the inverse in operand order; inv: the same, rows of floored pivots zero; smallest: the least pivot of the lane's rows and
+// what it was before, 0 if one of them was floored, infinity for zero vectors; wanted: the same of the block's first n_wanted rows.
+__device__ __forceinline__ void factor_block(f64x4 a, const double (&e0)[4], double* __restrict__ out, double* __restrict__ inv,
+                                             int n_wanted, double& smallest, double& wanted) {
   const int lane = threadIdx.x & (kWave - 1), sub = lane & 15, kq = lane >> 4;
   double f[4], d[4], least[4];
   bool bad = false;
@@ -215,16 +217,16 @@ __device__ __forceinline__ double factor_block(f64x4 a, const double (&e0)[4], d
     bad |= d[j] < least[j];
   }
   if (__builtin_expect(__any(bad), 0)) factor_panels<true>(a, least, f, d);
-  double smallest = INFINITY;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const bool none = least[j] == INFINITY, floored = d[j] < least[j];
     const double piv = none ? 1.0 : (floored ? least[j] : d[j]), x = f[j] * rsqrt_f64(piv);
-    smallest = none ? smallest : fmin(smallest, floored ? 0.0 : piv);
+    const double p = none ? INFINITY : floored ? 0.0 : piv;
+    smallest = fmin(smallest, p);
+    wanted = 4 * j + kq < n_wanted ? fmin(wanted, p) : wanted;
     out[op_index(4 * j + kq, sub)] = x;
     inv[op_index(4 * j + kq, sub)] = floored ? 0.0 : x;
   }
-  return smallest;
 }
 
 // Cholesky factor of S [16 nb][16 nb] (lower triangle read; zero beyond the vectors), one workgroup of eight waves per
@@ -239,16 +241,18 @@ __device__ __forceinline__ double factor_block(f64x4 a, const double (&e0)[4], d
 // pivots, column, trailing blocks with four barriers a step, took 49.  Above 192 vectors a wave's blocks fill its registers.
 // A pivot below kPivotFloor of the vector's own square is rounding: it is set to that floor, which leaves the vector's
 // remainder at a size that the next pass can work on, and nothing is projected on it; a zero vector stays zero.
-// shift (may be NULL): of each sequence b, the least entry of L's diagonal, 0 where a pivot was set to its floor, and the power
-// of two that brings the longest vector between 1/2 and 1; and `pause`: 0 where b is 0, else how many of the steps that follow may
-// go without an orthonormalisation in between, one more than that.  What an earlier vector leaves in a later one by rounding (1e-16) grows by
+// shift (may be NULL): of each sequence b, the least entry of L's diagonal, 0 where a pivot was set to its floor or where one of
+// the first r entries is less than kShiftRatio times the least (see launch_factorize), and the power of two that brings the
+// longest vector between 1/2 and 1; and `pause`: 0 where b is 0, else how many of the steps that follow may go without an
+// orthonormalisation in between, one more than that.  What an earlier vector leaves in a later one by rounding (1e-16) grows by
 // the ratio of their eigenvalues in every step; up to three steps, as long as the largest ratio (that of the longest vector and
 // the least entry) to their number is below 1e13.  The products of vectors three steps apart from orthonormal ones are sixth
 // powers of eigenvalues, twelfth powers of singular values: without the power of two those of keys beyond 2^82 leave fp64, and
 // those of keys below 2^-82 fall under what counts as a zero vector.
 template <int NBW>
 __global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S, double* __restrict__ Lp, int nb,
-                                                   Shift* __restrict__ shift, int32_t* __restrict__ pause, Every every) {
+                                                   int r, Shift* __restrict__ shift, int32_t* __restrict__ pause,
+                                                   Every every) {
   if (step_left_out(every, blockIdx.x)) return;
   __shared__ double col[kMaxFactorBlocks][272];   // current block column, rows at a pitch of 17
   __shared__ double sol[kMaxFactorBlocks][256];   // the same times the diagonal block's inverse, operand order
@@ -284,7 +288,7 @@ __global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S,
 #pragma unroll
       for (int j = 0; j < 4; ++j) d[j] = -Sl[(16 + 4 * j) * ld + 16];
     __builtin_amdgcn_s_setprio(3);
-    double least = INFINITY;
+    double least = INFINITY, least_wanted = INFINITY;
     double e1[4];   // squares of the next block's vectors 4 j + kq, ahead of their use
 #pragma unroll
     for (int j = 0; j < 4; ++j) e1[j] = S[(size_t)(4 * j + kq) * (ld + 1)];
@@ -295,7 +299,7 @@ __global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S,
         e0[j] = e1[j];
         e1[j] = S[(size_t)(16 * min(k + 1, nb - 1) + 4 * j + kq) * (ld + 1)];
       }
-      least = fmin(least, factor_block(a, e0, Lp + (size_t)tri_block(nb, k, k) * 256, inv));
+      factor_block(a, e0, Lp + (size_t)tri_block(nb, k, k) * 256, inv, r - 16 * k, least, least_wanted);
       __syncthreads();   // B: the inverse, column k and the next diagonal block are in LDS
       if (k + 1 >= nb) break;
       if (k > 0)
@@ -329,13 +333,16 @@ __global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S,
     if (shift) {
       least = fmin(least, shfl_xor_f64(least, 16));
       least = fmin(least, shfl_xor_f64(least, 32));
+      least_wanted = fmin(least_wanted, shfl_xor_f64(least_wanted, 16));
+      least_wanted = fmin(least_wanted, shfl_xor_f64(least_wanted, 32));
       double longest = 0.0;
       for (int i = lane; i < ld; i += kWave) longest = fmax(longest, S[(size_t)i * (ld + 1)]);
       longest = wave_max_f64(longest);
       if (lane == 0) {
         // (the root first: its exponent is the vector's; zeros and what is not finite are left as they are)
         const bool finite = longest > 0.0 && longest < INFINITY;
-        const bool shifts = least > 0.0 && least < INFINITY;   // (infinity: no vector but zeros)
+        // (squares of entries; infinity: no vector but zeros)
+        const bool shifts = least > 0.0 && least < INFINITY && least_wanted >= kShiftRatio * kShiftRatio * least;
         shift[blockIdx.x] = {shifts ? sqrt(least) : 0.0,
                              finite ? ldexp(1.0, -__builtin_amdgcn_frexp_exp(sqrt(longest))) : 1.0};
         const double x = longest / least;   // squared ratio

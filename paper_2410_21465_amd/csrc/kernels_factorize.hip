@@ -576,7 +576,7 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
     if (err != hipSuccess) return err;
 #define SKV_ORTH(NBW_, NB_)                                                                                       \
   do {                                                                                                            \
-    hipLaunchKernelGGL(chol_kernel<NBW_>, dim3(batch), dim3(512), 0, st, S, Lp, nbc, shift, pause, every); \
+    hipLaunchKernelGGL(chol_kernel<NBW_>, dim3(batch), dim3(512), 0, st, S, Lp, nbc, r, shift, pause, every); \
     hipLaunchKernelGGL(trsm_kernel<NB_>, dim3(D / 16, batch), dim3(256), 0, st, Lp, Y, X, m, nbc, D, every);         \
   } while (0)
     // (blocks per wave of the eight, block rows held): up to 80, 192, 224, 288 vectors
@@ -594,10 +594,14 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
   };
   // Steps of G alone damp what lies beyond the m vectors by lam_(m+1) / lam_r each.  By default four of these are followed by
   // nine of G - theta_j with theta_j the Chebyshev points of [0, b], b the least entry of the fourth factor's diagonal: 0.8 to
-  // 1.2 lam_m on every spectrum tried, at which the nine damp like 1 / T_9(2 lam_r / b - 1).  On spectra with lam_(m+1) / lam_r
-  // from 0.9 to 0.15 the r vectors come out 5 to 1000 times closer than after 16 steps of G, below that alike to rounding (numpy
-  // model, keys of 30 kinds).  Where a pivot was rounding b is 0, nothing is shifted, and three steps more make sixteen plain
-  // ones.  Of the nine every third, or second, is followed by an
+  // 1.2 lam_m on every spectrum tried, at which the nine damp like 1 / T_9(2 lam_r / b - 1).  They do so where the least of the
+  // diagonal's first r entries is at least kShiftRatio = 4 times b: everything up to b is then damped by 1e-10 on top of its
+  // fourth power, whatever comes after the m vectors (numpy model, 125 spectra of 256, 512 and 1024 columns, ramps and plateaus
+  // that drop at any place among them: residuals up to 300 times smaller than after sixteen steps of G, or within 5e-14 lam_1 per
+  // vector, which is D rounding units).  With the r-th eigenvalue closer to b the points' polynomial is not small on [0, b], and a
+  // spectrum that drops there loses: 64 equal eigenvalues and the rest 0.117 of these, r = 32, residual 1.8e-4 against 1e-13.
+  // Such sequences, and those where a pivot was rounding, have b = 0: nothing is shifted, every step is followed by an
+  // orthonormalisation, and three steps more (four launches of 2 us each for the others) make sixteen.  Of the nine every third, or second, is followed by an
   // orthonormalisation where the eigenvalues lie close enough (see chol_kernel), and the last: after four steps the vectors are
   // near enough to single eigenvectors that another step mostly scales them.  (Same model, 25 kinds,
   // eigenvalues from alike to 1e30 apart: the same residuals to two digits.  1 x 32K: 56 us each, now 10.)  So the order of the points matters to rounding only; large and

@@ -110,3 +110,32 @@ def test_sequences_whose_weakest_pivots_are_rounding_take_sixteen_plain_steps(le
     out = _factored(k, h, d, r)
     for name in ("psi", "sigma", "A", "B"):
         assert torch.equal(out[0][name].cpu(), out[16][name].cpu()), name
+
+
+@pytest.mark.parametrize("h,d,r,level,drop", [(2, 128, 32, 64, 0.117), (2, 128, 32, 74, 0.117), (2, 128, 32, 74, 0.25), (2, 128, 32, 40, 0.25),
+                                              (4, 128, 160, 202, 0.117), (4, 128, 160, 192, 0.25), (4, 128, 160, 170, 0.06)])
+def test_level_spectra_that_drop(h, d, r, level, drop):
+    """`level` equal eigenvalues and the rest `drop` of these, the drop anywhere from inside the r + 32 vectors to beyond them: points of
+    [0, b] with b hardly below the r-th eigenvalue would damp next to nothing."""
+    D = h * d
+    print(f"\n[case] D {D} r {r} level {level} drop {drop}", flush=True)
+    gen = torch.Generator(device="cpu").manual_seed(level)
+    scale = torch.where(torch.arange(D) < level, 1.0, drop ** 0.5).double()
+    # orthonormal columns; rounding to storage moves the eigenvalues by some thousandths
+    q = torch.linalg.qr(torch.randn(2 * D, D, generator=gen, dtype=torch.float64))[0]
+    k = (q * scale[torch.randperm(D, generator=gen)]).to(torch.bfloat16).contiguous()[None]
+    out = _factored(k, h, d, r)
+    K = k[0].double().numpy()
+    G = K.T @ K
+    lam = np.linalg.eigvalsh(G)[::-1]
+    res, miss = {}, {}
+    for n, got in out.items():
+        psi, sig = got["psi"][0].cpu().numpy(), got["sigma"][0].cpu().numpy()
+        assert np.abs(psi @ psi.T - np.eye(r)).max() < 1e-12
+        res[n] = np.linalg.norm(psi @ G - (sig ** 2)[:, None] * psi)
+        miss[n] = lam[:r].sum() - np.einsum("ij,ij->", psi @ G, psi)
+    print(f"[steps] residual / lam_1 {res[0] / lam[0]:.1e} (16: {res[16] / lam[0]:.1e}), energy {miss[0] / lam[0]:.1e} "
+          f"({miss[16] / lam[0]:.1e})", flush=True)
+    # rounding: 1e-12 of the largest eigenvalue for sums of a few hundred terms
+    assert res[0] <= res[16] + 1e-12 * lam[0]
+    assert miss[0] <= miss[16] + 1e-12 * lam[0]
