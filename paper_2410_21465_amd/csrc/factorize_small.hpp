@@ -495,19 +495,16 @@ __device__ __forceinline__ bool jacobi_active(const int32_t* sweep_max, int swee
   // (a stored cosine that is not a number counts as not done)
   return sweep == 0 || !(__int_as_float(sweep_max[sweep - 1]) < kJacobiDone);
 }
-// (c, s) of a rotation that makes two columns with squares al, be and product ga nearly orthogonal: t = tan theta with
-// tan 2 theta = 2 ga / (be - al), |theta| <= pi / 4, in fp32 with the exponent taken out first, which leaves 2^-22 of ga; then
-// c = 1 / sqrt(1 + t^2) and s = t c to fp64, so that the columns' lengths and what is accumulated lose nothing.  The angle in
-// fp64 takes the same number of sweeps; a round is a chain of latencies that begins with this.
+// (c, s) of the rotation that makes two columns with squares al, be and product ga orthogonal: tan 2 theta = 2 ga / (be - al),
+// |theta| <= pi / 4, through cos 2 theta and two reciprocal square roots; the exponent is taken out first.
 __device__ __forceinline__ void rotation(double al, double be, double ga, double& c, double& s) {
-  const double d = be - al, g = 2.0 * ga;
+  double d = be - al, g = 2.0 * ga;
   const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(d), fabs(g)));
-  const float df = (float)__builtin_amdgcn_ldexp(d, ex), gf = (float)__builtin_amdgcn_ldexp(g, ex);   // the larger in [1/2, 1], or both 0
-  const float den = fmaxf(fabsf(df) + __builtin_amdgcn_sqrtf(fmaf(df, df, gf * gf)), 0.25f);
-  const float tf = gf * __builtin_amdgcn_rcpf(den);
-  const double t = (double)(df < 0.0f ? -tf : tf);
-  c = rsqrt_f64(fma(t, t, 1.0));
-  s = t * c;
+  d = __builtin_amdgcn_ldexp(d, ex); g = __builtin_amdgcn_ldexp(g, ex);   // the larger in [1/2, 1], or both 0
+  const double h2 = fma(d, d, g * g), r = rsqrt_f64(h2);
+  const double c2 = fma(0.5 * fabs(d), r, 0.5), rc = rsqrt_f64(c2), sn = 0.5 * g * r * rc;
+  c = h2 == 0.0 ? 1.0 : c2 * rc;
+  s = h2 == 0.0 ? 0.0 : d < 0.0 ? -sn : sn;
 }
 // lane J of each row of 16 in all lanes of the row
 template <int J>
@@ -612,14 +609,13 @@ __global__ __launch_bounds__(512) void jacobi_block_kernel(double* __restrict__ 
       if (t == 2) S0[(16 + r) * P + 16 + c] = v;
     }
     __syncthreads();
-    // largest cosine among the pairs this step is about (its reciprocal roots from the hardware's estimates: a few parts in
-    // 10^7, as it only says whether to go on), and the rounds in which there is something to rotate
+    // largest cosine among the pairs this step is about, and the rounds in which there is something to rotate
     uint32_t big = 0, rounds = 0;           // (cosines are >= 0: their bits are in their order, not-a-numbers above all)
     for (int i = threadIdx.x; i < 1024; i += 512) {
       const int r = i >> 5, c = i & 31;
       const double ga = fabs(S0[r * P + c]), al = S0[r * P + r], be = S0[c * P + c];
       if (r < c && (st == 0 || (r < 16 && c >= 16)) && !(ga <= 1e-300)) {
-        const float x = (float)(ga * __builtin_amdgcn_rsq(al) * __builtin_amdgcn_rsq(be));
+        const float x = (float)(ga * rsqrt_f64(al) * rsqrt_f64(be));
         big = max(big, __float_as_uint(x));
         // (the round of a pair, see members below: (c - r) mod 16, or with 31 the other one, else half the sum mod 31)
         if (!(x <= 2e-16f)) rounds |= 1u << (st != 0 ? (c - r) & 15 : c == 31 ? r : (r + c) * 16 % 31);
