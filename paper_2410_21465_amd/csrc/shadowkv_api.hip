@@ -140,8 +140,11 @@ AttnPlan plan_attention(const Shape& sh, bool with_cache = false) {
   } else {
     // Two workgroups or more per compute unit: the largest split (fewest B^T stagings) that still gives >= 512 workgroups, but
     // no fewer rows than the four waves take at a time (1 x 32K without groups, 100 chunks: 19.1 us with 32, 14.6 with 64),
-    // and beside a gather, which wants compute units of its own, twice that (1 x 1M 49.7 us with 32, 48.5 with 64, 40.7).
-    len = std::max(len, gathers ? 128l : 64l);
+    // and beside a gather, which wants compute units of its own, twice that (1 x 1M 49.7 us with 32, 48.5 with 64, 40.7).  A
+    // gather of 2048 rows or fewer in all ends before the longer splits do (whole steps with 64 and 128 rows a split, 1 x 32K:
+    // 4 KV heads of 512 rows 35.5 and 38.5 us, 2 of 512 37.3 and 40.6, of heads of 64 30.6 and 32.5, but 2 of 1600 44.2 and
+    // 43.2, 8 of 512 43.5 and 43.2, 12 of 512 65.4 and 57.8).
+    len = std::max(len, gathers && sh.units * kc > 2048 ? 128l : 64l);
   }
   // tuning override: rows per split (read once)
   static const long forced = [] { const char* ov = std::getenv("SHADOWKV_SPARSE_SPLIT"); return ov ? std::atol(ov) : 0l; }();

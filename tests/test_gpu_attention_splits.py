@@ -26,3 +26,24 @@ def test_odd_splits(b, hq, hkv, d, k, r, rows, kd):
         t = to_fp8_storage(t)
     ref_b, _ = PU.run_build_parity(wl, t, kv_dtype=kd)
     PU.run_decode_parity(wl, t, ref_b, check_keys=False, kv_dtype=kd)
+
+
+# Values in host memory: splits of 64 rows where the gather fetches 2048 rows or fewer in all, of 128 beyond; the values summed in
+# parts of 128 rows, of 256 where the first phase leaves no room for more (the last shape, 7 splits); last parts of 1, of all
+# and of some rows
+# (batch, query heads, KV heads, head_dim, chunk size, selected chunks, rows per split)
+@pytest.mark.parametrize("b,hq,hkv,d,c,k,rows", [(1, 8, 2, 64, 1, 129, 64), (2, 4, 2, 128, 8, 64, 64), (2, 4, 2, 96, 8, 65, 128),
+                                                 (3, 7, 1, 128, 8, 96, 128), (20, 4, 4, 64, 8, 103, 128)])
+@pytest.mark.parametrize("kd", [0, 1])
+def test_splits_beside_a_gather(b, hq, hkv, d, c, k, rows, kd):
+    wl = Workload("gather", batch=b, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, ctx_len=150 * c, chunk_size=c, rank=32,
+                  n_outlier_chunks=3, topk_chunks=k, local_len=7, rope_theta=1e4, seed=23, n_queries=1, value_location="host")
+    plan = S.decode_plan(S.Params.from_workload(wl, kv_dtype=kd))
+    print(f"[case] {wl} kv_dtype {kd} {plan}", flush=True)
+    assert plan["rows_per_split"] == rows
+    t = PU.draw(wl)
+    if kd:
+        from workloads import to_fp8_storage
+        t = to_fp8_storage(t)
+    ref_b, _ = PU.run_build_parity(wl, t, kv_dtype=kd)
+    PU.run_decode_parity(wl, t, ref_b, check_keys=False, kv_dtype=kd)
