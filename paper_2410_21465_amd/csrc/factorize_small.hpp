@@ -9,12 +9,13 @@ namespace skv {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-// Of the steps 1, 2, ... a sequence takes every every[sequence]-th (all of them without `every`, and where that is 0); step 0 is
-// for those sequences alone where it is 0.
-struct Every { const int32_t* every; int step; };
+// Of the steps 1, 2, ... a sequence takes every n-th, n = every[sequence] without kMoreSteps (all of them without `every`); with
+// `more` those sequences alone whose entry has kMoreSteps, the others are done.
+constexpr int kMoreSteps = 4;
+struct Every { const int32_t* every; int step; bool more; };
+__device__ __forceinline__ bool sequence_done(Every e, int sequence) { return e.more && !(e.every[sequence] & kMoreSteps); }
 __device__ __forceinline__ bool step_left_out(Every e, int sequence) {
-  const int n = e.every ? e.every[sequence] : 0;
-  return n != 0 && (e.step == 0 || e.step % n != 0);
+  return sequence_done(e, sequence) || (e.every && e.step % (e.every[sequence] & ~kMoreSteps) != 0);
 }
 
 // What a factor says of the shifted steps of its sequence: b, of whose shares the shifts are, and a power of two that brings the
@@ -243,8 +244,8 @@ __device__ __forceinline__ void factor_block(f64x4 a, const double (&e0)[4], dou
 // remainder at a size that the next pass can work on, and nothing is projected on it; a zero vector stays zero.
 // shift (may be NULL): of each sequence b, the least entry of L's diagonal, 0 where a pivot was set to its floor or where one of
 // the first r entries is less than kShiftRatio times the least (see launch_factorize), and the power of two that brings the
-// longest vector between 1/2 and 1; and `pause`: 0 where b is 0, else how many of the steps that follow may go without an
-// orthonormalisation in between, one more than that.  What an earlier vector leaves in a later one by rounding (1e-16) grows by
+// longest vector between 1/2 and 1; and `pause`: how many of the steps that follow may go without an orthonormalisation in
+// between, one more than that, and kMoreSteps where b is 0.  What an earlier vector leaves in a later one by rounding (1e-16) grows by
 // the ratio of their eigenvalues in every step; up to three steps, as long as the largest ratio (that of the longest vector and
 // the least entry) to their number is below 1e13.  The products of vectors three steps apart from orthonormal ones are sixth
 // powers of eigenvalues, twelfth powers of singular values: without the power of two those of keys beyond 2^82 leave fp64, and
@@ -346,7 +347,8 @@ __global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S,
         shift[blockIdx.x] = {shifts ? sqrt(least) : 0.0,
                              finite ? ldexp(1.0, -__builtin_amdgcn_frexp_exp(sqrt(longest))) : 1.0};
         const double x = longest / least;   // squared ratio
-        pause[blockIdx.x] = !shifts ? 0 : x * x * x <= 1e26 ? 3 : x * x <= 1e26 ? 2 : 1;
+        const int steps = !(least > 0.0 && least < INFINITY) ? 1 : x * x * x <= 1e26 ? 3 : x * x <= 1e26 ? 2 : 1;
+        pause[blockIdx.x] = steps | (shifts ? 0 : kMoreSteps);
       }
     }
     return;
@@ -404,8 +406,8 @@ __global__ __launch_bounds__(512) void chol_kernel(const double* __restrict__ S,
 template <int NB>
 __global__ __launch_bounds__(256) void trsm_kernel(const double* __restrict__ Lp, const double* __restrict__ Y,
                                                    double* __restrict__ X, int m, int nb, int D, Every every) {
-  if (step_left_out(every, blockIdx.y)) {   // X <- Y, in step 0 nothing
-    if (every.step == 0) return;
+  if (sequence_done(every, blockIdx.y)) return;
+  if (step_left_out(every, blockIdx.y)) {   // X <- Y
     const size_t at = (size_t)blockIdx.y * m * D + blockIdx.x * 16 + (threadIdx.x & 15);
 #pragma unroll 8
     for (int r = threadIdx.x >> 4; r < m; r += 16) X[at + (size_t)r * D] = Y[at + (size_t)r * D];

@@ -333,7 +333,7 @@ struct Mat { const double* p; int ld; size_t stride; };
 template <bool BT>
 static hipError_t gemm64(Mat A, Mat B, double* C, int ldc, size_t strideC, int M, int N, int K, int Kb, int Mw, int Nw,
                          int batch, hipStream_t st, const int32_t* a_rows = nullptr, int a_rows_stride = 0,
-                         const Shift* shift = nullptr, double node = 0.0, Every every = {nullptr, 0}, bool lower = false) {
+                         const Shift* shift = nullptr, double node = 0.0, Every every = {nullptr, 0, false}, bool lower = false) {
   const long tiles = (long)((Mw + 31) / 32) * ((Nw + 31) / 32) * batch;
 #define SKV_GEMM(T_, WM_, WN_, WK_)                                                                                       \
   hipLaunchKernelGGL((gemm64_kernel<T_, WM_, WN_, WK_, BT>), dim3((Nw + 16 * T_ * WN_ - 1) / (16 * T_ * WN_),             \
@@ -570,7 +570,7 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
   const int nbc = (m + 15) / 16;
   // (with `every` for those sequences whose turn it is, X <- Y for the others)
   auto orthonormalise = [&](const double* Y, double* X, Shift* shift = nullptr, int32_t* pause = nullptr,
-                            Every every = {nullptr, 0}) -> hipError_t {
+                            Every every = {nullptr, 0, false}) -> hipError_t {
     hipError_t err = gemm64<true>({Y, D, (size_t)m * D}, {Y, D, (size_t)m * D}, S, 16 * nbc, (size_t)256 * nbc * nbc, m, m, D, D, 16 * nbc, 16 * nbc, batch, st,
                                   nullptr, 0, nullptr, 0.0, every, true);
     if (err != hipSuccess) return err;
@@ -588,7 +588,7 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
     return hipGetLastError();
   };
   // Y = X (G - node shift); G is symmetric, so its rows are its columns
-  auto times_gram = [&](const double* X, double* Y, const Shift* by = nullptr, double node = 0.0, Every every = {nullptr, 0}) {
+  auto times_gram = [&](const double* X, double* Y, const Shift* by = nullptr, double node = 0.0, Every every = {nullptr, 0, false}) {
     return gemm64<true>({X, D, (size_t)m * D}, {G, D, (size_t)D * D}, Y, D, (size_t)m * D, m, D, D, D, m, D, batch, st, nullptr, 0, by,
                         node, every);
   };
@@ -600,12 +600,12 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
   // that drop at any place among them: residuals up to 300 times smaller than after sixteen steps of G, or within 5e-14 lam_1 per
   // vector, which is D rounding units).  With the r-th eigenvalue closer to b the points' polynomial is not small on [0, b], and a
   // spectrum that drops there loses: 64 equal eigenvalues and the rest 0.117 of these, r = 32, residual 1.8e-4 against 1e-13.
-  // Such sequences, and those where a pivot was rounding, have b = 0: nothing is shifted, every step is followed by an
-  // orthonormalisation, and three steps more (four launches of 2 us each for the others) make sixteen.  Of the nine every third, or second, is followed by an
-  // orthonormalisation where the eigenvalues lie close enough (see chol_kernel), and the last: after four steps the vectors are
-  // near enough to single eigenvectors that another step mostly scales them.  (Same model, 25 kinds,
-  // eigenvalues from alike to 1e30 apart: the same residuals to two digits.  1 x 32K: 56 us each, now 10.)  So the order of the points matters to rounding only; large and
-  // small ones take turns.
+  // Such sequences, and those where a pivot was rounding, have b = 0: nothing is shifted, and three steps more (four launches of
+  // 2 us each for the others) make sixteen.  Of the nine, or twelve, every third, or second, is followed by an orthonormalisation
+  // where the eigenvalues lie close enough (see chol_kernel), and the last: after four steps the vectors are near enough to single
+  // eigenvectors that another step mostly scales them, so the order of the points matters to rounding only; large and small ones
+  // take turns.  (Same model: the same residuals to two digits, eigenvalues from alike to 1e30 apart.  1 x 32K: 56 us for an
+  // orthonormalisation, 10 for one left out.)
   constexpr int kPlain = 4, kPoints = 9, kMost = 16;
   const bool shifted = n_iter == 0 && m < D;
   Shift* shift = reinterpret_cast<Shift*>(ws + pl.shift);
@@ -616,11 +616,11 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
     const double node = 0.5 - 0.5 * std::cos(3.14159265358979323846 * (2 * (4 * j % kPoints) + 1) / (2 * kPoints));
     if ((e = j < 0 ? times_gram(Xt, Yt) : times_gram(Xt, Yt, shift, node)) != hipSuccess) return e;
     const bool pauses = j >= 0 && it + 1 < steps;
-    if ((e = orthonormalise(Yt, Xt, j == -1 && shifted ? shift : nullptr, pause, {pauses ? pause : nullptr, j + 1})) != hipSuccess) return e;
+    if ((e = orthonormalise(Yt, Xt, j == -1 && shifted ? shift : nullptr, pause, {pauses ? pause : nullptr, j + 1, false})) != hipSuccess) return e;
   }
   for (int it = steps; shifted && it < kMost; ++it) {   // sequences without a shift
-    if ((e = times_gram(Xt, Yt, nullptr, 0.0, {pause, 0})) != hipSuccess) return e;
-    if ((e = orthonormalise(Yt, Xt, nullptr, nullptr, {pause, 0})) != hipSuccess) return e;
+    if ((e = times_gram(Xt, Yt, shift, 0.0, {pause, 0, true})) != hipSuccess) return e;
+    if ((e = orthonormalise(Yt, Xt, nullptr, nullptr, {pause, it - kPlain + 1, true})) != hipSuccess) return e;
   }
   // twice more before the Ritz step: the first brings the basis to the rounding unit, the second does the same for
   // vectors whose pivots were rounding in the one before
