@@ -346,6 +346,9 @@ void *shadowkv_decode_workspace_view(const shadowkv_params *params, void *worksp
  */
 int shadowkv_decode_plan(const shadowkv_params *params, int32_t *plan);
 
+/* Landmark rows per scoring workgroup of a decode step of this shape: 64, 128 or 256 (0 if params are invalid). */
+int shadowkv_decode_score_rows(const shadowkv_params *params);
+
 /*
  * Per-stage timing of decode steps with HIP events recorded on the caller's stream at the
  * stage boundaries (measurement aid, not part of the method).  Between begin and end every

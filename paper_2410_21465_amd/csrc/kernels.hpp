@@ -9,9 +9,9 @@
 namespace skv {
 
 constexpr int kMaxHalfDim = 64;   // head_dim <= 128
-constexpr int kScoreTile = 256;   // landmark rows per scoring workgroup, at most
-// workgroups of four waves with `tiles` tiles of 16 rows each, for n_c landmark rows
-inline int score_tile_count(int n_c, int tiles) { return (n_c + 64 * tiles - 1) / (64 * tiles); }
+constexpr int kScoreRows = 64;    // landmark rows per scoring workgroup of four waves and tile of 16 rows per wave
+// workgroups with `tiles` tiles per wave for n_c landmark rows
+inline int score_tile_count(int n_c, int tiles) { return (n_c + kScoreRows * tiles - 1) / (kScoreRows * tiles); }
 
 // Rotary frequencies, in revolutions per position (inv_freq / 2 pi), fp64, by value.
 struct RopeFreqs {

@@ -167,6 +167,14 @@ AttnPlan plan_attention(const Shape& sh, bool with_cache = false) {
   return ap;
 }
 
+// 16-row tiles per wave of a step's scoring.  Smaller tiles leave more pairs than the workspace's place for them holds: they go
+// where the selected rows' logits of the two-phase path will, as far as they fit.
+int decode_score_tiles(const Shape& sh) {
+  int tiles = score_tiles(sh.units, sh.G, sh.n_c, sh.eb);
+  while (tiles < 4 && (size_t)score_tile_count(sh.n_c, tiles) * sizeof(double2) > (size_t)sh.k * sh.c * sizeof(float)) tiles *= 2;
+  return tiles;
+}
+
 struct DecodeLayout {
   size_t logits, partials, lse, key_top, cand_key, cand_idx, sel_ids, miss_slots, sel_slots, n_miss, logit_buf, k_sparse, v_sparse, part_acc, part_ml, total;
   SelectPlan sel;
@@ -390,6 +398,11 @@ int shadowkv_decode_plan(const shadowkv_params* params, int32_t* plan) {
   return SHADOWKV_OK;
 }
 
+int shadowkv_decode_score_rows(const shadowkv_params* params) {
+  Shape sh;
+  return check_params(params, true, &sh) == SHADOWKV_OK ? kScoreRows * decode_score_tiles(sh) : 0;
+}
+
 size_t shadowkv_build_workspace_bytes(const shadowkv_params* params) {
   Shape sh;
   BuildLayout L;
@@ -520,10 +533,7 @@ static int decode_impl(const shadowkv_params* params, const shadowkv_bf16* q, co
   const int pstep = (g_prof.on && g_prof.n_steps < g_prof.max_steps) ? g_prof.n_steps++ : -1;
   prof_mark(st, pstep, 0);
   // 1. P = Q L^T / sqrt(d), per-tile softmax statistics
-  //    (smaller tiles leave more pairs than the workspace's place for them holds: they go where the selected rows' logits
-  //    of the two-phase path will, as far as they fit)
-  int tiles = score_tiles(sh.units, sh.G, sh.n_c, sh.eb);
-  while (tiles < 4 && (size_t)score_tile_count(sh.n_c, tiles) * sizeof(double2) > (size_t)sh.k * sh.c * sizeof(float)) tiles *= 2;
+  const int tiles = decode_score_tiles(sh);
   if (tiles < 4) partials = reinterpret_cast<double2*>(ws + L.logit_buf);
   hipError_t e = launch_score(q, landmarks, sh.eb, logits, L.ld, partials, sh.b, sh.hq, sh.hkv, sh.d, sh.n_c, sh.nc_cap, scale, tiles, st);
   if (e != hipSuccess) return fail_hip("score", e);

@@ -30,6 +30,7 @@ EXPORTS = (
     "shadowkv_value_cache_reset", "shadowkv_append_chunk", "shadowkv_argtopk", "shadowkv_argtopk_workspace_bytes",
     "shadowkv_factorize_keys", "shadowkv_factorize_workspace_bytes", "shadowkv_decode_step_static",
     "shadowkv_static_scratch_bytes", "shadowkv_decode_plan", "shadowkv_factorize_plan",
+    "shadowkv_decode_score_rows",
 )
 STAGES = ("score", "select", "gather_values", "attention")
 
@@ -91,6 +92,8 @@ def lib() -> C.CDLL:
         L.shadowkv_factorize_workspace_bytes.argtypes = [vp]
         L.shadowkv_factorize_plan.restype = i32
         L.shadowkv_factorize_plan.argtypes = [vp, vp]
+        L.shadowkv_decode_score_rows.restype = i32
+        L.shadowkv_decode_score_rows.argtypes = [vp]
         L.shadowkv_build_workspace_bytes.restype = sz
         L.shadowkv_build_workspace_bytes.argtypes = [vp]
         L.shadowkv_decode_workspace_bytes.restype = sz
@@ -136,6 +139,12 @@ def decode_plan(p: "Params") -> dict:
     return {"splits": plan[0], "rows_per_split": plan[1], "resident_rows_in_selection_launch": bool(plan[2]),
             "key_and_value_waves": bool(plan[3]), "selection_threads": plan[4], "selection_candidates_per_thread": plan[5],
             "selection_launches": plan[6], "logit_row_floats": plan[7]}
+
+
+def decode_score_rows(p: "Params") -> int:
+    """shadowkv_decode_score_rows: landmark rows per scoring workgroup of a decode step of this shape."""
+    st = p.c_struct()
+    return lib().shadowkv_decode_score_rows(C.byref(st))
 
 
 def profile_end() -> dict:
