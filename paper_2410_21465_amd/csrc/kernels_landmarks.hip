@@ -194,8 +194,10 @@ __global__ __launch_bounds__(256) void chunk_stats_kernel(const uint8_t* __restr
   mn = allmin16_f64(mn);
   if (ok) {
     uint32_t hm[RW];
-    if constexpr (D * EB < 256) pack_means<EPL, EB>(mean, hm);
-    else pack_kv<EPL, EB>(mean, hm);   // (bound by memory; 16 x 128K, c = 8: 1146 us against 1154)
+    // (chunks of eight bf16 rows are bound by memory and lose: 16 x 128K of 128 1146 -> 1154 us, 4 x 128K of 32 heads of 96 850 ->
+    // 869; chunks of four rows of 96 gain, 1092 -> 1075)
+    if constexpr (D * EB < (EXACT ? 256 : 192)) pack_means<EPL, EB>(mean, hm);
+    else pack_kv<EPL, EB>(mean, hm);
     store_raw<EPL, EB>(chunk_mean + (((size_t)unit * n_ch + j) * D + sub * EPL) * EB, hm);
     if (sub == 0) chunk_min_cos[(size_t)unit * n_ch + j] = mn;
   }
@@ -259,13 +261,14 @@ hipError_t launch_chunk_stats(const void* k_rope, int kv_bytes, void* chunk_mean
   const double inv_c = 1.0 / (double)c;
   // Rows counted by the compiler need no guards and chunks of four no work for eight (16 x 128K of 128: 1725 -> 1395 us for the
   // whole call, FP8 476 -> 390; c = 16, read once instead of twice: 4 x 128K 367 -> 295).  Chunks of eight gain in FP8 (3 x 61K
-  // 97 -> 93) and heads of 96 (4 x 128K 256 -> 247); bf16 rows of 256 bytes, all requested at once, lose (16 x 128K 1145 ->
-  // 1158: the memory system is full either way) and stay with the guarded form.
+  // 97 -> 93, heads of 96 4 x 128K 755 -> 729) and heads of 64 (4 x 61K 84 -> 81); longer bf16 rows, all requested at once, lose
+  // (16 x 128K of 128 1145 -> 1158, 8 x 128K of 96 432 -> 444: the memory system is full either way) and stay with the
+  // guarded form.
 #define SKV_STATS_R(D_, R_, EB_)                                                                                  \
   hipLaunchKernelGGL((chunk_stats_kernel<D_, R_, EB_>), grid, block, 0, st, kr, cm, chunk_min_cos, s, c, n_ch, inv_c)
 #define SKV_STATS(D_, EB_)                                                                                        \
   do {                                                                                                            \
-    if (c == 8 && D_ * EB_ < 256) SKV_STATS_R(D_, 8, EB_);\
+    if (c == 8) SKV_STATS_R(D_, (D_ * EB_ < 192 ? 8 : 0), EB_);                                                   \
     else if (c == 4) SKV_STATS_R(D_, 4, EB_);                                                                     \
     else if (c == 16) SKV_STATS_R(D_, 16, EB_);                                                                   \
     else if (c <= 8) SKV_STATS_R(D_, 0, EB_);                                                                     \
