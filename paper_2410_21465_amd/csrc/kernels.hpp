@@ -25,7 +25,7 @@ struct RopeFreqs {
 // kv_bytes (here and below): bytes per element of the KV-cache tensors, 2 = bf16, 1 = FP8 E5M2.
 // tiles: 16-row tiles per wave (1, 2 or 4; a workgroup of four waves makes one pair of partials per head, n_tiles =
 // score_tile_count(n_c, tiles)); score_tiles: how many the sizes call for.
-int score_tiles(int units, int G, int n_c, int kv_bytes);
+int score_tiles(int units, int G, int d, int n_c, int kv_bytes);
 hipError_t launch_score(const bf16_t* q, const void* landmarks, int kv_bytes, float* logits, int ld, double2* partials,
                         int batch, int hq, int hkv, int d, int n_c, int nc_stride, double scale, int tiles, hipStream_t st);
 

@@ -280,15 +280,19 @@ __global__ __launch_bounds__(256) void score_kernel_g16(const bf16_t* __restrict
 }
 
 // 16-row tiles per wave.  Many waves of few rows start and end evenly and fill a chip that few workgroups would leave idle;
-// where there is enough of both, fewer workgroups stage the queries less often and leave fewer pairs to merge.  In workgroups of
-// 256 rows, us with four / two / one tiles per wave, and where the limits lie:
-//   up to four heads: 16 (1 x 4K) 9.4 / 7.3 / 6.7; 512 (4 x 32K) 16.5 / 13.9 / 12.8; 1024 (8 x 32K) 21.6 / 19.1 / 19.6;
-//     4096 (16 x 64K) 57.1 / 56.6 / 64.9; 8192 107.9 / 107.7 / 123.7; FP8: 1024 17.1 / 15.9 / 17.8, 2048 24.3 / 25.8 / 28.0
-//   five to eight: 360 (3 x 61K) 16.4 / 13.4 / 13.8; 1440 33.2 / 32.8 / 36.9; FP8: 1024 23.5 / 22.9 / 24.6
-//   sixteen: 32 (1 x 32K) 12.1 / 8.8 / 7.4; 128 12.4 / 9.2 / 9.5; 512 18.8 / 18.9 / 20.7
-int score_tiles(int units, int G, int n_c, int kv_bytes) {
+// where there is enough of both, fewer workgroups stage the queries less often and leave fewer pairs to merge.  Short rows are
+// there sooner, so that this line lies lower for them.  In workgroups of 256 rows, us with four / two / one tiles per wave:
+//   up to four heads, rows of 256 bytes: 16 (1 x 4K) 9.4 / 7.3 / 6.7; 512 (4 x 32K) 15.6 / 13.3 / 12.6; 1024 23.4 / 20.6 / 20.5;
+//     4096 (16 x 64K) 57.2 / 56.6 / 65.0; 8192 107.7 / 107.6 / 123.5; of 192: 512 11.7 / 11.3 / 11.7; 4096 45.4 / 44.4 / 50.7;
+//     of 128: 256 9.1 / 8.5 / 8.6; 1024 16.7 / 16.1 / 17.7 (FP8), 13.1 / 12.1 / 13.5 (heads of 64); 2048 24.2 / 26.4 / 29.3, 18.9 /
+//     19.3 / 21.8; of 96: 512 10.0 / 10.0 / 10.5
+//   five to eight, rows of 256 bytes: 256 13.3 / 12.0 / 11.6; 1024 30.2 / 26.8 / 29.1; 4096 86.2 / 83.3 / 97.1; of 128: 128 10.1 /
+//     8.2 / 7.9; 256 9.4 / 8.9 / 9.1; 1024 23.2 / 23.2 / 24.6, 17.4 / 17.2 / 18.5; 2048 36.4 / 39.6 / 43.5, 26.4 / 28.4 / 31.6
+//   sixteen: 32 (1 x 32K) 12.1 / 8.8 / 7.4; 128 12.5 / 9.5 / 9.5; 512 18.7 / 18.8 / 20.2
+int score_tiles(int units, int G, int d, int n_c, int kv_bytes) {
   const long z = G > 8 ? (G + 15) / 16 : 1, wgs = units * z * score_tile_count(n_c, 4);
-  const long one = G > 8 ? 64 : G > 4 ? 256 : 512, two = G > 8 ? 256 : kv_bytes == 1 ? 1024 : 4096;
+  const bool short_rows = d * kv_bytes <= 128;
+  const long one = G > 8 ? 64 : (G > 4 ? 256 : 512) / (short_rows ? 2 : 1), two = G > 8 ? 256 : short_rows ? 1024 : 4096;
   return wgs <= one ? 1 : wgs <= two ? 2 : 4;
 }
 

@@ -170,7 +170,7 @@ AttnPlan plan_attention(const Shape& sh, bool with_cache = false) {
 // 16-row tiles per wave of a step's scoring.  Smaller tiles leave more pairs than the workspace's place for them holds: they go
 // where the selected rows' logits of the two-phase path will, as far as they fit.
 int decode_score_tiles(const Shape& sh) {
-  int tiles = score_tiles(sh.units, sh.G, sh.n_c, sh.eb);
+  int tiles = score_tiles(sh.units, sh.G, sh.d, sh.n_c, sh.eb);
   while (tiles < 4 && (size_t)score_tile_count(sh.n_c, tiles) * sizeof(double2) > (size_t)sh.k * sh.c * sizeof(float)) tiles *= 2;
   return tiles;
 }

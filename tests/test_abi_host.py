@@ -230,3 +230,14 @@ def test_decode_plan_of_the_benchmark_shapes():
     assert S.lib().shadowkv_decode_plan(C.byref(st), None) == S.EINVAL
     bad = S.Params(**{**GOOD, "rank": 12}).c_struct()
     assert S.lib().shadowkv_decode_plan(C.byref(bad), (C.c_int32 * 8)()) == S.EINVAL
+
+
+@pytest.mark.parametrize("d,kd,G,units,n_c,rows", [(64, 0, 7, 64, 8144, 256), (64, 0, 4, 128, 8144, 256), (128, 0, 7, 64, 8144, 128),
+                                                    (96, 0, 4, 128, 8144, 128), (64, 0, 7, 32, 8144, 128), (128, 1, 4, 64, 4048, 128),
+                                                    (128, 1, 4, 16, 4048, 64), (96, 1, 4, 32, 4048, 128), (128, 0, 4, 32, 4048, 64),
+                                                    (64, 0, 16, 4, 4048, 64), (64, 0, 16, 64, 4048, 256)])
+def test_rows_of_a_scoring_workgroup(d, kd, G, units, n_c, rows):
+    """shadowkv_decode_score_rows on both sides of the lines: short rows take long workgroups sooner."""
+    p = S.Params(batch=units, n_q_heads=G, n_kv_heads=1, head_dim=d, ctx_len=n_c * 8, chunk_size=8, rank=64, n_outlier_chunks=0,
+                 topk_chunks=64, local_len=0, kv_dtype=kd)
+    assert S.decode_score_rows(p) == rows
