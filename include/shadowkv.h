@@ -271,7 +271,7 @@ int shadowkv_append_chunk(const shadowkv_params *params, const shadowkv_kv *k_pr
  *   psi_out    dev out  [b, r, h_kv*d] fp64 optional (NULL): the right singular vectors before rounding, as rows
  *   sigma_out  dev out  [b, r] fp64         optional (NULL): singular values, largest first
  *   workspace  dev      >= shadowkv_factorize_workspace_bytes(), 256-byte aligned
- * Needs rank <= h_kv*d.  topk_chunks, local_len, n_outlier_chunks are ignored.  Enqueues some 180 launches at rank
+ * Needs rank <= h_kv*d.  topk_chunks, local_len, n_outlier_chunks are ignored.  Enqueues some 190 launches at rank
  * 160, most of them small (one per dependent step of the orthogonalisation and of the Jacobi sweeps).
  */
 int shadowkv_factorize_keys(const shadowkv_params *params, const shadowkv_kv *k_pre, shadowkv_kv *A,

@@ -486,8 +486,8 @@ __global__ __launch_bounds__(256) void trsm_kernel(const double* __restrict__ Lp
 // step of a sweep and ahead of the sweeps all pairs of its 32 columns): it forms the 32 x 32 products of the columns on the
 // matrix instruction, rotates those (two-sided, in LDS, 16 disjoint rotations at a time, accumulated in J) and applies J to
 // its columns as one product.  A rotation's angle thus costs two rounds of LDS and a barrier, not a pass over the columns and
-// a launch: a sweep of 192 columns is 11 launches of 14 us (the first 21, those without a rotation 6) where a launch per set of
-// 96 single rotations took 191 of 4.5 us.  In all 0.67 ms for one sequence, 1.0 with six sweeps and no passes ahead of them, 8.1
+// a launch: a sweep of 192 columns is 11 launches of 15 us (the first 22, those without a rotation 6) where a launch per set of
+// 96 single rotations took 191 of 4.5 us.  In all 0.68 ms for one sequence, 1.0 with six sweeps and no passes ahead of them, 8.1
 // with single rotations.
 // V is not needed before the end: its product with J is done by other workgroups of the next step's launch.
 // A sweep in which every cosine met was below kJacobiDone needs no successor (what is left is its square): the launches of
@@ -515,11 +515,12 @@ __device__ __forceinline__ double row_lane_f64(double x) {
 }
 // Ahead of the sweeps come passes over neighbouring blocks only, all pairs of 32 columns each, in two steps a pass: after
 // the subspace iteration T is a matrix whose entries fall off fast from the diagonal, so these settle most of it and spare more
-// sweeps (of nb - 1 steps) than they cost.  Launch by launch, in numpy, keys of the spectra exp(-i / 40), exp(-i / 100), 1 / i
-// and one with a gap, us without, with two, with three passes: 192 vectors 844 / 668 / 638, 974 / 792 / 780, 973 / 757 / 793,
-// 1109 / 993 / 938; 288 vectors 1238 / 898 / 830 ..; 128: 578 / 509 / 509, 639 / 584 / 591; 96 446 / 433 / 444, 491 / 477 /
-// 483; 64 317 / 356 / 383.  After a first pass without a cosine above kLocalWorth (flat spectra, which take nine sweeps either
-// way) the others are left out.
+// sweeps (of nb - 1 steps) than they cost.  Whole calls, 1 x 8K x 1024, us without and with one, two, three, four passes:
+//   exp(-i / 40): 56 vectors 962 / 970 / 973 / 991 / 1018, 96 1180 / 1164 / 1146 / 1143 / 1181, 120 1407 / 1362 / 1321 / 1313 /
+//     1349, 160 1657 / 1593 / 1522 / 1499 / 1531, 192 1911 / 1833 / 1726 / 1686 / 1732, 288 3973 / 3758 / 3566 / 3401 / 3446
+//   exp(-i / 100): 96 1300 / 1291 / 1270 / 1289 / 1331, 128 1530 / 1485 / 1452 / 1473 / 1503, 192 2172 / 2020 / 1938 / 1952 / 1981
+//   flat: 96 1436 / 1479 / 1476 / 1519 / 1555, 128 1767 / 1757 / 1791 / 1771 / 1819, 192 2571 / 2526 / 2573 / 2617 / 2623
+// After a first pass without a cosine above kLocalWorth (flat spectra, which take nine sweeps either way) the others are left out.
 constexpr float kLocalWorth = 1e-3f;
 __host__ __device__ __forceinline__ int local_steps(int nb) { return nb >= 10 ? 6 : nb >= 8 ? 4 : 0; }
 // local_max [batch]: the largest cosine of the first of them, as in sweep_max.

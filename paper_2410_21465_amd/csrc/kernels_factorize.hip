@@ -579,7 +579,7 @@ hipError_t launch_factorize(const void* k_pre, int kv_bytes, void* A, void* B, d
     hipLaunchKernelGGL(chol_kernel<NBW_>, dim3(batch), dim3(512), 0, st, S, Lp, nbc, r, shift, pause, every); \
     hipLaunchKernelGGL(trsm_kernel<NB_>, dim3(D / 16, batch), dim3(256), 0, st, Lp, Y, X, m, nbc, D, every);         \
   } while (0)
-    // (blocks per wave of the eight, block rows held): up to 80, 192, 224, 288 vectors
+    // (trailing blocks per wave of seven, block rows held): up to 80, 192, 224, 288 vectors
     if (nbc <= 5) SKV_ORTH(2, 5);
     else if (nbc <= 12) SKV_ORTH(11, 12);
     else if (nbc <= 14) SKV_ORTH(14, 14);
